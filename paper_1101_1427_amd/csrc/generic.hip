@@ -1,6 +1,5 @@
 // Generic kernels: initial state, per-site half-sweeps for any edge L and
-// dimension, Heisenberg renormalisation, measurements and the
-// parallel-tempering exchange.  The optimised kernels (lattice2d.hip,
+// dimension, Heisenberg renormalisation and the parallel-tempering exchange.  The optimised kernels (lattice2d.hip,
 // pt3d.hip) produce the same results; these serve every shape.
 #include <string.h>
 
@@ -28,19 +27,6 @@ __device__ __forceinline__ long long block_sum_ll(long long v, long long *smem) 
     if (threadIdx.x == 0)
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) tot += smem[w];
     return tot;  // valid in thread 0
-}
-
-__device__ __forceinline__ double block_sum_d(double v, double *smem) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) smem[wave] = v;
-    __syncthreads();
-    double tot = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) tot += smem[w];
-    return tot;
 }
 
 // Lattice position of the colour-c site of the pair (2h, 2h+1).
@@ -240,105 +226,6 @@ __global__ __launch_bounds__(kBlock) void k_heis_renorm(Batch b, float *spins, i
     s[2] = u.z;
 }
 
-// ------------------------------------------------------------ measurement ----
-struct Partial {
-    double e, mx, my, mz;
-};
-
-__global__ __launch_bounds__(kBlock) void k_measure_partials(Batch b, const void *spins, const int8_t *coup,
-                                                             Partial *part, int nblk) {
-    __shared__ double red[kBlock / 64];
-    const int r = blockIdx.x / nblk;
-    const int bx = blockIdx.x % nblk;
-    const smc_inst g = replica_geom(b, r);
-    const int L = g.L, dim = b.dim;
-    const int64_t N = n_sites(dim, L);
-    const int64_t LL = L;
-    double e = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
-    if (b.model == SMC_HEISENBERG) {
-        const float *s = (const float *)spins + 3 * g.spin_off;
-        for (int64_t i = (int64_t)bx * blockDim.x + threadIdx.x; i < N; i += (int64_t)nblk * blockDim.x) {
-            const int x = (int)(i % L);
-            const int64_t q = i / L;
-            const int y = (int)(q % L);
-            const int z = dim == 3 ? (int)(q / L) : 0;
-            const float3 si = ld3(s, i);
-            const float3 a = ld3(s, i + (x == L - 1 ? 1 - LL : 1));
-            const float3 bb = ld3(s, i + (y == L - 1 ? (1 - LL) * LL : LL));
-            double loc = (double)si.x * a.x + (double)si.y * a.y + (double)si.z * a.z;
-            loc += (double)si.x * bb.x + (double)si.y * bb.y + (double)si.z * bb.z;
-            if (dim == 3) {
-                const int64_t P = LL * LL;
-                const float3 cc = ld3(s, i + (z == L - 1 ? (1 - LL) * P : P));
-                loc += (double)si.x * cc.x + (double)si.y * cc.y + (double)si.z * cc.z;
-            }
-            e -= loc;
-            mx += si.x;
-            my += si.y;
-            mz += si.z;
-        }
-    } else {
-        const int8_t *s = (const int8_t *)spins + g.spin_off;
-        const int8_t *J = coup ? coup + g.coup_off : nullptr;
-        long long ei = 0, mi = 0;
-        for (int64_t i = (int64_t)bx * blockDim.x + threadIdx.x; i < N; i += (int64_t)nblk * blockDim.x) {
-            const int x = (int)(i % L);
-            const int64_t q = i / L;
-            const int y = (int)(q % L);
-            const int z = dim == 3 ? (int)(q / L) : 0;
-            const int si = s[i];
-            const int a = s[i + (x == L - 1 ? 1 - LL : 1)];
-            const int bb = s[i + (y == L - 1 ? (1 - LL) * LL : LL)];
-            int loc = J ? J[i] * a + J[N + i] * bb : a + bb;
-            if (dim == 3) {
-                const int64_t P = LL * LL;
-                const int cc = s[i + (z == L - 1 ? (1 - LL) * P : P)];
-                loc += J ? J[2 * N + i] * cc : cc;
-            }
-            ei -= si * loc;
-            mi += si;
-        }
-        e = (double)ei;  // exact: |partial| < 2^53
-        mx = (double)mi;
-    }
-    const double te = block_sum_d(e, red);
-    const double tx = block_sum_d(mx, red);
-    const double ty = block_sum_d(my, red);
-    const double tz = block_sum_d(mz, red);
-    if (threadIdx.x == 0) part[(int64_t)r * nblk + bx] = Partial{te, tx, ty, tz};
-}
-
-__global__ void k_measure_final(int n_rep, int nblk, int vec, const Partial *part, double *energy, double *magnet) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rep) return;
-    double e = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
-    for (int k = 0; k < nblk; ++k) {
-        const Partial p = part[(int64_t)r * nblk + k];
-        e += p.e;
-        mx += p.mx;
-        my += p.my;
-        mz += p.mz;
-    }
-    energy[r] = e;
-    if (magnet) {
-        if (vec) {
-            magnet[3 * r] = mx;
-            magnet[3 * r + 1] = my;
-            magnet[3 * r + 2] = mz;
-        } else {
-            magnet[r] = mx;
-        }
-    }
-}
-
-int measure_blocks(const Batch &b, int max_L) {
-    const int64_t N = b.dim == 3 ? (int64_t)max_L * max_L * max_L : (int64_t)max_L * max_L;
-    int64_t nb = (N + 4095) / 4096;
-    if (nb < 1) nb = 1;
-    if (nb > 2048) nb = 2048;
-    return (int)nb;
-}
-
 // -------------------------------------------------------- parallel tempering --
 // Energies in, and the threshold row of every replica from the chain's
 // permutation; a chain whose slot_of_temp row is not a permutation gets row
@@ -441,23 +328,6 @@ hipError_t launch_heis_half_sweep_generic(const SweepArgs &a, int c, hipStream_t
 hipError_t launch_heis_renorm(const Batch &b, float *spins, int max_L, hipStream_t s) {
     const int bpr = blocks_for(sites_of(b.dim, max_L));
     SMC_LAUNCH(k_heis_renorm, dim3(bpr * b.n_rep), dim3(kBlock), 0, s, b, spins, bpr);
-    return hipGetLastError();
-}
-
-size_t measure_scratch_bytes(const Batch &b, int max_L) {
-    return (size_t)measure_blocks(b, max_L) * (size_t)b.n_rep * sizeof(Partial);
-}
-
-hipError_t launch_measure(const Batch &b, const void *spins, const int8_t *coup, int max_L, double *energy,
-                          double *magnet, void *scratch, size_t scratch_bytes, hipStream_t s) {
-    const int nblk = measure_blocks(b, max_L);
-    if (scratch_bytes < measure_scratch_bytes(b, max_L)) return hipErrorInvalidValue;
-    Partial *part = (Partial *)scratch;
-    SMC_LAUNCH(k_measure_partials, dim3(nblk * b.n_rep), dim3(kBlock), 0, s, b, spins, coup, part, nblk);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    SMC_LAUNCH(k_measure_final, dim3((b.n_rep + 255) / 256), dim3(256), 0, s, b.n_rep, nblk,
-                       b.model == SMC_HEISENBERG ? 1 : 0, part, energy, magnet);
     return hipGetLastError();
 }
 
