@@ -561,6 +561,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
     a.dE = dE_accum;
+    a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     void *p = nullptr;
@@ -780,6 +781,7 @@ int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
     a.thr = (const ThrRow *)p;
     a.key = make_key(desc->seed);
     a.dE = dE_accum;
+    a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     a.rng_shift = word_bits == 64 ? 6 : 5;  // the draw group r / word_bits
@@ -1182,6 +1184,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
     a.dE = (int64_t *)E64;
+    a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.thr = (const ThrRow *)thr;
     a.row_of_rep = (const int32_t *)rowrep;

@@ -1,6 +1,7 @@
 // Generic kernels: initial state, per-site half-sweeps for any edge L and
 // dimension, Heisenberg renormalisation and the parallel-tempering exchange.  The optimised kernels (lattice2d.hip,
 // pt3d.hip) produce the same results; these serve every shape.
+#include <stdlib.h>
 #include <string.h>
 
 #include "heis_math.hpp"
@@ -313,7 +314,12 @@ hipError_t launch_init_couplings(int dim, int n_samples, const smc_inst *samples
     return hipGetLastError();
 }
 
+// A piece of 16 sites spans at most two rows when every edge is at least 16;
+// smaller edges keep a thread per pair of sites, and so does
+// SPINMC_PIECES=0 (same results).
 hipError_t launch_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s) {
+    const char *env = getenv("SPINMC_PIECES");
+    if (a.min_L >= 16 && !(env && env[0] == '0')) return launch_half_sweep_pieces(a, c, s);
     const int bpr = blocks_for(sites_of(a.b.dim, a.max_L) / 2);
     SMC_LAUNCH(k_half_sweep_generic, dim3(bpr * a.b.n_rep), dim3(kBlock), 0, s, a, c, bpr);
     return hipGetLastError();

@@ -67,7 +67,7 @@ struct SweepArgs {
     Key key;
     uint32_t t;                // sweep index
     int64_t *dE;               // nullable per-replica accumulator
-    int max_L;                 // largest edge in the batch
+    int min_L, max_L;          // smallest and largest edge in the batch
     int rng_shift;             // the Metropolis draws of replica r use index r >> rng_shift
 };
 
@@ -89,8 +89,11 @@ hipError_t launch_init_heis(const Batch &b, int max_L, float *spins, Key key, hi
 hipError_t launch_init_couplings(int dim, int n_samples, const smc_inst *samples_dev, int max_L, int8_t *coup,
                                  Key key, hipStream_t s);
 
-// Generic in-place half-sweep of colour c over every replica (any L, d).
+// Generic in-place half-sweep of colour c over every replica (any L, d): a
+// thread per 16 sites (pieces.hip) when every edge is at least 16, a thread
+// per pair of sites otherwise.
 hipError_t launch_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s);
+hipError_t launch_half_sweep_pieces(const SweepArgs &a, int c, hipStream_t s);
 hipError_t launch_heis_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s);
 hipError_t launch_heis_renorm(const Batch &b, float *spins, int max_L, hipStream_t s);
 

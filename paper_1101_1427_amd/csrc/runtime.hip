@@ -285,7 +285,7 @@ int validate(const smc_desc *d, bool need_coup, Plan &plan) {
         if (d->L > (d->dim == 3 ? 1024 : 65536)) return fail(SMC_EINVAL, "L too large (got %d)", d->L);
         b.N = sites(d->dim, d->L);
         if (b.N / 2 > 0xFFFFFFFFll) return fail(SMC_EINVAL, "lattice too large for 32-bit site counters");
-        plan.max_L = d->L;
+        plan.min_L = plan.max_L = d->L;
         if ((int64_t)d->n_rep * b.N * per_site > d->spins_len)
             return fail(SMC_EINVAL, "spin buffer too small: need %lld elements, have %lld",
                         (long long)((int64_t)d->n_rep * b.N * per_site), (long long)d->spins_len);
@@ -321,6 +321,7 @@ int validate(const smc_desc *d, bool need_coup, Plan &plan) {
                 }
             }
             if (g.L > plan.max_L) plan.max_L = g.L;
+            if (r == 0 || g.L < plan.min_L) plan.min_L = g.L;
         }
         for (auto &kv : seen) plan.samples.push_back(kv.second);
         plan.n_samples = (int64_t)plan.samples.size();
