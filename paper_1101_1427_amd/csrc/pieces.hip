@@ -43,91 +43,153 @@ __device__ __forceinline__ b8 put_byte(b8 v, uint32_t k, uint32_t byte) {
     return (v & ~m) | ((b8)byte << (8 * k));
 }
 
-template <int DIM, bool EA>
+// Sixteen bytes from site i of an array of N: where i .. i + 15 runs over an
+// end of the array the loaded bytes are moved into place by into_place, so the
+// loads of a piece are all issued before the first is waited for.
+template <typename I>
+__device__ __forceinline__ uint4 load_inside(const int8_t *p, I i, I N) {
+    return load16_any(p + max((I)0, min(i, N - 16)));
+}
+template <typename I>
+__device__ __forceinline__ void into_place(uint4 &v, I i, I N) {
+    if (i < 0) v = bytes_up(v, (uint32_t)min(-i, (I)16));
+    if (i > N - 16) v = bytes_down(v, (uint32_t)min(i - (N - 16), (I)16));
+}
+
+// I: int where a replica has at most 2^30 sites, else int64_t.
+template <int DIM, bool EA, typename I>
 __global__ __launch_bounds__(kThreads) void k_half_sweep_pieces(SweepArgs a, int c, int bpr, uint32_t one2) {
-    __shared__ long long red[kThreads / 64];
+    __shared__ int red[kThreads / 64];
+    constexpr int kDir = DIM == 3 ? 4 : 2;  // neighbours outside the row
     const int r = blockIdx.x / bpr;
     const smc_inst g = replica_geom(a.b, r);
     const int L = g.L;
-    const int64_t LL = L, P = DIM == 3 ? LL * LL : LL, N = P * LL;  // P: sites per plane (3D) or row (2D)
+    const I LL = L, P = DIM == 3 ? LL * LL : LL, N = P * LL;  // P: sites per plane (3D) or row (2D)
     const uint32_t piece = (uint32_t)(blockIdx.x % bpr) * kThreads + threadIdx.x;
-    const int64_t i0 = (int64_t)piece * 16;
     const int row = a.row_of_rep ? a.row_of_rep[r] : r;
-    long long dE = 0;
-    if (i0 < N && row >= 0) {
+    int dE = 0;
+    if ((int64_t)piece * 16 < (int64_t)N && row >= 0) {
+        const I i0 = (I)piece * 16;
         int8_t *S = (int8_t *)a.spins + g.spin_off;
         const int8_t *J = EA ? a.coup + g.coup_off : nullptr;
-        const int n = (int)min((int64_t)16, N - i0);  // sites of the piece (a multiple of 4)
+        const int n = (int)min((I)16, N - i0);  // sites of the piece (a multiple of 4)
         // first row of the piece, the row after it, and the first pair of the latter
         const uint32_t q = (uint32_t)i0 / (uint32_t)L;
         const int x0 = (int)((uint32_t)i0 - q * (uint32_t)L), left = L - x0;
         const uint32_t b = left >= 16 ? 8u : (uint32_t)left >> 1;
+        const bool border = left < 16 && n > left;  // the piece holds sites of two rows
         const int z1 = DIM == 3 ? (int)(q / (uint32_t)L) : (int)q, y1 = DIM == 3 ? (int)(q - (uint32_t)z1 * L) : 0;
         int y2 = y1, z2 = z1;
-        if (b < 8) {
+        if (left < 16) {
             y2 = DIM == 3 ? (y1 == L - 1 ? 0 : y1 + 1) : 0;
             z2 = DIM == 3 ? (y1 == L - 1 ? z1 + 1 : z1) : z1 + 1;
         }
+        // offsets of the neighbours for the sites of the first and of the second row
+        auto off = [&](int k, int y, int z) -> I {
+            if (k == 0) return z == L - 1 ? P - N : P;
+            if (k == 1) return z == 0 ? N - P : -P;
+            if (k == 2) return y == L - 1 ? LL - P : LL;
+            return y == 0 ? P - LL : -LL;
+        };
+        I d1[kDir], d2[kDir];
+        bool over = i0 > N - 16, split = false;  // a load beyond the array; two offsets in one piece
+#pragma unroll
+        for (int k = 0; k < kDir; ++k) {
+            d1[k] = off(k, y1, z1);
+            d2[k] = off(k, y2, z2);
+            over |= i0 + d1[k] < 0 || i0 + d1[k] > N - 16;
+            split |= d1[k] != d2[k];
+        }
+        split &= border;
+
+        // every load of the ordinary case
+        uint4 w = load_inside(S, i0, N), nb[kDir], jx, jf[DIM - 1], jb[kDir / 2];
+#pragma unroll
+        for (int k = 0; k < kDir; ++k) nb[k] = load_inside(S, i0 + d1[k], N);
+        const I iL = x0 == 0 ? i0 + L - 1 : i0 - 1, s2 = i0 + left, e2 = s2 + L - 1;
+        uint32_t eL = (uint8_t)S[iL], eR = (uint8_t)S[left == 16 ? i0 + 16 - L : i0 + 16 < N ? i0 + 16 : i0];
+        uint32_t wR = 0, wL = 0, jeL = 0, jwL = 0;
+        if constexpr (EA) {
+            jx = load_inside(J, i0, N);
+            jeL = (uint8_t)J[iL];
+#pragma unroll
+            for (int k = 0; k < kDir / 2; ++k) {
+                const int8_t *Jm = J + (int64_t)(k == 0 ? DIM - 1 : 1) * N;
+                jf[k] = load_inside(Jm, i0, N);                // bonds forward
+                jb[k] = load_inside(Jm, i0 + d1[2 * k + 1], N);  // bonds of the neighbours behind
+            }
+        }
+        if (left < 16) {
+            wR = (uint8_t)S[s2 - L];  // the first row's periodic end
+            if (border) {
+                wL = (uint8_t)S[e2];  // the second row's periodic start
+                if constexpr (EA) jwL = (uint8_t)J[e2];
+            }
+        }
+        if (__builtin_expect(over, 0)) {
+            into_place(w, i0, N);
+#pragma unroll
+            for (int k = 0; k < kDir; ++k) into_place(nb[k], i0 + d1[k], N);
+            if constexpr (EA) {
+                into_place(jx, i0, N);
+#pragma unroll
+                for (int k = 0; k < kDir / 2; ++k) {
+                    into_place(jf[k], i0, N);
+                    into_place(jb[k], i0 + d1[2 * k + 1], N);
+                }
+            }
+        }
+        if (split) {
+            // bytes 2b .. 15 of the neighbours come from the second row's offset
+            const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u), m = bytes_up(ones, 2 * b);
+            auto second_from = [&](uint4 &v, const int8_t *p, I i) {
+                const uint4 u = load16(p, (int64_t)i, (int64_t)N);
+                v = make_uint4((u.x & m.x) | (v.x & ~m.x), (u.y & m.y) | (v.y & ~m.y), (u.z & m.z) | (v.z & ~m.z),
+                               (u.w & m.w) | (v.w & ~m.w));
+            };
+#pragma unroll
+            for (int k = 0; k < kDir; ++k)
+                if (d1[k] != d2[k]) {
+                    second_from(nb[k], S, i0 + d2[k]);
+                    if constexpr (EA)
+                        if (k & 1) second_from(jb[k >> 1], J + (int64_t)(k == 1 ? DIM - 1 : 1) * N, i0 + d2[k]);
+                }
+        }
+
         const bool A1 = (((y1 + z1) & 1) ^ c) != 0, A2 = (((y2 + z2) & 1) ^ c) != 0;  // own sites odd in x
         const b8 second = from_pair(b);
         const b8 odd_own = (A1 ? ~second : 0ull) | (A2 ? second : 0ull);
-
-        const uint4 w = load16(S, i0, N);
         const b8 E = even8(w), O = odd8(w);
         const b8 own = merge(odd_own, O, E), oth = merge(odd_own, E, O);
         // x neighbours in the next pair (own sites odd) or the one before (even)
-        const uint32_t eL = (uint8_t)S[x0 == 0 ? i0 + L - 1 : i0 - 1];
-        const uint32_t eR = (uint8_t)S[left == 16 ? i0 + 16 - L : i0 + 16 < N ? i0 + 16 : i0];
-        b8 up = (O << 8) | eL, down = (E >> 8) | ((b8)eR << 56);
-        const int64_t s2 = i0 + left, e2 = s2 + L - 1;  // ends of the second row
-        const bool border = left < 16 && n > left;      // the piece holds sites of two rows
-        if (left < 16) down = put_byte(down, b - 1, (uint8_t)S[s2 - L]);
-        if (border) up = put_byte(up, b, (uint8_t)S[e2]);
-        const b8 sh = merge(odd_own, down, up);
-
-        // the neighbour sites (or their bonds) at offset d1 for the first row, d2 for the second
-        auto beside = [&](const int8_t *p, int64_t d1, int64_t d2) {
-            const uint4 v = load16(p, i0 + d1, N);
-            b8 s = merge(odd_own, odd8(v), even8(v));
-            if (border && d2 != d1) {
-                const uint4 v2 = load16(p, i0 + d2, N);
-                s = merge(second, merge(odd_own, odd8(v2), even8(v2)), s);
-            }
-            return s;
-        };
-        const int64_t zp1 = z1 == L - 1 ? P - N : P, zp2 = z2 == L - 1 ? P - N : P;
-        const int64_t zm1 = z1 == 0 ? N - P : -P, zm2 = z2 == 0 ? N - P : -P;
-        const int64_t yp1 = y1 == L - 1 ? LL - P : LL, yp2 = y2 == L - 1 ? LL - P : LL;
-        const int64_t ym1 = y1 == 0 ? P - LL : -LL, ym2 = y2 == 0 ? P - LL : -LL;
+        b8 up = (O << 8) | eL, down = (E >> 8) | ((b8)eR << 56), jup = 0;
+        if (left < 16) {
+            down = put_byte(down, b - 1, wR);
+            if (border) up = put_byte(up, b, wL);
+        }
         uint32_t n0 = 0, n1 = 0;  // twice the unsatisfied bonds of each own site
-        auto count = [&](b8 nb, b8 bond) {
-            const uint2 s = to_u2(own ^ bond), v = to_u2(nb);
+        auto count = [&](b8 v8, b8 bond) {
+            const uint2 s = to_u2(own ^ bond), v = to_u2(v8);
             n0 += unsat(s.x, v.x, 0x02020202u);
             n1 += unsat(s.y, v.y, 0x02020202u);
         };
+        auto mine = [&](const uint4 &v) { return merge(odd_own, odd8(v), even8(v)); };
         if constexpr (EA) {
-            const uint4 jw = load16(J, i0, N);
-            const b8 jE = even8(jw), jO = odd8(jw);
-            b8 jup = (jO << 8) | (uint8_t)J[x0 == 0 ? i0 + L - 1 : i0 - 1];
-            if (border) jup = put_byte(jup, b, (uint8_t)J[e2]);
+            const b8 jE = even8(jx), jO = odd8(jx);
+            jup = (jO << 8) | jeL;
+            if (border) jup = put_byte(jup, b, jwL);
             count(oth, jE);
-            count(sh, merge(odd_own, jO, jup));
-            const int8_t *Jz = J + (DIM - 1) * N;
-            count(beside(S, zp1, zp2), beside(Jz, 0, 0));
-            count(beside(S, zm1, zm2), beside(Jz, zm1, zm2));
-            if constexpr (DIM == 3) {
-                count(beside(S, yp1, yp2), beside(J + N, 0, 0));
-                count(beside(S, ym1, ym2), beside(J + N, ym1, ym2));
+            count(merge(odd_own, down, up), merge(odd_own, jO, jup));
+#pragma unroll
+            for (int k = 0; k < kDir / 2; ++k) {
+                count(mine(nb[2 * k]), mine(jf[k]));
+                count(mine(nb[2 * k + 1]), mine(jb[k]));
             }
         } else {
             count(oth, 0ull);
-            count(sh, 0ull);
-            count(beside(S, zp1, zp2), 0ull);
-            count(beside(S, zm1, zm2), 0ull);
-            if constexpr (DIM == 3) {
-                count(beside(S, yp1, yp2), 0ull);
-                count(beside(S, ym1, ym2), 0ull);
-            }
+            count(merge(odd_own, down, up), 0ull);
+#pragma unroll
+            for (int k = 0; k < kDir; ++k) count(mine(nb[k]), 0ull);
         }
 
         // Table by the count of unsatisfied bonds: Delta E = 4 (DIM - count).
@@ -165,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void k_half_sweep_pieces(SweepArgs a, int
                 if (n > 8) __builtin_memcpy(S + i0 + 8, &out.z, 4);
             }
             // flip_energy counts 12 - 4 n per flip; in 2D it is 8 - 4 n
-            dE = flip_energy(o);
+            dE = (int)flip_energy(o);
             if constexpr (DIM == 2) dE -= 4 * (__popc(o.F0) + __popc(o.F1));
         }
     }
@@ -175,7 +237,7 @@ __global__ __launch_bounds__(kThreads) void k_half_sweep_pieces(SweepArgs a, int
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dE;
         __syncthreads();
         if (threadIdx.x == 0) {
-            const long long tot = red[0] + red[1] + red[2] + red[3];
+            const long long tot = (long long)red[0] + red[1] + red[2] + red[3];
             if (tot != 0) atomicAdd((unsigned long long *)&a.dE[r], (unsigned long long)tot);
         }
     }
@@ -191,16 +253,22 @@ hipError_t launch_half_sweep_pieces(const SweepArgs &a, int c, hipStream_t s) {
         return reject_launch("k_half_sweep_pieces", (uint64_t)blocks, kThreads, 0, why);
     const dim3 grid((unsigned)blocks);
     const uint32_t one2 = 0x00010001u;
+    const bool ea = a.coup != nullptr;
     if (a.b.dim == 3) {
-        if (a.coup)
-            SMC_LAUNCH((k_half_sweep_pieces<3, true>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+        if (ea)
+            SMC_LAUNCH((k_half_sweep_pieces<3, true, int>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
         else
-            SMC_LAUNCH((k_half_sweep_pieces<3, false>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+            SMC_LAUNCH((k_half_sweep_pieces<3, false, int>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+    } else if (N <= ((int64_t)1 << 30)) {
+        if (ea)
+            SMC_LAUNCH((k_half_sweep_pieces<2, true, int>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+        else
+            SMC_LAUNCH((k_half_sweep_pieces<2, false, int>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
     } else {
-        if (a.coup)
-            SMC_LAUNCH((k_half_sweep_pieces<2, true>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+        if (ea)
+            SMC_LAUNCH((k_half_sweep_pieces<2, true, int64_t>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
         else
-            SMC_LAUNCH((k_half_sweep_pieces<2, false>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
+            SMC_LAUNCH((k_half_sweep_pieces<2, false, int64_t>), grid, dim3(kThreads), 0, s, a, c, bpr, one2);
     }
     return hipGetLastError();
 }
