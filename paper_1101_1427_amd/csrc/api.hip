@@ -336,6 +336,54 @@ int run_sweep_lds2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Pla
     return SMC_OK;
 }
 
+// The per-replica sums of one sweep call.  With fewer than 16 workgroups per
+// replica and launch they add to the caller's total directly (16 additions
+// to one address take about a microsecond, the collecting launch takes
+// more); otherwise each keeps a slot, collected once by finish().
+struct CallTally {
+    Tally t{nullptr, nullptr, 0};
+    int n_rep = 0, groups = 0;
+
+    int begin(StreamCtx &c, int reps, int groups_per_rep, int64_t *total) {
+        n_rep = reps;
+        groups = groups_per_rep;
+        t.total = total;
+        t.first = 1;
+        if (!total || groups < 16) return SMC_OK;
+        void *p = nullptr;
+        if (int rc = ensure(c, kTallySlots, sizeof(int64_t) * (size_t)n_rep * (size_t)groups, &p)) return rc;
+        t.slots = (int64_t *)p;
+        return SMC_OK;
+    }
+    // The tally of the next launch.
+    Tally next() {
+        const Tally now = t;
+        t.first = 0;
+        return now;
+    }
+    int finish(hipStream_t s) {
+        if (t.slots) SMC_HIP(launch_collect(t.slots, t.total, n_rep, groups, false, s));
+        return SMC_OK;
+    }
+};
+
+// The generic half-sweeps of a call.
+int run_generic(StreamCtx &c, hipStream_t s, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps, int64_t *dE) {
+    CallTally tally;
+    int rc = tally.begin(c, a.b.n_rep, half_sweep_groups(a), dE);
+    if (rc) return rc;
+    SweepTimer timer(s, 2 * (int64_t)n_sweeps);
+    for (int32_t k = 0; k < n_sweeps; ++k) {
+        a.t = (uint32_t)(sweep0 + (uint64_t)k);
+        for (int col = 0; col < 2; ++col) {
+            a.tally = tally.next();
+            SMC_HIP(launch_half_sweep_generic(a, col, s));
+        }
+    }
+    timer.finish();
+    return tally.finish(s);
+}
+
 }  // namespace
 }  // namespace smc
 
@@ -560,7 +608,6 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.spins = spins;
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
-    a.dE = dE_accum;
     a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
@@ -576,6 +623,8 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             void *pp = nullptr;
             if ((rc = ensure(c, kHeisPing, bytes, &pp))) return rc;
             float *A = (float *)spins, *B = (float *)pp;
+            CallTally tally;
+            if ((rc = tally.begin(c, desc->n_rep, heis3d_tiled_groups(desc->L), dE_accum))) return rc;
             SweepTimer timer(s, n_sweeps);
             for (int32_t k = 0; k < n_sweeps; ++k) {
                 a.t = (uint32_t)(sweep0 + (uint64_t)k);
@@ -583,20 +632,25 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
                 // the renormalisation is applied as the sweep stores its spins
                 const bool renorm =
                     desc->renorm_every > 0 && ((uint64_t)a.t + 1) % (uint64_t)desc->renorm_every == 0;
-                SMC_HIP(launch_heis3d_tiled(src, dst, a.beta_f, dE_accum, desc->n_rep, desc->L, a.key, a.t, renorm,
-                                            s));
+                SMC_HIP(launch_heis3d_tiled(src, dst, a.beta_f, tally.next(), desc->n_rep, desc->L, a.key, a.t,
+                                            renorm, s));
             }
             timer.finish();
+            if ((rc = tally.finish(s))) return rc;
             if (n_sweeps & 1) SMC_HIP(hipMemcpyAsync(A, B, bytes, hipMemcpyDeviceToDevice, s));
             return SMC_OK;
         }
-        SweepTimer timer(s, 2 * (int64_t)n_sweeps);  // the renormalisations run inside the same pair
         const bool fast = use_heis3d(desc);
+        CallTally tally;
+        if ((rc = tally.begin(c, desc->n_rep, fast ? heis3d_half_groups(desc->L) : heis_half_sweep_groups(a), dE_accum)))
+            return rc;
+        SweepTimer timer(s, 2 * (int64_t)n_sweeps);  // the renormalisations run inside the same pair
         for (int32_t k = 0; k < n_sweeps; ++k) {
             a.t = (uint32_t)(sweep0 + (uint64_t)k);
             for (int col = 0; col < 2; ++col) {
+                a.tally = tally.next();
                 if (fast)
-                    SMC_HIP(launch_heis3d_half((float *)spins, a.beta_f, dE_accum, desc->n_rep, desc->L, a.key, a.t,
+                    SMC_HIP(launch_heis3d_half((float *)spins, a.beta_f, a.tally, desc->n_rep, desc->L, a.key, a.t,
                                                col, s));
                 else
                     SMC_HIP(launch_heis_half_sweep_generic(a, col, s));
@@ -604,7 +658,8 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             if (desc->renorm_every > 0 && ((uint64_t)a.t + 1) % (uint64_t)desc->renorm_every == 0)
                 SMC_HIP(launch_heis_renorm(plan.b, (float *)spins, plan.max_L, s));
         }
-        return SMC_OK;
+        timer.finish();
+        return tally.finish(s);
     }
     std::vector<ThrRow> rows(desc->n_rep);
     for (int r = 0; r < desc->n_rep; ++r) rows[r] = threshold_row(beta[r], desc->dim);
@@ -683,32 +738,36 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             void *q = nullptr;
             if ((rc = ensure(c, kPass3d, bytes, &q))) return rc;
             int8_t *A = (int8_t *)spins, *B = (int8_t *)q;
+            Shape shape{{0, 0, 0}};
+            if (!pass3d_launch_shape(desc->L, packed != nullptr, desc->n_rep, &shape))
+                return fail(SMC_EINVAL, "no strip shape for L=%d", desc->L);
+            CallTally tally;
+            if ((rc = tally.begin(c, desc->n_rep, pass3d_groups(desc->L, shape), dE_accum))) return rc;
             SweepTimer timer(s, n_sweeps);
             for (int32_t k = 0; k < n_sweeps; ++k) {
                 const uint32_t t = (uint32_t)(sweep0 + (uint64_t)k);
                 SMC_HIP(launch_ising3d_pass(k & 1 ? B : A, k & 1 ? A : B, packed, plan.b.rep_per_sample, a.thr,
-                                            dE_accum, desc->n_rep, desc->L, a.key, t, s));
+                                            tally.next(), desc->n_rep, desc->L, a.key, t, shape, s));
             }
             timer.finish();
+            if ((rc = tally.finish(s))) return rc;
             if (n_sweeps & 1) SMC_HIP(hipMemcpyAsync(A, B, bytes, hipMemcpyDeviceToDevice, s));
             return SMC_OK;
         }
+        const int Z = sweep3d_rows(desc->L, desc->model == SMC_EA, desc->n_rep);
+        CallTally tally;
+        if ((rc = tally.begin(c, desc->n_rep, sweep3d_groups(desc->L, Z), dE_accum))) return rc;
         SweepTimer timer(s, 2 * (int64_t)n_sweeps);
         for (int32_t k = 0; k < n_sweeps; ++k) {
             const uint32_t t = (uint32_t)(sweep0 + (uint64_t)k);
             for (int col = 0; col < 2; ++col)
-                SMC_HIP(launch_ising3d_half((int8_t *)spins, coup8, packed, plan.b.rep_per_sample, a.thr, dE_accum,
-                                            desc->n_rep, desc->L, a.key, t, col, s));
+                SMC_HIP(launch_ising3d_half((int8_t *)spins, coup8, packed, plan.b.rep_per_sample, a.thr,
+                                            tally.next(), desc->n_rep, desc->L, a.key, t, col, Z, s));
         }
-        return SMC_OK;
+        timer.finish();
+        return tally.finish(s);
     }
-    SweepTimer timer(s, 2 * (int64_t)n_sweeps);
-    for (int32_t k = 0; k < n_sweeps; ++k) {
-        a.t = (uint32_t)(sweep0 + (uint64_t)k);
-        SMC_HIP(launch_half_sweep_generic(a, 0, s));
-        SMC_HIP(launch_half_sweep_generic(a, 1, s));
-    }
-    return SMC_OK;
+    return run_generic(c, s, a, sweep0, n_sweeps, dE_accum);
 }
 
 int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, const double *beta, uint64_t sweep0,
@@ -780,18 +839,11 @@ int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
     a.coup = ea ? couplings : nullptr;
     a.thr = (const ThrRow *)p;
     a.key = make_key(desc->seed);
-    a.dE = dE_accum;
     a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     a.rng_shift = word_bits == 64 ? 6 : 5;  // the draw group r / word_bits
-    SweepTimer timer(s, 2 * (int64_t)n_sweeps);
-    for (int32_t k = 0; k < n_sweeps; ++k) {
-        a.t = (uint32_t)(sweep0 + (uint64_t)k);
-        SMC_HIP(launch_half_sweep_generic(a, 0, s));
-        SMC_HIP(launch_half_sweep_generic(a, 1, s));
-    }
-    return SMC_OK;
+    return run_generic(c, s, a, sweep0, n_sweeps, dE_accum);
 }
 
 // The packed double-checkerboard kernel: thresholds with 16-bit high halves,
@@ -890,11 +942,11 @@ int smc_dcb_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
                                      make_key(desc->seed), (uint32_t)t, rev ? 1 - ci : ci, rev, packed, s));
         }
         if (dE_trace)
-            SMC_HIP(launch_dcb_collect((const int64_t *)sp, dE_trace + (int64_t)m * desc->n_rep, desc->n_rep, per_rep,
+            SMC_HIP(launch_collect((const int64_t *)sp, dE_trace + (int64_t)m * desc->n_rep, desc->n_rep, per_rep,
                                        true, s));
     }
     timer.finish();
-    if (dE_accum) SMC_HIP(launch_dcb_collect((const int64_t *)sp, dE_accum, desc->n_rep, per_rep, false, s));
+    if (dE_accum) SMC_HIP(launch_collect((const int64_t *)sp, dE_accum, desc->n_rep, per_rep, false, s));
     return SMC_OK;
 }
 
@@ -953,7 +1005,7 @@ int smc_heis_dcb_sweep(const smc_desc *desc, void *spins, const double *beta, ui
             SMC_HIP(launch_heis_dcb_renorm(spins, n_spins, precision, s));
     }
     timer.finish();
-    if (accepts) SMC_HIP(launch_dcb_collect((const int64_t *)sp, accepts, desc->n_rep, per_rep, false, s));
+    if (accepts) SMC_HIP(launch_collect((const int64_t *)sp, accepts, desc->n_rep, per_rep, false, s));
     return SMC_OK;
 }
 
@@ -1183,7 +1235,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     a.spins = spins;
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
-    a.dE = (int64_t *)E64;
+    a.tally.total = (int64_t *)E64;
     a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.thr = (const ThrRow *)thr;

@@ -495,22 +495,6 @@ __global__ __launch_bounds__(256) void k_dcb_zero(int64_t *p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-// dE[r] = (assign) or += the sum of replica r's slots.
-__global__ __launch_bounds__(256) void k_dcb_collect(const int64_t *slots, int64_t *dE, int per_rep, int assign) {
-    __shared__ long long red[4];
-    const int r = (int)blockIdx.x;
-    long long v = 0;
-    for (int i = (int)threadIdx.x; i < per_rep; i += 256) v += slots[(int64_t)r * per_rep + i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const long long sum = red[0] + red[1] + red[2] + red[3];
-        dE[r] = assign ? sum : dE[r] + sum;
-    }
-}
-
 }  // namespace
 
 bool dcb2d_supported(int L, int T) {
@@ -527,11 +511,6 @@ int dcb2d_tiles_per_colour(int L, int T) {
 hipError_t launch_dcb_zero(int64_t *p, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     SMC_LAUNCH(k_dcb_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_dcb_collect(const int64_t *slots, int64_t *dE, int n_rep, int per_rep, bool assign, hipStream_t s) {
-    SMC_LAUNCH(k_dcb_collect, dim3((unsigned)n_rep), dim3(256), 0, s, slots, dE, per_rep, assign ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -153,10 +153,9 @@ __global__ __launch_bounds__(kBlock) void k_half_sweep_generic(SweepArgs a, int 
             dE = d;
         }
     }
-    if (a.dE) {
+    if (tally_wanted(a.tally)) {
         const long long tot = block_sum_ll(dE, red);
-        if (threadIdx.x == 0 && tot != 0)
-            atomicAdd((unsigned long long *)&a.dE[r], (unsigned long long)tot);
+        if (threadIdx.x == 0) tally_put(a.tally, blockIdx.x, r, tot);
     }
 }
 
@@ -207,10 +206,9 @@ __global__ __launch_bounds__(kBlock) void k_heis_half_sweep_generic(SweepArgs a,
             n_acc = 1;
         }
     }
-    if (a.dE) {
+    if (tally_wanted(a.tally)) {
         const long long tot = block_sum_ll(n_acc, red);
-        if (threadIdx.x == 0 && tot != 0)
-            atomicAdd((unsigned long long *)&a.dE[r], (unsigned long long)tot);
+        if (threadIdx.x == 0) tally_put(a.tally, blockIdx.x, r, tot);
     }
 }
 
@@ -317,13 +315,23 @@ hipError_t launch_init_couplings(int dim, int n_samples, const smc_inst *samples
 // A piece of 16 sites spans at most two rows when every edge is at least 16;
 // smaller edges keep a thread per pair of sites, and so does
 // SPINMC_PIECES=0 (same results).
-hipError_t launch_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s) {
+static bool use_pieces(const SweepArgs &a) {
     const char *env = getenv("SPINMC_PIECES");
-    if (a.min_L >= 16 && !(env && env[0] == '0')) return launch_half_sweep_pieces(a, c, s);
+    return a.min_L >= 16 && !(env && env[0] == '0');
+}
+
+int half_sweep_groups(const SweepArgs &a) {
+    return use_pieces(a) ? pieces_groups(a) : blocks_for(sites_of(a.b.dim, a.max_L) / 2);
+}
+
+hipError_t launch_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s) {
+    if (use_pieces(a)) return launch_half_sweep_pieces(a, c, s);
     const int bpr = blocks_for(sites_of(a.b.dim, a.max_L) / 2);
     SMC_LAUNCH(k_half_sweep_generic, dim3(bpr * a.b.n_rep), dim3(kBlock), 0, s, a, c, bpr);
     return hipGetLastError();
 }
+
+int heis_half_sweep_groups(const SweepArgs &a) { return blocks_for(sites_of(a.b.dim, a.max_L) / 2); }
 
 hipError_t launch_heis_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s) {
     const int bpr = blocks_for(sites_of(a.b.dim, a.max_L) / 2);

@@ -17,7 +17,7 @@ constexpr int kThreads = 256;
 struct Heis3dArgs {
     float *spins;       // [n_rep][N][3]
     const float *beta;  // per replica (float32)
-    int64_t *acc;       // per replica: += accepted moves, or nullptr
+    Tally acc;          // accepted moves
     Key key;
     uint32_t t;
     int lgL;            // log2 of the edge
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_heis3d_half(Heis3dArgs a, int c) {
             ++n_acc;
         }
     }
-    if (a.acc) {
+    if (tally_wanted(a.acc)) {
         int v = n_acc;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void k_heis3d_half(Heis3dArgs a, int c) {
         __syncthreads();
         if (threadIdx.x == 0) {
             const int tot = red[0] + red[1] + red[2] + red[3];
-            if (tot) atomicAdd((unsigned long long *)&a.acc[r], (unsigned long long)tot);
+            tally_put(a.acc, blockIdx.x, r, tot);
         }
     }
 }
@@ -145,7 +145,7 @@ struct TiledArgs {
     const float *src;  // [n_rep][N][3]
     float *dst;
     const float *beta;
-    int64_t *acc;
+    Tally acc;  // accepted moves
     Key key;
     uint32_t t;
     int lgL;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
             }
         }
     }
-    if (a.acc) {
+    if (tally_wanted(a.acc)) {
         int v = n_acc;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
         if (threadIdx.x == 0) {
             int tot = 0;
             for (int w = 0; w < kTiledThreads / 64; ++w) tot += red[w];
-            if (tot) atomicAdd((unsigned long long *)&a.acc[r], (unsigned long long)tot);
+            tally_put(a.acc, lb, r, tot);
         }
     }
 }
@@ -352,7 +352,12 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
 
 bool heis3d_supported(int dim, int L) { return dim == 3 && L >= 4 && L <= 1024 && (L & (L - 1)) == 0; }
 
-hipError_t launch_heis3d_half(float *spins, const float *beta, int64_t *acc, int n_rep, int L, Key key, uint32_t t,
+int heis3d_half_groups(int L) {
+    const int64_t pairs = (int64_t)L * L * L / 2;
+    return (int)((pairs + kThreads * kSitesPerThread - 1) / (kThreads * kSitesPerThread));
+}
+
+hipError_t launch_heis3d_half(float *spins, const float *beta, const Tally &acc, int n_rep, int L, Key key, uint32_t t,
                               int c, hipStream_t s) {
     Heis3dArgs a;
     a.spins = spins;
@@ -363,16 +368,18 @@ hipError_t launch_heis3d_half(float *spins, const float *beta, int64_t *acc, int
     a.lgL = 0;
     while ((1 << a.lgL) < L) ++a.lgL;
     a.N = (int64_t)L * L * L;
-    a.bpr = (int)((a.N / 2 + kThreads * kSitesPerThread - 1) / (kThreads * kSitesPerThread));
+    a.bpr = heis3d_half_groups(L);
     SMC_LAUNCH(k_heis3d_half, dim3((unsigned)(a.bpr * n_rep)), dim3(kThreads), 0, s, a, c);
     return hipGetLastError();
 }
 
 bool heis3d_tiled_supported(int dim, int L) { return heis3d_supported(dim, L) && L >= kTile; }
 
+int heis3d_tiled_groups(int L) { return (L / kTile) * (L / kTile) * (L > kSeg ? L / kSeg : 1); }
+
 size_t heis3d_tiled_lds_bytes() { return (size_t)kRing * 3 * kPlane * sizeof(float); }
 
-hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, int64_t *acc, int n_rep, int L, Key key,
+hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, const Tally &acc, int n_rep, int L, Key key,
                                uint32_t t, bool renorm, hipStream_t s) {
     TiledArgs a;
     a.renorm = renorm ? 1 : 0;

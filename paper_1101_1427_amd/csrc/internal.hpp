@@ -10,6 +10,7 @@
 #include "launch_check.hpp"
 #include "philox.hpp"
 #include "tables.hpp"
+#include "tally.hpp"
 
 namespace smc {
 
@@ -66,7 +67,7 @@ struct SweepArgs {
     const int32_t *row_of_rep; // nullptr: row = replica index
     Key key;
     uint32_t t;                // sweep index
-    int64_t *dE;               // nullable per-replica accumulator
+    Tally tally;               // energy changes (accepted moves: Heisenberg)
     int min_L, max_L;          // smallest and largest edge in the batch
     int rng_shift;             // the Metropolis draws of replica r use index r >> rng_shift
 };
@@ -94,17 +95,23 @@ hipError_t launch_init_couplings(int dim, int n_samples, const smc_inst *samples
 // per pair of sites otherwise.
 hipError_t launch_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s);
 hipError_t launch_half_sweep_pieces(const SweepArgs &a, int c, hipStream_t s);
+// Workgroups per replica of the half-sweep launches above.
+int half_sweep_groups(const SweepArgs &a);
+int pieces_groups(const SweepArgs &a);
+int heis_half_sweep_groups(const SweepArgs &a);
 hipError_t launch_heis_half_sweep_generic(const SweepArgs &a, int c, hipStream_t s);
 hipError_t launch_heis_renorm(const Batch &b, float *spins, int max_L, hipStream_t s);
 
 // Heisenberg half-sweeps of uniform 3D batches with a power-of-two edge.
 bool heis3d_supported(int dim, int L);
-hipError_t launch_heis3d_half(float *spins, const float *beta, int64_t *acc, int n_rep, int L, Key key, uint32_t t,
+int heis3d_half_groups(int L);  // workgroups per replica
+hipError_t launch_heis3d_half(float *spins, const float *beta, const Tally &acc, int n_rep, int L, Key key, uint32_t t,
                               int c, hipStream_t s);
 // One-pass (tiled, colour 0 then colour 1 in one launch) sweep from src to dst, L >= 32;
 // with renorm the spins written to dst are renormalised.
 bool heis3d_tiled_supported(int dim, int L);
-hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, int64_t *acc, int n_rep, int L, Key key,
+int heis3d_tiled_groups(int L);  // workgroups per replica
+hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, const Tally &acc, int n_rep, int L, Key key,
                                uint32_t t, bool renorm, hipStream_t s);
 
 // Parallel tempering of 3D edge-16 chains, all steps in one launch.
@@ -174,8 +181,6 @@ hipError_t launch_dcb2d(int8_t *spins, const int8_t *coup, int rep_per_sample, c
                         int n_rep, int L, int T, int k, Key key, uint32_t t, int tile_colour, bool rev, bool packed,
                         hipStream_t s);
 hipError_t launch_dcb_zero(int64_t *p, int64_t n, hipStream_t s);
-// dE[r] = (assign) or += (otherwise) the sum of replica r's slots.
-hipError_t launch_dcb_collect(const int64_t *slots, int64_t *dE, int n_rep, int per_rep, bool assign, hipStream_t s);
 
 // Half-sweeps of uniform 3D Ising / EA batches with L a multiple of 16
 // (sweep3d.hip): in place, 16-byte aligned spins and couplings, threshold
@@ -184,11 +189,12 @@ hipError_t launch_dcb_collect(const int64_t *slots, int64_t *dE, int n_rep, int 
 // launch_pack_bonds3d: [sample][L^3 / 16] uint2), the other nullptr.
 bool sweep3d_supported(int L);
 hipError_t launch_pack_bonds3d(const int8_t *coup, uint2 *out, int L, int n_samples, hipStream_t s);
-// Rows per thread along z of the next half-sweep of this batch.
+// Rows per thread along z for this batch (chosen once per call).
 int sweep3d_rows(int L, bool ea, int n_rep);
+int sweep3d_groups(int L, int Z);  // workgroups per replica
 hipError_t launch_ising3d_half(int8_t *spins, const int8_t *coup, const uint2 *pbonds, int rep_per_sample,
-                               const ThrRow *thr, int64_t *dE, int n_rep, int L, Key key, uint32_t t, int c,
-                               hipStream_t s);
+                               const ThrRow *thr, const Tally &dE, int n_rep, int L, Key key, uint32_t t, int c,
+                               int Z, hipStream_t s);
 
 // 3D double checkerboard (dcb3d.hip): 16^3 tiles, L / 16 even or 1.
 bool dcb3d_supported(int L, int T);
@@ -249,12 +255,13 @@ bool pass3d_supported(int L);
 // Whether (rows per strip, segments per thread, planes per z segment) is a
 // launch shape of the one-pass sweep for this edge and model.
 bool pass3d_shape_valid(int L, bool ea, int ty, int segs, int D);
-// The launch shape the next one-pass sweep of this batch takes (false if
-// the edge has none).
+// The launch shape for this batch, chosen once per call (false if the edge
+// has none).
 bool pass3d_launch_shape(int L, bool ea, int n_rep, Shape *out);
+int pass3d_groups(int L, const Shape &shape);  // workgroups per replica
 hipError_t launch_ising3d_pass(const int8_t *src, int8_t *dst, const uint2 *pbonds, int rep_per_sample,
-                               const ThrRow *thr, int64_t *dE, int n_rep, int L, Key key, uint32_t t,
-                               hipStream_t s);
+                               const ThrRow *thr, const Tally &dE, int n_rep, int L, Key key, uint32_t t,
+                               const Shape &shape, hipStream_t s);
 
 // ---- random-number study (rngstudy.hip) ----
 bool rng_study_lags(int gen, int *r, int *s);

@@ -650,32 +650,6 @@ __global__ __launch_bounds__(256) void k_from_split(const uint8_t *src, int8_t *
     *(uint4 *)(dst + r * N + (int64_t)y * L + 16 * xc) = v;
 }
 
-// Energy changes of a call: replica r adds the partial sums of its
-// workgroups' compute waves (slots [r * per_rep, (r + 1) * per_rep)).  One
-// workgroup per replica, so the update of dE[r] needs no atomics.
-// One workgroup per replica adds its per-wave slots (8192 at 16384^2 with
-// 16-row bands).  1024 threads with their loads unrolled keep the few
-// memory round trips in flight together: a serial loop of 32 dependent
-// round trips per thread took 15 us per call.
-__global__ __launch_bounds__(1024) void k_de_collect(const int64_t *part, int64_t *dE, int per_rep) {
-    __shared__ long long red[16];
-    const int r = (int)blockIdx.x;
-    const int64_t *p = part + (int64_t)r * per_rep;
-    long long v = 0;
-#pragma unroll 8
-    for (int i = (int)threadIdx.x; i < per_rep; i += 1024) v += p[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long tot = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) tot += red[w];
-        dE[r] += tot;
-    }
-}
-
 }  // namespace
 
 // Launch shape: chunks of 16 x-positions per lane (one workgroup spans a
@@ -795,8 +769,7 @@ size_t lattice2d_de_slots(int L, int n_rep) {
 hipError_t launch_lattice2d_de_collect(const int64_t *part, int64_t *dE, int L, int n_rep, hipStream_t s) {
     const size_t slots = lattice2d_de_slots(L, n_rep);
     if (slots == 0 || n_rep <= 0) return hipErrorInvalidValue;
-    SMC_LAUNCH(k_de_collect, dim3((unsigned)n_rep), dim3(1024), 0, s, part, dE, (int)(slots / n_rep));
-    return hipGetLastError();
+    return launch_collect(part, dE, n_rep, (int)(slots / n_rep), false, s);
 }
 
 hipError_t launch_ising2d_split(const void *src, bool src_rows, void *dst, bool dst_rows, int L, int n_rep,

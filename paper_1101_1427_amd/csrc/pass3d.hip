@@ -67,7 +67,7 @@ struct Pass3dArgs {
     const uint2 *pbonds;   // EA: bit-packed bonds [sample][L^3 / 16] (pack_bonds3d), else nullptr
     int rep_per_sample;
     const ThrRow *thr;     // per replica (high halves <= 0xFFFF)
-    unsigned long long *dE;  // per replica, or nullptr
+    Tally dE;              // energy changes
     Key key;
     uint32_t t;
     int L, D;              // edge; planes per z segment
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(pass3d_max_threads(TY, SEGS)) void k_ising3d_pass(P
         if (threadIdx.x == 0) {
             long long tot = 0;
             for (int w = 0; w < (int)((blockDim.x + 63) >> 6); ++w) tot += red[w];
-            if (tot != 0) atomicAdd(&a.dE[r], (unsigned long long)tot);
+            tally_put(a.dE, lb, r, tot);
         }
     }
 }
@@ -429,11 +429,14 @@ bool pass3d_shape_valid(int L, bool ea, int ty, int segs, int D) {
     return shape_fits(L, ea, ty, segs, D, &threads);
 }
 
+int pass3d_groups(int L, const Shape &shape) { return (L / shape.v[0]) * (L / shape.v[2]); }
+
 hipError_t launch_ising3d_pass(const int8_t *src, int8_t *dst, const uint2 *pbonds, int rep_per_sample,
-                               const ThrRow *thr, int64_t *dE, int n_rep, int L, Key key, uint32_t t,
-                               hipStream_t s) {
-    int ty, segs, D, threads;
-    if (n_rep < 1 || src == dst || !pass3d_shape(L, pbonds != nullptr, n_rep, &ty, &segs, &D, &threads))
+                               const ThrRow *thr, const Tally &dE, int n_rep, int L, Key key, uint32_t t,
+                               const Shape &shape, hipStream_t s) {
+    const int ty = shape.v[0], segs = shape.v[1], D = shape.v[2];
+    int threads;
+    if (n_rep < 1 || src == dst || !shape_fits(L, pbonds != nullptr, ty, segs, D, &threads))
         return hipErrorInvalidValue;
     Pass3dArgs a;
     a.src = src;
@@ -441,7 +444,7 @@ hipError_t launch_ising3d_pass(const int8_t *src, int8_t *dst, const uint2 *pbon
     a.pbonds = pbonds;
     a.rep_per_sample = rep_per_sample;
     a.thr = thr;
-    a.dE = (unsigned long long *)dE;
+    a.dE = dE;
     a.key = key;
     a.t = t;
     a.L = L;
@@ -453,7 +456,7 @@ hipError_t launch_ising3d_pass(const int8_t *src, int8_t *dst, const uint2 *pbon
     const size_t lds = (size_t)kRing * (size_t)(ty + 4) * (size_t)L * (pbonds ? 5 : 4) / 4;
     const dim3 grid((unsigned)((int64_t)n_rep * a.strips * a.zsegs));
 #define SMC_PASS3D(MM, TT, SS, DD)                                                                          \
-    if ((pbonds ? 2 : 0) == MM && ty == TT && segs == SS && (dE != nullptr) == DD) {                        \
+    if ((pbonds ? 2 : 0) == MM && ty == TT && segs == SS && (dE.slots || dE.total) == DD) {                        \
         (void)hipFuncSetAttribute((const void *)k_ising3d_pass<MM, TT, SS, DD>,                             \
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                    \
         SMC_LAUNCH((k_ising3d_pass<MM, TT, SS, DD>), grid, dim3(threads), lds, s, a);                       \

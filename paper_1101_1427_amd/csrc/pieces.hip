@@ -16,8 +16,8 @@
 // Bound: launches and VALU.  Per eight updates one Philox block, 2d + 1 piece
 // loads and byte-parallel counting, where a thread per site draws a block and
 // computes 64-bit indices per update.
-// 512^2 Ising, per half-sweep: 9.4 -> 4.2 us; 64 x 200^2 EA: 23 -> 7.5 us;
-// 4 x 100^3 Ising: 96 -> 18 us.
+// 512^2 Ising, per half-sweep: 9.4 -> 3.8 us; 64 x 200^2 EA: 23 -> 6.5 us;
+// 4 x 100^3 Ising: 96 -> 8 us.
 #include "internal.hpp"
 #include "rows.hpp"
 #include "segment3d.hpp"
@@ -231,23 +231,28 @@ __global__ __launch_bounds__(kThreads) void k_half_sweep_pieces(SweepArgs a, int
             if constexpr (DIM == 2) dE -= 4 * (__popc(o.F0) + __popc(o.F1));
         }
     }
-    if (a.dE) {
+    if (tally_wanted(a.tally)) {
 #pragma unroll
         for (int k = 32; k > 0; k >>= 1) dE += __shfl_xor(dE, k, 64);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dE;
         __syncthreads();
         if (threadIdx.x == 0) {
             const long long tot = (long long)red[0] + red[1] + red[2] + red[3];
-            if (tot != 0) atomicAdd((unsigned long long *)&a.dE[r], (unsigned long long)tot);
+            tally_put(a.tally, blockIdx.x, r, tot);
         }
     }
 }
 
 }  // namespace
 
+int pieces_groups(const SweepArgs &a) {
+    const int64_t N = a.b.dim == 3 ? (int64_t)a.max_L * a.max_L * a.max_L : (int64_t)a.max_L * a.max_L;
+    return (int)((N + 16 * kThreads - 1) / (16 * kThreads));
+}
+
 hipError_t launch_half_sweep_pieces(const SweepArgs &a, int c, hipStream_t s) {
     const int64_t N = a.b.dim == 3 ? (int64_t)a.max_L * a.max_L * a.max_L : (int64_t)a.max_L * a.max_L;
-    const int bpr = (int)((N + 16 * kThreads - 1) / (16 * kThreads));
+    const int bpr = pieces_groups(a);
     const int64_t blocks = (int64_t)bpr * a.b.n_rep;
     if (const char *why = launch_config_error((uint64_t)blocks, kThreads, 0))
         return reject_launch("k_half_sweep_pieces", (uint64_t)blocks, kThreads, 0, why);

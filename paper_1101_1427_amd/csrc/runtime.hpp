@@ -70,6 +70,7 @@ enum Slot {
     kMscEnergy,
     kMscGauge,
     kDcbSlots,
+    kTallySlots, // per-workgroup sums of a sweep call
     kPtThr,
     kPtDelta,
     kPtOut,

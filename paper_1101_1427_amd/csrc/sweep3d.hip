@@ -33,7 +33,7 @@ struct Sweep3dArgs {
     int rep_per_sample;
     const ThrRow *thr;      // per replica (high halves <= 0xFFFF, checked on the host)
     const uint2 *pbonds;    // EA bit-packed: [sample][L^3 / 16] (pack_bonds3d), or nullptr
-    int64_t *dE;            // per replica, or nullptr
+    Tally dE;               // energy changes
     Key key;
     uint32_t t;
     int L, c;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void k_ising3d_half(Sweep3dArgs a) {
                 else
                     *(uint4 *)(S + i0) = out;
             }
-            if (a.dE) dE += flip_energy(o);
+            if (tally_wanted(a.dE)) dE += flip_energy(o);
             // next row: z + 1 is its own row, this row its z - 1 neighbour (only
             // the other colour's bytes are read from it, which did not change)
             rzm = own;
@@ -132,14 +132,14 @@ __global__ __launch_bounds__(kThreads) void k_ising3d_half(Sweep3dArgs a) {
             i0 = izp;
         }
     }
-    if (a.dE) {
+    if (tally_wanted(a.dE)) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) dE += __shfl_xor(dE, o, 64);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dE;
         __syncthreads();
         if (threadIdx.x == 0) {
             const long long tot = red[0] + red[1] + red[2] + red[3];
-            if (tot != 0) atomicAdd((unsigned long long *)&a.dE[r], (unsigned long long)tot);
+            tally_put(a.dE, blockIdx.x, r, tot);
         }
     }
 }
@@ -208,7 +208,7 @@ hipError_t launch_model(int Z, bool nt, unsigned blocks, const Sweep3dArgs &a, h
 // faster.  SPINMC_SWEEP3D_Z = 1, 2, 4, 8 or 16 sets it, else a value
 // smc_autotune measured for the edge, model and replica count; non-temporal
 // stores of the updated segments are on unless SPINMC_SWEEP3D_NT = 0.
-int sweep3d_rows(int L, bool ea, int n_rep) {
+static int preferred_rows(int L, bool ea, int n_rep) {
     const char *env = getenv("SPINMC_SWEEP3D_Z");
     if (env && env[0]) {
         const int z = atoi(env);
@@ -222,16 +222,25 @@ int sweep3d_rows(int L, bool ea, int n_rep) {
     return 4;
 }
 
-hipError_t launch_ising3d_half(int8_t *spins, const int8_t *coup, const uint2 *pbonds, int rep_per_sample,
-                               const ThrRow *thr, int64_t *dE, int n_rep, int L, Key key, uint32_t t, int c,
-                               hipStream_t s) {
-    if (!sweep3d_supported(L) || rep_per_sample < 1 || n_rep < 1) return hipErrorInvalidValue;
-    // a replica's (L / 16)^3 workgroups of one-row threads regroup into whole
-    // workgroups of Z-row threads when Z divides (L / 16)^3
+// A replica's (L / 16)^3 workgroups of one-row threads regroup into whole
+// workgroups of Z-row threads when Z divides (L / 16)^3.
+int sweep3d_rows(int L, bool ea, int n_rep) {
     const int B = L / 16;
-    int Z = sweep3d_rows(L, coup != nullptr || pbonds != nullptr, n_rep);
+    int Z = preferred_rows(L, ea, n_rep);
     while ((B * B * B) % Z) Z >>= 1;
-    const int64_t threads = (int64_t)L * L * L / (16 * Z);  // per replica
+    return Z;
+}
+
+int sweep3d_groups(int L, int Z) {
+    const int64_t threads = (int64_t)L * L * L / (16 * Z);
+    return (int)((threads + kThreads - 1) / kThreads);
+}
+
+hipError_t launch_ising3d_half(int8_t *spins, const int8_t *coup, const uint2 *pbonds, int rep_per_sample,
+                               const ThrRow *thr, const Tally &dE, int n_rep, int L, Key key, uint32_t t, int c,
+                               int Z, hipStream_t s) {
+    if (!sweep3d_supported(L) || rep_per_sample < 1 || n_rep < 1 || Z < 1 || (L / 16) * (L / 16) * (L / 16) % Z)
+        return hipErrorInvalidValue;
     Sweep3dArgs a;
     a.spins = spins;
     a.coup = coup;
@@ -243,7 +252,7 @@ hipError_t launch_ising3d_half(int8_t *spins, const int8_t *coup, const uint2 *p
     a.t = t;
     a.L = L;
     a.c = c;
-    a.blocks_per_rep = (int)((threads + kThreads - 1) / kThreads);
+    a.blocks_per_rep = sweep3d_groups(L, Z);
     a.one2 = 0x00010001u;
     const int64_t blocks = (int64_t)n_rep * a.blocks_per_rep;
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;

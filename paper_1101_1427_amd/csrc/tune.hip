@@ -164,8 +164,10 @@ int tune_pass3d(StreamCtx &c, hipStream_t s, const Batch &b, bool ea, int64_t n_
             for (int D : {16, 32, 64, 128, 256, 512})
                 if (pass3d_shape_valid(L, ea, ty, segs, D)) cands.push_back(Shape{{ty, segs, D}});
     return pick_shape(kShapePass3d, L, ea ? 1 : 0, n_rep, cands, dflt, s, [&](int k) {
+        Shape now{{0, 0, 0}};
+        if (!pass3d_launch_shape(L, ea, n_rep, &now)) return hipErrorInvalidValue;
         return launch_ising3d_pass((const int8_t *)(k & 1 ? B : A), (int8_t *)(k & 1 ? A : B), (const uint2 *)pb, rps,
-                                   (const ThrRow *)tp, nullptr, n_rep, L, key, (uint32_t)k, s);
+                                   (const ThrRow *)tp, Tally{}, n_rep, L, key, (uint32_t)k, now, s);
     });
 }
 
@@ -185,8 +187,8 @@ int tune_half3d(StreamCtx &c, hipStream_t s, const Batch &b, bool ea, int64_t n_
     return pick_shape(kShapeHalf3d, L, ea ? 1 : 0, n_rep, cands, dflt, s, [&](int k) {
         hipError_t e = hipSuccess;
         for (int col = 0; col < 2 && e == hipSuccess; ++col)
-            e = launch_ising3d_half((int8_t *)A, nullptr, (const uint2 *)pb, rps, (const ThrRow *)tp, nullptr, n_rep,
-                                    L, key, (uint32_t)k, col, s);
+            e = launch_ising3d_half((int8_t *)A, nullptr, (const uint2 *)pb, rps, (const ThrRow *)tp, Tally{}, n_rep,
+                                    L, key, (uint32_t)k, col, sweep3d_rows(L, ea, n_rep), s);
         return e;
     });
 }
