@@ -14,6 +14,7 @@
 #include <utility>
 #include <vector>
 
+#include "bands2d.hpp"
 #include "internal.hpp"
 #include "runtime.hpp"
 
@@ -367,8 +368,59 @@ struct CallTally {
     }
 };
 
-// The generic half-sweeps of a call.
+// Uniform 2D batches of the general path run several sweeps per launch on
+// bands of rows in LDS where the estimate says that it is faster than two
+// half-sweep launches per sweep (measured: about 3.5 us and 1.2 fs per site
+// each); a band needs about 5 K bytes of LDS per row of 4 K sites, so large
+// edges keep the half-sweeps, and so does a call of one sweep unless the
+// lattice fits in LDS as a whole.  SPINMC_BANDS2D=0 keeps the half-sweeps
+// (same results).
+bool use_bands2d(const SweepArgs &a, int32_t n_sweeps, BandShape *sh) {
+    const char *env = getenv("SPINMC_BANDS2D");
+    if ((env && env[0] == '0') || a.b.dim != 2 || a.b.L <= 0) return false;
+    if (!bands2d_shape(a.b.L, a.b.n_rep, a.coup != nullptr, n_sweeps, sh)) return false;
+    if (env && env[0] == '1') return true;
+    return sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)a.b.n_rep * (double)a.b.N);
+}
+
+int run_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandShape &sh, void *other, uint64_t sweep0,
+                int32_t n_sweeps, int64_t *dE) {
+    CallTally tally;
+    int rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), dE);
+    if (rc) return rc;
+    Bands2dArgs ba;
+    ba.coup = a.coup;
+    ba.rep_per_sample = a.b.rep_per_sample;
+    ba.thr = a.thr;
+    ba.row_of_rep = a.row_of_rep;
+    ba.key = a.key;
+    ba.rng_shift = a.rng_shift;
+    ba.n_rep = a.b.n_rep;
+    ba.L = a.b.L;
+    const int launches = bands2d_launches(sh, n_sweeps);
+    SweepTimer timer(s, launches);
+    int32_t done = 0;
+    for (int k = 0; k < launches; ++k) {
+        const int32_t n = (n_sweeps - done + launches - k - 1) / (launches - k);
+        ba.src = (const int8_t *)(sh.whole || !(k & 1) ? a.spins : other);
+        ba.dst = (int8_t *)(sh.whole || (k & 1) ? a.spins : other);
+        ba.t = (uint32_t)(sweep0 + (uint64_t)done);
+        SMC_HIP(launch_bands2d(ba, sh, n, tally.next(), s));
+        done += n;
+    }
+    timer.finish();
+    return tally.finish(s);
+}
+
+// The sweeps of a call on the general path.
 int run_generic(StreamCtx &c, hipStream_t s, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps, int64_t *dE) {
+    BandShape sh;
+    if (use_bands2d(a, n_sweeps, &sh)) {
+        void *other = nullptr;
+        if (sh.whole || ensure(c, kBands2d, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
+            return run_bands2d(c, s, a, sh, other, sweep0, n_sweeps, dE);
+        last_error().clear();  // no room for a second lattice: the half-sweeps need none
+    }
     CallTally tally;
     int rc = tally.begin(c, a.b.n_rep, half_sweep_groups(a), dE);
     if (rc) return rc;

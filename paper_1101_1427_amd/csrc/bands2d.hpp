@@ -1,0 +1,38 @@
+// Sweeps of uniform 2D Ising / +-J EA batches of any even edge with bands of
+// rows in LDS, several sweeps per launch (bands2d.hip).
+#pragma once
+#include "internal.hpp"
+
+namespace smc {
+
+// How a batch is cut: `rows` rows per workgroup (the whole lattice when
+// whole), `sweeps` sweeps per launch, `threads` per workgroup.
+struct BandShape {
+    int rows = 0, sweeps = 0, threads = 0;
+    bool whole = false;
+    double ns_per_sweep = 0.0;  // the model's estimate for the batch
+};
+
+// The shape for a batch of n_rep lattices and a call of n_sweeps sweeps;
+// false if none fits in LDS.
+bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, BandShape *out);
+int bands2d_groups(int L, const BandShape &sh);  // workgroups per replica
+// Launches of a call: an even number unless the shape is whole, so that the
+// result ends where it began (more than n_sweeps: the shape does not serve the call).
+int bands2d_launches(const BandShape &sh, int n_sweeps);
+
+struct Bands2dArgs {
+    const int8_t *src;         // [n_rep][L * L]
+    int8_t *dst;               // may be src when the shape is whole
+    const int8_t *coup;        // EA: [sample][2][L * L], else nullptr
+    int rep_per_sample;
+    const ThrRow *thr;
+    const int32_t *row_of_rep; // threshold row per replica (-1: copied unchanged), or nullptr
+    Key key;
+    uint32_t t;                // first sweep of the launch
+    int rng_shift;
+    int n_rep, L;
+};
+hipError_t launch_bands2d(const Bands2dArgs &a, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s);
+
+}  // namespace smc

@@ -43,19 +43,6 @@ __device__ __forceinline__ b8 put_byte(b8 v, uint32_t k, uint32_t byte) {
     return (v & ~m) | ((b8)byte << (8 * k));
 }
 
-// Sixteen bytes from site i of an array of N: where i .. i + 15 runs over an
-// end of the array the loaded bytes are moved into place by into_place, so the
-// loads of a piece are all issued before the first is waited for.
-template <typename I>
-__device__ __forceinline__ uint4 load_inside(const int8_t *p, I i, I N) {
-    return load16_any(p + max((I)0, min(i, N - 16)));
-}
-template <typename I>
-__device__ __forceinline__ void into_place(uint4 &v, I i, I N) {
-    if (i < 0) v = bytes_up(v, (uint32_t)min(-i, (I)16));
-    if (i > N - 16) v = bytes_down(v, (uint32_t)min(i - (N - 16), (I)16));
-}
-
 // I: int where a replica has at most 2^30 sites, else int64_t.
 template <int DIM, bool EA, typename I>
 __global__ __launch_bounds__(kThreads) void k_half_sweep_pieces(SweepArgs a, int c, int bpr, uint32_t one2) {

@@ -35,6 +35,19 @@ __device__ __forceinline__ uint4 load16(const int8_t *p, int64_t i, int64_t N) {
     return bytes_down(load16_any(p + (N - 16)), (uint32_t)min(i - (N - 16), (int64_t)16));
 }
 
+// Sixteen bytes from site i of an array of N: where i .. i + 15 runs over an
+// end of the array the loaded bytes are moved into place by into_place, so that
+// several loads can be issued before the first is waited for.
+template <typename I>
+__device__ __forceinline__ uint4 load_inside(const int8_t *p, I i, I N) {
+    return load16_any(p + max((I)0, min(i, N - 16)));
+}
+template <typename I>
+__device__ __forceinline__ void into_place(uint4 &v, I i, I N) {
+    if (i < 0) v = bytes_up(v, (uint32_t)min(-i, (I)16));
+    if (i > N - 16) v = bytes_down(v, (uint32_t)min(i - (N - 16), (I)16));
+}
+
 // The end of a row in a piece of which `left` sites (even, > 0) remain in
 // the row; left >= 16: a whole piece.
 struct RowEnd {

@@ -70,6 +70,7 @@ enum Slot {
     kMscEnergy,
     kMscGauge,
     kDcbSlots,
+    kBands2d,    // second lattice of the 2D bands
     kTallySlots, // per-workgroup sums of a sweep call
     kPtThr,
     kPtDelta,
