@@ -64,12 +64,18 @@
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place;
- *   everything else takes generic per-site kernels.  All paths give
- *   identical results.  Environment variables for comparisons and tuning
+ *   everything else takes the general path ("k_half_sweep_generic"): two
+ *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
+ *   thread where an edge is below 16), or, for uniform 2D batches where an
+ *   estimate says that it is faster, bands of rows held on chip for several
+ *   sweeps per launch, alternating with a library-held second lattice.  All
+ *   paths give identical results.  Environment variables for comparisons and tuning
  *   (read at each call): SPINMC_PT3D=0, SPINMC_UNEVEN2D=0 and
  *   SPINMC_PT_SPLIT2D=0 send tempering to the generic kernels,
  *   SPINMC_SWEEP_LDS2D=0 small 2D sweeps, SPINMC_SWEEP3D=0 3D Ising / EA
- *   sweeps; SPINMC_SWEEP3D_PASS=0 keeps the two launches per sweep for
+ *   sweeps; on the general path SPINMC_BANDS2D=0 keeps the half-sweeps, =1
+ *   takes the bands wherever they fit (SPINMC_BANDS2D_ROWS and _SWEEPS set
+ *   their shape) and SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps the two launches per sweep for
  *   every edge, =1 takes the one launch from edge 32 (SPINMC_PASS3D_TY,
  *   _SEGS and _D set its rows per strip, segments per thread and planes
  *   per z segment; SPINMC_SWEEP3D_Z = 1 .. 16 rows per thread and
@@ -287,7 +293,8 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream);
 
 /*
  * How smc_metropolis_sweep will execute this batch: the number of kernel
- * launches per sweep and the name of the sweep kernel (a static string).
+ * launches per sweep (at most) and the name of the sweep kernel (a static
+ * string; "k_half_sweep_generic" stands for the general path).
  * Used by benchmarks to attribute per-launch time; no device work.
  */
 int smc_sweep_plan(const smc_desc *desc, int32_t *launches_per_sweep, const char **kernel_name);
