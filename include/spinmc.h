@@ -66,7 +66,9 @@
  *   device copy back), below in two launches per sweep, in place;
  *   everything else takes the general path ("k_half_sweep_generic"): two
  *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
- *   thread where an edge is below 16), or, for uniform 2D batches where an
+ *   thread where an edge is below 16), or, for uniform 3D batches of edge 4
+ *   .. 14, whole replicas held on chip for the call (tempering too, with up
+ *   to 64 temperatures that fit), or, for uniform 2D batches where an
  *   estimate says that it is faster, bands of rows held on chip for several
  *   sweeps per launch, alternating with a library-held second lattice.  All
  *   paths give identical results.  Environment variables for comparisons and tuning
@@ -75,7 +77,8 @@
  *   SPINMC_SWEEP_LDS2D=0 small 2D sweeps, SPINMC_SWEEP3D=0 3D Ising / EA
  *   sweeps; on the general path SPINMC_BANDS2D=0 keeps the half-sweeps, =1
  *   takes the bands wherever they fit (SPINMC_BANDS2D_ROWS and _SWEEPS set
- *   their shape) and SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps the two launches per sweep for
+ *   their shape), SPINMC_SMALL3D=0 keeps the small 3D edges on the
+ *   half-sweeps and SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps the two launches per sweep for
  *   every edge, =1 takes the one launch from edge 32 (SPINMC_PASS3D_TY,
  *   _SEGS and _D set its rows per strip, segments per thread and planes
  *   per z segment; SPINMC_SWEEP3D_Z = 1 .. 16 rows per thread and
@@ -312,8 +315,8 @@ int smc_kernel_timing_enable(int enable);
 int smc_kernel_timing_read(double *elapsed_ms, int64_t *launches);
 
 /*
- * How smc_pt_sweep_swap will execute: the number of kernel launches for a
- * call of n_steps steps and the name of the sweep kernel (a static string).
+ * How smc_pt_sweep_swap will execute: the number of kernel launches (at most)
+ * for a call of n_steps steps and the name of the sweep kernel (a static string).
  * 3D lattices of edge 16 with n_temps <= 32 (EA: rep_per_sample a multiple
  * of n_temps) run all steps of a call in one launch, one workgroup per chain
  * with the chain resident in LDS; other shapes take three launches per step

@@ -17,6 +17,7 @@
 #include "bands2d.hpp"
 #include "internal.hpp"
 #include "runtime.hpp"
+#include "small3d.hpp"
 
 namespace smc {
 namespace {
@@ -412,8 +413,43 @@ int run_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandShape
     return tally.finish(s);
 }
 
+// Sweeps of small 3D replicas in LDS, up to kSmall3dSweeps per launch (so
+// that one launch stays short).  A workgroup takes enough replicas to fill a
+// wavefront, and more only once there are four workgroups per compute unit.
+constexpr int kSmall3dSweeps = 4096;
+
+int run_small3d(hipStream_t s, const SweepArgs &a, uint64_t sweep0, int32_t n_sweeps, int64_t *dE) {
+    Small3dArgs sa;
+    memset(&sa, 0, sizeof sa);
+    sa.spins = (int8_t *)a.spins;
+    sa.coup = a.coup;
+    sa.rep_per_sample = a.b.rep_per_sample;
+    sa.L = a.b.L;
+    sa.n_rep = a.b.n_rep;
+    const int blocks = (int)((a.b.N / 2 + 7) / 8);  // Philox blocks, one lane each
+    const int fill = (63 + blocks) / blocks, spread = (a.b.n_rep + 1023) / 1024;
+    sa.n = fill > spread ? fill : spread;
+    const int most = small3d_max_reps(a.b.L);
+    if (sa.n > most) sa.n = most;
+    sa.thr = a.thr;
+    sa.key = a.key;
+    sa.n_steps = 1;
+    sa.rng_shift = a.rng_shift;
+    sa.dE = dE;
+    SweepTimer timer(s, (n_sweeps + kSmall3dSweeps - 1) / kSmall3dSweeps);
+    for (int32_t done = 0; done < n_sweeps; done += sa.m) {
+        sa.m = n_sweeps - done < kSmall3dSweeps ? n_sweeps - done : kSmall3dSweeps;
+        sa.t0 = (uint32_t)(sweep0 + (uint64_t)done);
+        SMC_HIP(launch_small3d(sa, s));
+    }
+    timer.finish();
+    return SMC_OK;
+}
+
 // The sweeps of a call on the general path.
-int run_generic(StreamCtx &c, hipStream_t s, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps, int64_t *dE) {
+int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps,
+                int64_t *dE) {
+    if (use_small3d(desc)) return run_small3d(s, a, sweep0, n_sweeps, dE);
     BandShape sh;
     if (use_bands2d(a, n_sweeps, &sh)) {
         void *other = nullptr;
@@ -819,7 +855,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         timer.finish();
         return tally.finish(s);
     }
-    return run_generic(c, s, a, sweep0, n_sweeps, dE_accum);
+    return run_generic(c, s, desc, a, sweep0, n_sweeps, dE_accum);
 }
 
 int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, const double *beta, uint64_t sweep0,
@@ -895,7 +931,7 @@ int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     a.rng_shift = word_bits == 64 ? 6 : 5;  // the draw group r / word_bits
-    return run_generic(c, s, a, sweep0, n_sweeps, dE_accum);
+    return run_generic(c, s, desc, a, sweep0, n_sweeps, dE_accum);
 }
 
 // The packed double-checkerboard kernel: thresholds with 16-bit high halves,
@@ -1263,6 +1299,29 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
                             desc->rep_per_sample, pt->n_chains, n, pt->beta_per_chain ? 1 : 0, (const double *)bdev,
                             (const ThrRow *)thr, slot_of_temp, energy, (unsigned long long *)swap_accepts,
                             make_key(desc->seed), (uint32_t)step0, n_steps, m, s));
+        return SMC_OK;
+    }
+    if (use_small3d(desc) && n <= small3d_max_reps(desc->L)) {
+        // every step of the call in one launch, a workgroup per chain
+        Small3dArgs sa;
+        memset(&sa, 0, sizeof sa);
+        sa.spins = (int8_t *)spins;
+        sa.coup = desc->model == SMC_EA ? couplings : nullptr;
+        sa.rep_per_sample = plan.b.rep_per_sample;
+        sa.L = desc->L;
+        sa.n_rep = desc->n_rep;
+        sa.n = n;
+        sa.thr = (const ThrRow *)thr;
+        sa.key = make_key(desc->seed);
+        sa.t0 = (uint32_t)step0;
+        sa.n_steps = n_steps;
+        sa.m = m;
+        sa.beta_per_chain = pt->beta_per_chain ? 1 : 0;
+        sa.beta = (const double *)bdev;
+        sa.slot_of_temp = slot_of_temp;
+        sa.energy = energy;
+        sa.acc = (unsigned long long *)swap_accepts;
+        SMC_HIP(launch_small3d(sa, s));
         return SMC_OK;
     }
     if ((rc = ensure(c, kEnergy64, sizeof(int64_t) * desc->n_rep, &E64))) return rc;

@@ -22,7 +22,7 @@
 // piece are eight consecutive bytes.  A row that starts or ends inside a piece
 // shares it with another row; each row holds its own copy and masks the
 // positions that are not its own.  Rows y - 1 and y + 1 have other offsets,
-// so their bytes are read shifted by half the difference (unaligned LDS reads).
+// so their bytes are read shifted by half the difference.
 // One byte before array O holds a copy of the row's last site and the byte after
 // the row's end in array E one of its first, so that x neighbours never wrap.
 // Where these bytes lie in a piece that a thread updates, flips are
@@ -64,12 +64,6 @@ __host__ __device__ constexpr int pieces_of(int L) { return L % 16 == 0 ? L / 16
 // E (8 K bytes), eight bytes with the two copies, O (8 K bytes).
 __host__ __device__ constexpr int pitch_of(int L) { return 16 * pieces_of(L) + 8; }
 
-__device__ __forceinline__ uint2 lds8(const uint8_t *p) { return *(const uint2 *)__builtin_assume_aligned(p, 8); }
-__device__ __forceinline__ uint2 lds8_any(const uint8_t *p) {
-    uint2 v;
-    __builtin_memcpy(&v, p, 8);
-    return v;
-}
 
 // Bits 0 of four bytes: (a ^ b) & 1, (a ^ b ^ c) & 1.
 __device__ __forceinline__ uint32_t x2(uint32_t a, uint32_t b) {
@@ -120,14 +114,13 @@ struct Band {
         const uint2 own = lds8(own_at);
         const uint2 oth = lds8(T + t.base + (odd ? 0u : K8 + 8u) + k8);
         // the word before (even own sites: array O) or after (odd: array E)
-        const uint32_t ext = *(const uint32_t *)__builtin_assume_aligned(
-            T + t.base + (odd ? k8 + 8u : K8 + 8u + k8 - 4u), 4);
+        const uint32_t ext = lds4(T + t.base + (odd ? k8 + 8u : K8 + 8u + k8 - 4u));
         uint2 dn, un;
         if constexpr (RAG) {
             const uint32_t pd = t.y == 0 ? ((L - 1u) * L) & 15u : (t.p - L) & 15u;
             const uint32_t pu = t.y == (int)L - 1 ? 0u : (t.p + L) & 15u;
-            dn = lds8_any(T + down + mine + ((int)(pd - t.p) >> 1));
-            un = lds8_any(T + up + mine + ((int)(pu - t.p) >> 1));
+            dn = lds8_at(T + down + mine, (int)(pd - t.p) >> 1);
+            un = lds8_at(T + up + mine, (int)(pu - t.p) >> 1);
         } else {
             dn = lds8(T + down + mine);
             un = lds8(T + up + mine);

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "runtime.hpp"
+#include "small3d.hpp"
 
 namespace smc {
 
@@ -184,6 +185,15 @@ bool use_heis3d_tiled(const smc_desc *d) {
 bool pt3d_enabled() {
     const char *env = getenv("SPINMC_PT3D");
     return !(env && env[0] == '0');
+}
+
+// Uniform 3D Ising / EA batches with an edge of 4 .. 14 keep whole replicas
+// in LDS for a call (any alignment, any beta); SPINMC_SMALL3D=0 keeps them on
+// the half-sweep launches (same results).
+bool use_small3d(const smc_desc *d) {
+    const char *env = getenv("SPINMC_SMALL3D");
+    if (env && env[0] == '0') return false;
+    return (d->model == SMC_ISING || d->model == SMC_EA) && d->L > 0 && small3d_supported(d->dim, d->L);
 }
 
 bool use_pt3d(const smc_desc *d, const smc_pt_desc *pt, const void *spins, const std::vector<ThrRow> &rows) {

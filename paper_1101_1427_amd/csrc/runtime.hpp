@@ -112,6 +112,8 @@ ThrRow threshold_row(double beta, int dim);
 bool use_heis3d(const smc_desc *d);
 bool use_heis3d_tiled(const smc_desc *d);
 bool pt3d_enabled();
+// Small 3D edges with whole replicas on chip (SPINMC_SMALL3D=0: never).
+bool use_small3d(const smc_desc *d);
 bool use_pt3d(const smc_desc *d, const smc_pt_desc *pt, const void *spins, const std::vector<ThrRow> &rows);
 bool use_lattice2d(const smc_desc *d, const void *spins, const std::vector<ThrRow> &rows);
 bool sweep3d_shape(const smc_desc *d);

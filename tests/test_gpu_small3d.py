@@ -1,0 +1,84 @@
+"""Small 3D lattices with whole replicas in LDS: every edge (pieces that hold
+several rows, wraps at every face, a partial last piece), several replicas per
+workgroup with a short last one, one to three passes of the threads over the
+replicas, beta = 0, tempering with and without per-chain ladders."""
+import numpy as np
+import pytest
+
+import paper_1101_1427_amd as S
+import workloads as W
+from oracle import oracle as O
+from tests import refrun
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(a).reshape(-1)).to("cuda")
+
+
+@pytest.mark.parametrize("model", [S.ISING, S.EA])
+@pytest.mark.parametrize("L,n_rep", [(4, 1), (4, 37), (6, 7), (8, 5), (10, 3), (12, 2), (14, 3)])
+def test_small3d_sweeps_against_oracle(model, L, n_rep):
+    import torch
+
+    seed, n = W.seed_for(400 + L), 4
+    betas = np.linspace(0.0, 1.2, n_rep)
+    b = S.Batch(model, 3, L, n_rep, seed, rep_per_sample=3)
+    ref_s, ref_c = refrun.init_uniform(model, 3, L, n_rep, seed, 3)
+    spins = torch.cat([torch.zeros(1, dtype=torch.int8, device="cuda"), _dev(ref_s)])[1:]  # odd address
+    coup = None if ref_c is None else _dev(ref_c)
+    dE = torch.full((n_rep,), 3, dtype=torch.int64, device="cuda")
+    S.metropolis_sweep(b, spins, betas, 5, n, couplings=coup, dE_accum=dE)
+    ref_dE = refrun.sweep_uniform(model, 3, L, ref_s, ref_c, betas, seed, 5, n, 3) + 3
+    assert np.array_equal(spins.cpu().numpy().reshape(ref_s.shape), ref_s)
+    assert np.array_equal(dE.cpu().numpy(), ref_dE)
+
+
+@pytest.mark.parametrize("L,n_temps,per_chain,m", [(4, 5, False, 1), (6, 64, False, 1), (8, 12, True, 2),
+                                                   (10, 24, False, 1), (12, 9, False, 3), (14, 32, True, 1)])
+def test_small3d_tempering_against_oracle(L, n_temps, per_chain, m):
+    import torch
+
+    n_chains, steps, t0, seed = 3, 6, 3, W.seed_for(420 + L)
+    beta = W.geometric_ladder(0.8, 2.0, n_temps)
+    betas = np.stack([beta * (1 + 0.05 * q) for q in range(n_chains)]) if per_chain else np.stack([beta] * n_chains)
+    n_rep, N = n_chains * n_temps, L ** 3
+    b = S.Batch(S.EA, 3, L, n_rep, seed, rep_per_sample=n_temps)
+    ref_s, ref_c = refrun.init_uniform(S.EA, 3, L, n_rep, seed, n_temps)
+    spins, coup = _dev(ref_s), _dev(ref_c)
+    E0 = np.array([O.energy(3, L, ref_c[r // n_temps], ref_s[r]) for r in range(n_rep)], np.int64)
+    E = torch.from_numpy(E0.astype(np.float64)).to("cuda")
+    perm = np.stack([np.roll(np.arange(n_temps, dtype=np.int32), q) for q in range(n_chains)])
+    sot = _dev(perm)
+    acc = torch.zeros(n_chains * (n_temps - 1), dtype=torch.int64, device="cuda")
+    S.pt_sweep_swap(b, n_chains, n_temps, betas if per_chain else beta, spins, sot, E, t0, steps, couplings=coup,
+                    swap_accepts=acc, beta_per_chain=per_chain, sweeps_per_step=m)
+    for q in range(n_chains):
+        rows = slice(q * n_temps, (q + 1) * n_temps)
+        s, e, p = ref_s[rows].copy(), E0[rows].copy(), perm[q].copy()
+        a = np.zeros(n_temps - 1, np.uint64)
+        O.pt_run(3, L, ref_c[q], s, betas[q], p, e, seed, q, q * n_temps, t0, steps, a, sweeps_per_step=m)
+        assert np.array_equal(spins.cpu().numpy().reshape(n_rep, N)[rows], s), q
+        assert np.array_equal(E.cpu().numpy()[rows], e.astype(np.float64))
+        assert np.array_equal(sot.cpu().numpy().reshape(n_chains, n_temps)[q], p)
+        assert np.array_equal(acc.cpu().numpy().reshape(n_chains, -1)[q].astype(np.uint64), a)
+
+
+def test_small3d_ties_equal_half_sweeps(monkeypatch):
+    """2^23 updates meet the exact (tail) decisions; shared multi-spin draws."""
+    import torch
+
+    outs = []
+    for way in ("1", "0"):
+        monkeypatch.setenv("SPINMC_SMALL3D", way)
+        b = S.Batch(S.EA, 3, 10, 512, W.seed_for(431))
+        spins = torch.zeros(b.spins_shape()[0], dtype=torch.int8, device="cuda")
+        coup = torch.zeros(b.coup_len(), dtype=torch.int8, device="cuda")
+        S.spin_init(b, spins, coup)
+        dE = torch.zeros(512, dtype=torch.int64, device="cuda")
+        S.msc_sweep(b, spins, np.repeat(np.linspace(0.2, 1.0, 16), 32), 3, 17, couplings=coup, dE_accum=dE)
+        outs.append((spins.cpu().numpy(), dE.cpu().numpy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
