@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "bands2d.hpp"
+#include "bins2d.hpp"
 #include "internal.hpp"
 #include "runtime.hpp"
 #include "small3d.hpp"
@@ -23,9 +24,10 @@ namespace smc {
 namespace {
 
 // ------------------------------------------------ uneven 2D tempering ----
-// Batches of 2D lattices with edges in {16, 32, ..., 256} (uniform or uneven)
-// go to the per-replica LDS kernel; the replicas of one edge form a class
-// with its own launch shape.
+// Batches of 2D lattices with edges in {16, 32, ..., 256}: tempering (uniform
+// or uneven) goes to the bins of replicas, sweeps of small uniform batches to
+// the per-replica LDS kernel, where the replicas of one edge form a class with
+// its own launch shape.
 struct EdgeClass {
     int L = 0, threads = 0;
     int32_t first = 0, count = 0;  // range of the work list
@@ -122,104 +124,42 @@ int lds2d_setup(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Plan &p
     return SMC_OK;
 }
 
-int run_uneven2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Plan &plan, const smc_pt_desc *pt,
-                 void *spins, const int8_t *couplings, SwapArgs &sw, const ThrRow *thr, double *energy,
-                 uint64_t step0, int32_t n_steps, int m) {
+int run_uneven2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, void *spins, const int8_t *couplings,
+                 SwapArgs &sw, const ThrRow *thr, double *energy, uint64_t step0, int32_t n_steps, int m) {
     int rc;
-    Lds2dSetup st;
-    if ((rc = lds2d_setup(c, s, desc, plan, couplings, st))) return rc;
-    std::vector<EdgeClass> &classes = st.classes;
-    const std::vector<int32_t> &work = st.work;
-    const std::vector<smc_inst> &rows = st.rows;
-    void *inst_dev = st.inst_dev, *work_dev = st.work_dev;
-    uint8_t *csplit = st.csplit;
-    // device counters: the step index (exchange rounds) and, with m > 1
-    // sweeps per step, the sweep index t*m + j (with m = 1 they coincide)
-    void *tp = nullptr;
-    if ((rc = ensure(c, kStep, 2 * sizeof(uint32_t), &tp))) return rc;
-    uint32_t *t_dev = (uint32_t *)tp;
-    uint32_t *sweep_dev = m > 1 ? t_dev + 1 : t_dev;
-    SMC_HIP(launch_set_step(t_dev, (uint32_t)step0, s));
-    if (m > 1) SMC_HIP(launch_set_step(sweep_dev, (uint32_t)(step0 * (uint64_t)m), s));
-    sw.t_dev = t_dev;
-    SMC_HIP(launch_pt_prepare(sw, energy, s));
-    // every sweep launch runs the m sweeps of a step with the replica in LDS
-    Uneven2dArgs a = make_uneven2d_args((int8_t *)spins, (const smc_inst *)inst_dev, csplit, sw.row_of_rep, thr,
-                                        sw.E, sweep_dev, make_key(desc->seed));
-    const int32_t *wl = (const int32_t *)work_dev;
-    const bool ea = desc->model == SMC_EA;
-    for (auto &e : classes) {
-        const std::vector<int32_t> reps(work.begin() + e.first, work.begin() + e.first + e.count);
-        if ((rc = uneven2d_threads(c, s, a, e.L, ea, reps, rows, &e.threads))) return rc;
+    const std::vector<smc_inst> rows = inst_rows(desc);
+    std::vector<Bin2d> bins;
+    std::vector<int32_t> work;
+    const size_t lds = make_bins2d(rows, &bins, &work);
+    void *ip = nullptr, *bp = nullptr, *wp = nullptr, *pp = nullptr;
+    if ((rc = upload(c, s, kInst, rows.data(), sizeof(smc_inst) * rows.size(), &ip))) return rc;
+    if ((rc = upload(c, s, kBins2d, bins.data(), sizeof(Bin2d) * bins.size(), &bp))) return rc;
+    if ((rc = upload(c, s, kWork, work.data(), sizeof(int32_t) * work.size(), &wp))) return rc;
+    // Between the steps of a call the replicas stay in a packed copy; without
+    // room for it every step reads and writes the caller's arrays.
+    const Bin2d &end = bins.back();
+    if (n_steps > 1 && ensure(c, kBinsPacked, (size_t)(end.packed + (int64_t)end.count * end.L * end.L / 2), &pp)) {
+        last_error().clear();
+        pp = nullptr;
     }
+    Bins2dArgs a;
+    a.spins = (int8_t *)spins;
+    a.coup = desc->model == SMC_EA ? couplings : nullptr;
+    a.packed = (uint8_t *)pp;
+    a.inst = (const smc_inst *)ip;
+    a.bins = (const Bin2d *)bp;
+    a.work = (const int32_t *)wp;
+    a.row_of_rep = sw.row_of_rep;
+    a.thr = thr;
+    a.E = sw.E;
+    a.key = make_key(desc->seed);
     a.sweeps = m;
-
-    if (n_steps < 4) {
-        // a few steps: plain launches in step order
-        for (int32_t k = 0; k < n_steps; ++k) {
-            for (const EdgeClass &e : classes)
-                SMC_HIP(launch_uneven2d_sweep(a, wl + e.first, e.count, e.L, ea, e.threads, s));
-            SMC_HIP(launch_pt_swap(sw, s));
-            if (m > 1) SMC_HIP(launch_advance_step(sweep_dev, s, (uint32_t)m));
-            SMC_HIP(launch_advance_step(t_dev, s));
-        }
-    } else {
-        // a graph of K steps: per step the edge classes run as parallel
-        // branches (m sweeps each), then the exchange round, then (m > 1) the
-        // sweep counter, then the step counter
-        const int32_t K = n_steps < 32 ? n_steps : 32;
-        const int32_t reps = n_steps / K, rest = n_steps % K;
-        for (int which = 0; which < 2; ++which) {
-            const int32_t steps = which == 0 ? K : rest;
-            if (steps == 0) continue;
-            std::vector<uint64_t> sig = {(uint64_t)steps, (uint64_t)(uintptr_t)a.spins, (uint64_t)(uintptr_t)a.inst,
-                                         (uint64_t)(uintptr_t)a.csplit, (uint64_t)(uintptr_t)a.row_of_rep,
-                                         (uint64_t)(uintptr_t)a.thr, (uint64_t)(uintptr_t)a.E,
-                                         (uint64_t)(uintptr_t)t_dev, a.key.k0, a.key.k1, (uint64_t)(uintptr_t)wl,
-                                         (uint64_t)(uintptr_t)sw.beta, (uint64_t)(uintptr_t)sw.slot_of_temp,
-                                         (uint64_t)(uintptr_t)sw.acc, (uint64_t)sw.n_chains, (uint64_t)sw.n_temps,
-                                         (uint64_t)sw.beta_per_chain, (uint64_t)m};
-            for (const EdgeClass &e : classes) {
-                sig.push_back((uint64_t)e.L);
-                sig.push_back((uint64_t)e.threads);
-                sig.push_back((uint64_t)e.first);
-                sig.push_back((uint64_t)e.count);
-            }
-            GraphCache &gc = c.graphs[which];
-            if (gc.exec == nullptr || gc.sig != sig) {
-                if (gc.exec) {
-                    SMC_HIP(hipStreamSynchronize(s));  // the old executable may still be in flight
-                    SMC_HIP(hipGraphExecDestroy(gc.exec));
-                    gc.exec = nullptr;
-                }
-                hipGraph_t g = nullptr;
-                SMC_HIP(hipGraphCreate(&g, 0));
-                hipError_t e = hipSuccess;
-                hipGraphNode_t prev = nullptr;
-                std::vector<hipGraphNode_t> sweeps(classes.size());
-                for (int32_t k = 0; k < steps && e == hipSuccess; ++k) {
-                    for (size_t q = 0; q < classes.size() && e == hipSuccess; ++q) {
-                        const EdgeClass &ec = classes[q];
-                        e = add_uneven2d_sweep_node(g, &sweeps[q], prev ? &prev : nullptr, prev ? 1 : 0, a,
-                                                    wl + ec.first, ec.count, ec.L, ea, ec.threads);
-                    }
-                    hipGraphNode_t swap = nullptr, after = nullptr;
-                    if (e == hipSuccess) e = add_pt_swap_node(g, &swap, sweeps.data(), sweeps.size(), sw);
-                    after = swap;
-                    if (m > 1 && e == hipSuccess) e = add_advance_node(g, &after, &swap, 1, sweep_dev, (uint32_t)m);
-                    if (e == hipSuccess) e = add_advance_node(g, &prev, &after, 1, t_dev);
-                }
-                if (e == hipSuccess) e = hipGraphInstantiate(&gc.exec, g, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(g);
-                if (e != hipSuccess) {
-                    gc.exec = nullptr;
-                    return fail(SMC_EHIP, "building the tempering graph: %s", hipGetErrorString(e));
-                }
-                gc.sig = sig;
-            }
-            const int32_t launches = which == 0 ? reps : 1;
-            for (int32_t k = 0; k < launches; ++k) SMC_HIP(hipGraphLaunch(gc.exec, s));
-        }
+    SMC_HIP(launch_pt_prepare(sw, energy, s));
+    for (int32_t k = 0; k < n_steps; ++k) {
+        sw.t = (uint32_t)(step0 + (uint64_t)k);
+        a.t = sw.t * (uint32_t)m;
+        SMC_HIP(launch_bins2d(a, (int)bins.size(), lds, !pp || k == 0, !pp || k == n_steps - 1, s));
+        SMC_HIP(launch_pt_swap(sw, s));
     }
     SMC_HIP(launch_pt_finish(sw, energy, s));
     return SMC_OK;
@@ -306,18 +246,15 @@ int run_sweep_lds2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Pla
     // threshold row of replica r: row r; energy changes into dE_accum (or scratch)
     std::vector<int32_t> ident(desc->n_rep);
     for (int r = 0; r < desc->n_rep; ++r) ident[r] = r;
-    void *rp = nullptr, *ep = nullptr, *tp = nullptr;
+    void *rp = nullptr, *ep = nullptr;
     if ((rc = upload(c, s, kRows, ident.data(), sizeof(int32_t) * ident.size(), &rp))) return rc;
     int64_t *E = dE_accum;
     if (!E) {
         if ((rc = ensure(c, kEnergy64, sizeof(int64_t) * desc->n_rep, &ep))) return rc;
         E = (int64_t *)ep;
     }
-    if ((rc = ensure(c, kStep, 2 * sizeof(uint32_t), &tp))) return rc;
-    uint32_t *t_dev = (uint32_t *)tp;
-    SMC_HIP(launch_set_step(t_dev, (uint32_t)sweep0, s));
     Uneven2dArgs a = make_uneven2d_args((int8_t *)spins, (const smc_inst *)st.inst_dev, st.csplit,
-                                        (const int32_t *)rp, thr, E, t_dev, make_key(desc->seed));
+                                        (const int32_t *)rp, thr, E, make_key(desc->seed));
     const bool ea = desc->model == SMC_EA;
     for (auto &e : st.classes) {
         const std::vector<int32_t> reps(st.work.begin() + e.first, st.work.begin() + e.first + e.count);
@@ -329,10 +266,10 @@ int run_sweep_lds2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Pla
     for (int32_t done = 0; done < n_sweeps;) {
         const int32_t chunk = n_sweeps - done < kLdsSweeps ? n_sweeps - done : kLdsSweeps;
         a.sweeps = chunk;
+        a.t = (uint32_t)(sweep0 + (uint64_t)done);
         for (const EdgeClass &e : st.classes)
             SMC_HIP(launch_uneven2d_sweep(a, wl + e.first, e.count, e.L, ea, e.threads, s));
         done += chunk;
-        if (done < n_sweeps) SMC_HIP(launch_advance_step(t_dev, s, (uint32_t)chunk));
     }
     timer.finish();
     return SMC_OK;
@@ -606,11 +543,8 @@ int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, in
         *launches = n_steps > 0 ? 6 + n_steps * (m + 4) : 0;
         *kernel_name = "k_ising2d_split";
     } else if (fits2d) {
-        // set step(s), prepare, (coupling split), graph launches of up to 32 steps, finish
-        const int32_t K = n_steps < 32 ? n_steps : 32;
-        const int32_t graphs = n_steps < 4 ? 0 : n_steps / K + (n_steps % K ? 1 : 0);
-        const int32_t direct = n_steps < 4 ? n_steps * (int32_t)(2 + 7) : 0;
-        *launches = n_steps > 0 ? 3 + (desc->model == SMC_EA ? 1 : 0) + graphs + direct : 0;
+        // prepare; per step the sweeps of every edge and the exchange round; finish
+        *launches = n_steps > 0 ? 2 + 2 * n_steps : 0;
         *kernel_name = "k_uneven2d_sweep";
     } else {
         *launches = n_steps > 0 ? (2 * m + 1) * n_steps + 2 : 0;
@@ -1328,7 +1262,6 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     if ((rc = ensure(c, kRows, sizeof(int32_t) * desc->n_rep, &rowrep))) return rc;
 
     SwapArgs sw;
-    sw.t_dev = nullptr;
     sw.n_chains = pt->n_chains;
     sw.n_temps = n;
     sw.beta_per_chain = pt->beta_per_chain ? 1 : 0;
@@ -1355,8 +1288,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     if (use_pt_split2d(desc, spins, rows))
         return run_pt_split2d(c, s, desc, spins, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
     if (use_uneven2d(desc, spins, couplings, rows))
-        return run_uneven2d(c, s, desc, plan, pt, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps,
-                            m);
+        return run_uneven2d(c, s, desc, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
     SMC_HIP(launch_pt_prepare(sw, energy, s));
     for (int32_t k = 0; k < n_steps; ++k) {
         const uint32_t t = (uint32_t)(step0 + (uint64_t)k);

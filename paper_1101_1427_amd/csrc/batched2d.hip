@@ -1,10 +1,7 @@
-// Sweeps of batches of small 2D lattices with each replica in LDS: parallel
-// tempering of uneven batches (Sec. 6, Eq. 12; many independent instances at
-// once) and plain sweeps of small uniform batches.
+// Sweeps of small uniform 2D batches with each replica in LDS.
 //
-// A launch per lattice size runs one workgroup per replica: it holds the
-// replica in LDS, runs `sweeps` sweeps (colour 0 then colour 1 each, sweep
-// indices from the device counter *t_dev on) and writes it back, tracking
+// A launch runs one workgroup per replica: it holds the replica in LDS, runs
+// `sweeps` sweeps (colour 0 then colour 1 each) and writes it back, tracking
 // the replica's energy.  Couplings are read from a
 // colour-split copy made once per call; the replicas of one instance run
 // next to each other on one XCD, so the copy is served from its L2 (keeping
@@ -246,7 +243,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_uneven2d_sweep(Uneven2dArgs a, 
     }
     const ThrRow &th = a.thr[row];
     const Lut2 K = lut2(th);
-    const uint32_t t0 = *a.t_dev;
+    const uint32_t t0 = a.t;
     __syncthreads();
 
     uint32_t cnt = 0u, nsum = 0u;
@@ -354,9 +351,6 @@ __global__ __launch_bounds__(256) void k_coup_split2d(const int8_t *coup, uint8_
     *(uint2 *)(o + half + 8 * m) = make_uint2(perm(b1, b0, 0x07050301u), perm(b3, b2, 0x07050301u));
 }
 
-__global__ void k_set_step(uint32_t *t_dev, uint32_t t) { *t_dev = t; }
-__global__ void k_advance_step(uint32_t *t_dev, uint32_t inc) { *t_dev += inc; }
-
 }  // namespace
 
 bool uneven2d_edge_supported(int L) { return L >= 16 && L <= 256 && L % 16 == 0; }
@@ -373,7 +367,7 @@ hipError_t uneven2d_prepare_kernel(bool ea, int L) {
 }
 
 Uneven2dArgs make_uneven2d_args(int8_t *spins, const smc_inst *inst, const uint8_t *csplit, const int32_t *row_of_rep,
-                                const ThrRow *thr, int64_t *E, const uint32_t *t_dev, Key key) {
+                                const ThrRow *thr, int64_t *E, Key key) {
     Uneven2dArgs a;
     a.spins = spins;
     a.inst = inst;
@@ -381,7 +375,7 @@ Uneven2dArgs make_uneven2d_args(int8_t *spins, const smc_inst *inst, const uint8
     a.row_of_rep = row_of_rep;
     a.thr = thr;
     a.E = E;
-    a.t_dev = t_dev;
+    a.t = 0;
     a.sweeps = 1;
     a.key = key;
     a.one2 = 0x00010001u;
@@ -396,47 +390,6 @@ hipError_t launch_coup_split2d(const int8_t *coup, uint8_t *out, const smc_inst 
     return hipGetLastError();
 }
 
-hipError_t launch_set_step(uint32_t *t_dev, uint32_t t, hipStream_t s) {
-    SMC_LAUNCH(k_set_step, dim3(1), dim3(1), 0, s, t_dev, t);
-    return hipGetLastError();
-}
-
-// ---- graph nodes ----
-hipError_t add_uneven2d_sweep_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                                   const Uneven2dArgs &a, const int32_t *work, int n_work, int L, bool ea,
-                                   int threads) {
-    Uneven2dArgs args = a;
-    const int32_t *w = work;
-    int edge = L;
-    void *params[] = {&args, &w, &edge};
-    hipKernelNodeParams p;
-    memset(&p, 0, sizeof p);
-    p.func = const_cast<void *>(uneven2d_kernel(ea));
-    p.gridDim = dim3((unsigned)n_work);
-    p.blockDim = dim3((unsigned)threads);
-    p.sharedMemBytes = (unsigned)uneven2d_lds_bytes(L);
-    p.kernelParams = params;
-    p.extra = nullptr;
-    if (const char *why = launch_config_error((uint64_t)n_work, (uint64_t)threads, p.sharedMemBytes))
-        return reject_launch("k_uneven2d_sweep (graph node)", (uint64_t)n_work, (uint64_t)threads, p.sharedMemBytes,
-                             why);
-    return hipGraphAddKernelNode(node, g, deps, n_deps, &p);
-}
-
-hipError_t add_advance_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                            uint32_t *t_dev, uint32_t inc) {
-    uint32_t *tp = t_dev;
-    uint32_t by = inc;
-    void *params[] = {&tp, &by};
-    hipKernelNodeParams p;
-    memset(&p, 0, sizeof p);
-    p.func = (void *)k_advance_step;
-    p.gridDim = dim3(1);
-    p.blockDim = dim3(1);
-    p.kernelParams = params;
-    return hipGraphAddKernelNode(node, g, deps, n_deps, &p);
-}
-
 hipError_t launch_uneven2d_sweep(const Uneven2dArgs &a, const int32_t *work, int n_work, int L, bool ea, int threads,
                                  hipStream_t s) {
     const size_t lds = uneven2d_lds_bytes(L);
@@ -444,11 +397,6 @@ hipError_t launch_uneven2d_sweep(const Uneven2dArgs &a, const int32_t *work, int
         SMC_LAUNCH(k_uneven2d_sweep<true>, dim3(n_work), dim3(threads), lds, s, a, work, L);
     else
         SMC_LAUNCH(k_uneven2d_sweep<false>, dim3(n_work), dim3(threads), lds, s, a, work, L);
-    return hipGetLastError();
-}
-
-hipError_t launch_advance_step(uint32_t *t_dev, hipStream_t s, uint32_t inc) {
-    SMC_LAUNCH(k_advance_step, dim3(1), dim3(1), 0, s, t_dev, inc);
     return hipGetLastError();
 }
 

@@ -1,0 +1,42 @@
+// Tempering sweeps of 2D batches with edges in {16, 32, ..., 256}, uniform or
+// uneven: bins of replicas in LDS, one launch per step (bins2d.hip).
+#pragma once
+#include <vector>
+
+#include "internal.hpp"
+
+namespace smc {
+
+// Up to kBinReps replicas of one edge that a workgroup sweeps together.
+constexpr int kBinReps = 64;
+struct Bin2d {
+    int64_t packed;  // first byte of the bin in the packed copy
+    int32_t first;   // first entry of the work list (replica indices)
+    int32_t count;
+    int32_t L;
+    int32_t pad;
+};
+
+struct Bins2dArgs {
+    int8_t *spins;             // caller's spins (row-major int8 +-1 per replica)
+    const int8_t *coup;        // EA, else nullptr
+    uint8_t *packed;           // the replicas in LDS layout between steps, or nullptr
+    const smc_inst *inst;      // device [n_rep]
+    const Bin2d *bins;
+    const int32_t *work;
+    const int32_t *row_of_rep; // threshold row per replica; -1 leaves the replica unchanged
+    const ThrRow *thr;
+    int64_t *E;                // tracked energy per replica
+    Key key;
+    uint32_t t;                // first sweep
+    int sweeps;
+};
+
+// The bins of a batch (rows: edge and offsets of every replica), largest
+// edges first; returns the dynamic LDS of a launch.
+size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, std::vector<int32_t> *work);
+// raw_in: from the caller's spins and couplings (else from the packed copy);
+// raw_out: to the caller's spins.
+hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_in, bool raw_out, hipStream_t s);
+
+}  // namespace smc

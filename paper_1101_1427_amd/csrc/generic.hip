@@ -251,30 +251,30 @@ __global__ void k_pt_prepare(SwapArgs a, const double *energy_in) {
         for (int k = 0; k < n; ++k) a.row_of_rep[q * n + k] = -1;
 }
 
+// The exchange round of step t: the pairs (k, k + 1) with k = t (mod 2) are
+// disjoint, one thread each.
 __global__ void k_pt_swap(SwapArgs a) {
 #pragma clang fp contract(off)
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.n_chains) return;
-    a.t = a.t_dev ? *a.t_dev : a.t;
-    const int n = a.n_temps;
+    const int n = a.n_temps, pairs = n / 2;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int q = (int)(i / pairs), k = 2 * (int)(i - (int64_t)q * pairs) + (int)(a.t & 1u);
+    if (q >= a.n_chains || k + 1 >= n) return;
     const int base = a.beta_per_chain ? q * n : 0;
     int32_t *sot = a.slot_of_temp + (int64_t)q * n;
     if (a.row_of_rep[q * n] < 0) return;  // not a permutation: chain left unchanged
-    for (int k = (int)(a.t & 1u); k + 1 < n; k += 2) {
-        const int A = sot[k], B = sot[k + 1];
-        const double x = (a.beta[base + k + 1] - a.beta[base + k]) * (double)(a.E[q * n + B] - a.E[q * n + A]);
-        bool accept = x >= 0.0;
-        if (!accept) {
-            const uint4 w = philox4x32_10(make_uint4((uint32_t)k, a.t, (uint32_t)q, 2 * kTagSwap), a.key);
-            accept = unit53(w.x, w.y) < exp(x);
-        }
-        if (accept) {
-            sot[k] = B;
-            sot[k + 1] = A;
-            a.row_of_rep[q * n + B] = base + k;
-            a.row_of_rep[q * n + A] = base + k + 1;
-            if (a.acc) a.acc[(int64_t)q * (n - 1) + k] += 1ull;
-        }
+    const int A = sot[k], B = sot[k + 1];
+    const double x = (a.beta[base + k + 1] - a.beta[base + k]) * (double)(a.E[q * n + B] - a.E[q * n + A]);
+    bool accept = x >= 0.0;
+    if (!accept) {
+        const uint4 w = philox4x32_10(make_uint4((uint32_t)k, a.t, (uint32_t)q, 2 * kTagSwap), a.key);
+        accept = unit53(w.x, w.y) < exp(x);
+    }
+    if (accept) {
+        sot[k] = B;
+        sot[k + 1] = A;
+        a.row_of_rep[q * n + B] = base + k;
+        a.row_of_rep[q * n + A] = base + k + 1;
+        if (a.acc) a.acc[(int64_t)q * (n - 1) + k] += 1ull;
     }
 }
 
@@ -351,23 +351,9 @@ hipError_t launch_pt_prepare(const SwapArgs &a, const double *energy_in, hipStre
 }
 
 hipError_t launch_pt_swap(const SwapArgs &a, hipStream_t s) {
-    SMC_LAUNCH(k_pt_swap, dim3((a.n_chains + 255) / 256), dim3(256), 0, s, a);
+    const int64_t threads = (int64_t)a.n_chains * (a.n_temps / 2);
+    SMC_LAUNCH(k_pt_swap, dim3((unsigned)((threads + 127) / 128)), dim3(128), 0, s, a);
     return hipGetLastError();
-}
-
-hipError_t add_pt_swap_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                            const SwapArgs &a) {
-    SwapArgs args = a;
-    void *params[] = {&args};
-    hipKernelNodeParams p;
-    memset(&p, 0, sizeof p);
-    p.func = (void *)k_pt_swap;
-    p.gridDim = dim3((unsigned)((a.n_chains + 255) / 256));
-    p.blockDim = dim3(256);
-    p.kernelParams = params;
-    if (const char *why = launch_config_error(p.gridDim.x, 256, 0))
-        return reject_launch("k_pt_swap (graph node)", p.gridDim.x, 256, 0, why);
-    return hipGraphAddKernelNode(node, g, deps, n_deps, &p);
 }
 
 hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s) {

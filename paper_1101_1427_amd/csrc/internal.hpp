@@ -73,7 +73,6 @@ struct SweepArgs {
 };
 
 struct SwapArgs {
-    const uint32_t *t_dev;     // step index in device memory, or nullptr: use t
     int n_chains, n_temps, beta_per_chain;
     const double *beta;        // device [rows][n_temps]
     int32_t *slot_of_temp;     // [n_chains][n_temps]
@@ -130,8 +129,8 @@ struct Uneven2dArgs {
     const int32_t *row_of_rep; // threshold row per replica; -1 leaves the replica unchanged
     const ThrRow *thr;
     int64_t *E;                // tracked energy per replica
-    const uint32_t *t_dev;     // first sweep index of the launch (device)
-    int sweeps;                // sweeps per launch (indices *t_dev .. *t_dev + sweeps - 1), the replica kept in LDS
+    uint32_t t;                // first sweep of the launch
+    int sweeps;                // sweeps per launch, the replica kept in LDS
     Key key;
     uint32_t one2;  // 0x00010001 (opaque to the compiler)
 };
@@ -139,20 +138,11 @@ bool uneven2d_edge_supported(int L);
 size_t uneven2d_lds_bytes(int L);
 hipError_t uneven2d_prepare_kernel(bool ea, int L);
 Uneven2dArgs make_uneven2d_args(int8_t *spins, const smc_inst *inst, const uint8_t *csplit, const int32_t *row_of_rep,
-                                const ThrRow *thr, int64_t *E, const uint32_t *t_dev, Key key);
+                                const ThrRow *thr, int64_t *E, Key key);
 hipError_t launch_coup_split2d(const int8_t *coup, uint8_t *out, const smc_inst *samples, int n_samples,
                                int64_t chunks_total, const int64_t *chunk_start, hipStream_t s);
-hipError_t launch_set_step(uint32_t *t_dev, uint32_t t, hipStream_t s);
 hipError_t launch_uneven2d_sweep(const Uneven2dArgs &a, const int32_t *work, int n_work, int L, bool ea, int threads,
                                  hipStream_t s);
-hipError_t launch_advance_step(uint32_t *t_dev, hipStream_t s, uint32_t inc = 1);
-hipError_t add_uneven2d_sweep_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                                   const Uneven2dArgs &a, const int32_t *work, int n_work, int L, bool ea,
-                                   int threads);
-hipError_t add_advance_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                            uint32_t *t_dev, uint32_t inc = 1);
-hipError_t add_pt_swap_node(hipGraph_t g, hipGraphNode_t *node, const hipGraphNode_t *deps, size_t n_deps,
-                            const SwapArgs &a);
 
 // Asynchronous multi-spin coding (2D EA/Ising, L in {16, 32, 64}): replicas
 // 32g .. 32g+31 packed into one word per site, all sweeps in one launch.

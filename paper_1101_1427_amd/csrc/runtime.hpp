@@ -57,7 +57,6 @@ enum Slot {
     kCoupSplit,
     kChunks,
     kWork,
-    kStep,
     kTuneSpins,
     kTuneInst,
     kTuneWork,
@@ -70,6 +69,8 @@ enum Slot {
     kMscEnergy,
     kMscGauge,
     kDcbSlots,
+    kBins2d,     // bins of the 2D tempering batches and their packed copy
+    kBinsPacked,
     kBands2d,    // second lattice of the 2D bands
     kTallySlots, // per-workgroup sums of a sweep call
     kPtThr,
@@ -82,17 +83,9 @@ enum Slot {
     kNumSlots
 };
 
-// An instantiated tempering graph of `steps` steps and the launch arguments
-// it was built from (rebuilt when they change).
-struct GraphCache {
-    std::vector<uint64_t> sig;
-    hipGraphExec_t exec = nullptr;
-};
-
 struct StreamCtx {
     hipStream_t stream = nullptr;  // the stream whose calls use this set
     Buffer dev[kNumSlots];
-    GraphCache graphs[2];  // full chunk of steps, remainder
 };
 
 StreamCtx &ctx_for(hipStream_t s);

@@ -382,10 +382,8 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
     Shape known;
     if (!count.empty()) {
         const ThrRow row = threshold_row(0.44, 2);
-        void *tp = nullptr, *st = nullptr;
+        void *tp = nullptr;
         if ((rc = upload(c, s, kTables, &row, sizeof row, &tp))) return rc;
-        if ((rc = ensure(c, kStep, 2 * sizeof(uint32_t), &st))) return rc;
-        SMC_HIP(launch_set_step((uint32_t *)st, 0u, s));
         for (auto &kv : count) {
             const int L = kv.first, M = std::min(kv.second, 4096);
             const int64_t N = (int64_t)L * L;
@@ -404,7 +402,7 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
             }
             SMC_HIP(uneven2d_prepare_kernel(ea, L));
             const Uneven2dArgs a = make_uneven2d_args((int8_t *)sp, nullptr, (const uint8_t *)cp, nullptr,
-                                                      (const ThrRow *)tp, nullptr, (const uint32_t *)st, key);
+                                                      (const ThrRow *)tp, nullptr, key);
             int th = 0;
             if ((rc = uneven2d_threads(c, s, a, L, ea, reps, rows, &th))) return rc;
         }
