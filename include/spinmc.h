@@ -54,12 +54,10 @@
  * - Return value: SMC_OK (0) or a negative smc_status.
  * - Execution paths.  Uniform 2D Ising batches with L a power of two in
  *   [1024, 16384] sweep on a colour-split copy of the lattice in one launch
- *   per sweep (tempering too); uniform 2D Ising / EA batches of edge 16 ..
- *   128 (or 256 with at least 2^19 sites) keep each replica in one
- *   workgroup's LDS for up to 256 sweeps per launch; 3D edge-16 tempering
- *   runs all steps of a call in one launch; 2D tempering with edges in
- *   {16, 32, ..., 256} runs one workgroup per replica per step (a graph of
- *   steps); uniform 3D Ising / EA batches with L a multiple of 16 sweep
+ *   per sweep (tempering too); 2D tempering with edges in {16, 32, ..., 256}
+ *   keeps bins of replicas on chip for a step, one launch per step for all
+ *   edges; 3D edge-16 tempering runs all steps of a call in one launch;
+ *   uniform 3D Ising / EA batches with L a multiple of 16 sweep
  *   16-site row segments per thread: for L in [512, 1024] in one launch per
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
@@ -69,16 +67,23 @@
  *   thread where an edge is below 16), or, for uniform 3D batches of edge 4
  *   .. 14, whole replicas held on chip for the call (tempering too, with up
  *   to 64 temperatures that fit), or, for uniform 2D batches where an
- *   estimate says that it is faster, bands of rows held on chip for several
- *   sweeps per launch, alternating with a library-held second lattice.  All
- *   paths give identical results.  Environment variables for comparisons and tuning
+ *   estimate says that it is faster, bands of rows (or a whole lattice) held
+ *   on chip for several sweeps per launch, alternating with a library-held
+ *   second lattice.  Small 2D batches (L a multiple of 16 up to 128, or 256
+ *   with at least 2^19 sites in the batch: "k_uneven2d_sweep") run on these
+ *   bands as well, and so do calls of two and more sweeps on power-of-two
+ *   edges up to 2048 with at most 2^25 sites in the batch.  All paths give
+ *   identical results.  Environment variables for comparisons and tuning
  *   (read at each call): SPINMC_PT3D=0, SPINMC_UNEVEN2D=0 and
- *   SPINMC_PT_SPLIT2D=0 send tempering to the generic kernels,
- *   SPINMC_SWEEP_LDS2D=0 small 2D sweeps, SPINMC_SWEEP3D=0 3D Ising / EA
- *   sweeps; on the general path SPINMC_BANDS2D=0 keeps the half-sweeps, =1
- *   takes the bands wherever they fit (SPINMC_BANDS2D_ROWS and _SWEEPS set
- *   their shape), SPINMC_SMALL3D=0 keeps the small 3D edges on the
- *   half-sweeps and SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps the two launches per sweep for
+ *   SPINMC_PT_SPLIT2D=0 send tempering to the general path,
+ *   SPINMC_SWEEP_LDS2D=0 small 2D sweeps to the half-sweeps,
+ *   SPINMC_SWEEP3D=0 3D Ising / EA sweeps to the general path;
+ *   SPINMC_BANDS2D=0 keeps the half-sweeps, =1 takes the bands wherever they
+ *   fit (SPINMC_BANDS2D_ROWS and _SWEEPS set their shape,
+ *   SPINMC_U2D_THREADS the workgroup of a whole lattice);
+ *   SPINMC_SMALL3D=0 keeps the small 3D edges on the half-sweeps and
+ *   SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps
+ *   the two launches per sweep for
  *   every edge, =1 takes the one launch from edge 32 (SPINMC_PASS3D_TY,
  *   _SEGS and _D set its rows per strip, segments per thread and planes
  *   per z segment; SPINMC_SWEEP3D_Z = 1 .. 16 rows per thread and
@@ -87,7 +92,8 @@
  *   SPINMC_L2D_H (band height, a multiple of 4), SPINMC_L2D_H1 /
  *   SPINMC_L2D_H2 (heights of the bands of the first and second half of
  *   the grid) and SPINMC_L2D_PAD (row padding in bytes) set the launch
- *   shape of the 2D Ising sweep.  SPINMC_HEIS3D=0 sends uniform 3D
+ *   shape of the one-pass 2D Ising sweep (and keep the edges it serves on
+ *   it).  SPINMC_HEIS3D=0 sends uniform 3D
  *   Heisenberg batches to the generic kernel.
  */
 #ifndef SPINMC_H
@@ -267,10 +273,9 @@ int smc_measure_energy_magnetisation_noalloc(const smc_desc *desc, const void *s
  * Autotuning of launch shapes; it never changes results.  It measures, on
  * scratch lattices of the batch's shape with random spins, and keeps for
  * later calls in the process on this device:
- *  - 2D Ising / EA: the workgroup size of the LDS-resident 2D kernel
- *    (small lattices, uneven tempering) for every edge of the batch that
- *    this kernel takes (calls that meet an edge first measure it
- *    themselves, on copies of their own replicas);
+ *  - 2D Ising / EA with an edge in {16, 32, ..., 256}: the workgroup size of
+ *    sweeps that hold a whole lattice on chip (calls choose it by a rule
+ *    unless it was measured);
  *  - uniform 2D Ising with L a power of two in [1024, 16384]: the band
  *    height of the one-pass sweep (rows per workgroup, 4 .. 128), per edge
  *    and replica count;

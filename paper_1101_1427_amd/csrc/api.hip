@@ -24,15 +24,8 @@ namespace smc {
 namespace {
 
 // ------------------------------------------------ uneven 2D tempering ----
-// Batches of 2D lattices with edges in {16, 32, ..., 256}: tempering (uniform
-// or uneven) goes to the bins of replicas, sweeps of small uniform batches to
-// the per-replica LDS kernel, where the replicas of one edge form a class with
-// its own launch shape.
-struct EdgeClass {
-    int L = 0, threads = 0;
-    int32_t first = 0, count = 0;  // range of the work list
-};
-
+// Tempering of 2D batches with edges in {16, 32, ..., 256}, uniform or uneven,
+// goes to the bins of replicas.
 bool use_uneven2d(const smc_desc *d, const void *spins, const int8_t *coup, const std::vector<ThrRow> &rows) {
     if (d->dim != 2 || (d->model != SMC_ISING && d->model != SMC_EA)) return false;
     const char *env = getenv("SPINMC_UNEVEN2D");
@@ -64,64 +57,6 @@ std::vector<smc_inst> inst_rows(const smc_desc *d) {
         }
     }
     return rows;
-}
-
-// What the LDS-resident 2D kernel needs for a batch: the instance table, the
-// replicas grouped by edge (classes, largest first; replica order within a
-// class) and the colour-split couplings of every sample.
-struct Lds2dSetup {
-    std::vector<smc_inst> rows;
-    std::vector<EdgeClass> classes;
-    std::vector<int32_t> work;
-    void *inst_dev = nullptr;
-    void *work_dev = nullptr;
-    uint8_t *csplit = nullptr;
-};
-
-int lds2d_setup(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Plan &plan, const int8_t *couplings,
-                Lds2dSetup &st) {
-    int rc;
-    st.rows = inst_rows(desc);
-    if ((rc = upload(c, s, kInst, st.rows.data(), sizeof(smc_inst) * st.rows.size(), &st.inst_dev))) return rc;
-    std::map<int, std::vector<int32_t>, std::greater<int>> by_edge;
-    for (int r = 0; r < desc->n_rep; ++r) by_edge[st.rows[r].L].push_back(r);
-    for (auto &kv : by_edge) {
-        EdgeClass e;
-        e.L = kv.first;
-        e.threads = 0;  // chosen by the caller
-        e.first = (int32_t)st.work.size();
-        e.count = (int32_t)kv.second.size();
-        st.work.insert(st.work.end(), kv.second.begin(), kv.second.end());
-        st.classes.push_back(e);
-        SMC_HIP(uneven2d_prepare_kernel(desc->model == SMC_EA, e.L));
-    }
-    if ((rc = upload(c, s, kWork, st.work.data(), sizeof(int32_t) * st.work.size(), &st.work_dev))) return rc;
-    if (desc->model == SMC_EA) {
-        std::vector<smc_inst> samples;
-        if (desc->L > 0) {
-            samples.resize((size_t)plan.n_samples);
-            for (int64_t q = 0; q < plan.n_samples; ++q)
-                samples[(size_t)q] = smc_inst{desc->L, (int32_t)q, 0, q * 2 * (int64_t)desc->L * desc->L};
-        } else {
-            std::map<int32_t, smc_inst> seen;
-            for (const smc_inst &g : st.rows) seen.emplace(g.sample, g);
-            for (auto &kv : seen) samples.push_back(kv.second);
-        }
-        std::vector<int64_t> start(samples.size());
-        int64_t total = 0;
-        for (size_t k = 0; k < samples.size(); ++k) {
-            start[k] = total;
-            total += 2 * (int64_t)samples[k].L * samples[k].L / 16;
-        }
-        void *samp_dev = nullptr, *start_dev = nullptr, *cs = nullptr;
-        if ((rc = upload(c, s, kSamples, samples.data(), sizeof(smc_inst) * samples.size(), &samp_dev))) return rc;
-        if ((rc = upload(c, s, kChunks, start.data(), sizeof(int64_t) * start.size(), &start_dev))) return rc;
-        if ((rc = ensure(c, kCoupSplit, (size_t)desc->coup_len, &cs))) return rc;
-        st.csplit = (uint8_t *)cs;
-        SMC_HIP(launch_coup_split2d(couplings, st.csplit, (const smc_inst *)samp_dev, (int)samples.size(), total,
-                                    (const int64_t *)start_dev, s));
-    }
-    return SMC_OK;
 }
 
 int run_uneven2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, void *spins, const int8_t *couplings,
@@ -216,63 +151,18 @@ struct SweepTimer {
     ~SweepTimer() { finish(); }
 };
 
-// Sweeps of a uniform 2D Ising / EA batch of edge 16 .. 256 (a multiple of
-// 16) on the LDS-resident kernel: each replica stays in one workgroup's LDS
-// for up to kLdsSweeps sweeps per launch, so small lattices are not bound
-// by two launches per sweep.  Same results as the generic kernels;
-// SPINMC_SWEEP_LDS2D=0 sends such batches to them.
-constexpr int kLdsSweeps = 256;
-
-// A workgroup sweeps about 6e9 sites per second, so one replica of edge 256
-// (65536 sites) takes longer in one workgroup than the generic kernels take
-// over the whole chip; above edge 128 the batch must hold at least 2^19 sites.
-bool lds2d_sweep_shape(const smc_desc *d) {
-    const char *env = getenv("SPINMC_SWEEP_LDS2D");
-    if (env && env[0] == '0') return false;
-    if (d->dim != 2 || d->L <= 0 || !uneven2d_edge_supported(d->L)) return false;
+// Small uniform 2D batches of edge 16 .. 128 (a multiple of 16), and of edge
+// 256 with at least 2^19 sites, whose path has its own name in the plans and
+// its own switch: SPINMC_SWEEP_LDS2D=0 sends them to the half-sweeps.
+bool small2d_shape(const smc_desc *d) {
+    if (d->dim != 2 || d->L <= 0 || (d->model != SMC_ISING && d->model != SMC_EA) || !uneven2d_edge_supported(d->L))
+        return false;
     return d->L <= 128 || (int64_t)d->n_rep * d->L * d->L >= (int64_t)1 << 19;
 }
 
-bool use_sweep_lds2d(const smc_desc *d, const void *spins, const int8_t *coup, const std::vector<ThrRow> &rows) {
-    return lds2d_sweep_shape(d) && use_uneven2d(d, spins, coup, rows);
-}
-
-int run_sweep_lds2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, const Plan &plan, void *spins,
-                    const int8_t *couplings, const ThrRow *thr, int64_t *dE_accum, uint64_t sweep0,
-                    int32_t n_sweeps) {
-    int rc;
-    Lds2dSetup st;
-    if ((rc = lds2d_setup(c, s, desc, plan, couplings, st))) return rc;
-    // threshold row of replica r: row r; energy changes into dE_accum (or scratch)
-    std::vector<int32_t> ident(desc->n_rep);
-    for (int r = 0; r < desc->n_rep; ++r) ident[r] = r;
-    void *rp = nullptr, *ep = nullptr;
-    if ((rc = upload(c, s, kRows, ident.data(), sizeof(int32_t) * ident.size(), &rp))) return rc;
-    int64_t *E = dE_accum;
-    if (!E) {
-        if ((rc = ensure(c, kEnergy64, sizeof(int64_t) * desc->n_rep, &ep))) return rc;
-        E = (int64_t *)ep;
-    }
-    Uneven2dArgs a = make_uneven2d_args((int8_t *)spins, (const smc_inst *)st.inst_dev, st.csplit,
-                                        (const int32_t *)rp, thr, E, make_key(desc->seed));
-    const bool ea = desc->model == SMC_EA;
-    for (auto &e : st.classes) {
-        const std::vector<int32_t> reps(st.work.begin() + e.first, st.work.begin() + e.first + e.count);
-        if ((rc = uneven2d_threads(c, s, a, e.L, ea, reps, st.rows, &e.threads))) return rc;
-    }
-    const int32_t *wl = (const int32_t *)st.work_dev;
-    const int64_t launches = ((int64_t)n_sweeps + kLdsSweeps - 1) / kLdsSweeps * (int64_t)st.classes.size();
-    SweepTimer timer(s, launches);
-    for (int32_t done = 0; done < n_sweeps;) {
-        const int32_t chunk = n_sweeps - done < kLdsSweeps ? n_sweeps - done : kLdsSweeps;
-        a.sweeps = chunk;
-        a.t = (uint32_t)(sweep0 + (uint64_t)done);
-        for (const EdgeClass &e : st.classes)
-            SMC_HIP(launch_uneven2d_sweep(a, wl + e.first, e.count, e.L, ea, e.threads, s));
-        done += chunk;
-    }
-    timer.finish();
-    return SMC_OK;
+bool small2d_enabled() {
+    const char *env = getenv("SPINMC_SWEEP_LDS2D");
+    return !(env && env[0] == '0');
 }
 
 // The per-replica sums of one sweep call.  With fewer than 16 workgroups per
@@ -306,48 +196,104 @@ struct CallTally {
     }
 };
 
-// Uniform 2D batches of the general path run several sweeps per launch on
-// bands of rows in LDS where the estimate says that it is faster than two
-// half-sweep launches per sweep (measured: about 3.5 us and 1.2 fs per site
-// each); a band needs about 5 K bytes of LDS per row of 4 K sites, so large
-// edges keep the half-sweeps, and so does a call of one sweep unless the
-// lattice fits in LDS as a whole.  SPINMC_BANDS2D=0 keeps the half-sweeps
-// (same results).
-bool use_bands2d(const SweepArgs &a, int32_t n_sweeps, BandShape *sh) {
+// Uniform 2D batches run several sweeps per launch on bands of rows in LDS
+// where the estimate says that it is faster than two half-sweep launches per
+// sweep (measured: about 3.5 us and 1.2 fs per site each).  A band needs about
+// 5 K bytes of LDS per row of 4 K sites, so large edges keep the half-sweeps,
+// and so does a call of one sweep unless the lattice fits in LDS as a whole.
+// SPINMC_BANDS2D=0 keeps the half-sweeps (same results), and so does
+// SPINMC_PT_SPLIT2D=0 in tempering (even is false there).
+bool use_bands2d(const smc_desc *d, const SweepArgs &a, int32_t n_sweeps, bool even, BandShape *sh) {
     const char *env = getenv("SPINMC_BANDS2D");
     if ((env && env[0] == '0') || a.b.dim != 2 || a.b.L <= 0) return false;
-    if (!bands2d_shape(a.b.L, a.b.n_rep, a.coup != nullptr, n_sweeps, sh)) return false;
-    if (env && env[0] == '1') return true;
-    return sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)a.b.n_rep * (double)a.b.N);
+    const bool forced = env && env[0] == '1';
+    if (!forced && small2d_shape(d) && !small2d_enabled()) return false;
+    const char *split = getenv("SPINMC_PT_SPLIT2D");
+    if (!forced && !even && split && split[0] == '0') return false;
+    if (!bands2d_shape(a.b.L, a.b.n_rep, a.coup != nullptr, n_sweeps, even, sh)) return false;
+    return forced || sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)a.b.n_rep * (double)a.b.N);
 }
+
+// Edges that the one-pass kernel (lattice2d.hip) serves: up to 2048 and 2^25
+// sites the bands are faster, because they move the lattice once per several
+// sweeps and need one launch for them (1024^2: 3.1 against 6.4 us per sweep,
+// eight of 2048^2: 24 against 33); above, the one-pass kernel's fewer
+// instructions per site win (16 of 2048^2: 37 against 46, 4096^2: 13.6
+// against 15.3).  A launch shape asked for in the environment is the one-pass
+// kernel's.
+bool bands_before_lattice2d(const smc_desc *d) {
+    for (const char *name : {"SPINMC_L2D_CHUNKS", "SPINMC_L2D_H", "SPINMC_L2D_H1", "SPINMC_L2D_H2", "SPINMC_L2D_PAD",
+                             "SPINMC_L2D_FUSE"})
+        if (getenv(name)) return false;
+    return d->L <= 2048 && (int64_t)d->n_rep * d->L * d->L <= (int64_t)1 << 25;
+}
+
+// Sweeps on bands, from a.spins to `other` and back, launch by launch.
+struct BandRun {
+    Bands2dArgs ba;
+    BandShape sh;
+    int8_t *lattice[2];
+    int at = 0;  // the lattice that holds the spins
+
+    BandRun(const SweepArgs &a, const BandShape &shape, void *other) : sh(shape) {
+        lattice[0] = (int8_t *)a.spins;
+        lattice[1] = shape.whole ? (int8_t *)a.spins : (int8_t *)other;
+        ba.coup = a.coup;
+        ba.rep_per_sample = a.b.rep_per_sample;
+        ba.thr = a.thr;
+        ba.row_of_rep = a.row_of_rep;
+        ba.key = a.key;
+        ba.rng_shift = a.rng_shift;
+        ba.n_rep = a.b.n_rep;
+        ba.L = a.b.L;
+    }
+    int sweeps(hipStream_t s, uint64_t sweep0, int32_t n_sweeps, int launches, CallTally &tally) {
+        int32_t done = 0;
+        for (int k = 0; k < launches; ++k) {
+            const int32_t n = (n_sweeps - done + launches - k - 1) / (launches - k);
+            ba.src = lattice[at];
+            ba.dst = lattice[1 - at];
+            ba.t = (uint32_t)(sweep0 + (uint64_t)done);
+            SMC_HIP(launch_bands2d(ba, sh, n, tally.next(), s));
+            done += n;
+            at = 1 - at;
+        }
+        return SMC_OK;
+    }
+};
 
 int run_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandShape &sh, void *other, uint64_t sweep0,
                 int32_t n_sweeps, int64_t *dE) {
     CallTally tally;
     int rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), dE);
     if (rc) return rc;
-    Bands2dArgs ba;
-    ba.coup = a.coup;
-    ba.rep_per_sample = a.b.rep_per_sample;
-    ba.thr = a.thr;
-    ba.row_of_rep = a.row_of_rep;
-    ba.key = a.key;
-    ba.rng_shift = a.rng_shift;
-    ba.n_rep = a.b.n_rep;
-    ba.L = a.b.L;
-    const int launches = bands2d_launches(sh, n_sweeps);
+    BandRun run(a, sh, other);
+    const int launches = bands2d_launches(sh, n_sweeps, true);
     SweepTimer timer(s, launches);
-    int32_t done = 0;
-    for (int k = 0; k < launches; ++k) {
-        const int32_t n = (n_sweeps - done + launches - k - 1) / (launches - k);
-        ba.src = (const int8_t *)(sh.whole || !(k & 1) ? a.spins : other);
-        ba.dst = (int8_t *)(sh.whole || (k & 1) ? a.spins : other);
-        ba.t = (uint32_t)(sweep0 + (uint64_t)done);
-        SMC_HIP(launch_bands2d(ba, sh, n, tally.next(), s));
-        done += n;
-    }
+    if ((rc = run.sweeps(s, sweep0, n_sweeps, launches, tally))) return rc;
     timer.finish();
     return tally.finish(s);
+}
+
+// Tempering on the bands: m sweeps, then the exchange round, per step.
+int run_pt_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandShape &sh, void *other, SwapArgs &sw,
+                   double *energy, uint64_t step0, int32_t n_steps, int m) {
+    int rc;
+    SMC_HIP(launch_pt_prepare(sw, energy, s));
+    BandRun run(a, sh, other);
+    const int launches = bands2d_launches(sh, m, false);
+    for (int32_t k = 0; k < n_steps; ++k) {
+        sw.t = (uint32_t)(step0 + (uint64_t)k);
+        CallTally tally;
+        if ((rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), sw.E))) return rc;
+        if ((rc = run.sweeps(s, (uint64_t)sw.t * (uint64_t)m, m, launches, tally))) return rc;
+        if ((rc = tally.finish(s))) return rc;
+        SMC_HIP(launch_pt_swap(sw, s));
+    }
+    if (!sh.whole && run.at)
+        SMC_HIP(hipMemcpyAsync(a.spins, other, (size_t)a.b.n_rep * (size_t)a.b.N, hipMemcpyDeviceToDevice, s));
+    SMC_HIP(launch_pt_finish(sw, energy, s));
+    return SMC_OK;
 }
 
 // Sweeps of small 3D replicas in LDS, up to kSmall3dSweeps per launch (so
@@ -388,7 +334,7 @@ int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a,
                 int64_t *dE) {
     if (use_small3d(desc)) return run_small3d(s, a, sweep0, n_sweeps, dE);
     BandShape sh;
-    if (use_bands2d(a, n_sweeps, &sh)) {
+    if (use_bands2d(desc, a, n_sweeps, true, &sh)) {
         void *other = nullptr;
         if (sh.whole || ensure(c, kBands2d, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
             return run_bands2d(c, s, a, sh, other, sweep0, n_sweeps, dE);
@@ -493,7 +439,8 @@ int smc_sweep_plan(const smc_desc *desc, int32_t *launches_per_sweep, const char
         const bool pass = pass3d_enabled(desc);
         *launches_per_sweep = pass ? 1 : 2;
         *kernel_name = pass ? "k_ising3d_pass" : "k_ising3d_half";
-    } else if (lds2d_sweep_shape(desc) && !(getenv("SPINMC_UNEVEN2D") && getenv("SPINMC_UNEVEN2D")[0] == '0')) {
+    } else if (small2d_shape(desc) && small2d_enabled() &&
+               !(getenv("SPINMC_UNEVEN2D") && getenv("SPINMC_UNEVEN2D")[0] == '0')) {
         *launches_per_sweep = 1;  // at most: up to 256 sweeps per launch
         *kernel_name = "k_uneven2d_sweep";
     } else {
@@ -687,9 +634,9 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     for (int r = 0; r < desc->n_rep; ++r) rows[r] = threshold_row(beta[r], desc->dim);
     if ((rc = upload(c, s, kTables, rows.data(), sizeof(ThrRow) * rows.size(), &p))) return rc;
     a.thr = (const ThrRow *)p;
-    if (use_sweep_lds2d(desc, spins, couplings, rows))
-        return run_sweep_lds2d(c, s, desc, plan, spins, couplings, a.thr, dE_accum, sweep0, n_sweeps);
-    if (use_lattice2d(desc, spins, rows)) {
+    BandShape sh;
+    if (use_lattice2d(desc, spins, rows) &&
+        !(bands_before_lattice2d(desc) && use_bands2d(desc, a, n_sweeps, true, &sh))) {
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);
         void *pp = nullptr;
@@ -1279,25 +1226,37 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     a.spins = spins;
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
-    a.tally.total = (int64_t *)E64;
     a.min_L = plan.min_L;
     a.max_L = plan.max_L;
     a.thr = (const ThrRow *)thr;
     a.row_of_rep = (const int32_t *)rowrep;
 
-    if (use_pt_split2d(desc, spins, rows))
+    BandShape sh;
+    const bool bands = use_bands2d(desc, a, m, false, &sh);
+    if (use_pt_split2d(desc, spins, rows) && !(bands && bands_before_lattice2d(desc)))
         return run_pt_split2d(c, s, desc, spins, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
     if (use_uneven2d(desc, spins, couplings, rows))
         return run_uneven2d(c, s, desc, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
+    if (bands) {
+        void *other = nullptr;
+        if (sh.whole || ensure(c, kBands2d, (size_t)desc->n_rep * (size_t)plan.b.N, &other) == SMC_OK)
+            return run_pt_bands2d(c, s, a, sh, other, sw, energy, step0, n_steps, m);
+        last_error().clear();  // no room for a second lattice: the half-sweeps need none
+    }
     SMC_HIP(launch_pt_prepare(sw, energy, s));
     for (int32_t k = 0; k < n_steps; ++k) {
         const uint32_t t = (uint32_t)(step0 + (uint64_t)k);
         sw.t = t;
+        CallTally tally;
+        if ((rc = tally.begin(c, desc->n_rep, half_sweep_groups(a), sw.E))) return rc;
         for (int j = 0; j < m; ++j) {
             a.t = t * (uint32_t)m + (uint32_t)j;
-            SMC_HIP(launch_half_sweep_generic(a, 0, s));
-            SMC_HIP(launch_half_sweep_generic(a, 1, s));
+            for (int col = 0; col < 2; ++col) {
+                a.tally = tally.next();
+                SMC_HIP(launch_half_sweep_generic(a, col, s));
+            }
         }
+        if ((rc = tally.finish(s))) return rc;
         SMC_HIP(launch_pt_swap(sw, s));
     }
     SMC_HIP(launch_pt_finish(sw, energy, s));

@@ -373,16 +373,18 @@ __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
 
 // Fills the rest of a shape from (rows, sweeps per launch, whole) and
 // estimates its time per sweep; false if it does not fit.
-bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps) {
+bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even) {
     const int K = pieces_of(L), halo = sh.whole ? 0 : 2 * sh.sweeps, R = sh.rows + 2 * halo;
     const size_t lds = (size_t)R * pitch_of(L) + 2 * kPad;
     if (lds > kMaxLdsBytes - 1024 || halo > L) return false;
-    const int launches = bands2d_launches(sh, n_sweeps);
+    const int launches = bands2d_launches(sh, n_sweeps, even);
     if (launches > n_sweeps) return false;
     const int64_t pieces = (int64_t)R * K;
     const int rounds = (int)((pieces + kMaxThreads - 1) / kMaxThreads);
     sh.threads = (int)std::max<int64_t>(64, ((pieces + rounds - 1) / rounds + 63) / 64 * 64);
     if (sh.threads > kMaxThreads) sh.threads = kMaxThreads;
+    if (sh.whole)
+        if (const int tuned = small2d_threads(L, ea)) sh.threads = tuned;
     // Workgroups per compute unit, and how many run there at once.
     const int64_t groups = (int64_t)n_rep * ((L + sh.rows - 1) / sh.rows);
     const double per_cu = (double)((groups + 255) / 256);
@@ -402,18 +404,18 @@ bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps) {
 
 }  // namespace
 
-bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, BandShape *out) {
+bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out) {
     BandShape best;
     auto offer = [&](int rows, int sweeps, bool whole) {
         BandShape sh;
         sh.rows = rows;
         sh.sweeps = sweeps;
         sh.whole = whole;
-        if (complete(sh, L, n_rep, ea, n_sweeps) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
+        if (complete(sh, L, n_rep, ea, n_sweeps, even) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
     };
     offer(L, std::min(n_sweeps, 256), true);
     for (int sweeps : {1, 2, 3, 4, 6, 8})
-        if (sweeps <= (n_sweeps + 1) / 2)
+        if (sweeps <= (even ? (n_sweeps + 1) / 2 : n_sweeps))
             for (int rows = 2; rows < L; rows += rows < 16 ? 2 : rows < 64 ? 8 : 32) offer(rows, sweeps, false);
     const char *er = getenv("SPINMC_BANDS2D_ROWS"), *es = getenv("SPINMC_BANDS2D_SWEEPS");
     if (er && es && atoi(er) > 0 && atoi(es) > 0) {
@@ -424,9 +426,9 @@ bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, BandShape *out) {
     return best.rows > 0;
 }
 
-int bands2d_launches(const BandShape &sh, int n_sweeps) {
+int bands2d_launches(const BandShape &sh, int n_sweeps, bool even) {
     const int n = (n_sweeps + sh.sweeps - 1) / sh.sweeps;
-    return sh.whole ? n : n + (n & 1);
+    return sh.whole || !even ? n : n + (n & 1);
 }
 
 int bands2d_groups(int L, const BandShape &sh) { return (L + sh.rows - 1) / sh.rows; }

@@ -13,13 +13,14 @@ struct BandShape {
     double ns_per_sweep = 0.0;  // the model's estimate for the batch
 };
 
-// The shape for a batch of n_rep lattices and a call of n_sweeps sweeps;
-// false if none fits in LDS.
-bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, BandShape *out);
+// The shape for a batch of n_rep lattices and n_sweeps sweeps; false if none
+// fits in LDS.  even: see bands2d_launches.
+bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out);
 int bands2d_groups(int L, const BandShape &sh);  // workgroups per replica
-// Launches of a call: an even number unless the shape is whole, so that the
-// result ends where it began (more than n_sweeps: the shape does not serve the call).
-int bands2d_launches(const BandShape &sh, int n_sweeps);
+// Launches for n_sweeps sweeps; with even, an even number unless the shape is
+// whole, so that the result ends where it began (more than n_sweeps: the shape
+// does not serve the call).
+int bands2d_launches(const BandShape &sh, int n_sweeps, bool even);
 
 struct Bands2dArgs {
     const int8_t *src;         // [n_rep][L * L]

@@ -7,6 +7,9 @@
 
 namespace smc {
 
+// Edges that the bins serve.
+inline bool uneven2d_edge_supported(int L) { return L >= 16 && L <= 256 && L % 16 == 0; }
+
 // Up to kBinReps replicas of one edge that a workgroup sweeps together.
 constexpr int kBinReps = 64;
 struct Bin2d {

@@ -121,29 +121,6 @@ hipError_t launch_pt3d(int model, int8_t *spins, const int8_t *coup, int rep_per
                        double *energy, unsigned long long *acc, Key key, uint32_t t0, int n_steps, int m,
                        hipStream_t s);
 
-// Uneven 2D batches: one workgroup per replica with the replica in LDS.
-struct Uneven2dArgs {
-    int8_t *spins;             // caller's spins (row-major int8 +-1 per replica)
-    const smc_inst *inst;      // device [n_rep]
-    const uint8_t *csplit;     // colour-split coupling planes at each sample's coup_off, or nullptr (Ising)
-    const int32_t *row_of_rep; // threshold row per replica; -1 leaves the replica unchanged
-    const ThrRow *thr;
-    int64_t *E;                // tracked energy per replica
-    uint32_t t;                // first sweep of the launch
-    int sweeps;                // sweeps per launch, the replica kept in LDS
-    Key key;
-    uint32_t one2;  // 0x00010001 (opaque to the compiler)
-};
-bool uneven2d_edge_supported(int L);
-size_t uneven2d_lds_bytes(int L);
-hipError_t uneven2d_prepare_kernel(bool ea, int L);
-Uneven2dArgs make_uneven2d_args(int8_t *spins, const smc_inst *inst, const uint8_t *csplit, const int32_t *row_of_rep,
-                                const ThrRow *thr, int64_t *E, Key key);
-hipError_t launch_coup_split2d(const int8_t *coup, uint8_t *out, const smc_inst *samples, int n_samples,
-                               int64_t chunks_total, const int64_t *chunk_start, hipStream_t s);
-hipError_t launch_uneven2d_sweep(const Uneven2dArgs &a, const int32_t *work, int n_work, int L, bool ea, int threads,
-                                 hipStream_t s);
-
 // Asynchronous multi-spin coding (2D EA/Ising, L in {16, 32, 64}): replicas
 // 32g .. 32g+31 packed into one word per site, all sweeps in one launch.
 bool msc2d_supported(int dim, int L);
@@ -237,6 +214,10 @@ enum ShapeKind { kShapeBand2d = 0, kShapePass3d = 1, kShapeHalf3d = 2 };
 struct Shape {
     int v[3];  // band2d: rows per band; pass3d: rows per strip, segments per thread, planes per z segment; half3d: rows per thread
 };
+// Workgroup size of the whole-lattice shape of the 2D bands for an edge (a
+// multiple of 16 up to 256): SPINMC_U2D_THREADS, else what smc_autotune
+// measured, else 0 (the shape's own).
+int small2d_threads(int L, bool ea);
 bool tuned_shape(int kind, int L, int model, int n_rep, Shape *out);
 void set_tuned_shape(int kind, int L, int model, int n_rep, const Shape &s);
 

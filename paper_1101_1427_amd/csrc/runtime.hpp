@@ -54,14 +54,8 @@ enum Slot {
     kRows,
     kBeta,
     kPingPong,
-    kCoupSplit,
-    kChunks,
     kWork,
     kTuneSpins,
-    kTuneInst,
-    kTuneWork,
-    kTuneRows,
-    kTuneE,
     kHeisPing,
     kL2dPart,
     kMscSpins,
@@ -128,13 +122,5 @@ void fill_uniform_samples(const smc_desc *d, Plan &plan);
 int validate(const smc_desc *d, bool need_coup, Plan &plan);
 // The instance table of an uneven batch into its scratch slot (plan.b.inst).
 int upload_inst(StreamCtx &c, hipStream_t s, const smc_desc *d, Plan &plan);
-
-// --------------------------------------------------------------- tuning ----
-// Workgroup size of the LDS-resident 2D kernel for an edge without
-// measurement, and with it (tune.hip): measured once per process and
-// (device, edge, model) on scratch copies of the replicas reps of rows.
-int uneven2d_threads_default(int L);
-int uneven2d_threads(StreamCtx &c, hipStream_t s, const Uneven2dArgs &a, int L, bool ea,
-                     const std::vector<int32_t> &reps, const std::vector<smc_inst> &rows, int *out);
 
 }  // namespace smc

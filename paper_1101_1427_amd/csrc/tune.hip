@@ -1,5 +1,5 @@
-// Launch-shape tuning: the workgroup size of the LDS-resident 2D kernel
-// per edge, the band height of the one-pass 2D Ising sweep, the strip shape
+// Launch-shape tuning: the workgroup size of the whole-lattice 2D sweep per
+// edge, the band height of the one-pass 2D Ising sweep, the strip shape
 // of the one-pass 3D sweep and the rows per thread of the 3D half-sweeps,
 // each measured on scratch lattices of the batch's shape (smc_autotune) and
 // kept per process and device (and in an optional cache file).  A shape
@@ -18,13 +18,15 @@
 #include <tuple>
 #include <vector>
 
+#include "bands2d.hpp"
+#include "bins2d.hpp"
 #include "runtime.hpp"
 
 namespace smc {
 namespace {
 
 std::mutex g_tune_mutex;
-std::map<std::tuple<int, int, int>, int> g_tuned;  // (device, edge, EA) -> workgroup size of the 2D LDS kernel
+std::map<std::tuple<int, int, int>, int> g_tuned;  // (device, edge, EA) -> workgroup size of the whole-lattice 2D sweep
 std::map<std::tuple<int, int, int, int, int>, Shape> g_shapes;  // (device, kind, edge, model, replicas) -> shape
 
 const char *const kKindName[] = {"band2d", "pass3d", "half3d"};
@@ -209,107 +211,82 @@ void set_tuned_shape(int kind, int L, int model, int n_rep, const Shape &sh) {
     g_shapes[std::make_tuple(current_device(), kind, L, model, n_rep)] = sh;
 }
 
-// Threads per workgroup for an edge, without measurement: about four draw
-// groups per thread and colour, between one and eight waves.
-int uneven2d_threads_default(int L) {
-    const int groups = L * L / 16;
-    int t = 64;
-    while (t < 512 && 4 * t < groups) t <<= 1;
-    return t;
-}
-
-// Autotuned workgroup size per (device, edge, model), measured once per
-// process: the sweep kernel runs on scratch copies of up to 4096 replicas of
-// the edge (enough workgroups to fill the chip) with every candidate size and
-// the fastest is kept.  The choice changes
-// the schedule only, never the results.  SPINMC_U2D_THREADS=n forces n;
-// SPINMC_AUTOTUNE=0 takes the default without measuring.
-
-int uneven2d_threads(StreamCtx &c, hipStream_t s, const Uneven2dArgs &a, int L, bool ea,
-                     const std::vector<int32_t> &reps, const std::vector<smc_inst> &rows, int *out) {
+int small2d_threads(int L, bool ea) {
+    if (!uneven2d_edge_supported(L)) return 0;
     if (const char *f = getenv("SPINMC_U2D_THREADS")) {
         const int v = atoi(f);
-        if (v == 64 || v == 128 || v == 256 || v == 512) {
-            *out = v;
-            return SMC_OK;
-        }
+        if (v == 64 || v == 128 || v == 256 || v == 512) return v;
     }
+    std::lock_guard<std::mutex> lk(g_tune_mutex);
+    auto it = g_tuned.find(std::make_tuple(current_device(), L, ea ? 1 : 0));
+    return it == g_tuned.end() ? 0 : it->second;
+}
+
+namespace {
+
+// Workgroup size of the whole-lattice shape for (device, edge, model): the
+// sweep kernel runs 16 sweeps of up to 4096 scratch replicas with every
+// candidate size and the fastest is kept.  The choice changes the schedule
+// only, never the results.
+int tune_small2d(StreamCtx &c, hipStream_t s, int L, bool ea, int n_rep, Key key) {
     const char *env = getenv("SPINMC_AUTOTUNE");
-    if (env && env[0] == '0') {
-        *out = uneven2d_threads_default(L);
-        return SMC_OK;
-    }
-    int dev = 0;
-    SMC_HIP(hipGetDevice(&dev));
-    const auto key = std::make_tuple(dev, L, ea ? 1 : 0);
+    if (getenv("SPINMC_U2D_THREADS") || (env && env[0] == '0')) return SMC_OK;
+    const auto id = std::make_tuple(current_device(), L, ea ? 1 : 0);
     {
         std::lock_guard<std::mutex> lk(g_tune_mutex);
-        auto it = g_tuned.find(key);
-        if (it != g_tuned.end()) {
-            *out = it->second;
-            return SMC_OK;
-        }
+        if (g_tuned.count(id)) return SMC_OK;
     }
-    // scratch copies of the first replicas of the edge (couplings are read in place)
-    int rc;
-    const int M = (int)std::min<size_t>(reps.size(), 4096);
     const int64_t N = (int64_t)L * L;
-    void *sp = nullptr, *ip = nullptr, *wp = nullptr, *rp = nullptr, *ep = nullptr;
-    if ((rc = ensure(c, kTuneSpins, (size_t)(M * N), &sp))) return rc;
-    std::vector<smc_inst> tinst(M);
-    std::vector<int32_t> twork(M), trows(M, 0);
-    for (int m = 0; m < M; ++m) {
-        tinst[m] = rows[reps[m]];
-        tinst[m].spin_off = (int64_t)m * N;
-        twork[m] = m;
+    Batch b{};
+    b.dim = 2;
+    b.model = SMC_ISING;
+    b.n_rep = std::min(n_rep, 4096);
+    b.L = L;
+    b.N = N;
+    b.rep_per_sample = b.n_rep;
+    void *sp = nullptr, *cp = nullptr, *tp = nullptr;
+    int rc;
+    if ((rc = ensure(c, kTuneA, (size_t)(b.n_rep * N), &sp))) return rc;
+    SMC_HIP(launch_init_spins(b, L, (int8_t *)sp, key, s));
+    if (ea) {
+        if ((rc = ensure(c, kTuneB, (size_t)(2 * N), &cp))) return rc;
+        SMC_HIP(hipMemsetAsync(cp, 1, (size_t)(2 * N), s));
     }
-    // one copy per run of replicas that sit back to back in the caller's
-    // array (the temperatures of a chain usually do)
-    for (int m = 0; m < M;) {
-        int e = m + 1;
-        while (e < M && rows[reps[e]].spin_off == rows[reps[e - 1]].spin_off + N) ++e;
-        SMC_HIP(hipMemcpyAsync((int8_t *)sp + (int64_t)m * N, a.spins + rows[reps[m]].spin_off,
-                               (size_t)((int64_t)(e - m) * N), hipMemcpyDeviceToDevice, s));
-        m = e;
-    }
-    if ((rc = upload(c, s, kTuneInst, tinst.data(), sizeof(smc_inst) * M, &ip))) return rc;
-    if ((rc = upload(c, s, kTuneWork, twork.data(), sizeof(int32_t) * M, &wp))) return rc;
-    if ((rc = upload(c, s, kTuneRows, trows.data(), sizeof(int32_t) * M, &rp))) return rc;
-    if ((rc = ensure(c, kTuneE, sizeof(int64_t) * M, &ep))) return rc;
-    Uneven2dArgs t = a;
-    t.spins = (int8_t *)sp;
-    t.inst = (const smc_inst *)ip;
-    t.row_of_rep = (const int32_t *)rp;
-    t.E = (int64_t *)ep;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    SMC_HIP(hipEventCreate(&e0));
-    SMC_HIP(hipEventCreate(&e1));
-    int best = uneven2d_threads_default(L);
+    const std::vector<ThrRow> rows((size_t)b.n_rep, threshold_row(0.44, 2));
+    if ((rc = upload(c, s, kTables, rows.data(), sizeof(ThrRow) * rows.size(), &tp))) return rc;
+    Bands2dArgs a{};
+    a.src = (const int8_t *)sp;
+    a.dst = (int8_t *)sp;
+    a.coup = (const int8_t *)cp;
+    a.rep_per_sample = b.n_rep;
+    a.thr = (const ThrRow *)tp;
+    a.key = key;
+    a.n_rep = b.n_rep;
+    a.L = L;
+    BandShape sh;
+    sh.rows = L;
+    sh.sweeps = 16;
+    sh.whole = true;
+    int best = 0;
     float best_ms = 1e30f;
-    hipError_t err = hipSuccess;
-    for (int th = 64; th <= 512 && err == hipSuccess; th <<= 1) {
-        err = launch_uneven2d_sweep(t, (const int32_t *)wp, M, L, ea, th, s);  // warm-up
-        if (err == hipSuccess) err = hipEventRecord(e0, s);
-        for (int k = 0; k < 3 && err == hipSuccess; ++k) err = launch_uneven2d_sweep(t, (const int32_t *)wp, M, L, ea, th, s);
-        if (err == hipSuccess) err = hipEventRecord(e1, s);
-        if (err == hipSuccess) err = hipEventSynchronize(e1);
+    for (sh.threads = 64; sh.threads <= 512; sh.threads <<= 1) {
         float ms = 0.0f;
-        if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
-        if (err == hipSuccess && ms < best_ms) {
+        rc = time_calls(s, 3, [&](int k) {
+            a.t = 16u * (uint32_t)k;
+            return launch_bands2d(a, sh, 16, Tally{}, s);
+        }, &ms);
+        if (rc) return rc;
+        if (ms < best_ms) {
             best_ms = ms;
-            best = th;
+            best = sh.threads;
         }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    if (err != hipSuccess) return fail(SMC_EHIP, "autotuning the 2D sweep: %s", hipGetErrorString(err));
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mutex);
-        g_tuned[key] = best;
-    }
-    *out = best;
+    std::lock_guard<std::mutex> lk(g_tune_mutex);
+    g_tuned[id] = best;
     return SMC_OK;
 }
+
+}  // namespace
 
 }  // namespace smc
 
@@ -325,7 +302,7 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
     const int model = ea ? 1 : 0;
     const bool spin_model = desc->model == SMC_ISING || ea;
     // what this batch has to tune
-    std::map<int, int> count;  // 2D edges of the LDS-resident kernel -> replicas
+    std::map<int, int> count;  // 2D edges of the whole-lattice bands -> replicas
     if (desc->dim == 2 && spin_model)
         for (int r = 0; r < desc->n_rep; ++r) {
             const int L = desc->L > 0 ? desc->L : desc->inst[r].L;
@@ -380,33 +357,8 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
     StreamCtx &c = ctx_for(s);
     const Key key = make_key(desc->seed);
     Shape known;
-    if (!count.empty()) {
-        const ThrRow row = threshold_row(0.44, 2);
-        void *tp = nullptr;
-        if ((rc = upload(c, s, kTables, &row, sizeof row, &tp))) return rc;
-        for (auto &kv : count) {
-            const int L = kv.first, M = std::min(kv.second, 4096);
-            const int64_t N = (int64_t)L * L;
-            void *sp = nullptr, *cp = nullptr;
-            if ((rc = ensure(c, kPingPong, (size_t)(M * N), &sp))) return rc;
-            SMC_HIP(hipMemsetAsync(sp, 0x01, (size_t)(M * N), s));
-            if (ea) {
-                if ((rc = ensure(c, kCoupSplit, (size_t)(2 * N), &cp))) return rc;
-                SMC_HIP(hipMemsetAsync(cp, 0, (size_t)(2 * N), s));
-            }
-            std::vector<smc_inst> rows(M);
-            std::vector<int32_t> reps(M);
-            for (int m = 0; m < M; ++m) {
-                rows[m] = smc_inst{L, 0, (int64_t)m * N, 0};
-                reps[m] = m;
-            }
-            SMC_HIP(uneven2d_prepare_kernel(ea, L));
-            const Uneven2dArgs a = make_uneven2d_args((int8_t *)sp, nullptr, (const uint8_t *)cp, nullptr,
-                                                      (const ThrRow *)tp, nullptr, key);
-            int th = 0;
-            if ((rc = uneven2d_threads(c, s, a, L, ea, reps, rows, &th))) return rc;
-        }
-    }
+    for (auto &kv : count)
+        if ((rc = tune_small2d(c, s, kv.first, ea, kv.second, key))) return rc;
     if (band2d && !tuned_shape(kShapeBand2d, desc->L, 0, desc->n_rep, &known))
         if ((rc = tune_band2d(c, s, plan.b, key))) return rc;
     if (pass3d && !tuned_shape(kShapePass3d, desc->L, model, desc->n_rep, &known))
@@ -420,7 +372,7 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
         FILE *f = fopen(cache_path, "w");
         if (!f) return fail(SMC_EINVAL, "cannot write the autotune cache %s", cache_path);
         fprintf(f, "# spinmc autotune cache: device kind edge model(0 Ising, 1 EA) replicas v0 v1 v2\n"
-                   "# u2d: workgroup size of the LDS-resident 2D sweep (replicas 0: any); band2d: rows per band of\n"
+                   "# u2d: workgroup size of the whole-lattice 2D sweep (replicas 0: any); band2d: rows per band of\n"
                    "# the one-pass 2D sweep; pass3d: rows per strip, segments per thread, planes per z segment of\n"
                    "# the one-pass 3D sweep; half3d: rows per thread of the 3D half-sweeps\n");
         for (const std::string &l : keep) fputs(l.c_str(), f);
