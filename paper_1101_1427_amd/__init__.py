@@ -31,6 +31,9 @@ class Inst(C.Structure):
     _fields_ = [("L", C.c_int32), ("sample", C.c_int32), ("spin_off", C.c_int64), ("coup_off", C.c_int64)]
 
 
+INST_DTYPE = np.dtype([("L", np.int32), ("sample", np.int32), ("spin_off", np.int64), ("coup_off", np.int64)])
+
+
 class Desc(C.Structure):
     _fields_ = [("model", C.c_int32), ("dim", C.c_int32), ("L", C.c_int32), ("n_rep", C.c_int32),
                 ("rep_per_sample", C.c_int32), ("renorm_every", C.c_int32), ("seed", C.c_uint64),
@@ -54,7 +57,7 @@ def lib():
         L = C.CDLL(LIB_PATH)
         vp, P = C.c_void_p, C.POINTER
         L.smc_spin_init.argtypes = [P(Desc), vp, vp, vp]
-        L.smc_metropolis_sweep.argtypes = [P(Desc), vp, vp, P(C.c_double), C.c_uint64, C.c_int32, vp, vp]
+        L.smc_metropolis_sweep.argtypes = [P(Desc), vp, vp, vp, C.c_uint64, C.c_int32, vp, vp]
         L.smc_pt_sweep_swap.argtypes = [P(Desc), P(PTDesc), vp, vp, vp, vp, C.c_uint64, C.c_int32, vp, vp]
         L.smc_measure_energy_magnetisation.argtypes = [P(Desc), vp, vp, vp, vp, vp]
         L.smc_measure_energy_magnetisation_noalloc.argtypes = [P(Desc), vp, vp, vp, vp, vp]
@@ -69,26 +72,26 @@ def lib():
         L.smc_kernel_timing_enable.restype = C.c_int
         L.smc_kernel_timing_read.argtypes = [P(C.c_double), P(C.c_int64)]
         L.smc_kernel_timing_read.restype = C.c_int
-        L.smc_msc_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32,
+        L.smc_msc_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_uint64, C.c_int32,
                                     C.c_int32, C.c_void_p, C.c_void_p]
         L.smc_msc_sweep.restype = C.c_int
         L.smc_msc_plan.argtypes = [P(Desc), C.c_int32, C.c_int32, P(C.c_int32), P(C.c_char_p)]
         L.smc_msc_plan.restype = C.c_int
-        L.smc_dcb_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32,
+        L.smc_dcb_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_uint64, C.c_int32,
                                     C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
         L.smc_dcb_sweep.restype = C.c_int
-        L.smc_heis_dcb_sweep.argtypes = [P(Desc), C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32, C.c_int32,
+        L.smc_heis_dcb_sweep.argtypes = [P(Desc), C.c_void_p, vp, C.c_uint64, C.c_int32, C.c_int32,
                                          C.c_int32, C.c_int32, C.c_int32, C.c_double, C.c_void_p, C.c_void_p]
         L.smc_heis_dcb_sweep.restype = C.c_int
         L.smc_autotune.argtypes = [P(Desc), C.c_char_p, C.c_void_p]
         L.smc_autotune.restype = C.c_int
-        L.smc_dcb_plan.argtypes = [P(Desc), P(C.c_double), C.c_int32, P(C.c_char_p)]
+        L.smc_dcb_plan.argtypes = [P(Desc), vp, C.c_int32, P(C.c_char_p)]
         L.smc_dcb_plan.restype = C.c_int
         L.smc_rng_study_state_bytes.argtypes = [P(Desc), C.c_int32, C.c_int32, P(C.c_int64)]
         L.smc_rng_study_state_bytes.restype = C.c_int
         L.smc_rng_study_init.argtypes = [P(Desc), C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
         L.smc_rng_study_init.restype = C.c_int
-        L.smc_rng_study_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_int32, C.c_int32,
+        L.smc_rng_study_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_int32, C.c_int32,
                                           C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
         L.smc_rng_study_sweep.restype = C.c_int
         L.smc_philox_bench.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32, C.c_int32, C.c_int32,
@@ -109,13 +112,29 @@ def _check(rc: int, func: str):
 
 
 def _stream(stream):
+    """The raw stream of a call: the given one's, else the current stream's (asked for by
+    device index where torch offers that: building a Stream object takes longer than a launch)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _betas(beta, n: int):
+    """The host inverse temperatures of n replicas: contiguous float64 [n] (a number or sequence is broadcast)."""
+    b = np.asarray(beta, np.float64)
+    return b if b.shape == (n,) and b.flags.c_contiguous else np.ascontiguousarray(np.broadcast_to(b, (n,)))
+
+
+def _address(a):
+    """Address of a host array's first element (the array has to outlive the call)."""
+    return a.__array_interface__["data"][0]
 
 
 @dataclass
@@ -154,11 +173,12 @@ class Batch:
         d = Desc(self.model, self.dim, self.L, self.n_rep, self.rep_per_sample, self.renorm_every,
                  self.seed & 0xFFFFFFFFFFFFFFFF, None, spins_len, coup_len)
         if self.L == 0:
-            rows = (Inst * self.n_rep)()
-            for k, r in enumerate(self.inst):
-                rows[k] = Inst(int(r[0]), int(r[1]), int(r[2]), int(r[3]))
+            inst = np.asarray(self.inst, np.int64)
+            rows = np.empty(self.n_rep, INST_DTYPE)
+            for k, name in enumerate(INST_DTYPE.names):
+                rows[name] = inst[:self.n_rep, k]
             d._inst_keep = rows  # keep alive for the call
-            d.inst = C.cast(rows, C.POINTER(Inst))
+            d.inst = rows.ctypes.data_as(C.POINTER(Inst))
         return d
 
 
@@ -176,9 +196,9 @@ def metropolis_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, coup
                      stream=None):
     """n_sweeps checkerboard Metropolis sweeps; beta is a host sequence [n_rep]."""
     d = _desc(batch, spins, couplings)
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
+    b = _betas(beta, batch.n_rep)
     _check(lib().smc_metropolis_sweep(C.byref(d), _ptr(spins), _ptr(couplings),
-                                      b.ctypes.data_as(C.POINTER(C.c_double)), sweep0, n_sweeps,
+                                      _address(b), sweep0, n_sweeps,
                                       _ptr(dE_accum), _stream(stream)), "smc_metropolis_sweep")
 
 
@@ -188,8 +208,8 @@ def msc_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, couplings=N
     word_bits (32 or 64) share their random numbers (see smc_msc_sweep); beta is
     a host sequence [n_rep], equal within each group."""
     d = _desc(batch, spins, couplings)
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
-    _check(lib().smc_msc_sweep(C.byref(d), _ptr(spins), _ptr(couplings), b.ctypes.data_as(C.POINTER(C.c_double)),
+    b = _betas(beta, batch.n_rep)
+    _check(lib().smc_msc_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
                                sweep0, n_sweeps, word_bits, _ptr(dE_accum), _stream(stream)), "smc_msc_sweep")
 
 
@@ -199,7 +219,7 @@ def dcb_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, tile: int, 
     tile and sweep; see smc_dcb_sweep); beta is a host sequence [n_rep];
     dE_trace, if given, is an int64 device tensor of n_sweeps * n_rep entries."""
     d = _desc(batch, spins, couplings)
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
+    b = _betas(beta, batch.n_rep)
     if dE_trace is not None:
         import torch
 
@@ -208,7 +228,7 @@ def dcb_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, tile: int, 
         if dE_trace.numel() < n_sweeps * batch.n_rep:
             raise ValueError(f"dE_trace holds {dE_trace.numel()} entries, needs n_sweeps * n_rep = "
                              f"{n_sweeps * batch.n_rep}")
-    _check(lib().smc_dcb_sweep(C.byref(d), _ptr(spins), _ptr(couplings), b.ctypes.data_as(C.POINTER(C.c_double)),
+    _check(lib().smc_dcb_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
                                sweep0, n_sweeps, tile, hits, 1 if palindromic else 0, _ptr(dE_accum),
                                _ptr(dE_trace), _stream(stream)), "smc_dcb_sweep")
 
@@ -227,8 +247,8 @@ def heis_dcb_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, tile: 
     if spins.dtype != want or not spins.is_cuda or not spins.is_contiguous():
         raise TypeError(f"spins must be a contiguous {want} device tensor for precision {precision}")
     d = _desc(batch, spins, None)
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
-    _check(lib().smc_heis_dcb_sweep(C.byref(d), _ptr(spins), b.ctypes.data_as(C.POINTER(C.c_double)), sweep0,
+    b = _betas(beta, batch.n_rep)
+    _check(lib().smc_heis_dcb_sweep(C.byref(d), _ptr(spins), _address(b), sweep0,
                                     n_sweeps, tile, hits, precision, 1 if palindromic else 0, float(cap),
                                     _ptr(accepts), _stream(stream)), "smc_heis_dcb_sweep")
 
@@ -244,9 +264,9 @@ def autotune(batch: Batch, cache_path=None, stream=None):
 def dcb_plan(batch: Batch, beta, tile: int) -> str:
     """Name of the kernel smc_dcb_sweep uses for this batch, beta and tile (aligned buffers)."""
     d = batch.desc(batch.spins_shape()[0], batch.coup_len())
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
+    b = _betas(beta, batch.n_rep)
     name = C.c_char_p()
-    _check(lib().smc_dcb_plan(C.byref(d), b.ctypes.data_as(C.POINTER(C.c_double)), tile, C.byref(name)),
+    _check(lib().smc_dcb_plan(C.byref(d), _address(b), tile, C.byref(name)),
            "smc_dcb_plan")
     return name.value.decode()
 
@@ -315,8 +335,8 @@ def rng_study_sweep(batch: Batch, spins, beta, n_sweeps: int, tile: int, hits: i
                     couplings=None, dE_accum=None, stream=None):
     """n_sweeps double-checkerboard sweeps drawing from a study generator (smc_rng_study_sweep)."""
     d = _desc(batch, spins, couplings)
-    b = np.ascontiguousarray(np.broadcast_to(np.asarray(beta, np.float64), (batch.n_rep,)))
-    _check(lib().smc_rng_study_sweep(C.byref(d), _ptr(spins), _ptr(couplings), b.ctypes.data_as(C.POINTER(C.c_double)),
+    b = _betas(beta, batch.n_rep)
+    _check(lib().smc_rng_study_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
                                      n_sweeps, tile, hits, generator, _ptr(state),
                                      state.numel() * state.element_size(), _ptr(dE_accum), _stream(stream)),
            "smc_rng_study_sweep")
