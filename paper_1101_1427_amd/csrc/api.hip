@@ -586,14 +586,19 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         for (int r = 0; r < desc->n_rep; ++r) bf[r] = (float)beta[r];
         if ((rc = upload(c, s, kTables, bf.data(), sizeof(float) * bf.size(), &p))) return rc;
         a.beta_f = (const float *)p;
-        if (use_heis3d_tiled(desc)) {
+        void *pp = nullptr;
+        const size_t bytes = (size_t)desc->n_rep * 3 * sizeof(float) * (size_t)plan.b.N;
+        bool tiled = use_heis3d_tiled(desc);
+        if (tiled && ensure(c, kHeisPing, bytes, &pp)) {
+            last_error().clear();  // no room for a second lattice: the half-sweeps need none
+            tiled = false;
+        }
+        if (tiled) {
             // one-pass sweeps, ping-pong between the caller's buffer and a scratch copy
-            const size_t bytes = (size_t)desc->n_rep * 3 * sizeof(float) * (size_t)plan.b.N;
-            void *pp = nullptr;
-            if ((rc = ensure(c, kHeisPing, bytes, &pp))) return rc;
             float *A = (float *)spins, *B = (float *)pp;
+            const int planes = heis3d_tiled_planes(desc->L, desc->n_rep);
             CallTally tally;
-            if ((rc = tally.begin(c, desc->n_rep, heis3d_tiled_groups(desc->L), dE_accum))) return rc;
+            if ((rc = tally.begin(c, desc->n_rep, heis3d_tiled_groups(desc->L, planes), dE_accum))) return rc;
             SweepTimer timer(s, n_sweeps);
             for (int32_t k = 0; k < n_sweeps; ++k) {
                 a.t = (uint32_t)(sweep0 + (uint64_t)k);
@@ -602,7 +607,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
                 const bool renorm =
                     desc->renorm_every > 0 && ((uint64_t)a.t + 1) % (uint64_t)desc->renorm_every == 0;
                 SMC_HIP(launch_heis3d_tiled(src, dst, a.beta_f, tally.next(), desc->n_rep, desc->L, a.key, a.t,
-                                            renorm, s));
+                                            renorm, planes, s));
             }
             timer.finish();
             if ((rc = tally.finish(s))) return rc;

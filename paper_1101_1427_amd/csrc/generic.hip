@@ -37,15 +37,15 @@ struct Site {
 };
 
 __device__ __forceinline__ Site site_of_pair(int dim, int L, int64_t h, int c) {
-    const int64_t i0 = 2 * h;
+    // a lattice has at most 2^32 sites, so its first site of a pair fits 32 bits
+    const uint32_t i0 = 2u * (uint32_t)h, l = (uint32_t)L, q = i0 / l;
     Site st;
-    st.x = (int)(i0 % L);
-    const int64_t q = i0 / L;
-    st.y = (int)(q % L);
-    st.z = dim == 3 ? (int)(q / L) : 0;
+    st.x = (int)(i0 - q * l);
+    st.z = dim == 3 ? (int)(q / l) : 0;
+    st.y = (int)(q - (uint32_t)st.z * l);
     const int dx = ((st.y + st.z) & 1) ^ c;  // x of i0 is even
     st.x += dx;
-    st.i = i0 + dx;
+    st.i = (int64_t)i0 + dx;
     return st;
 }
 

@@ -116,8 +116,9 @@ __global__ __launch_bounds__(kThreads) void k_heis3d_half(Heis3dArgs a, int c) {
 
 // ----------------------------------------------------------------------
 // One-pass sweep (colour 0 then colour 1 in a single pass over the
-// lattice).  A workgroup owns a tile of kTile x kTile sites in (x, y) over a
-// segment of kSeg planes in z and streams down the planes: at step z it
+// lattice), any even edge from 32 on.  A workgroup owns a tile of kTile x kTile
+// sites in (x, y) (fewer at the end of an edge that is no multiple) over a
+// segment of planes in z and streams down the planes: at step z it
 // updates colour 0 of plane z on the tile plus a one-site ring, then colour 1
 // of plane z-1 on the tile (its neighbours are then final), and writes plane
 // z-1 of the tile.  The ring's colour-0 values are recomputed identically by
@@ -133,8 +134,15 @@ __global__ __launch_bounds__(kThreads) void k_heis3d_half(Heis3dArgs a, int c) {
 // completion counter on this target, so a wait for data also waits for
 // every store issued before it; in this order the stores a wait covers were
 // issued two update phases earlier and have completed.
+//
+// Bound: at 256^3 the HBM traffic (95 us per sweep, 5.3 TB/s with the halos);
+// below, the latency of a plane step (1.5 us alone on a compute unit, the wait
+// for the plane that it requests), so short segments fill the chip first.
+// Per sweep: one 64^3 lattice 10 us (58 with segments of 32 planes), 128^3 20
+// (58); on edges that took the half-sweep kernel 96^3 16 us (31), 160^3 36 (88),
+// 200^3 74 (163).
 constexpr int kTile = 32;
-constexpr int kSeg = 32;
+constexpr int kMaxSeg = 32;
 constexpr int kW = kTile + 4;       // staged width with the halo
 constexpr int kPlane = kW * kW;     // sites per staged plane
 constexpr int kRing = 5;
@@ -148,9 +156,10 @@ struct TiledArgs {
     Tally acc;  // accepted moves
     Key key;
     uint32_t t;
-    int lgL;
+    int L, lgL;        // edge and, for a power of two, its logarithm
     int64_t N;
     int tiles, segs;   // tiles per row of tiles, segments per replica
+    int D;             // planes per segment (the last one may have fewer)
     int xcd_remap;     // 1: consecutive tiles of a segment on one XCD (shared halo lines in its L2)
     int renorm;        // 1: the stored spins are renormalised (this sweep ends a renormalisation period)
 };
@@ -159,16 +168,31 @@ struct PlaneRegs {
     F3 v[kLoadsPerThread];
 };
 
-__device__ __forceinline__ void load_plane(const float *src, int L, int lgL, int x0, int y0, int z, PlaneRegs &pr) {
-    const uint32_t m = (uint32_t)L - 1u;
-    const uint32_t zz = (uint32_t)z & m;
+// A coordinate in [-L, 2 L) in the lattice, and the index of a site.
+template <bool POW2>
+__device__ __forceinline__ uint32_t wrapped(int v, const TiledArgs &a) {
+    if constexpr (POW2) return (uint32_t)v & ((1u << a.lgL) - 1u);
+    return (uint32_t)(v < 0 ? v + a.L : v >= a.L ? v - a.L : v);
+}
+template <bool POW2>
+__device__ __forceinline__ uint32_t site(uint32_t x, uint32_t y, uint32_t z, const TiledArgs &a) {
+    if constexpr (POW2) return (((z << a.lgL) + y) << a.lgL) + x;
+    return (z * (uint32_t)a.L + y) * (uint32_t)a.L + x;
+}
+
+template <bool POW2>
+__device__ __forceinline__ void load_plane(const float *src, const TiledArgs &a, int x0, int y0, int z,
+                                           PlaneRegs &pr) {
+    const uint32_t zz = wrapped<POW2>(z, a);
 #pragma unroll
     for (int j = 0; j < kLoadsPerThread; ++j) {
         const int q = (int)threadIdx.x + j * kTiledThreads;
         if (q < kPlane) {
             const int v = q / kW, u = q - v * kW;
-            const uint32_t x = (uint32_t)(x0 - 2 + u) & m, y = (uint32_t)(y0 - 2 + v) & m;
-            pr.v[j] = ld(src, (((zz << lgL) + y) << lgL) + x);
+            // (a tile that ends before its 32nd column or row stages its halo
+            // next to it; what lies beyond is clamped and not used)
+            const int ux = POW2 ? u : min(u, a.L - x0 + 3), vy = POW2 ? v : min(v, a.L - y0 + 3);
+            pr.v[j] = ld(src, site<POW2>(wrapped<POW2>(x0 - 2 + ux, a), wrapped<POW2>(y0 - 2 + vy, a), zz, a));
         }
     }
 }
@@ -197,14 +221,74 @@ __device__ __forceinline__ F3 lds3(const float *ring, int slot, int q) {
     return r;
 }
 
-// Update the colour-c site at staged cell (u, v) of plane z (ring slot sz);
-// planes z-1 and z+1 sit in slots sm and sp.  Returns whether it moved.
-__device__ __forceinline__ bool update_cell(float *ring, int sm, int sz, int sp, int u, int v, int c, int x0, int y0,
-                                            int z, const TiledArgs &a, int r, float beta) {
-    const uint32_t m = (1u << a.lgL) - 1u;
-    const uint32_t zz = (uint32_t)z & m;
-    const uint32_t x = (uint32_t)(x0 - 2 + u) & m, y = (uint32_t)(y0 - 2 + v) & m;
-    const int q = v * kW + u;
+// First staged column u >= lo of staged row v whose site has colour c in plane z.
+__device__ __forceinline__ int first_cell(int lo, int v, int c, int x0, int y0, int z) {
+    return lo + ((c - (x0 - 2 + lo) - (y0 - 2 + v) - z) & 1);
+}
+
+// A thread's cell of a half-step: staged column u and row v, and the
+// in-colour index of its site (the counter of its draw).
+struct Cell {
+    int u, v;
+    bool on, own;  // updated at all; a site of the tile (not of its ring)
+    uint32_t h;
+};
+
+template <bool POW2>
+__device__ __forceinline__ uint32_t pair_of(int u, int v, int z, int x0, int y0, const TiledArgs &a) {
+    return site<POW2>(wrapped<POW2>(x0 - 2 + u, a), wrapped<POW2>(y0 - 2 + v, a), wrapped<POW2>(z, a), a) >> 1;
+}
+
+// Colour 0 of plane z on the tile and on the one-site ring around it without
+// the ring's corners (no tile site neighbours them): staged rows 1 and kW-2
+// over columns [2, kW-2), rows 2 .. kW-3 over columns [1, kW-1).  That is
+// kTile/2 + kTile*(kTile/2 + 1) + kTile/2 cells, one per thread.
+constexpr int kRingRowCells = kTile / 2;
+constexpr int kMidRowCells = kTile / 2 + 1;
+constexpr int kColour0Cells = 2 * kRingRowCells + kTile * kMidRowCells;
+static_assert(kColour0Cells == kTiledThreads, "one colour-0 cell per thread");
+
+template <bool POW2>
+__device__ __forceinline__ Cell cell0(int x0, int y0, int z, const TiledArgs &a) {
+    const int tw = POW2 ? kTile : min(kTile, a.L - x0), th = POW2 ? kTile : min(kTile, a.L - y0);
+    const int k = (int)threadIdx.x;
+    int lo, j;
+    Cell c;
+    if (k < kRingRowCells) {
+        c.v = 1, lo = 2, j = k;
+    } else if (k < kRingRowCells + kTile * kMidRowCells) {
+        const int kk = k - kRingRowCells;
+        c.v = 2 + kk / kMidRowCells, lo = 1, j = kk % kMidRowCells;
+    } else {
+        c.v = th + 2, lo = 2, j = k - kRingRowCells - kTile * kMidRowCells;
+    }
+    c.u = first_cell(lo, c.v, 0, x0, y0, z) + 2 * j;
+    c.on = POW2 || (c.u <= (lo == 1 ? tw + 2 : tw + 1) && (lo != 1 || c.v <= th + 1));
+    c.own = c.on && c.u >= 2 && c.u < 2 + tw && c.v >= 2 && c.v < 2 + th;
+    c.h = c.on ? pair_of<POW2>(c.u, c.v, z, x0, y0, a) : 0u;
+    return c;
+}
+
+// Colour 1 of plane z on the tile: kTile * kTile / 2 cells, one per thread
+// of the first kTile * kTile / 2.
+template <bool POW2>
+__device__ __forceinline__ Cell cell1(int x0, int y0, int z, const TiledArgs &a) {
+    const int k = (int)threadIdx.x;
+    Cell c;
+    c.v = 2 + k / (kTile / 2);
+    c.u = first_cell(2, c.v, 1, x0, y0, z) + 2 * (k % (kTile / 2));
+    c.on = k < kTile * kTile / 2;
+    if constexpr (!POW2) c.on = c.on && c.u <= min(kTile, a.L - x0) + 1 && c.v <= min(kTile, a.L - y0) + 1;
+    c.own = c.on;
+    c.h = c.on ? pair_of<POW2>(c.u, c.v, z, x0, y0, a) : 0u;
+    return c;
+}
+
+// Updates the site of cell c of the plane in ring slot sz with the draw w;
+// the planes below and above sit in slots sm and sp.  Returns whether it moved.
+__device__ __forceinline__ bool update_cell(float *ring, int sm, int sz, int sp, const Cell &c, const uint4 &w,
+                                            float beta) {
+    const int q = c.v * kW + c.u;
     const F3 nx1 = lds3(ring, sz, q + 1), nx0 = lds3(ring, sz, q - 1);
     const F3 ny1 = lds3(ring, sz, q + kW), ny0 = lds3(ring, sz, q - kW);
     const F3 nz1 = lds3(ring, sp, q), nz0 = lds3(ring, sm, q);
@@ -216,8 +300,6 @@ __device__ __forceinline__ bool update_cell(float *ring, int sm, int sz, int sp,
     hf.x += ny0.x; hf.y += ny0.y; hf.z += ny0.z;
     hf.x += nz1.x; hf.y += nz1.y; hf.z += nz1.z;
     hf.x += nz0.x; hf.y += nz0.y; hf.z += nz0.z;
-    const uint32_t i = (((zz << a.lgL) + y) << a.lgL) + x;
-    const uint4 w = philox4x32_10_wide(make_uint4(i >> 1, a.t, (uint32_t)r, 2 * kTagHeis + (uint32_t)c), a.key);
     const float3 sp3 = heis_proposal(unit23f(w.x), unit23f(w.y));
     const float dE = -((sp3.x - so.x) * hf.x + (sp3.y - so.y) * hf.y + (sp3.z - so.z) * hf.z);
     if (dE <= 0.0f || unit23f(w.z) < heis_boltzmann(beta, dE)) {
@@ -230,52 +312,12 @@ __device__ __forceinline__ bool update_cell(float *ring, int sm, int sz, int sp,
     return false;
 }
 
-// First staged column u >= lo of staged row v whose site has colour c in plane z.
-__device__ __forceinline__ int first_cell(int lo, int v, int c, int x0, int y0, int z) {
-    return lo + ((c - (x0 - 2 + lo) - (y0 - 2 + v) - z) & 1);
-}
-
-// Colour 0 of plane z on the tile and on the one-site ring around it without
-// the ring's corners (no tile site neighbours them): staged rows 1 and kW-2
-// over columns [2, kW-2), rows 2 .. kW-3 over columns [1, kW-1).  That is
-// kTile/2 + kTile*(kTile/2 + 1) + kTile/2 cells, one per thread.
-constexpr int kRingRowCells = kTile / 2;
-constexpr int kMidRowCells = kTile / 2 + 1;
-constexpr int kColour0Cells = 2 * kRingRowCells + kTile * kMidRowCells;
-static_assert(kColour0Cells == kTiledThreads, "one colour-0 cell per thread");
-
-__device__ __forceinline__ int update_colour0(float *ring, int sm, int sz, int sp, int x0, int y0, int z,
-                                              const TiledArgs &a, int r, float beta, bool count) {
-    const int k = (int)threadIdx.x;
-    int v, lo, j;
-    if (k < kRingRowCells) {
-        v = 1, lo = 2, j = k;
-    } else if (k < kRingRowCells + kTile * kMidRowCells) {
-        const int kk = k - kRingRowCells;
-        v = 2 + kk / kMidRowCells, lo = 1, j = kk % kMidRowCells;
-    } else {
-        v = kW - 2, lo = 2, j = k - kRingRowCells - kTile * kMidRowCells;
-    }
-    const int u = first_cell(lo, v, 0, x0, y0, z) + 2 * j;
-    const bool moved = update_cell(ring, sm, sz, sp, u, v, 0, x0, y0, z, a, r, beta);
-    return moved && count && u >= 2 && u < 2 + kTile && v >= 2 && v < 2 + kTile ? 1 : 0;
-}
-
-// Colour 1 of plane z on the tile: kTile * kTile / 2 cells, one per thread
-// of the first kTile * kTile / 2.
-__device__ __forceinline__ int update_colour1(float *ring, int sm, int sz, int sp, int x0, int y0, int z,
-                                              const TiledArgs &a, int r, float beta) {
-    const int k = (int)threadIdx.x;
-    if (k >= kTile * kTile / 2) return 0;
-    const int v = 2 + k / (kTile / 2), j = k % (kTile / 2);
-    const int u = first_cell(2, v, 1, x0, y0, z) + 2 * j;
-    return update_cell(ring, sm, sz, sp, u, v, 1, x0, y0, z, a, r, beta) ? 1 : 0;
-}
-
+// POW2: L is a power of two (shifts and masks; whole tiles).
+template <bool POW2>
 __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
     extern __shared__ __align__(16) float ring[];  // [kRing][3][kPlane]
     __shared__ int red[kTiledThreads / 64];
-    const int L = 1 << a.lgL;
+    const int L = a.L;
     const int per_rep = a.tiles * a.tiles * a.segs;
     // Workgroups go to the XCDs round-robin; with the remap, XCD k runs a
     // contiguous range of logical blocks (whole segments), so the halo rows
@@ -286,30 +328,35 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
     const int rem = lb % per_rep;
     const int seg = rem / (a.tiles * a.tiles), tile = rem % (a.tiles * a.tiles);
     const int x0 = (tile % a.tiles) * kTile, y0 = (tile / a.tiles) * kTile;
-    const int z0 = seg * kSeg, z1 = z0 + (kSeg < L ? kSeg : L);
+    const int z0 = seg * a.D, z1 = min(z0 + a.D, L);
     const float *src = a.src + (size_t)r * 3 * (size_t)a.N;
     float *dst = a.dst + (size_t)r * 3 * (size_t)a.N;
     const float beta = a.beta[r];
-    const uint32_t m = (uint32_t)L - 1u;
 
     // planes z0-2 .. z0 into their slots
     PlaneRegs pr;
     for (int z = z0 - 2; z <= z0; ++z) {
-        load_plane(src, L, a.lgL, x0, y0, z, pr);
+        load_plane<POW2>(src, a, x0, y0, z, pr);
         store_plane(ring, slot_of(z), pr);
     }
     __syncthreads();
     int n_acc = 0;
     for (int z = z0 - 1; z <= z1; ++z) {
         const bool fetch = z + 2 <= z1 + 1;
-        if (fetch) load_plane(src, L, a.lgL, x0, y0, z + 2, pr);
+        if (fetch) load_plane<POW2>(src, a, x0, y0, z + 2, pr);
+        // the draws of both half-steps depend on the sites alone: made together,
+        // two chains in flight, and before the first wait
+        const Cell c0 = cell0<POW2>(x0, y0, z, a), c1 = cell1<POW2>(x0, y0, z - 1, a);
+        uint4 w[2] = {make_uint4(c0.h, a.t, (uint32_t)r, 2 * kTagHeis),
+                      make_uint4(c1.h, a.t, (uint32_t)r, 2 * kTagHeis + 1u)};
+        philox4x32_10_multi<2>(w, a.key);
         // colour 0 of plane z on the tile and a one-site ring (planes z-1 .. z+1)
-        n_acc += update_colour0(ring, slot_of(z - 1), slot_of(z), slot_of(z + 1), x0, y0, z, a, r, beta,
-                                z >= z0 && z < z1);
+        if (c0.on && update_cell(ring, slot_of(z - 1), slot_of(z), slot_of(z + 1), c0, w[0], beta))
+            n_acc += c0.own && z >= z0 && z < z1 ? 1 : 0;
         __syncthreads();
         // colour 1 of plane z-1 on the tile (planes z-2 .. z)
-        if (z >= z0 + 1) n_acc += update_colour1(ring, slot_of(z - 2), slot_of(z - 1), slot_of(z), x0, y0, z - 1, a,
-                                                 r, beta);
+        if (z >= z0 + 1 && c1.on)
+            n_acc += update_cell(ring, slot_of(z - 2), slot_of(z - 1), slot_of(z), c1, w[1], beta) ? 1 : 0;
         // plane z+2 into the slot of plane z-3.  The wait is explicit and on
         // every path, so that no load is left pending across the loop (the
         // next step's request would otherwise wait behind this step's stores).
@@ -319,9 +366,10 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
         if (z >= z0 + 1) {
             // the tile's plane z-1 out
             const int zc = z - 1;
-            const uint32_t zz = (uint32_t)zc & m;
             for (int k = threadIdx.x; k < kTile * kTile; k += kTiledThreads) {
                 const int v = 2 + k / kTile, u = 2 + k % kTile;
+                if constexpr (!POW2)
+                    if (x0 + u - 2 >= L || y0 + v - 2 >= L) continue;
                 F3 val = lds3(ring, slot_of(zc), v * kW + u);
                 if (a.renorm) {
                     const float3 n = heis_unit(val.x, val.y, val.z);
@@ -329,8 +377,8 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
                     val.y = n.y;
                     val.z = n.z;
                 }
-                const uint32_t x = (uint32_t)(x0 + u - 2) & m, y = (uint32_t)(y0 + v - 2) & m;
-                *(F3 *)(dst + 3 * (size_t)((((zz << a.lgL) + y) << a.lgL) + x)) = val;
+                *(F3 *)(dst + 3 * (size_t)site<POW2>((uint32_t)(x0 + u - 2), (uint32_t)(y0 + v - 2), (uint32_t)zc, a)) =
+                    val;
             }
         }
     }
@@ -373,14 +421,38 @@ hipError_t launch_heis3d_half(float *spins, const float *beta, const Tally &acc,
     return hipGetLastError();
 }
 
-bool heis3d_tiled_supported(int dim, int L) { return heis3d_supported(dim, L) && L >= kTile; }
+bool heis3d_tiled_supported(int dim, int L) { return dim == 3 && L % 2 == 0 && L >= kTile && L <= 1024; }
 
-int heis3d_tiled_groups(int L) { return (L / kTile) * (L / kTile) * (L > kSeg ? L / kSeg : 1); }
+static int tiles_of(int L) { return (L + kTile - 1) / kTile; }
+
+// Planes per segment.  A segment of D planes takes D + 2 steps after the
+// planes of its prologue, and two workgroups share a compute unit: long
+// segments recompute and reload fewer planes, short ones fill the chip.  The
+// shortest total of rounds over 512 workgroups, one round at half the cost
+// when the workgroups have a compute unit each.
+int heis3d_tiled_planes(int L, int n_rep) {
+    if (const char *e = getenv("SPINMC_HEIS_PLANES"))
+        if (atoi(e) >= 2 && atoi(e) <= 1024) return atoi(e);
+    int best = kMaxSeg;
+    double least = 1e30;
+    for (int D : {2, 3, 4, 6, 8, 12, 16, 24, kMaxSeg}) {
+        const int64_t groups = (int64_t)tiles_of(L) * tiles_of(L) * ((L + D - 1) / D) * n_rep;
+        const double cost = (groups <= 256 ? 0.6 : (double)((groups + 511) / 512)) * (D + 4);
+        if (cost < least) {
+            least = cost;
+            best = D;
+        }
+    }
+    return best;
+}
+
+int heis3d_tiled_groups(int L, int planes) { return tiles_of(L) * tiles_of(L) * ((L + planes - 1) / planes); }
 
 size_t heis3d_tiled_lds_bytes() { return (size_t)kRing * 3 * kPlane * sizeof(float); }
 
 hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, const Tally &acc, int n_rep, int L, Key key,
-                               uint32_t t, bool renorm, hipStream_t s) {
+                               uint32_t t, bool renorm, int planes, hipStream_t s) {
+    if (!heis3d_tiled_supported(3, L) || n_rep < 1 || planes < 2 || src == dst) return hipErrorInvalidValue;
     TiledArgs a;
     a.renorm = renorm ? 1 : 0;
     a.src = src;
@@ -389,19 +461,30 @@ hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, 
     a.acc = acc;
     a.key = key;
     a.t = t;
+    a.L = L;
     a.lgL = 0;
     while ((1 << a.lgL) < L) ++a.lgL;
     a.N = (int64_t)L * L * L;
-    a.tiles = L / kTile;
-    a.segs = L > kSeg ? L / kSeg : 1;
+    a.tiles = tiles_of(L);
+    a.D = planes;
+    a.segs = (L + planes - 1) / planes;
     {
         const char *e = getenv("SPINMC_XCD_REMAP");
         a.xcd_remap = (e && e[0] == '0') ? 0 : 1;
     }
     const size_t lds = heis3d_tiled_lds_bytes();
-    (void)hipFuncSetAttribute((const void *)k_heis3d_tiled, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const unsigned blocks = (unsigned)(a.tiles * a.tiles * a.segs * n_rep);
-    SMC_LAUNCH(k_heis3d_tiled, dim3(blocks), dim3(kTiledThreads), lds, s, a);
+    const int64_t blocks = (int64_t)a.tiles * a.tiles * a.segs * n_rep;
+    if (const char *why = launch_config_error((uint64_t)blocks, kTiledThreads, lds))
+        return reject_launch("k_heis3d_tiled", (uint64_t)blocks, kTiledThreads, lds, why);
+    if (L == 1 << a.lgL) {
+        (void)hipFuncSetAttribute((const void *)k_heis3d_tiled<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds);
+        SMC_LAUNCH(k_heis3d_tiled<true>, dim3((unsigned)blocks), dim3(kTiledThreads), lds, s, a);
+    } else {
+        (void)hipFuncSetAttribute((const void *)k_heis3d_tiled<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds);
+        SMC_LAUNCH(k_heis3d_tiled<false>, dim3((unsigned)blocks), dim3(kTiledThreads), lds, s, a);
+    }
     return hipGetLastError();
 }
 
