@@ -1240,7 +1240,9 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     const bool bands = use_bands2d(desc, a, m, false, &sh);
     if (use_pt_split2d(desc, spins, rows) && !(bands && bands_before_lattice2d(desc)))
         return run_pt_split2d(c, s, desc, spins, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
-    if (use_uneven2d(desc, spins, couplings, rows))
+    // (few replicas: bands of their rows give more workgroups than a bin each)
+    if (use_uneven2d(desc, spins, couplings, rows) &&
+        !(bands && sh.ns_per_sweep * m < bins2d_ns(desc->L, desc->n_rep) * m + 3500.0))
         return run_uneven2d(c, s, desc, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
     if (bands) {
         void *other = nullptr;

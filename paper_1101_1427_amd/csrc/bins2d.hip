@@ -289,6 +289,8 @@ size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, 
     constexpr int kEdges = 17;  // edge / 16, 1 .. 16
     std::vector<int32_t> of[kEdges];
     for (size_t r = 0; r < rows.size(); ++r) of[rows[r].L / 16].push_back((int32_t)r);
+    // (several replicas per bin only once there are four workgroups per compute unit)
+    const size_t most = std::min<size_t>(kBinReps, rows.size() / 1024);
     int64_t packed = 0;
     size_t lds = 0;
     bins->clear();
@@ -297,7 +299,7 @@ size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, 
         const int L = 16 * e;
         const size_t N = (size_t)L * L / 2;  // bytes
         size_t per = 1;
-        for (size_t p = 2; p <= kBinReps && p * N <= kSmallBin; p *= 2)
+        for (size_t p = 2; p <= most && p * N <= kSmallBin; p *= 2)
             if (2 * p * N <= kSmallBin || lanes_used(L, (int)p) > lanes_used(L, (int)per)) per = p;
         for (size_t i = 0; i < of[e].size(); i += per) {
             const size_t n = std::min(per, of[e].size() - i);
@@ -308,6 +310,12 @@ size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, 
         }
     }
     return lds;
+}
+
+double bins2d_ns(int L, int n_rep) {
+    const int pieces = L * L / 16, rounds = (pieces + kThreads - 1) / kThreads;
+    const double per_cu = ((n_rep + 255) / 256) * (double)pieces;
+    return 2.0 * std::max(700.0 * rounds * ((n_rep + 1023) / 1024), 1.3 * per_cu);
 }
 
 hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_in, bool raw_out, hipStream_t s) {

@@ -203,9 +203,10 @@ hipError_t launch_model(int Z, bool nt, unsigned blocks, const Sweep3dArgs &a, h
 
 // Rows per thread along z: Z rows fetch Z + 2 row segments of every column
 // instead of 3 Z, so a launch reads the lattice (Z + 2) / Z times.  Z = 4
-// (the default) runs the Ising sweep at 512^3 and 1024^3 about 20 % faster
-// than Z = 1; 8 and 16 fetch less but leave fewer threads and are no
-// faster.  SPINMC_SWEEP3D_Z = 1, 2, 4, 8 or 16 sets it, else a value
+// runs the Ising sweep at 512^3 and 1024^3 about 20 % faster than Z = 1; 8 and
+// 16 fetch less but leave fewer threads and are no faster.  With few sites
+// threads count for more: Z = 1 up to 2^21 sites (64^3 8.2 us per sweep against
+// 11.2, 128^3 10.0 against 12.9), 2 up to 2^22 (level with 4 there), 4 above.  SPINMC_SWEEP3D_Z = 1, 2, 4, 8 or 16 sets it, else a value
 // smc_autotune measured for the edge, model and replica count; non-temporal
 // stores of the updated segments are on unless SPINMC_SWEEP3D_NT = 0.
 static int preferred_rows(int L, bool ea, int n_rep) {
@@ -219,7 +220,8 @@ static int preferred_rows(int L, bool ea, int n_rep) {
         const int z = t.v[0];
         if (z == 1 || z == 2 || z == 4 || z == 8 || z == 16) return z;
     }
-    return 4;
+    const int64_t sites = (int64_t)n_rep * L * L * L;
+    return sites > (int64_t)1 << 22 ? 4 : sites > (int64_t)1 << 21 ? 2 : 1;
 }
 
 // A replica's (L / 16)^3 workgroups of one-row threads regroup into whole

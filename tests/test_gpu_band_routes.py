@@ -47,6 +47,30 @@ def test_small_lattices_equal_half_sweeps(monkeypatch, model, L, n_rep, n, threa
     assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
 
 
+def test_sweeps_after_tempering_use_their_own_tables():
+    """The same sweep before and after a tempering call of another batch on the
+    same stream: both against the oracle (tables kept for a stream are not
+    taken for ones that tempering has overwritten)."""
+    import torch
+
+    L, n_rep, seed = 16, 24, W.seed_for(512)
+    betas = np.linspace(0.4, 1.4, n_rep)
+    b = S.Batch(S.EA, 2, L, n_rep, seed, rep_per_sample=4)
+    ref_s, ref_c = refrun.init_uniform(S.EA, 2, L, n_rep, seed, 4)
+    spins, coup = (torch.from_numpy(a.reshape(-1).copy()).to("cuda") for a in (ref_s, ref_c))
+    t = S.Batch(S.ISING, 2, 32, n_rep, seed)
+    ts = torch.ones(t.spins_shape()[0], dtype=torch.int8, device="cuda")
+    E = torch.full((n_rep,), -2.0 * 32 * 32, dtype=torch.float64, device="cuda")
+    sot = torch.from_numpy(np.roll(np.arange(n_rep, dtype=np.int32), 5)).to("cuda")
+    for k in range(2):
+        dE = torch.zeros(n_rep, dtype=torch.int64, device="cuda")
+        S.metropolis_sweep(b, spins, betas, 9 * k, 9, couplings=coup, dE_accum=dE)
+        ref_dE = refrun.sweep_uniform(S.EA, 2, L, ref_s, ref_c, betas, seed, 9 * k, 9, 4)
+        assert np.array_equal(spins.cpu().numpy().reshape(ref_s.shape), ref_s), k
+        assert np.array_equal(dE.cpu().numpy(), ref_dE), k
+        S.pt_sweep_swap(t, 1, n_rep, W.geometric_ladder(1.8, 3.2, n_rep), ts, sot, E, k, 1)
+
+
 @pytest.mark.parametrize("m,steps", [(1, 3), (3, 2)])
 def test_large_tempering_equal_one_pass_kernel(monkeypatch, m, steps):
     import torch
