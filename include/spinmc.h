@@ -61,12 +61,16 @@
  *   16-site row segments per thread: for L in [512, 1024] in one launch per
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
- *   device copy back), below in two launches per sweep, in place;
+ *   device copy back), below in two launches per sweep, in place, or, for
+ *   calls of three and more sweeps and L >= 32 (EA: up to 1024), on a
+ *   library-held packed copy of half a byte per site, and with L = 16 on
+ *   chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
  *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
  *   thread where an edge is below 16), or, for uniform 3D batches of edge 4
- *   .. 14, whole replicas held on chip for the call (tempering too, with up
- *   to 64 temperatures that fit), or, for uniform 2D batches where an
+ *   .. 24, whole replicas held on chip for the call (tempering too, with up
+ *   to 64 temperatures that fit and enough chains), or of larger edges the
+ *   packed copy (calls of two and more sweeps), or, for uniform 2D batches where an
  *   estimate says that it is faster, bands of rows (or a whole lattice) held
  *   on chip for several sweeps per launch, alternating with a library-held
  *   second lattice.  Small 2D batches (L a multiple of 16 up to 128, or 256
@@ -81,8 +85,11 @@
  *   SPINMC_BANDS2D=0 keeps the half-sweeps, =1 takes the bands wherever they
  *   fit (SPINMC_BANDS2D_ROWS and _SWEEPS set their shape,
  *   SPINMC_U2D_THREADS the workgroup of a whole lattice);
- *   SPINMC_SMALL3D=0 keeps the small 3D edges on the half-sweeps and
- *   SPINMC_PIECES=0 a pair of sites per thread; SPINMC_SWEEP3D_PASS=0 keeps
+ *   SPINMC_SMALL3D=0 keeps the small 3D edges on the half-sweeps,
+ *   SPINMC_PAIRS3D=0 the 3D half-sweeps on the caller's bytes (=1 takes the
+ *   packed copy wherever it fits) and SPINMC_PIECES=0 a pair of sites per
+ *   thread; the launch shapes of the 3D kernels asked for below keep their
+ *   edges on those; SPINMC_SWEEP3D_PASS=0 keeps
  *   the two launches per sweep for
  *   every edge, =1 takes the one launch from edge 32 (SPINMC_PASS3D_TY,
  *   _SEGS and _D set its rows per strip, segments per thread and planes

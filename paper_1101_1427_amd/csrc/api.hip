@@ -17,6 +17,7 @@
 #include "bands2d.hpp"
 #include "bins2d.hpp"
 #include "internal.hpp"
+#include "pairs3d.hpp"
 #include "runtime.hpp"
 #include "small3d.hpp"
 
@@ -329,10 +330,102 @@ int run_small3d(hipStream_t s, const SweepArgs &a, uint64_t sweep0, int32_t n_sw
     return SMC_OK;
 }
 
+// 3D batches of edge 16 and more run calls of several sweeps on a packed copy
+// of their lattices (packing and unpacking take about as long as one
+// sweep saves two or three times over).  Among the multiples of 16, edge 16
+// keeps the kernel on the caller's bytes (its rows of one piece leave half of
+// the packed kernel's threads idle: 9.7 us per sweep of 512 replicas against
+// 11.7) and Ising edges of 512 and more the one-pass kernel (512^3 level, 1024^3
+// 570 us against 810; EA 512^3 143 against 98, 1024^3 1000 against 920).
+// SPINMC_PAIRS3D=0 keeps the kernels on the caller's bytes (same results), and
+// so does a launch shape of those asked for in the environment.
+bool sweep3d_asked_for() {
+    for (const char *name : {"SPINMC_SWEEP3D", "SPINMC_SWEEP3D_Z", "SPINMC_SWEEP3D_PASS", "SPINMC_SWEEP3D_NT",
+                             "SPINMC_SWEEP3D_PACK"})
+        if (getenv(name)) return true;
+    return false;
+}
+
+bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
+    const char *env = getenv("SPINMC_PAIRS3D");
+    if ((env && env[0] == '0') || d->L <= 0 || (d->model != SMC_ISING && d->model != SMC_EA) ||
+        !pairs3d_supported(d->dim, d->L))
+        return false;
+    if (env && env[0] == '1') return true;
+    if (d->L % 16) return n_sweeps >= 2;
+    if (sweep3d_asked_for()) return false;
+    return n_sweeps >= 3 && d->L >= 32 && (d->model == SMC_EA || !pass3d_enabled(d));
+}
+
+// The packed copy of a call; SMC_ENOMEM (the caller's bytes serve then) if
+// there is no room for it.
+int pairs3d_args(StreamCtx &c, const SweepArgs &a, Pairs3dArgs *p) {
+    void *q = nullptr;
+    const size_t bytes = pairs3d_bytes(a.b.L, a.b.n_rep);
+    if (int rc = ensure(c, kPairs3d, bytes, &q)) return rc;
+    p->packed = (uint8_t *)q + pairs3d_pad();
+    p->rep_per_sample = a.b.rep_per_sample;
+    p->thr = a.thr;
+    p->row_of_rep = a.row_of_rep;
+    p->key = a.key;
+    p->t = 0;
+    p->rng_shift = a.rng_shift;
+    p->n_rep = a.b.n_rep;
+    p->L = a.b.L;
+    return SMC_OK;
+}
+
+int run_pairs3d(StreamCtx &c, hipStream_t s, const SweepArgs &a, Pairs3dArgs &p, uint64_t sweep0, int32_t n_sweeps,
+                int64_t *dE) {
+    const int planes = pairs3d_planes(p.L, p.n_rep);
+    CallTally tally;
+    int rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), dE);
+    if (rc) return rc;
+    SMC_HIP(launch_pairs3d_pack((const int8_t *)a.spins, a.coup, p, s));
+    SweepTimer timer(s, 2 * (int64_t)n_sweeps);
+    for (int32_t k = 0; k < n_sweeps; ++k) {
+        p.t = (uint32_t)(sweep0 + (uint64_t)k);
+        for (int col = 0; col < 2; ++col)
+            SMC_HIP(launch_pairs3d_half(p, a.coup != nullptr, col, planes, tally.next(), s));
+    }
+    timer.finish();
+    SMC_HIP(launch_pairs3d_unpack((int8_t *)a.spins, p, s));
+    return tally.finish(s);
+}
+
+int run_pt_pairs3d(StreamCtx &c, hipStream_t s, const SweepArgs &a, Pairs3dArgs &p, SwapArgs &sw, double *energy,
+                   uint64_t step0, int32_t n_steps, int m) {
+    int rc;
+    const int planes = pairs3d_planes(p.L, p.n_rep);
+    SMC_HIP(launch_pt_prepare(sw, energy, s));
+    SMC_HIP(launch_pairs3d_pack((const int8_t *)a.spins, a.coup, p, s));
+    for (int32_t k = 0; k < n_steps; ++k) {
+        sw.t = (uint32_t)(step0 + (uint64_t)k);
+        CallTally tally;
+        if ((rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), sw.E))) return rc;
+        for (int j = 0; j < m; ++j) {
+            p.t = sw.t * (uint32_t)m + (uint32_t)j;
+            for (int col = 0; col < 2; ++col)
+                SMC_HIP(launch_pairs3d_half(p, a.coup != nullptr, col, planes, tally.next(), s));
+        }
+        if ((rc = tally.finish(s))) return rc;
+        SMC_HIP(launch_pt_swap(sw, s));
+    }
+    SMC_HIP(launch_pairs3d_unpack((int8_t *)a.spins, p, s));
+    SMC_HIP(launch_pt_finish(sw, energy, s));
+    return SMC_OK;
+}
+
 // The sweeps of a call on the general path.
 int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps,
                 int64_t *dE) {
-    if (use_small3d(desc)) return run_small3d(s, a, sweep0, n_sweeps, dE);
+    if (use_small3d(desc) && !(desc->L % 16 == 0 && sweep3d_asked_for()))
+        return run_small3d(s, a, sweep0, n_sweeps, dE);
+    if (use_pairs3d(desc, n_sweeps)) {
+        Pairs3dArgs p;
+        if (pairs3d_args(c, a, &p) == SMC_OK) return run_pairs3d(c, s, a, p, sweep0, n_sweeps, dE);
+        last_error().clear();
+    }
     BandShape sh;
     if (use_bands2d(desc, a, n_sweeps, true, &sh)) {
         void *other = nullptr;
@@ -688,6 +781,13 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         if (part) SMC_HIP(launch_lattice2d_de_collect(part, dE_accum, desc->L, desc->n_rep, s));
         if (n_sweeps == 1) SMC_HIP(launch_from_split(A, (int8_t *)spins, desc->L, desc->n_rep, s));
         return SMC_OK;
+    }
+    if (desc->dim == 3 && desc->L % 16 == 0 && use_small3d(desc) && !sweep3d_asked_for())
+        return run_small3d(s, a, sweep0, n_sweeps, dE_accum);
+    if (desc->L % 16 == 0 && use_pairs3d(desc, n_sweeps)) {
+        Pairs3dArgs pa;
+        if (pairs3d_args(c, a, &pa) == SMC_OK) return run_pairs3d(c, s, a, pa, sweep0, n_sweeps, dE_accum);
+        last_error().clear();
     }
     if (use_sweep3d(desc, spins, a.coup, rows)) {
         // EA calls of several sweeps read the bonds bit-packed (one pass to
@@ -1187,7 +1287,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
                             make_key(desc->seed), (uint32_t)step0, n_steps, m, s));
         return SMC_OK;
     }
-    if (use_small3d(desc) && n <= small3d_max_reps(desc->L)) {
+    if (use_small3d(desc) && n <= small3d_max_reps(desc->L) && small3d_tempers(desc->L, n, pt->n_chains)) {
         // every step of the call in one launch, a workgroup per chain
         Small3dArgs sa;
         memset(&sa, 0, sizeof sa);
@@ -1244,6 +1344,12 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     if (use_uneven2d(desc, spins, couplings, rows) &&
         !(bands && sh.ns_per_sweep * m < bins2d_ns(desc->L, desc->n_rep) * m + 3500.0))
         return run_uneven2d(c, s, desc, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
+    if (use_pairs3d(desc, (int64_t)n_steps * m)) {
+        Pairs3dArgs pa;
+        if (pairs3d_args(c, a, &pa) == SMC_OK)
+            return run_pt_pairs3d(c, s, a, pa, sw, energy, step0, n_steps, m);
+        last_error().clear();
+    }
     if (bands) {
         void *other = nullptr;
         if (sh.whole || ensure(c, kBands2d, (size_t)desc->n_rep * (size_t)plan.b.N, &other) == SMC_OK)

@@ -1,0 +1,30 @@
+// Sweeps of uniform 3D Ising / +-J EA batches (any even edge from 16) on a
+// packed copy of half a byte per site (pairs3d.hip).
+#pragma once
+#include "internal.hpp"
+
+namespace smc {
+
+struct Pairs3dArgs {
+    uint8_t *packed;           // the replicas, pairs3d_stride(L) bytes each
+    int rep_per_sample;        // of the couplings (packing)
+    const ThrRow *thr;
+    const int32_t *row_of_rep; // threshold row per replica (-1: left unchanged), or nullptr
+    Key key;
+    uint32_t t;
+    int rng_shift;
+    int n_rep, L;
+};
+
+bool pairs3d_supported(int dim, int L);
+// Bytes of the buffer of a packed copy, and of its margin before the first
+// replica (packed points behind it): reads beside a piece stay inside.
+size_t pairs3d_bytes(int L, int n_rep);
+constexpr size_t pairs3d_pad() { return 64; }
+hipError_t launch_pairs3d_pack(const int8_t *spins, const int8_t *coup, const Pairs3dArgs &a, hipStream_t s);
+hipError_t launch_pairs3d_unpack(int8_t *spins, const Pairs3dArgs &a, hipStream_t s);
+int pairs3d_planes(int L, int n_rep);         // planes per thread for a batch
+int pairs3d_groups(int L, int planes);        // workgroups per replica of a half-sweep
+hipError_t launch_pairs3d_half(const Pairs3dArgs &a, bool ea, int c, int planes, const Tally &tally, hipStream_t s);
+
+}  // namespace smc

@@ -192,9 +192,10 @@ bool pt3d_enabled() {
     return !(env && env[0] == '0');
 }
 
-// Uniform 3D Ising / EA batches with an edge of 4 .. 14 keep whole replicas
+// Uniform 3D Ising / EA batches with an edge of 4 .. 24 keep whole replicas
 // in LDS for a call (any alignment, any beta); SPINMC_SMALL3D=0 keeps them on
-// the half-sweep launches (same results).
+// the half-sweep launches, =1 tempering here whatever the estimate (same
+// results).
 bool use_small3d(const smc_desc *d) {
     const char *env = getenv("SPINMC_SMALL3D");
     if (env && env[0] == '0') return false;

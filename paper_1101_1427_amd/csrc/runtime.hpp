@@ -66,6 +66,7 @@ enum Slot {
     kBins2d,     // bins of the 2D tempering batches and their packed copy
     kBinsPacked,
     kBands2d,    // second lattice of the 2D bands
+    kPairs3d,    // packed copy of the 3D half-sweeps
     kTallySlots, // per-workgroup sums of a sweep call
     kPtThr,
     kPtDelta,

@@ -1,5 +1,5 @@
 // Sweeps and parallel tempering of small 3D Ising / +-J EA lattices (even
-// edges 4 .. 14) with whole replicas in LDS for every sweep and exchange round of
+// edges 4 .. 24) with whole replicas in LDS for every sweep and exchange round of
 // a call (Eq. 2, Sec. 6, Eq. 12).
 //
 // A workgroup holds n replicas: the replicas of one tempering chain, or as
@@ -21,8 +21,12 @@
 // in bits 1 .. 3 (1: -1), so a neighbour pair's bond comes with the spins and
 // replicas of different samples can share a workgroup.
 //
-// 128 chains of 24 temperatures at edge 10, 20 steps: 886 -> 140 us.
+// 128 chains of 24 temperatures at edge 10, 20 steps: 886 -> 140 us.  Sweeps of
+// EA replicas against half-sweep launches: 64 of 16^3 2.1 us per sweep (7.9),
+// 4096 of 16^3 21 (32), one of 24^3 3.8 (7.0), 1024 of 24^3 19 (32).
 #include "small3d.hpp"
+
+#include <stdlib.h>
 
 #include <algorithm>
 
@@ -336,13 +340,25 @@ int groups_of(int L) { return (L * L * L / 2 + 7) / 8; }
 
 }  // namespace
 
-bool small3d_supported(int dim, int L) { return dim == 3 && L >= 4 && L <= 14 && L % 2 == 0; }
+bool small3d_supported(int dim, int L) { return dim == 3 && L >= 4 && L <= 24 && L % 2 == 0; }
 
 size_t small3d_lds_bytes(int L, int n) { return (size_t)n * 16 * groups_of(L) + 2 * (size_t)small3d_pad(L); }
 
 int small3d_max_reps(int L) {
     const size_t room = kMaxLdsBytes - sizeof(State) - 1024 - 2 * (size_t)small3d_pad(L);
     return (int)std::min<size_t>(kMaxReps, room / (16 * (size_t)groups_of(L)));
+}
+
+// A step takes a compute unit about 4 ns per Philox block of its chain; half-
+// sweep launches take 12 us per step and 28 ps per block of all chains (140 ps
+// below edge 16, a thread per pair of sites).  So 8 chains of 32 at edge 14 run
+// apart (17 us per step against 22), 128 of them together (23 against 107).
+bool small3d_tempers(int L, int n, int n_chains) {
+    const char *env = getenv("SPINMC_SMALL3D");
+    if (env && env[0] == '1') return true;
+    const double blocks = (double)n * groups_of(L);
+    const double together = 4.0e-3 * blocks * ((n_chains + 511) / 512) * (n_chains > 256 ? 1.25 : 1.0);
+    return together < 12.0 + (L < 16 ? 140e-6 : 28e-6) * blocks * n_chains;
 }
 
 hipError_t launch_small3d(const Small3dArgs &b, hipStream_t s) {

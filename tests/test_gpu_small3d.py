@@ -20,7 +20,8 @@ def _dev(a):
 
 
 @pytest.mark.parametrize("model", [S.ISING, S.EA])
-@pytest.mark.parametrize("L,n_rep", [(4, 1), (4, 37), (6, 7), (8, 5), (10, 3), (12, 2), (14, 3)])
+@pytest.mark.parametrize("L,n_rep", [(4, 1), (4, 37), (6, 7), (8, 5), (10, 3), (12, 2), (14, 3),
+                                     (16, 2), (16, 1025), (18, 1), (22, 2), (24, 3)])
 def test_small3d_sweeps_against_oracle(model, L, n_rep):
     import torch
 
@@ -38,10 +39,12 @@ def test_small3d_sweeps_against_oracle(model, L, n_rep):
 
 
 @pytest.mark.parametrize("L,n_temps,per_chain,m", [(4, 5, False, 1), (6, 64, False, 1), (8, 12, True, 2),
-                                                   (10, 24, False, 1), (12, 9, False, 3), (14, 32, True, 1)])
-def test_small3d_tempering_against_oracle(L, n_temps, per_chain, m):
+                                                   (10, 24, False, 1), (12, 9, False, 3), (14, 32, True, 1),
+                                                   (20, 4, False, 1), (24, 11, True, 1)])
+def test_small3d_tempering_against_oracle(monkeypatch, L, n_temps, per_chain, m):
     import torch
 
+    monkeypatch.setenv("SPINMC_SMALL3D", "1")
     n_chains, steps, t0, seed = 3, 6, 3, W.seed_for(420 + L)
     beta = W.geometric_ladder(0.8, 2.0, n_temps)
     betas = np.stack([beta * (1 + 0.05 * q) for q in range(n_chains)]) if per_chain else np.stack([beta] * n_chains)
