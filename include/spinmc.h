@@ -62,9 +62,9 @@
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place, or, for
- *   calls of three and more sweeps and L >= 32 (EA: up to 1024), on a
- *   library-held packed copy of half a byte per site, and with L = 16 on
- *   chip for the call;
+ *   calls of three and more sweeps and L >= 48 (EA: up to 1024), on a
+ *   library-held packed copy of half a byte per site, and with L = 16 or 32
+ *   on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
  *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
  *   thread where an edge is below 16), or, for uniform 3D batches of edge 4

@@ -557,11 +557,7 @@ int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, in
     const int rows_n = pt->beta_per_chain ? pt->n_chains : 1;
     std::vector<ThrRow> all_rows((size_t)rows_n * pt->n_temps);
     for (size_t k = 0; k < all_rows.size(); ++k) all_rows[k] = threshold_row(pt->beta[k], desc->dim);
-    bool fits = pt3d_enabled() && pt3d_supported(desc, pt->n_temps);
-    for (int64_t k = 0; fits && k < (int64_t)rows_n * pt->n_temps; ++k) {
-        const ThrRow r = threshold_row(pt->beta[k], desc->dim);
-        fits = r.m[1].x <= 0xFFFFu && r.m[2].x <= 0xFFFFu && r.m[3].x <= 0xFFFFu;
-    }
+    const bool fits = use_pt3d(desc, pt->n_temps);
     bool fits2d = !fits && desc->dim == 2 && (desc->model == SMC_ISING || desc->model == SMC_EA);
     if (fits2d) {
         const char *env = getenv("SPINMC_UNEVEN2D");
@@ -1280,14 +1276,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     void *thr = nullptr, *bdev = nullptr, *E64 = nullptr, *rowrep = nullptr;
     if ((rc = upload(c, s, kTables, rows.data(), sizeof(ThrRow) * rows.size(), &thr))) return rc;
     if ((rc = upload(c, s, kBeta, pt->beta, sizeof(double) * rows.size(), &bdev))) return rc;
-    if (use_pt3d(desc, pt, spins, rows)) {
-        SMC_HIP(launch_pt3d(desc->model, (int8_t *)spins, desc->model == SMC_EA ? couplings : nullptr,
-                            desc->rep_per_sample, pt->n_chains, n, pt->beta_per_chain ? 1 : 0, (const double *)bdev,
-                            (const ThrRow *)thr, slot_of_temp, energy, (unsigned long long *)swap_accepts,
-                            make_key(desc->seed), (uint32_t)step0, n_steps, m, s));
-        return SMC_OK;
-    }
-    if (use_small3d(desc) && n <= small3d_max_reps(desc->L) && small3d_tempers(desc->L, n, pt->n_chains)) {
+    if (use_small3d_pt(desc, n, pt->n_chains)) {
         // every step of the call in one launch, a workgroup per chain
         Small3dArgs sa;
         memset(&sa, 0, sizeof sa);

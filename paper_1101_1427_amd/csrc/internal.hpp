@@ -114,14 +114,6 @@ int heis3d_tiled_groups(int L, int planes);     // workgroups per replica
 hipError_t launch_heis3d_tiled(const float *src, float *dst, const float *beta, const Tally &acc, int n_rep, int L, Key key,
                                uint32_t t, bool renorm, int planes, hipStream_t s);
 
-// Parallel tempering of 3D edge-16 chains, all steps in one launch.
-bool pt3d_supported(const smc_desc *d, int n_temps);
-size_t pt3d_lds_bytes(int model, int n_temps);
-hipError_t launch_pt3d(int model, int8_t *spins, const int8_t *coup, int rep_per_sample, int n_chains, int n_temps,
-                       int beta_per_chain, const double *beta, const ThrRow *thr, int32_t *slot_of_temp,
-                       double *energy, unsigned long long *acc, Key key, uint32_t t0, int n_steps, int m,
-                       hipStream_t s);
-
 // Asynchronous multi-spin coding (2D EA/Ising, L in {16, 32, 64}): replicas
 // 32g .. 32g+31 packed into one word per site, all sweeps in one launch.
 bool msc2d_supported(int dim, int L);

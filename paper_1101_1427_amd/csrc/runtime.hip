@@ -187,12 +187,7 @@ bool use_heis3d_tiled(const smc_desc *d) {
     return heis3d_supported(d->dim, d->L) || (int64_t)d->n_rep * d->L * d->L * d->L >= (int64_t)1 << 18;
 }
 
-bool pt3d_enabled() {
-    const char *env = getenv("SPINMC_PT3D");
-    return !(env && env[0] == '0');
-}
-
-// Uniform 3D Ising / EA batches with an edge of 4 .. 24 keep whole replicas
+// Uniform 3D Ising / EA batches with an edge of 4 .. 24 or 32 keep whole replicas
 // in LDS for a call (any alignment, any beta); SPINMC_SMALL3D=0 keeps them on
 // the half-sweep launches, =1 tempering here whatever the estimate (same
 // results).
@@ -202,12 +197,18 @@ bool use_small3d(const smc_desc *d) {
     return (d->model == SMC_ISING || d->model == SMC_EA) && d->L > 0 && small3d_supported(d->dim, d->L);
 }
 
-bool use_pt3d(const smc_desc *d, const smc_pt_desc *pt, const void *spins, const std::vector<ThrRow> &rows) {
-    if (!pt3d_enabled() || !pt3d_supported(d, pt->n_temps)) return false;
-    if (((uintptr_t)spins & 15u) != 0) return false;
-    for (const ThrRow &r : rows)
-        if (r.m[1].x > 0xFFFFu || r.m[2].x > 0xFFFFu || r.m[3].x > 0xFFFFu) return false;
-    return true;
+bool use_pt3d(const smc_desc *d, int n_temps) {
+    const char *env = getenv("SPINMC_PT3D");
+    if (env && env[0] == '0') return false;
+    return (d->model == SMC_ISING || d->model == SMC_EA) && d->dim == 3 && d->L == 16 && n_temps >= 2 &&
+           n_temps <= 32 && !(d->model == SMC_EA && d->rep_per_sample % n_temps);
+}
+
+bool use_small3d_pt(const smc_desc *d, int n_temps, int n_chains) {
+    if (use_pt3d(d, n_temps)) return true;
+    const char *env = getenv("SPINMC_PT3D");
+    if (d->L == 16 && env && env[0] == '0') return false;
+    return use_small3d(d) && n_temps <= small3d_max_reps(d->L) && small3d_tempers(d->L, n_temps, n_chains);
 }
 
 // The one-pass split-layout kernel serves uniform 2D Ising batches whose

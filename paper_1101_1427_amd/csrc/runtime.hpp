@@ -99,10 +99,12 @@ ThrRow threshold_row(double beta, int dim);
 // ------------------------------------------------------------------ paths ----
 bool use_heis3d(const smc_desc *d);
 bool use_heis3d_tiled(const smc_desc *d);
-bool pt3d_enabled();
 // Small 3D edges with whole replicas on chip (SPINMC_SMALL3D=0: never).
 bool use_small3d(const smc_desc *d);
-bool use_pt3d(const smc_desc *d, const smc_pt_desc *pt, const void *spins, const std::vector<ThrRow> &rows);
+// 3D tempering of edge 16 and at most 32 temperatures, which always runs there
+// (the "k_pt3d_chain" path; SPINMC_PT3D=0: never), and of the other small edges.
+bool use_pt3d(const smc_desc *d, int n_temps);
+bool use_small3d_pt(const smc_desc *d, int n_temps, int n_chains);
 bool use_lattice2d(const smc_desc *d, const void *spins, const std::vector<ThrRow> &rows);
 bool sweep3d_shape(const smc_desc *d);
 bool pass3d_enabled(const smc_desc *d);

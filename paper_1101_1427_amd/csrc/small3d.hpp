@@ -30,9 +30,9 @@ int small3d_max_reps(int L);
 // Whether tempering of n_chains chains of n replicas is faster with a chain per
 // workgroup than with its replicas spread over the chip.
 bool small3d_tempers(int L, int n, int n_chains);
-// Bytes before and after the staged replicas: reads at the distances that a
-// group does not need (its masks drop them) stay inside.
-inline __host__ __device__ int small3d_pad(int L) { return (L * L * L / 2 + 7) / 8 * 8 + 16; }
+// Words before and after the staged replicas: reads at the distances that a
+// word does not need (its masks drop them) stay inside.
+inline __host__ __device__ int small3d_pad(int L) { return L % 16 ? (L * L * L / 2 + 7) / 8 + 4 : 0; }
 hipError_t launch_small3d(const Small3dArgs &a, hipStream_t s);
 
 }  // namespace smc

@@ -21,7 +21,8 @@ def _dev(a):
 
 @pytest.mark.parametrize("model", [S.ISING, S.EA])
 @pytest.mark.parametrize("L,n_rep", [(4, 1), (4, 37), (6, 7), (8, 5), (10, 3), (12, 2), (14, 3),
-                                     (16, 2), (16, 1025), (18, 1), (22, 2), (24, 3)])
+                                     (16, 2), (16, 1025), (16, 4100), (18, 1), (22, 2), (24, 3),
+                                     (32, 1), (32, 3)])
 def test_small3d_sweeps_against_oracle(model, L, n_rep):
     import torch
 
@@ -40,7 +41,9 @@ def test_small3d_sweeps_against_oracle(model, L, n_rep):
 
 @pytest.mark.parametrize("L,n_temps,per_chain,m", [(4, 5, False, 1), (6, 64, False, 1), (8, 12, True, 2),
                                                    (10, 24, False, 1), (12, 9, False, 3), (14, 32, True, 1),
-                                                   (20, 4, False, 1), (24, 11, True, 1)])
+                                                   (20, 4, False, 1), (24, 11, True, 1),
+                                                   (16, 2, False, 2), (16, 33, True, 1), (16, 64, False, 1),
+                                                   (32, 5, True, 2), (32, 8, False, 1)])
 def test_small3d_tempering_against_oracle(monkeypatch, L, n_temps, per_chain, m):
     import torch
 
