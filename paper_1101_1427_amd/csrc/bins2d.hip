@@ -11,13 +11,11 @@
 // staying within one replica, whose index, thresholds and random key are then
 // wave-uniform.
 //
-// LDS layout of a replica of edge L (L^2 / 2 bytes): byte i of row y is the pair
-// (2i, 2i + 1), the even site in the low four bits, the odd one in the high
-// four; each holds the spin and, for EA, the bonds to x + 1 and y + 1 (1: -1)
-// in bits 0, 1 and 2, so a half-sweep reads no couplings.  Even sites of row y
-// have colour y & 1, so the own sites of a piece of 16 are the low or the high
-// halves of its eight bytes, and their row neighbours the other halves.
-// The first step of a call builds the bytes from the caller's arrays, the steps
+// LDS layout of a replica of edge L (L^2 / 2 bytes, halves.hpp): two arrays of half-bytes
+// by colour, eight sites to a word, so the own sites, their partners and each kind
+// of neighbour of a Philox block are one word, and the bonds come with them.  Even
+// sites of row y have colour y & 1.
+// The first step of a call builds the words from the caller's arrays, the steps
 // between keep them in a packed copy in the same layout (half a byte per site
 // in and out, copied as it is), the last one writes the spins back.
 //
@@ -31,13 +29,13 @@
 
 #include <algorithm>
 
-#include "rows.hpp"
-#include "segment3d.hpp"
+#include "halves.hpp"
 
 namespace smc {
 namespace {
 
 using namespace seg3d;
+using namespace halves;
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
@@ -49,12 +47,6 @@ struct RepRow {
     int r, row;
 };
 
-// Bits 0 of four bytes: (a ^ b) & 1, (a ^ b ^ c) & 1.
-__device__ __forceinline__ uint32_t x2(uint32_t a, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, b, 0x01010101u, 0x28);
-}
-__device__ __forceinline__ uint32_t x3(uint32_t a, uint32_t b, uint32_t c) { return x2(a ^ b, c); }
-
 // In 2D the entries move up by one (a count of 2 reads a threshold of 2^32).
 __device__ __forceinline__ ThrRow table2d(const ThrRow &th) {
     ThrRow t;
@@ -65,62 +57,44 @@ __device__ __forceinline__ ThrRow table2d(const ThrRow &th) {
     return t;
 }
 
-// Row-major +-1 bytes of 16 sites (and their bonds) to the bytes of their pairs.
-template <bool EA>
-__device__ __forceinline__ uint2 pairs16(const uint4 &s, const uint4 &jx, const uint4 &jy) {
-    auto word = [](uint32_t v, uint32_t x, uint32_t y) -> uint32_t {
-        uint32_t w = (v >> 1) & 0x01010101u;
-        if constexpr (EA) w |= (x & 0x02020202u) | ((y << 1) & 0x04040404u);
-        return w;
-    };
-    const uint4 w =
-        make_uint4(word(s.x, jx.x, jy.x), word(s.y, jx.y, jy.y), word(s.z, jx.z, jy.z), word(s.w, jx.w, jy.w));
-    const uint2 e = half_of(w, 0x06040200u), o = half_of(w, 0x07050301u);
-    return make_uint2(e.x | (o.x << 4), e.y | (o.y << 4));
-}
-
-// Colour-c sites of piece k of row y (yH = y L/2) of the replica at S; adds the
+// Colour-c sites of word k of row y (yG = y L/16) of the replica at S; adds the
 // flips and the unsatisfied bonds of the flipped sites.
 template <bool EA>
-__device__ __forceinline__ void update(uint8_t *S, int L, int y, int yH, int k, uint32_t c, uint32_t t, uint32_t r,
-                                       Key key, const Lut3 &K, const ThrRow *thr, uint32_t one2, uint32_t &cnt,
-                                       uint32_t &nsum) {
-    const int half = L >> 1, bytes = L * half;
+__device__ __forceinline__ void update(uint32_t *S, int G, int words, int y, int yG, int k, uint32_t c, uint32_t t,
+                                       uint32_t r, Key key, const Lut3 &K, const ThrRow *thr, uint32_t one2,
+                                       uint32_t &cnt, uint32_t &nsum) {
     const bool odd = ((uint32_t)y & 1u) != c;  // own sites are the odd ones
-    const int below = yH == 0 ? bytes - half : yH - half, above = yH == bytes - half ? 0 : yH + half;
-    uint8_t *at = S + yH + 8 * k;
-    const uint2 p = lds8(at);
-    // the word before the piece (even own sites) or after it (odd), periodic in the row
-    const uint32_t ext = lds4(S + yH + (odd ? (8 * k + 8 == half ? 0 : 8 * k + 8) : (k == 0 ? half - 4 : 8 * k - 4)));
-    const uint2 dn = lds8(S + below + 8 * k), up = lds8(S + above + 8 * k);
-    const uint32_t g = (uint32_t)((yH >> 3) + k);
+    uint32_t *const mine = S + (c ? words : 0) + yG + k;
+    const uint32_t *const row = S + (c ? 0 : words) + k;
+    const uint32_t own = *mine, par = row[yG];
+    const uint32_t up = row[yG == words - G ? 0 : yG + G], dn = row[yG == 0 ? words - G : yG - G];
+    // the word after (odd own sites) or before it, periodic in the row
+    const uint32_t beside = row[yG + (odd ? (k == G - 1 ? 1 - G : 1) : (k == 0 ? G - 1 : -1))];
+    const uint32_t g = (uint32_t)(yG + k);
     const uint4 w = philox4x32_10(make_uint4(g, t, r, 2 * kTagHead + c), key);
-    // the pairs before (even own sites) or after (odd)
-    const uint32_t s = odd ? 1u : 3u;
-    const uint32_t mx = alignbyte(odd ? p.y : p.x, odd ? p.x : ext, s), my = alignbyte(odd ? ext : p.y, odd ? p.y : p.x, s);
-    // u: the x + 1 neighbours (own bond), v: the x - 1 neighbours (their bond)
-    const uint2 u = make_uint2(odd ? mx : p.x, odd ? my : p.y), v = make_uint2(odd ? p.x : mx, odd ? p.y : my);
-    const uint32_t mine = odd ? 4u : 0u, other = 4u - mine;
-    auto count = [&](uint32_t own, uint32_t u1, uint32_t v1, uint32_t up1, uint32_t dn1) -> uint32_t {
-        const uint32_t o1 = own >> mine;
-        if constexpr (EA)
-            return x3(o1, u1 >> other, own >> (mine + 1u)) + x3(o1, v1 >> other, v1 >> (other + 1u)) +
-                   x3(o1, up1 >> mine, own >> (mine + 2u)) + x3(o1, dn1 >> mine, dn1 >> (mine + 2u));
-        else
-            return x2(o1, u1 >> other) + x2(o1, v1 >> other) + x2(o1, up1 >> mine) + x2(o1, dn1 >> mine);
-    };
+    const uint32_t side = __builtin_amdgcn_alignbit(odd ? beside : par, odd ? par : beside, odd ? 4u : 28u);
+    uint32_t n;  // unsatisfied bonds
+    if constexpr (EA) {
+        // bond of the pair itself: the even site's; of the side pair: the lower site's
+        const uint32_t jp = odd ? par : own, js = odd ? own : side;
+        n = x3(own, par, jp >> 1) + x3(own, side, js >> 1) + x3(own, up, own >> 2) + x3(own, dn, dn >> 2);
+    } else {
+        n = x2(own, par) + x2(own, side) + x2(own, up) + x2(own, dn);
+    }
+    const uint2 by = to_bytes(n);
     RowOut o;
-    o.n0 = count(p.x, u.x, v.x, up.x, dn.x);
-    o.n1 = count(p.y, u.y, v.y, up.y, dn.y);
+    o.n0 = by.x;
+    o.n1 = by.y;
     uint32_t eq = 0xFFFFFFFFu;
     o.F0 = decide4(o.n0, w.x, w.y, K, one2, eq);
     o.F1 = decide4(o.n1, w.z, w.w, K, one2, eq);
     if (__builtin_expect(__any(has_tie(eq)), 0))
         exact_decisions(o, w, table2d(*thr), K, 8u * g, c, t, r, key, has_tie(eq));
-    *(uint2 *)__builtin_assume_aligned(at, 8) = make_uint2(p.x ^ (o.F0 << mine), p.y ^ (o.F1 << mine));
+    const uint32_t f = flags_of(o.F0, o.F1);
+    *mine = own ^ f;
     // Delta E of a flip with n unsatisfied bonds is 4 (2 - n)
-    cnt = __builtin_amdgcn_sad_u8(o.F0, 0u, __builtin_amdgcn_sad_u8(o.F1, 0u, cnt));
-    nsum = __builtin_amdgcn_sad_u8(o.n0 & bytes_ff(o.F0), 0u, __builtin_amdgcn_sad_u8(o.n1 & bytes_ff(o.F1), 0u, nsum));
+    cnt += (uint32_t)__builtin_popcount(f);
+    nsum = __builtin_amdgcn_udot8(n, f, nsum, false);
 }
 
 // (replica, row, piece) of index tid + j * threads over the pieces of a bin,
@@ -154,14 +128,14 @@ struct Walk {
 
 template <bool EA>
 __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in, int raw_out, uint32_t one2) {
-    extern __shared__ __align__(16) uint8_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     __shared__ RepRow tab[kBinReps];
     __shared__ int64_t spin_off[kBinReps], coup_off[kBinReps];
     __shared__ int dE[kBinReps];
     // consecutive bins (the replicas of one chain) on one XCD, sharing its L2
-    const uint32_t nblk = gridDim.x, b = blockIdx.x;
-    const Bin2d bin = a.bins[(nblk & 7u) ? b : (b & 7u) * (nblk >> 3) + (b >> 3)];
-    const int L = bin.L, N = L * L, half = L >> 1, bytes = N >> 1, tid = (int)threadIdx.x, reps = bin.count;
+    const uint32_t nblk = gridDim.x, blk = blockIdx.x;
+    const Bin2d bin = a.bins[(nblk & 7u) ? blk : (blk & 7u) * (nblk >> 3) + (blk >> 3)];
+    const int L = bin.L, N = L * L, G = L >> 4, words = N >> 4, tid = (int)threadIdx.x, reps = bin.count;
     if (tid < reps) {
         RepRow t;
         t.r = a.work[bin.first + tid];
@@ -181,26 +155,30 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
         constexpr int kBatch = 4;
         Walk wk(L, tid, kThreads);
         while (wk.rep < reps) {
-            uint4 v[kBatch], jx[kBatch], jy[kBatch];
-            int at[kBatch];
+            uint4 v[kBatch], j[kBatch][2];
+            int at[kBatch];  // word of the colour-0 array, twice, plus 1 where it takes the odd sites
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j) {
-                at[j] = -1;
+            for (int b = 0; b < kBatch; ++b) {
+                at[b] = -1;
                 if (wk.rep < reps) {
                     const int i = wk.y * L + 16 * wk.k;
-                    at[j] = wk.rep * bytes + wk.y * half + 8 * wk.k;
-                    v[j] = *(const uint4 *)(a.spins + spin_off[wk.rep] + i);
+                    at[b] = 2 * (2 * wk.rep * words + wk.y * G + wk.k) + (wk.y & 1);
+                    v[b] = *(const uint4 *)(a.spins + spin_off[wk.rep] + i);
                     if constexpr (EA) {
-                        jx[j] = *(const uint4 *)(a.coup + coup_off[wk.rep] + i);
-                        jy[j] = *(const uint4 *)(a.coup + coup_off[wk.rep] + N + i);
+                        j[b][0] = *(const uint4 *)(a.coup + coup_off[wk.rep] + i);
+                        j[b][1] = *(const uint4 *)(a.coup + coup_off[wk.rep] + N + i);
                     }
                 }
                 wk.next();
             }
 #pragma unroll
-            for (int j = 0; j < kBatch; ++j)
-                if (at[j] >= 0)
-                    *(uint2 *)__builtin_assume_aligned(smem + at[j], 8) = pairs16<EA>(v[j], jx[j], jy[j]);
+            for (int b = 0; b < kBatch; ++b)
+                if (at[b] >= 0) {
+                    const uint2 eo = words_of(v[b], j[b], EA ? 2 : 0);
+                    uint32_t *p = smem + (at[b] >> 1);
+                    p[0] = (at[b] & 1) ? eo.y : eo.x;
+                    p[words] = (at[b] & 1) ? eo.x : eo.y;
+                }
         }
     } else {
         const uint4 *src = (const uint4 *)(a.packed + bin.packed);
@@ -214,7 +192,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
     // ---- the sweeps: a wave (or several) per replica
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int share = reps >= kWaves ? 1 : kWaves / reps;  // waves per replica
-    const int G = L >> 4, step = 64 * share, i0 = 64 * (wave % share) + lane;
+    const int step = 64 * share, i0 = 64 * (wave % share) + lane;
     const int y0 = i0 / G, k0 = i0 - y0 * G, dy = step / G, dk = step - dy * G;
     const int rep0 = wave / share, reps_step = share > 1 ? kBinReps : kWaves;
     uint32_t cnt = 0, nsum = 0;
@@ -236,9 +214,9 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
                 Lut3 K;
                 K.lo = __builtin_amdgcn_readfirstlane(tab[rep].lut.x);
                 K.hi = __builtin_amdgcn_readfirstlane(tab[rep].lut.y);
-                uint8_t *S = smem + rep * bytes;
+                uint32_t *S = smem + 2 * rep * words;
                 for (int y = y0, k = k0; y < L;) {
-                    update<EA>(S, L, y, y * half, k, c, t, r, a.key, K, a.thr + row, one2, cnt, nsum);
+                    update<EA>(S, G, words, y, y * G, k, c, t, r, a.key, K, a.thr + row, one2, cnt, nsum);
                     y += dy;
                     k += dk;
                     if (k >= G) {
@@ -257,13 +235,10 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
     if (raw_out) {
         Walk wk(L, tid, kThreads);
         for (; wk.rep < reps; wk.next()) {
-            const uint2 e = lds8(smem + wk.rep * bytes + wk.y * half + 8 * wk.k), o = make_uint2(e.x >> 4, e.y >> 4);
-            auto word = [](uint32_t od, uint32_t ev, uint32_t sel) {
-                return bytes_pm1(perm(od, ev, sel) & 0x01010101u);
-            };
+            const uint32_t *p = smem + 2 * wk.rep * words + wk.y * G + wk.k;
+            const uint32_t c0 = p[0], c1 = p[words];
             *(uint4 *)(a.spins + spin_off[wk.rep] + wk.y * L + 16 * wk.k) =
-                make_uint4(word(o.x, e.x, 0x05010400u), word(o.x, e.x, 0x07030602u), word(o.y, e.y, 0x05010400u),
-                           word(o.y, e.y, 0x07030602u));
+                (wk.y & 1) ? spins_of(c1, c0) : spins_of(c0, c1);
         }
     } else {
         uint4 *dst = (uint4 *)(a.packed + bin.packed);

@@ -6,11 +6,9 @@
 // many independent ones as fill it.  Bound: VALU of the compute units that hold
 // a replica.
 //
-// Layout: half a byte per site.  Pair h of a replica is the sites (2h, 2h + 1);
-// each pair holds one site of either colour, so array C_c keeps the colour-c
-// site of pair h in its bits 4 h .. 4 h + 3: the spin in bit 0 and, for EA, the
-// bonds to x + 1, y + 1, z + 1 in bits 1 .. 3 (1: -1), so a neighbour pair's bond
-// comes with the spins and replicas of different samples can share a workgroup.
+// Layout (halves.hpp): half a byte per site, eight sites of one colour per word, so
+// a neighbour pair's bond comes with the spins and replicas of different samples can
+// share a workgroup.
 // The eight sites that share Philox block g are word g of C_c.  Their
 // neighbours are all in the other array, at fixed distances in h: the partner at
 // h, the other x neighbour at h + 1 or h - 1 (by the site's parity in x), y
@@ -38,18 +36,18 @@
 
 #include <algorithm>
 
+#include "halves.hpp"
 #include "rows.hpp"
-#include "segment3d.hpp"
 
 namespace smc {
 namespace {
 
 using namespace seg3d;
+using namespace halves;
 
 constexpr int kMaxThreads = 1024;
 constexpr int kMaxReps = kSmall3dMaxReps;
 constexpr int kSums = 8;  // energy sums per replica
-constexpr uint32_t kOnes = 0x11111111u;
 
 struct KArgs {
     Small3dArgs b;
@@ -80,30 +78,10 @@ __device__ __forceinline__ long long energy_of(const State &st, int rep) {
     return st.E[rep] + 4ll * (int)d;
 }
 
-__device__ __forceinline__ uint32_t pick(uint32_t m, uint32_t one, uint32_t zero) { return (one & m) | (zero & ~m); }
-// Bits 0 of eight half-bytes: (a ^ b) & 1, (a ^ b ^ c) & 1.
-__device__ __forceinline__ uint32_t x2(uint32_t a, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, b, kOnes, 0x28);
-}
-__device__ __forceinline__ uint32_t x3(uint32_t a, uint32_t b, uint32_t c) { return x2(a ^ b, c); }
-
 // The eight half-bytes at distance d (any) from word p.
 __device__ __forceinline__ uint32_t at(const uint32_t *p, int d) {
     const uint32_t *q = p + (d >> 3);
     return __builtin_amdgcn_alignbit(q[1], q[0], 4u * ((uint32_t)d & 7u));
-}
-
-// Eight bytes (each below 16) to half-bytes and back.
-__device__ __forceinline__ uint32_t halves_of(const uint2 &b) {
-    return perm(b.y | (b.y >> 4), b.x | (b.x >> 4), 0x06040200u);
-}
-__device__ __forceinline__ uint2 bytes_of(uint32_t w) {
-    const uint32_t e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
-    return make_uint2(perm(o, e, 0x05010400u), perm(o, e, 0x07030602u));
-}
-// Eight 0/1 bytes to bits 0 of half-bytes.
-__device__ __forceinline__ uint32_t flags_of(uint32_t F0, uint32_t F1) {
-    return perm(F1, F0, 0x06040200u) | (perm(F1, F0, 0x07050301u) << 4);
 }
 
 // Masks of the eight pairs of a word.
@@ -243,25 +221,17 @@ __global__ __launch_bounds__(kMaxThreads, LOG ? 8 : 4) void k_small3d(KArgs a) {
                 const int g = g0 + sl * lanes;
                 const int64_t i = 16 * (int64_t)g;
                 const int8_t *S = a.b.spins + (int64_t)(r0 + rep) * N;
-                auto word = [](uint32_t v, int shift) -> uint32_t {
-                    return shift ? (v << (shift - 1)) & (0x01010101u << shift) : (v >> 1) & 0x01010101u;
-                };
-                auto bits = [&](const uint4 &v, int shift) -> uint4 {
-                    return make_uint4(word(v.x, shift), word(v.y, shift), word(v.z, shift), word(v.w, shift));
-                };
-                uint4 w = bits(load16(S, i, N), 0);
+                const uint4 w = load16(S, i, N);
+                uint4 bonds[3];
                 if constexpr (EA) {
                     const int8_t *J = a.b.coup + (int64_t)((r0 + rep) / a.b.rep_per_sample) * 3 * N;
 #pragma unroll
-                    for (int mu = 0; mu < 3; ++mu) {
-                        const uint4 j = bits(load16(J + mu * N, i, N), mu + 1);
-                        w = make_uint4(w.x | j.x, w.y | j.y, w.z | j.z, w.w | j.w);
-                    }
+                    for (int mu = 0; mu < 3; ++mu) bonds[mu] = load16(J + mu * N, i, N);
                 }
-                const uint32_t e = halves_of(half_of(w, 0x06040200u)), o = halves_of(half_of(w, 0x07050301u));
+                const uint2 eo = words_of(w, bonds, EA ? 3 : 0);
                 uint32_t *p = T + rep * 2 * G + g;
-                p[0] = pick(colour0_odd(), o, e);
-                p[G] = pick(colour0_odd(), e, o);
+                p[0] = pick(colour0_odd(), eo.y, eo.x);
+                p[G] = pick(colour0_odd(), eo.x, eo.y);
             }
     __syncthreads();
 
@@ -325,7 +295,7 @@ __global__ __launch_bounds__(kMaxThreads, LOG ? 8 : 4) void k_small3d(KArgs a) {
                                 cnt = x2(own, par) + x2(own, side) + x2(own, yp) + x2(own, ym) + x2(own, zp) +
                                       x2(own, zm);
                             }
-                            const uint2 lu = st.lut[rep], by = bytes_of(cnt);
+                            const uint2 lu = st.lut[rep], by = to_bytes(cnt);
                             const Lut3 K{lu.x, lu.y};
                             uint32_t eq = 0xFFFFFFFFu;
                             RowOut o;
@@ -373,12 +343,7 @@ __global__ __launch_bounds__(kMaxThreads, LOG ? 8 : 4) void k_small3d(KArgs a) {
             for (int sl = 0; sl < kSlices; ++sl) {
                 const int g = g0 + sl * lanes;
                 const uint32_t *p = T + rep * 2 * G + g;
-                const uint2 e = bytes_of(pick(colour0_odd(), p[G], p[0])), o = bytes_of(pick(colour0_odd(), p[0], p[G]));
-                auto out = [](uint32_t od, uint32_t ev, uint32_t sel) {
-                    return bytes_pm1(perm(od, ev, sel) & 0x01010101u);
-                };
-                const uint4 w = make_uint4(out(o.x, e.x, 0x05010400u), out(o.x, e.x, 0x07030602u),
-                                           out(o.y, e.y, 0x05010400u), out(o.y, e.y, 0x07030602u));
+                const uint4 w = spins_of(pick(colour0_odd(), p[G], p[0]), pick(colour0_odd(), p[0], p[G]));
                 int8_t *D = a.b.spins + (int64_t)(r0 + rep) * N + 16 * (int64_t)g;
                 if (16 * (int64_t)g + 16 <= N)  // N is a multiple of 8
                     __builtin_memcpy(D, &w, 16);
