@@ -781,8 +781,9 @@ def dcb3d(S, W, L=256, hits=(1, 10, 100), beta=0.22, flips=4e9):
 
 def sweep3d(S, W, sizes=(256, 512, 1024), beta=0.2216, flips=8e9, models=("ising", "ea"), tune=True):
     """Plain 3D checkerboard sweeps (Ising, and EA with one coupling sample)
-    on one L^3 lattice: ps per attempted flip for the one-pass segment sweep,
-    the two half-sweep launches and the per-site kernels, and the rate at
+    on one L^3 lattice: ps per attempted flip for a call as it comes (the packed
+    copy), the one-pass segment sweep, the two half-sweep launches and the
+    general kernels, and the rate at
     2 B/flip (one read and one write of every spin per sweep) against 8 TB/s.
     With tune, smc_autotune first measures the launch shapes of both 3D
     paths for each lattice (the rows report them)."""
@@ -812,8 +813,8 @@ def sweep3d(S, W, sizes=(256, 512, 1024), beta=0.2216, flips=8e9, models=("ising
                 row["tuned"] = [t for t in autotune_report(S, b, envs=({"SPINMC_SWEEP3D_PASS": "1"},
                                                                       {"SPINMC_SWEEP3D_PASS": "0"}))
                                 if t["model"] == row["model"] and t["replicas"] == 1]
-            for key, env in (("pass", {"SPINMC_SWEEP3D_PASS": "1"}), ("half", {"SPINMC_SWEEP3D_PASS": "0"}),
-                             ("per_site", {"SPINMC_SWEEP3D": "0"})):
+            for key, env in (("call", {}), ("pass", {"SPINMC_SWEEP3D_PASS": "1"}),
+                             ("half", {"SPINMC_SWEEP3D_PASS": "0"}), ("per_site", {"SPINMC_SWEEP3D": "0"})):
                 os.environ.update(env)
                 S.metropolis_sweep(b, spins, [beta], 0, 2, couplings=coup)
                 S.kernel_timing_read()

@@ -62,9 +62,9 @@
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place, or, for
- *   calls of three and more sweeps and L >= 48 (EA: up to 1024), on a
- *   library-held packed copy of half a byte per site, and with L = 16 or 32
- *   on chip for the call;
+ *   calls of three and more sweeps (Ising with L >= 512: six) and L >= 48, on
+ *   a library-held packed copy of half a byte per site (two launches per sweep),
+ *   and with L = 16 or 32 on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
  *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
  *   thread where an edge is below 16), or, for uniform 3D batches of edge 4
@@ -308,8 +308,9 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream);
 
 /*
  * How smc_metropolis_sweep will execute this batch: the number of kernel
- * launches per sweep (at most) and the name of the sweep kernel (a static
- * string; "k_half_sweep_generic" stands for the general path).
+ * launches per sweep (at most; of a call of one sweep, where longer calls run
+ * on a packed copy) and the name of the sweep kernel (a static string;
+ * "k_half_sweep_generic" stands for the general path).
  * Used by benchmarks to attribute per-launch time; no device work.
  */
 int smc_sweep_plan(const smc_desc *desc, int32_t *launches_per_sweep, const char **kernel_name);

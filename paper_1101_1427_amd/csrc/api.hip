@@ -332,11 +332,10 @@ int run_small3d(hipStream_t s, const SweepArgs &a, uint64_t sweep0, int32_t n_sw
 
 // 3D batches of edge 16 and more run calls of several sweeps on a packed copy
 // of their lattices (packing and unpacking take about as long as one
-// sweep saves two or three times over).  Among the multiples of 16, edge 16
-// keeps the kernel on the caller's bytes (its rows of one piece leave half of
-// the packed kernel's threads idle: 9.7 us per sweep of 512 replicas against
-// 11.7) and Ising edges of 512 and more the one-pass kernel (512^3 level, 1024^3
-// 570 us against 810; EA 512^3 143 against 98, 1024^3 1000 against 920).
+// sweep saves two or three times over; against the one-pass kernel of Ising edges from
+// 512, five times).  Per sweep, packing included, against the kernels on the caller's
+// bytes: EA 256^3 24.0 -> 15.3 us (20 sweeps), 512^3 143 -> 82 (10), 1024^3 1000 -> 702 (6),
+// Ising 512^3 92 -> 68 (10), 768^3 290 -> 226 (6), 1024^3 565 -> 544 (6).
 // SPINMC_PAIRS3D=0 keeps the kernels on the caller's bytes (same results), and
 // so does a launch shape of those asked for in the environment.
 bool sweep3d_asked_for() {
@@ -354,7 +353,7 @@ bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
     if (env && env[0] == '1') return true;
     if (d->L % 16) return n_sweeps >= 2;
     if (sweep3d_asked_for()) return false;
-    return n_sweeps >= 3 && d->L >= 32 && (d->model == SMC_EA || !pass3d_enabled(d));
+    return n_sweeps >= (d->model == SMC_ISING && pass3d_enabled(d) ? 6 : 3) && d->L >= 32;
 }
 
 // The packed copy of a call; SMC_ENOMEM (the caller's bytes serve then) if
@@ -363,7 +362,7 @@ int pairs3d_args(StreamCtx &c, const SweepArgs &a, Pairs3dArgs *p) {
     void *q = nullptr;
     const size_t bytes = pairs3d_bytes(a.b.L, a.b.n_rep);
     if (int rc = ensure(c, kPairs3d, bytes, &q)) return rc;
-    p->packed = (uint8_t *)q + pairs3d_pad();
+    p->packed = (uint32_t *)q;
     p->rep_per_sample = a.b.rep_per_sample;
     p->thr = a.thr;
     p->row_of_rep = a.row_of_rep;

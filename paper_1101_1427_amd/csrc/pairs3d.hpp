@@ -6,7 +6,7 @@
 namespace smc {
 
 struct Pairs3dArgs {
-    uint8_t *packed;           // the replicas, pairs3d_stride(L) bytes each
+    uint32_t *packed;          // pairs3d_bytes(L, n_rep)
     int rep_per_sample;        // of the couplings (packing)
     const ThrRow *thr;
     const int32_t *row_of_rep; // threshold row per replica (-1: left unchanged), or nullptr
@@ -17,10 +17,8 @@ struct Pairs3dArgs {
 };
 
 bool pairs3d_supported(int dim, int L);
-// Bytes of the buffer of a packed copy, and of its margin before the first
-// replica (packed points behind it): reads beside a piece stay inside.
+// Bytes of the packed copy.
 size_t pairs3d_bytes(int L, int n_rep);
-constexpr size_t pairs3d_pad() { return 64; }
 hipError_t launch_pairs3d_pack(const int8_t *spins, const int8_t *coup, const Pairs3dArgs &a, hipStream_t s);
 hipError_t launch_pairs3d_unpack(int8_t *spins, const Pairs3dArgs &a, hipStream_t s);
 int pairs3d_planes(int L, int n_rep);         // planes per thread for a batch

@@ -23,10 +23,11 @@ def _dev(a, shift=0):
 
 @pytest.mark.parametrize("model", [S.ISING, S.EA])
 @pytest.mark.parametrize("L,planes", [(16, 1), (16, 4), (18, 1), (20, 1), (22, 1), (24, 1), (26, 1), (28, 1), (30, 1),
-                                      (32, 2), (34, 1), (46, 1), (48, 4), (64, 1)])
+                                      (32, 2), (34, 1), (46, 1), (48, 1), (48, 2), (48, 4), (48, 8), (64, 1)])
 def test_pairs_against_oracle(monkeypatch, model, L, planes):
     import torch
 
+    monkeypatch.setenv("SPINMC_SMALL3D", "0")
     monkeypatch.setenv("SPINMC_PAIRS3D", "1")
     monkeypatch.setenv("SPINMC_PAIRS3D_PLANES", str(planes))
     n_rep, seed, n = 3, W.seed_for(700 + L), 3
