@@ -36,9 +36,9 @@ KERNEL_SOURCES = {
     "k_heis3d_tiled": ("heis3d.hip", "heis_math.hpp", "philox.hpp"),
     "k_ising3d_half": ("sweep3d.hip", "segment3d.hpp", "intrin.hpp", "philox.hpp", "tables.hpp"),
     "k_ising3d_pass": ("pass3d.hip", "segment3d.hpp", "intrin.hpp", "philox.hpp", "tables.hpp"),
-    "k_pt3d_chain": ("small3d.hip", "small3d.hpp", "rows.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp",
+    "k_pt3d_chain": ("small3d.hip", "small3d.hpp", "halves.hpp", "rows.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp",
                      "tables.hpp"),
-    "k_uneven2d_sweep": ("bins2d.hip", "rows.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp", "tables.hpp"),
+    "k_uneven2d_sweep": ("bins2d.hip", "halves.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp", "tables.hpp"),
 }
 
 

@@ -71,19 +71,19 @@
  *   .. 24, whole replicas held on chip for the call (tempering too, with up
  *   to 64 temperatures that fit and enough chains), or of larger edges the
  *   packed copy (calls of two and more sweeps), or, for uniform 2D batches where an
- *   estimate says that it is faster, bands of rows (or a whole lattice) held
- *   on chip for several sweeps per launch, alternating with a library-held
+ *   estimate says that it is faster, bands of rows, tiles (or a whole lattice)
+ *   held on chip for several sweeps per launch, alternating with a library-held
  *   second lattice.  Small 2D batches (L a multiple of 16 up to 128, or 256
  *   with at least 2^19 sites in the batch: "k_uneven2d_sweep") run on these
  *   bands as well, and so do calls of two and more sweeps on power-of-two
- *   edges up to 2048 with at most 2^25 sites in the batch.  All paths give
+ *   edges up to 2048 (eight and more: 4096) with at most 2^25 sites in the batch.  All paths give
  *   identical results.  Environment variables for comparisons and tuning
  *   (read at each call): SPINMC_PT3D=0, SPINMC_UNEVEN2D=0 and
  *   SPINMC_PT_SPLIT2D=0 send tempering to the general path,
  *   SPINMC_SWEEP_LDS2D=0 small 2D sweeps to the half-sweeps,
  *   SPINMC_SWEEP3D=0 3D Ising / EA sweeps to the general path;
  *   SPINMC_BANDS2D=0 keeps the half-sweeps, =1 takes the bands wherever they
- *   fit (SPINMC_BANDS2D_ROWS and _SWEEPS set their shape,
+ *   fit (SPINMC_BANDS2D_ROWS, _WORDS and _SWEEPS set their shape,
  *   SPINMC_U2D_THREADS the workgroup of a whole lattice);
  *   SPINMC_SMALL3D=0 keeps the small 3D edges on the half-sweeps,
  *   SPINMC_PAIRS3D=0 the 3D half-sweeps on the caller's bytes (=1 takes the

@@ -199,9 +199,10 @@ struct CallTally {
 
 // Uniform 2D batches run several sweeps per launch on bands of rows in LDS
 // where the estimate says that it is faster than two half-sweep launches per
-// sweep (measured: about 3.5 us and 1.2 fs per site each).  A band needs about
-// 5 K bytes of LDS per row of 4 K sites, so large edges keep the half-sweeps,
-// and so does a call of one sweep unless the lattice fits in LDS as a whole.
+// sweep (measured: about 3.5 us and 1.2 fs per site each).  Edges that are
+// multiples of 16 are cut along their rows too (tiles2d.hip); of others a band needs
+// about 5 K bytes of LDS per row of 4 K sites, so large ones keep the half-sweeps.  So
+// does a call of one sweep unless the lattice fits in LDS as a whole.
 // SPINMC_BANDS2D=0 keeps the half-sweeps (same results), and so does
 // SPINMC_PT_SPLIT2D=0 in tempering (even is false there).
 bool use_bands2d(const smc_desc *d, const SweepArgs &a, int32_t n_sweeps, bool even, BandShape *sh) {
@@ -215,18 +216,20 @@ bool use_bands2d(const smc_desc *d, const SweepArgs &a, int32_t n_sweeps, bool e
     return forced || sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)a.b.n_rep * (double)a.b.N);
 }
 
-// Edges that the one-pass kernel (lattice2d.hip) serves: up to 2048 and 2^25
-// sites the bands are faster, because they move the lattice once per several
-// sweeps and need one launch for them (1024^2: 3.1 against 6.4 us per sweep,
-// eight of 2048^2: 24 against 33); above, the one-pass kernel's fewer
-// instructions per site win (16 of 2048^2: 37 against 46, 4096^2: 13.6
-// against 15.3).  A launch shape asked for in the environment is the one-pass
-// kernel's.
-bool bands_before_lattice2d(const smc_desc *d) {
+// Edges that the one-pass kernel (lattice2d.hip) serves: up to 2^25 sites and edge
+// 4096 the tiles are faster, because they move the lattice once per several
+// sweeps and need one launch for them (1024^2: 1.7 against 6.4 us per sweep,
+// eight of 2048^2: 20 against 33, 4096^2: 10.4 against 13.2, in calls of fewer than 8
+// sweeps 18 against 14.5); above, the one-pass kernel's fewer instructions per
+// site win (16 of 2048^2: 36.3 against 39.2, 8192^2: 34 against 40).  A launch shape
+// asked for in the environment is the one-pass kernel's.
+bool bands_before_lattice2d(const smc_desc *d, int32_t n_sweeps) {
     for (const char *name : {"SPINMC_L2D_CHUNKS", "SPINMC_L2D_H", "SPINMC_L2D_H1", "SPINMC_L2D_H2", "SPINMC_L2D_PAD",
                              "SPINMC_L2D_FUSE"})
         if (getenv(name)) return false;
-    return d->L <= 2048 && (int64_t)d->n_rep * d->L * d->L <= (int64_t)1 << 25;
+    const char *env = getenv("SPINMC_BANDS2D");
+    if (env && env[0] == '1') return true;
+    return d->L <= (n_sweeps >= 8 ? 4096 : 2048) && (int64_t)d->n_rep * d->L * d->L <= (int64_t)1 << 25;
 }
 
 // Sweeps on bands, from a.spins to `other` and back, launch by launch.
@@ -729,7 +732,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.thr = (const ThrRow *)p;
     BandShape sh;
     if (use_lattice2d(desc, spins, rows) &&
-        !(bands_before_lattice2d(desc) && use_bands2d(desc, a, n_sweeps, true, &sh))) {
+        !(bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, a, n_sweeps, true, &sh))) {
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);
         void *pp = nullptr;
@@ -1326,7 +1329,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
 
     BandShape sh;
     const bool bands = use_bands2d(desc, a, m, false, &sh);
-    if (use_pt_split2d(desc, spins, rows) && !(bands && bands_before_lattice2d(desc)))
+    if (use_pt_split2d(desc, spins, rows) && !(bands && bands_before_lattice2d(desc, m)))
         return run_pt_split2d(c, s, desc, spins, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
     // (few replicas: bands of their rows give more workgroups than a bin each)
     if (use_uneven2d(desc, spins, couplings, rows) &&

@@ -1,5 +1,6 @@
 // Sweeps of uniform 2D Ising / +-J EA batches of any even edge, several per
-// launch (Eq. 2, Sec. 3.2).
+// launch (Eq. 2, Sec. 3.2); the kernel for edges that are no multiples of 16 (the
+// others: tiles2d.hip) and the choice of the shape for both.
 //
 // A workgroup owns a band of rows (all x) and holds it in LDS with 2 S halo
 // rows on either side for S sweeps: half-sweep h updates the rows that are h + 1
@@ -31,9 +32,8 @@
 // A byte holds the spin in bit 0 and, for EA, the bonds to x + 1 and y + 1 in
 // bits 1 and 2 (1: -1), so the bond of a neighbour pair comes with the spin.
 //
-// Per sweep, against two half-sweep launches: one 512^2 Ising lattice 2.1 us
-// (7.9), 64 EA lattices of 200^2 4.6 us (14.3), 16 Ising lattices of 1000^2
-// 15.0 us (28.5).
+// Per sweep, against two half-sweep launches: 64 EA lattices of 200^2 4.6 us
+// (14.3), 16 Ising lattices of 1000^2 15.0 us (28.5).
 #include <stdlib.h>
 
 #include <algorithm>
@@ -80,8 +80,7 @@ struct At {
     int k;
 };
 
-// EA: with bonds; RAG: 16 does not divide L; DE: energy changes wanted.
-template <bool EA, bool RAG>
+template <bool EA>
 struct Band {
     const KArgs &a;
     uint8_t *T;      // the first staged row
@@ -96,7 +95,7 @@ struct Band {
         t.y = y_first + row;
         t.y += t.y < 0 ? L : t.y >= L ? -L : 0;
         const uint32_t yL = (uint32_t)t.y * (uint32_t)L;
-        t.p = RAG ? yL & 15u : 0u;
+        t.p = yL & 15u;
         t.g = (yL >> 4) + (uint32_t)k;
         t.base = (uint32_t)row * (uint32_t)a.pitch;
         t.k = k;
@@ -115,16 +114,10 @@ struct Band {
         const uint2 oth = lds8(T + t.base + (odd ? 0u : K8 + 8u) + k8);
         // the word before (even own sites: array O) or after (odd: array E)
         const uint32_t ext = lds4(T + t.base + (odd ? k8 + 8u : K8 + 8u + k8 - 4u));
-        uint2 dn, un;
-        if constexpr (RAG) {
-            const uint32_t pd = t.y == 0 ? ((L - 1u) * L) & 15u : (t.p - L) & 15u;
-            const uint32_t pu = t.y == (int)L - 1 ? 0u : (t.p + L) & 15u;
-            dn = lds8_at(T + down + mine, (int)(pd - t.p) >> 1);
-            un = lds8_at(T + up + mine, (int)(pu - t.p) >> 1);
-        } else {
-            dn = lds8(T + down + mine);
-            un = lds8(T + up + mine);
-        }
+        const uint32_t pd = t.y == 0 ? ((L - 1u) * L) & 15u : (t.p - L) & 15u;
+        const uint32_t pu = t.y == (int)L - 1 ? 0u : (t.p + L) & 15u;
+        const uint2 dn = lds8_at(T + down + mine, (int)(pd - t.p) >> 1);
+        const uint2 un = lds8_at(T + up + mine, (int)(pu - t.p) >> 1);
         // the other array moved by one site: x - 1 of even own sites, x + 1 of odd ones
         const uint32_t s = odd ? 1u : 3u;
         uint2 sh;
@@ -149,28 +142,22 @@ struct Band {
         if (__builtin_expect(__any(has_tie(eq)), 0))
             exact_decisions(o, w, th, K3, 8u * t.g, c, time, rr, a.b.key, has_tie(eq));
         uint8_t *row = T + t.base;
-        if constexpr (RAG) {
-            // positions p / 2 .. (p + L) / 2 - 1 of either array are the row's
-            const uint32_t first = t.p >> 1, end = (t.p + L) >> 1;
-            const uint32_t lo = first > k8 ? min(first - k8, 8u) : 0u, hi = end > k8 ? min(end - k8, 8u) : 0u;
-            const uint64_t m = (hi > lo ? ~0ull >> (64u - 8u * (hi - lo)) : 0ull) << (8u * (lo & 7u));
-            o.F0 &= (uint32_t)m;
-            o.F1 &= (uint32_t)(m >> 32);
-            const uint64_t F = ((uint64_t)o.F1 << 32) | o.F0;
-            (void)__hip_atomic_fetch_xor((unsigned long long *)__builtin_assume_aligned(own_at, 8),
-                                         (unsigned long long)F, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            // the copies: the first site after the row's end in E, the last one before its start in O
-            if (lo < hi && (odd ? end - k8 <= 8u : t.k == 0)) {
-                const uint32_t f = (uint32_t)(F >> (8u * (odd ? hi - 1u : lo))) & 1u;
-                uint8_t *copy = row + (odd ? K8 + 8u + first - 1u : end);
-                const uint32_t sub = (uint32_t)(uintptr_t)copy & 3u;
-                (void)__hip_atomic_fetch_xor((unsigned int *)__builtin_assume_aligned(copy - sub, 4), f << (8u * sub),
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        } else {
-            const uint2 now = make_uint2(own.x ^ o.F0, own.y ^ o.F1);
-            *(uint2 *)__builtin_assume_aligned(own_at, 8) = now;
-            if (odd ? t.k == a.K - 1 : t.k == 0) row[K8 + (odd ? 7u : 0u)] = (uint8_t)(odd ? now.y >> 24 : now.x);
+        // positions p / 2 .. (p + L) / 2 - 1 of either array are the row's
+        const uint32_t first = t.p >> 1, end = (t.p + L) >> 1;
+        const uint32_t lo = first > k8 ? min(first - k8, 8u) : 0u, hi = end > k8 ? min(end - k8, 8u) : 0u;
+        const uint64_t m = (hi > lo ? ~0ull >> (64u - 8u * (hi - lo)) : 0ull) << (8u * (lo & 7u));
+        o.F0 &= (uint32_t)m;
+        o.F1 &= (uint32_t)(m >> 32);
+        const uint64_t F = ((uint64_t)o.F1 << 32) | o.F0;
+        (void)__hip_atomic_fetch_xor((unsigned long long *)__builtin_assume_aligned(own_at, 8),
+                                     (unsigned long long)F, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the copies: the first site after the row's end in E, the last one before its start in O
+        if (lo < hi && (odd ? end - k8 <= 8u : t.k == 0)) {
+            const uint32_t f = (uint32_t)(F >> (8u * (odd ? hi - 1u : lo))) & 1u;
+            uint8_t *copy = row + (odd ? K8 + 8u + first - 1u : end);
+            const uint32_t sub = (uint32_t)(uintptr_t)copy & 3u;
+            (void)__hip_atomic_fetch_xor((unsigned int *)__builtin_assume_aligned(copy - sub, 4), f << (8u * sub),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         // Delta E of a flip with n unsatisfied bonds is 4 (2 - n)
         if (own_row) {
@@ -183,7 +170,7 @@ struct Band {
 
 // ONE: a thread per staged piece, which it keeps for the whole launch; the
 // draws of both colours are made together at the start of a sweep.
-template <bool EA, bool RAG, bool ONE>
+template <bool EA, bool ONE>
 __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ long long red[kMaxThreads / 64];
@@ -200,7 +187,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
     int8_t *D = a.b.dst + (int64_t)r * N;
     const int trow = a.b.row_of_rep ? a.b.row_of_rep[r] : r;
     uint8_t *T = smem + kPad;
-    Band<EA, RAG> bd{a, T};
+    Band<EA> bd{a, T};
     bd.rr = (uint32_t)r >> a.b.rng_shift;
 
     // (row, piece) of index i = tid + j * nt, advanced without divisions
@@ -238,7 +225,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
             if (rw[j] < R) {
                 const At t = bd.at(rw[j], kk[j], y_first);
                 const int64_t i = (int64_t)16 * t.g;
-                if (RAG && __builtin_expect(i > N - 16, 0)) {
+                if (__builtin_expect(i > N - 16, 0)) {
                     into_place<int64_t>(v[j], i, N);
                     if constexpr (EA) {
                         into_place<int64_t>(jx[j], i, N);
@@ -338,7 +325,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
                        bytes_pm1(perm(od.y, ev.y, 0x05010400u) & 0x01010101u),
                        bytes_pm1(perm(od.y, ev.y, 0x07030602u) & 0x01010101u));
         int8_t *out = D + (int64_t)16 * t.g;
-        const int lo = RAG ? max((int)t.p - 16 * k, 0) : 0, hi = RAG ? min((int)t.p + L - 16 * k, 16) : 16;
+        const int lo = max((int)t.p - 16 * k, 0), hi = min((int)t.p + L - 16 * k, 16);
         if (lo == 0 && hi == 16) {
             __builtin_memcpy(out, &w, 16);
         } else {
@@ -374,30 +361,39 @@ __global__ __launch_bounds__(kMaxThreads) void k_bands2d(KArgs a) {
 // Fills the rest of a shape from (rows, sweeps per launch, whole) and
 // estimates its time per sweep; false if it does not fit.
 bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even) {
-    const int K = pieces_of(L), halo = sh.whole ? 0 : 2 * sh.sweeps, R = sh.rows + 2 * halo;
-    const size_t lds = (size_t)R * pitch_of(L) + 2 * kPad;
-    if (lds > kMaxLdsBytes - 1024 || halo > L) return false;
+    const bool tiles = L % 16 == 0, cut = tiles && sh.words < L / 16;  // halo pieces beside the tile
+    const int halo = sh.rows >= L ? 0 : 2 * sh.sweeps, R = sh.rows + 2 * halo;
+    const int K = tiles ? sh.words + (cut ? 2 : 0) : pieces_of(L);
+    const size_t lds = tiles ? 8 * (size_t)R * K : (size_t)R * pitch_of(L) + 2 * kPad;
+    if (lds > kMaxLdsBytes - 1024 || halo > L || (cut && sh.sweeps > 8)) return false;
     const int launches = bands2d_launches(sh, n_sweeps, even);
     if (launches > n_sweeps) return false;
     const int64_t pieces = (int64_t)R * K;
     const int rounds = (int)((pieces + kMaxThreads - 1) / kMaxThreads);
     sh.threads = (int)std::max<int64_t>(64, ((pieces + rounds - 1) / rounds + 63) / 64 * 64);
+    if (tiles)  // whole rows of threads with 1, 2 or 4 words each, where they suffice
+        for (const int n : {4, 2, 1}) {
+            const int lanes = (R + n - 1) / n * K;
+            if (lanes <= kMaxThreads) sh.threads = (lanes + 63) / 64 * 64;
+        }
     if (sh.threads > kMaxThreads) sh.threads = kMaxThreads;
     if (sh.whole)
         if (const int tuned = small2d_threads(L, ea)) sh.threads = tuned;
     // Workgroups per compute unit, and how many run there at once.
-    const int64_t groups = (int64_t)n_rep * ((L + sh.rows - 1) / sh.rows);
+    const int64_t groups = (int64_t)n_rep * bands2d_groups(L, sh);
     const double per_cu = (double)((groups + 255) / 256);
     const double at_once = std::max(1.0, std::min({per_cu, (double)(kMaxLdsBytes / lds), 2048.0 / sh.threads}));
     // A half-sweep of one round takes about `latency` ns from barrier to barrier,
     // a busy compute unit updates a piece in about `piece` ns, a launch costs
     // about 3 us and its first loads and last stores 2 us more.  The shapes this
     // picks are within 7 % of the best measured over bands of 2 .. 128 rows and
-    // 1 .. 8 sweeps (edges 130 .. 3000, 1 .. 64 replicas), the 512^2 EA batch
-    // of 8 excepted (3.7 us for 3.1).
-    const double latency = (sh.threads >= pieces ? 450.0 : 550.0) * rounds, piece = ea ? 1.1 : 0.9;
+    // 1 .. 8 sweeps (edges 130 .. 3000, 1 .. 64 replicas) and tiles of 2 .. 256 rows and
+    // 1 .. 256 words (edges 64 .. 4096).
+    const double latency = (sh.threads >= pieces ? 450.0 : 550.0) * (tiles ? 0.75 : 1.0) * rounds;
+    // (a tile's words in registers, at most four per thread, or all of them in LDS)
+    const double piece = !tiles ? (ea ? 1.1 : 0.9) : (R + 3) / 4 * K <= sh.threads ? (ea ? 0.75 : 0.68) : ea ? 1.2 : 1.1;
     const double half = std::max(latency * per_cu / at_once, per_cu * (sh.rows + halo) * K * piece);
-    const double memory = per_cu * R * (double)L * (ea ? 4.0 : 2.0) / 20.0;
+    const double memory = per_cu * R * 16.0 * K * (ea ? 4.0 : 2.0) / 20.0;
     sh.ns_per_sweep = (5000.0 + memory) * launches / n_sweeps + 2.0 * half;
     return true;
 }
@@ -406,21 +402,37 @@ bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even)
 
 bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out) {
     BandShape best;
-    auto offer = [&](int rows, int sweeps, bool whole) {
+    const int all = L % 16 == 0 ? L / 16 : 0;  // pieces per row, where tiles are cut along rows
+    auto offer = [&](int rows, int words, int sweeps) {
         BandShape sh;
-        sh.rows = rows;
+        sh.rows = std::min(rows, L);
+        sh.words = words;
         sh.sweeps = sweeps;
-        sh.whole = whole;
+        sh.whole = rows >= L && words >= all;
         if (complete(sh, L, n_rep, ea, n_sweeps, even) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
     };
-    offer(L, std::min(n_sweeps, 256), true);
+    offer(L, all, std::min(n_sweeps, 256));
     for (int sweeps : {1, 2, 3, 4, 6, 8})
-        if (sweeps <= (even ? (n_sweeps + 1) / 2 : n_sweeps))
-            for (int rows = 2; rows < L; rows += rows < 16 ? 2 : rows < 64 ? 8 : 32) offer(rows, sweeps, false);
+        if (sweeps <= (even ? (n_sweeps + 1) / 2 : n_sweeps)) {
+            if (!all)
+                for (int rows = 2; rows < L; rows += rows < 16 ? 2 : rows < 64 ? 8 : 32) offer(rows, 0, sweeps);
+            // tiles: rows that give each compute unit 1, 2, 4 or 8 of them, and a few sizes
+            for (int parts = 1; parts <= all; ++parts) {
+                if (all % parts) continue;
+                for (int per_cu : {1, 2, 4, 8}) {
+                    const int strips = 256 * per_cu / std::min(256 * 8, n_rep * parts);
+                    if (strips > 0) offer(std::max(2, (L + strips - 1) / strips), all / parts, sweeps);
+                }
+                for (int rows : {32, 128})
+                    if (rows < L) offer(rows, all / parts, sweeps);
+            }
+        }
     const char *er = getenv("SPINMC_BANDS2D_ROWS"), *es = getenv("SPINMC_BANDS2D_SWEEPS");
+    const char *ew = getenv("SPINMC_BANDS2D_WORDS");
     if (er && es && atoi(er) > 0 && atoi(es) > 0) {
         best = BandShape{};
-        offer(std::min(atoi(er), L), std::min(atoi(es), std::max(1, n_sweeps)), atoi(er) >= L);
+        offer(std::min(atoi(er), L), ew && atoi(ew) > 0 ? std::min(atoi(ew), all) : all,
+              std::min(atoi(es), std::max(1, n_sweeps)));
     }
     *out = best;
     return best.rows > 0;
@@ -431,12 +443,15 @@ int bands2d_launches(const BandShape &sh, int n_sweeps, bool even) {
     return sh.whole || !even ? n : n + (n & 1);
 }
 
-int bands2d_groups(int L, const BandShape &sh) { return (L + sh.rows - 1) / sh.rows; }
+int bands2d_groups(int L, const BandShape &sh) {
+    return ((L + sh.rows - 1) / sh.rows) * (L % 16 == 0 ? (L / 16 + sh.words - 1) / sh.words : 1);
+}
 
 hipError_t launch_bands2d(const Bands2dArgs &b, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s) {
     if (sweeps < 1 || sh.rows < 1 || (!sh.whole && (sweeps > sh.sweeps || b.src == b.dst)) || b.L < 4 || b.L % 2 ||
         b.rep_per_sample < 1)
         return hipErrorInvalidValue;
+    if (b.L % 16 == 0) return launch_tiles2d(b, sh, sweeps, tally, s);
     KArgs a;
     a.b = b;
     a.tally = tally;
@@ -449,31 +464,18 @@ hipError_t launch_bands2d(const Bands2dArgs &b, const BandShape &sh, int sweeps,
     a.one2 = 0x00010001u;
     const int R = sh.rows + 2 * a.halo;
     const size_t lds = (size_t)R * a.pitch + 2 * kPad;
-    const bool one = (int64_t)R * a.K <= sh.threads, ea = b.coup != nullptr, rag = b.L % 16 != 0;
+    const bool one = (int64_t)R * a.K <= sh.threads, ea = b.coup != nullptr;
     const int64_t blocks = (int64_t)b.n_rep * a.bands;
     if (const char *why = launch_config_error((uint64_t)blocks, (uint64_t)sh.threads, lds))
         return reject_launch("k_bands2d", (uint64_t)blocks, (uint64_t)sh.threads, lds, why);
-#define SMC_BANDS(EE, RR, OO)                                                                                     \
-    if (ea == EE && rag == RR && one == OO) {                                                                     \
-        if (lds > 65536) {                                                                                        \
-            hipError_t e = hipFuncSetAttribute((const void *)k_bands2d<EE, RR, OO>,                               \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,                        \
-                                               (int)kMaxLdsBytes - 1024);                                         \
-            if (e != hipSuccess) return e;                                                                        \
-        }                                                                                                         \
-        SMC_LAUNCH((k_bands2d<EE, RR, OO>), dim3((unsigned)blocks), dim3(sh.threads), lds, s, a);                 \
-        return hipGetLastError();                                                                                 \
-    }
-    SMC_BANDS(false, false, false)
-    SMC_BANDS(false, false, true)
-    SMC_BANDS(false, true, false)
-    SMC_BANDS(false, true, true)
-    SMC_BANDS(true, false, false)
-    SMC_BANDS(true, false, true)
-    SMC_BANDS(true, true, false)
-    SMC_BANDS(true, true, true)
-#undef SMC_BANDS
-    return hipErrorInvalidValue;
+    void (*kernel)(KArgs) = ea ? (one ? k_bands2d<true, true> : k_bands2d<true, false>)
+                               : (one ? k_bands2d<false, true> : k_bands2d<false, false>);
+    if (lds > 65536)
+        if (hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)kMaxLdsBytes - 1024))
+            return e;
+    SMC_LAUNCH(kernel, dim3((unsigned)blocks), dim3(sh.threads), lds, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace smc

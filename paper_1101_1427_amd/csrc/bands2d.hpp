@@ -5,10 +5,11 @@
 
 namespace smc {
 
-// How a batch is cut: `rows` rows per workgroup (the whole lattice when
-// whole), `sweeps` sweeps per launch, `threads` per workgroup.
+// How a batch is cut: `rows` rows per workgroup and, of edges that are
+// multiples of 16 (tiles2d.hip), `words` pieces of 16 sites of them (the whole
+// lattice when whole), `sweeps` sweeps per launch, `threads` per workgroup.
 struct BandShape {
-    int rows = 0, sweeps = 0, threads = 0;
+    int rows = 0, words = 0, sweeps = 0, threads = 0;
     bool whole = false;
     double ns_per_sweep = 0.0;  // the model's estimate for the batch
 };
@@ -34,6 +35,8 @@ struct Bands2dArgs {
     int rng_shift;
     int n_rep, L;
 };
+// (edges that are multiples of 16 go on to launch_tiles2d)
 hipError_t launch_bands2d(const Bands2dArgs &a, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s);
+hipError_t launch_tiles2d(const Bands2dArgs &a, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s);
 
 }  // namespace smc

@@ -265,6 +265,7 @@ int tune_small2d(StreamCtx &c, hipStream_t s, int L, bool ea, int n_rep, Key key
     a.L = L;
     BandShape sh;
     sh.rows = L;
+    sh.words = L / 16;
     sh.sweeps = 16;
     sh.whole = true;
     int best = 0;

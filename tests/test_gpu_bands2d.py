@@ -46,6 +46,19 @@ def test_bands_against_oracle(monkeypatch, model, L, rows, per, n):
     assert np.array_equal(dE.cpu().numpy(), ref_dE)
 
 
+# (edge, rows and 16-site pieces per tile, sweeps per launch, sweeps): halo pieces that
+# repeat own ones, rows that wrap under cut columns, short last tiles
+TILES = [(16, 16, 1, 5, 5), (16, 4, 1, 2, 4), (32, 8, 1, 4, 8), (32, 32, 1, 8, 16), (48, 16, 2, 3, 6), (64, 20, 3, 8, 16),
+         (96, 40, 4, 6, 12), (112, 112, 2, 4, 8), (128, 2, 1, 8, 16), (208, 48, 5, 2, 4), (512, 128, 8, 2, 4)]
+
+
+@pytest.mark.parametrize("model", [S.ISING, S.EA])
+@pytest.mark.parametrize("L,rows,words,per,n", TILES)
+def test_tiles_against_oracle(monkeypatch, model, L, rows, words, per, n):
+    monkeypatch.setenv("SPINMC_BANDS2D_WORDS", str(words))
+    test_bands_against_oracle(monkeypatch, model, L, rows, per, n)
+
+
 @pytest.mark.parametrize("L,n_rep,n", [(200, 16, 40), (512, 2, 41), (1000, 3, 9)])
 def test_bands_chosen_shape_equals_half_sweeps(monkeypatch, L, n_rep, n):
     """The shape the library chooses against the half-sweep launches, over enough
