@@ -261,15 +261,12 @@ __global__ void k_pt_swap(SwapArgs a) {
     if (q >= a.n_chains || k + 1 >= n) return;
     const int base = a.beta_per_chain ? q * n : 0;
     int32_t *sot = a.slot_of_temp + (int64_t)q * n;
-    if (a.row_of_rep[q * n] < 0) return;  // not a permutation: chain left unchanged
     const int A = sot[k], B = sot[k + 1];
+    // (the draw while the loads are on their way)
+    const uint4 w = philox4x32_10(make_uint4((uint32_t)k, a.t, (uint32_t)q, 2 * kTagSwap), a.key);
+    if (a.row_of_rep[q * n] < 0) return;  // not a permutation: chain left unchanged
     const double x = (a.beta[base + k + 1] - a.beta[base + k]) * (double)(a.E[q * n + B] - a.E[q * n + A]);
-    bool accept = x >= 0.0;
-    if (!accept) {
-        const uint4 w = philox4x32_10(make_uint4((uint32_t)k, a.t, (uint32_t)q, 2 * kTagSwap), a.key);
-        accept = unit53(w.x, w.y) < exp(x);
-    }
-    if (accept) {
+    if (x >= 0.0 || below_exp(unit53(w.x, w.y), x)) {
         sot[k] = B;
         sot[k + 1] = A;
         a.row_of_rep[q * n + B] = base + k;

@@ -165,4 +165,21 @@ __device__ __forceinline__ double unit53(uint32_t w0, uint32_t w1) {
     return ((double)(w0 >> 5) * 67108864.0 + (double)(w1 >> 6)) * (1.0 / 9007199254740992.0);
 }
 
+// u < exp(x) for x < 0 (or not a number) and u a multiple of 2^-53 in [0, 1).  The
+// single-precision exponential decides where it can: its argument y = x log2(e) is off by
+// less than 3 2^-24 |y|, so that 2^y, for y > -64, is off by less than 1e-5 of itself with
+// the rounding of the instruction; below, exp(x) < 2^-53.  Everything else is decided in
+// double precision.
+__device__ __forceinline__ bool below_exp(double u, double x) {
+    const float y = (float)x * 1.44269504f;
+    const double e = (double)__builtin_amdgcn_exp2f(y);
+    if (y > -64.0f) {
+        if (u < e * (1.0 - 1e-4)) return true;
+        if (u > e * (1.0 + 1e-4)) return false;
+    } else if (u > 0.0 && y <= -64.0f) {
+        return false;
+    }
+    return u < exp(x);
+}
+
 }  // namespace smc

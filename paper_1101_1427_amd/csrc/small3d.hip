@@ -135,23 +135,6 @@ __device__ __forceinline__ uint2 packed_lut(const ThrRow &row) {
     return make_uint2(k.lo, k.hi);
 }
 
-// u < exp(x) for x < 0 (or not a number) and u a multiple of 2^-53 in [0, 1).  The
-// single-precision exponential decides where it can: its argument y = x log2(e) is off by
-// less than 3 2^-24 |y|, so that 2^y, for y > -64, is off by less than 1e-5 of itself with
-// the rounding of the instruction; below, exp(x) < 2^-53.  Everything else is decided in
-// double precision.
-__device__ __forceinline__ bool below_exp(double u, double x) {
-    const float y = (float)x * 1.44269504f;
-    const double e = (double)__builtin_amdgcn_exp2f(y);
-    if (y > -64.0f) {
-        if (u < e * (1.0 - 1e-4)) return true;
-        if (u > e * (1.0 + 1e-4)) return false;
-    } else if (u > 0.0 && y <= -64.0f) {
-        return false;
-    }
-    return u < exp(x);
-}
-
 template <bool EA, int LOG>
 __global__ __launch_bounds__(kMaxThreads, LOG ? 8 : 4) void k_small3d(KArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
