@@ -200,9 +200,9 @@ struct CallTally {
 // Uniform 2D batches run several sweeps per launch on bands of rows in LDS
 // where the estimate says that it is faster than two half-sweep launches per
 // sweep (measured: about 3.5 us and 1.2 fs per site each).  Edges that are
-// multiples of 16 are cut along their rows too (tiles2d.hip); of others a band needs
-// about 5 K bytes of LDS per row of 4 K sites, so large ones keep the half-sweeps.  So
-// does a call of one sweep unless the lattice fits in LDS as a whole.
+// multiples of 16 are cut along their rows too; others in bands of whole rows of half
+// a byte per site, of which large edges have too few in LDS, so they keep the
+// half-sweeps.  So does a call of one sweep unless the lattice fits in LDS as a whole.
 // SPINMC_BANDS2D=0 keeps the half-sweeps (same results), and so does
 // SPINMC_PT_SPLIT2D=0 in tempering (even is false there).
 bool use_bands2d(const smc_desc *d, const SweepArgs &a, int32_t n_sweeps, bool even, BandShape *sh) {

@@ -1,12 +1,12 @@
 // Sweeps of uniform 2D Ising / +-J EA batches of any even edge with bands of
-// rows in LDS, several sweeps per launch (bands2d.hip).
+// rows, or tiles, in LDS and several sweeps per launch (tiles2d.hip).
 #pragma once
 #include "internal.hpp"
 
 namespace smc {
 
 // How a batch is cut: `rows` rows per workgroup and, of edges that are
-// multiples of 16 (tiles2d.hip), `words` pieces of 16 sites of them (the whole
+// multiples of 16, `words` pieces of 16 sites of them (the whole
 // lattice when whole), `sweeps` sweeps per launch, `threads` per workgroup.
 struct BandShape {
     int rows = 0, words = 0, sweeps = 0, threads = 0;
@@ -18,6 +18,8 @@ struct BandShape {
 // fits in LDS.  even: see bands2d_launches.
 bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out);
 int bands2d_groups(int L, const BandShape &sh);  // workgroups per replica
+int bands2d_pieces(int L);                       // pieces per staged row
+size_t bands2d_lds(int cells);                   // bytes for so many staged pieces
 // Launches for n_sweeps sweeps; with even, an even number unless the shape is
 // whole, so that the result ends where it began (more than n_sweeps: the shape
 // does not serve the call).
@@ -35,8 +37,6 @@ struct Bands2dArgs {
     int rng_shift;
     int n_rep, L;
 };
-// (edges that are multiples of 16 go on to launch_tiles2d)
 hipError_t launch_bands2d(const Bands2dArgs &a, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s);
-hipError_t launch_tiles2d(const Bands2dArgs &a, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s);
 
 }  // namespace smc

@@ -1,29 +1,36 @@
-// Sweeps of uniform 2D Ising / +-J EA batches of edges that are multiples of 16,
-// several per launch (Eq. 2, Sec. 3.2): bands2d.hip's scheme on tiles.
+// Sweeps of uniform 2D Ising / +-J EA batches of any even edge, several per launch
+// (Eq. 2, Sec. 3.2).
 //
-// A workgroup owns a tile of rows and of 16-site pieces of them, and holds it in LDS
-// with 2 S halo rows above and below and a halo piece on either side for S <= 8
-// sweeps: half-sweep h updates the rows that are h + 1 or more from the staged edge,
-// and the sites of the halo pieces become wrong one per half-sweep from
-// outside, so after 2 S <= 16 half-sweeps the tile's own sites are final.  Halo sites are
-// recomputed by the neighbouring tiles with the same random numbers (every draw is
-// keyed by the site).  A tile of whole rows or columns wraps there in LDS and needs
-// no halo; a whole lattice runs all sweeps of a call in place.
+// A workgroup owns a tile of rows (and, where 16 divides the edge, of 16-site pieces
+// of them) and holds it in LDS with 2 S halo rows above and below and a halo piece on
+// either side for S sweeps: half-sweep h updates the rows that are h + 1 or more from
+// the staged edge, and the sites of the halo pieces become wrong one per half-sweep
+// from outside (so S <= 8 there); after 2 S half-sweeps the tile's own sites are final.
+// Halo sites are recomputed by the neighbouring tiles with the same random numbers
+// (every draw is keyed by the site), so tiles never exchange data within a launch;
+// launches alternate between two lattices.  A tile of whole rows or columns wraps
+// there in LDS and needs no halo; a whole lattice runs all sweeps of a call in place.
 //
-// Layout (halves.hpp): half a byte per site, the colours apart, a piece's eight
-// sites of a colour per word, so each neighbour of a Philox block is one word.
+// Layout (halves.hpp): half a byte per site, the colours apart, the eight sites of a
+// Philox block per word.  Where 16 divides the edge each neighbour of a block is one word.
+// Other rows start and end inside pieces that they share (RAG): each row holds its own
+// copy of those, masks what is not its own, shifts the rows beside it into place from two
+// words and takes the neighbour across its ends from the word that holds it.
 //
 // Bound: for small batches the latency of a half-sweep (Philox, LDS round trip,
 // barrier) and the launches, for large ones the VALU (about 105 instructions per
 // word).  bands2d_shape weighs them.
 //
 // A thread keeps one, two or four words of a column in registers for the whole launch
-// where the tile has at most 4096 (0.70 ns of a compute unit per word and half-sweep), and
-// reads three words per update; larger tiles are all in LDS (1.1 ns).  Against
-// bands of whole rows at a byte per site, per sweep: one 64^2 Ising lattice 0.88 -> 0.66 us,
-// 512^2 2.0 -> 1.3 (tiles of 32 rows x 2 words, 8 sweeps per launch), 1024^2 3.0 -> 1.7, 2048^2
-// 5.7 -> 3.2, 4096^2 EA 18.7 -> 11.9, 256 EA lattices of 256^2 10.9 -> 6.9, 64 of 208^2
-// 3.7 -> 2.5.
+// where the tile has at most 4096 (RAG: 2048), 0.70 ns of a compute unit per word and
+// half-sweep, and reads three words per update; larger tiles are all in LDS (1.1 ns).
+// Against bands of whole rows at a byte per site, per sweep: one 64^2 Ising lattice 0.88 ->
+// 0.65 us, 512^2 2.0 -> 1.3 (tiles of 32 rows x 2 words, 8 sweeps per launch), 1024^2 3.0 -> 1.7,
+// 2048^2 5.7 -> 3.3, 4096^2 EA 18.7 -> 11.9, 256 EA lattices of 256^2 10.9 -> 6.9, 64 of
+// 200^2 4.9 -> 3.3, 16 of 500^2 6.1 -> 4.2, 20 Ising lattices of 106^2 1.87 -> 1.54, 16 of
+// 1000^2 16.0 -> 14.8 (two half-sweep launches: 28.5), eight of 1502^2 17.0 -> 17.4.
+#include <stdlib.h>
+
 #include <algorithm>
 
 #include "bands2d.hpp"
@@ -38,10 +45,12 @@ using namespace halves;
 
 constexpr int kMaxThreads = 1024;
 
+constexpr int kPad = 4;  // words before and after the staged tile (reads beside the first and last row)
+
 struct KArgs {
     Bands2dArgs b;
     Tally tally;
-    int K;                 // pieces per row of the lattice
+    int K;                 // pieces per row of the lattice (RAG: that a row may touch)
     int words, W;          // pieces per row of a tile: its own, staged
     int rows, halo, side;  // own rows, halo rows on either side, halo pieces (0 or 1)
     int xtiles, tiles;     // tiles per row of tiles and per replica
@@ -50,7 +59,40 @@ struct KArgs {
     uint32_t one2;         // 0x00010001, opaque to the compiler
 };
 
-template <bool EA>
+// A cell of the staged tile.
+struct Cell {
+    int row, k;      // staged
+    int y;           // lattice row
+    uint32_t g;      // Philox block
+    bool mine;       // of the tile itself
+};
+
+// RAG: where the sites of row y lie in its words and in those of the rows beside it.
+// Pair x of the row is half-byte first + x of its words, counted from word 0.
+struct Ragged {
+    int first, last;   // the first and the last pair
+    int up, down;      // how much later a pair lies in the rows y + 1 and y - 1
+    __device__ __forceinline__ Ragged(int y, int L) {
+        const int Lh = L / 2;
+        first = (y * Lh) & 7;
+        last = first + Lh - 1;
+        up = (y == L - 1 ? 0 : (first + Lh) & 7) - first;
+        down = (y == 0 ? ((L - 1) * Lh) & 7 : (first - Lh) & 7) - first;
+    }
+    // Mask of the row's pairs in its word k.
+    __device__ __forceinline__ uint32_t in(int k) const {
+        const int lo = max(first - 8 * k, 0), n = min(last + 1 - 8 * k, 8) - lo;
+        return n > 0 ? (~0u >> (32 - 4 * n)) << (4 * lo) : 0u;
+    }
+};
+
+// The eight half-bytes d later than word p (-7 .. 7).
+__device__ __forceinline__ uint32_t later(const uint32_t *p, int d) {
+    const uint32_t *q = p + (d < 0 ? -1 : 0);
+    return __builtin_amdgcn_alignbit(q[1], q[0], 4u * ((uint32_t)d & 7u));
+}
+
+template <bool EA, bool RAG>
 struct Tile {
     const KArgs &a;
     uint32_t *T;     // colour 0, then colour 1
@@ -61,13 +103,28 @@ struct Tile {
     uint32_t cnt = 0, nsum = 0;
 
     // Colour-c sites of a staged word: own and par its words of colour c and of the
-    // other; returns the new own.
-    __device__ __forceinline__ uint32_t update(uint32_t own, uint32_t par, int cell, int up, int down, int next,
-                                               int prev, bool odd, uint32_t g, uint32_t c, uint32_t time,
-                                               const uint4 &w, bool mine) {
-        const uint32_t *other = T + (c ? 0 : cells) + cell;
-        const uint32_t yp = other[up], ym = other[down], beside = other[odd ? next : prev];
-        const uint32_t side = __builtin_amdgcn_alignbit(odd ? beside : par, odd ? par : beside, odd ? 4u : 28u);
+    // other; returns the new own.  up, down, next, prev: distances of the cells beside it.
+    __device__ __forceinline__ uint32_t update(uint32_t own, uint32_t par, const Cell &at, int up, int down, int next,
+                                               int prev, uint32_t c, uint32_t time, const uint4 &w) {
+        const bool odd = ((uint32_t)at.y & 1u) != c;  // own sites are the odd ones
+        const uint32_t *other = T + (c ? 0 : cells) + at.row * a.W + at.k;
+        uint32_t yp, ym, in = ~0u;
+        const uint32_t beside = other[odd ? next : prev];
+        uint32_t side = __builtin_amdgcn_alignbit(odd ? beside : par, odd ? par : beside, odd ? 4u : 28u);
+        if constexpr (RAG) {
+            const Ragged rg(at.y, a.b.L);
+            yp = later(other + up, rg.up);
+            ym = later(other + down, rg.down);
+            // the row's ends: the neighbour of the last pair is the first one, and the reverse
+            const int here = odd ? rg.last : rg.first, there = odd ? rg.first : rg.last;
+            const uint32_t wrap = other[(there >> 3) - at.k];
+            const uint32_t end = (here >> 3) == at.k ? 0xFu << (4 * (here & 7)) : 0u;
+            side = pick(end, __builtin_amdgcn_alignbit(wrap, wrap, 4u * ((uint32_t)(there - here) & 7u)), side);
+            in = rg.in(at.k);
+        } else {
+            yp = other[up];
+            ym = other[down];
+        }
         uint32_t n;  // unsatisfied bonds
         if constexpr (EA) {
             // bond of the pair itself: the even site's; of the side pair: the lower site's
@@ -84,28 +141,21 @@ struct Tile {
         o.F0 = decide4(o.n0, w.x, w.y, K3, a.one2, eq);
         o.F1 = decide4(o.n1, w.z, w.w, K3, a.one2, eq);
         if (__builtin_expect(__any(has_tie(eq)), 0))
-            exact_decisions(o, w, th, K3, 8u * g, c, time, rr, a.b.key, has_tie(eq));
-        const uint32_t f = flags_of(o.F0, o.F1);
+            exact_decisions(o, w, th, K3, 8u * at.g, c, time, rr, a.b.key, has_tie(eq));
+        uint32_t f = flags_of(o.F0, o.F1);
+        if constexpr (RAG) f &= in;
         // Delta E of a flip with n unsatisfied bonds is 4 (2 - n)
-        const uint32_t counted = mine ? f : 0u;
+        const uint32_t counted = at.mine ? f : 0u;
         cnt += (uint32_t)__builtin_popcount(counted);
         nsum = __builtin_amdgcn_udot8(n, counted, nsum, false);
         return own ^ f;
     }
 };
 
-// A cell of the staged tile.
-struct Cell {
-    int row, k;      // staged
-    int y;           // lattice row
-    uint32_t g;      // Philox block
-    bool mine;       // of the tile itself
-};
-
 // NI > 0: a thread keeps NI staged words of one column in registers for the whole launch
 // (the workgroup's threads are whole rows; with one word each, the draws of both
 // colours are made together at the start of a sweep).  NI = 0: any number, in LDS.
-template <bool EA, int NI>
+template <bool EA, bool RAG, int NI>
 __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ long long red[kMaxThreads / 64];
@@ -122,7 +172,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
     const int8_t *S = a.b.src + (int64_t)r * N;
     int8_t *D = a.b.dst + (int64_t)r * N;
     const int trow = a.b.row_of_rep ? a.b.row_of_rep[r] : r;
-    Tile<EA> t{a, smem, (a.rows + 2 * halo) * W};
+    Tile<EA, RAG> t{a, smem + kPad, (a.rows + 2 * halo) * W};
     t.rr = (uint32_t)r >> a.b.rng_shift;
     auto cell_of = [&](int row, int k) -> Cell {
         Cell c;
@@ -130,10 +180,15 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
         c.k = k;
         c.y = y_own - halo + row;
         c.y += c.y < 0 ? L : c.y >= L ? -L : 0;
-        int kx = k_own - side + k;
-        kx += kx < 0 ? K : kx >= K ? -K : 0;
-        c.g = (uint32_t)(c.y * K + kx);
-        c.mine = row >= halo && row < halo + own_rows && k >= side && k < side + own_words;
+        c.mine = row >= halo && row < halo + own_rows;
+        if constexpr (RAG) {
+            c.g = ((uint32_t)(c.y * (L / 2)) >> 3) + (uint32_t)k;
+        } else {
+            int kx = k_own - side + k;
+            kx += kx < 0 ? K : kx >= K ? -K : 0;
+            c.g = (uint32_t)(c.y * K + kx);
+            c.mine = c.mine && k >= side && k < side + own_words;
+        }
         return c;
     };
 
@@ -164,10 +219,11 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
                 const Cell c = cell_of(row, k);
                 const int64_t i = 16 * (int64_t)c.g;
                 at[b] = 2 * (row * W + k) + (c.y & 1);
-                v[b] = load16_any(S + i);
+                // (RAG: the last piece may run over the lattice's end, and one past it hold nothing)
+                v[b] = RAG ? load_inside<int64_t>(S, i, N) : load16_any(S + i);
                 if constexpr (EA) {
-                    j[b][0] = load16_any(J + i);
-                    j[b][1] = load16_any(J + N + i);
+                    j[b][0] = RAG ? load_inside<int64_t>(J, i, N) : load16_any(J + i);
+                    j[b][1] = RAG ? load_inside<int64_t>(J + N, i, N) : load16_any(J + N + i);
                 }
             }
             advance(row, k);
@@ -175,6 +231,17 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
 #pragma unroll
         for (int b = 0; b < kBatch; ++b)
             if (at[b] >= 0) {
+                if constexpr (RAG) {
+                    const int cell = at[b] >> 1, row = cell / W;
+                    const int64_t i = 16 * (int64_t)cell_of(row, cell - row * W).g;
+                    if (__builtin_expect(i > N - 16, 0)) {
+                        into_place<int64_t>(v[b], i, N);
+                        if constexpr (EA) {
+                            into_place<int64_t>(j[b][0], i, N);
+                            into_place<int64_t>(j[b][1], i, N);
+                        }
+                    }
+                }
                 const uint2 eo = words_of(v[b], j[b], EA ? 2 : 0);
                 const uint32_t c0 = (at[b] & 1) ? eo.y : eo.x, c1 = (at[b] & 1) ? eo.x : eo.y;
                 t.T[at[b] >> 1] = c0;
@@ -226,9 +293,8 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
                             w = both[col];
                         else
                             w = philox4x32_10(make_uint4(c[b].g, time, t.rr, 2 * kTagHead + (uint32_t)col), a.b.key);
-                        mine[b][col] = t.update(mine[b][col], mine[b][1 - col], cell, up, down, next, prev,
-                                                ((uint32_t)c[b].y & 1u) != (uint32_t)col, c[b].g, (uint32_t)col, time, w,
-                                                c[b].mine);
+                        mine[b][col] = t.update(mine[b][col], mine[b][1 - col], c[b], up, down, next, prev, (uint32_t)col,
+                                                time, w);
                         t.T[cell + (col ? t.cells : 0)] = mine[b][col];
                     }
                     __syncthreads();
@@ -249,8 +315,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
                         const uint4 w = philox4x32_10(make_uint4(c.g, time, t.rr, 2 * kTagHead + col), a.b.key);
                         uint32_t *own = t.T + cell + (col ? t.cells : 0);
                         const uint32_t par = t.T[cell + (col ? 0 : t.cells)];
-                        *own = t.update(*own, par, cell, up, down, next, prev, ((uint32_t)c.y & 1u) != col, c.g, col, time,
-                                        w, c.mine);
+                        *own = t.update(*own, par, c, up, down, next, prev, col, time, w);
                     }
                     __syncthreads();
                 }
@@ -264,7 +329,23 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
         if (!c.mine) continue;
         const uint32_t c0 = t.T[row * W + k], c1 = t.T[row * W + k + t.cells];
         const uint4 w = (c.y & 1) ? spins_of(c1, c0) : spins_of(c0, c1);
-        __builtin_memcpy(D + 16 * (int64_t)c.g, &w, 16);
+        int8_t *out = D + 16 * (int64_t)c.g;
+        if constexpr (RAG) {
+            const uint32_t in = Ragged(c.y, L).in(k);
+            if (in == ~0u) {
+                __builtin_memcpy(out, &w, 16);
+            } else {
+                // the row's part of a shared piece, two sites at a time
+                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const uint16_t two = (uint16_t)(ws[p >> 1] >> (16 * (p & 1)));
+                    if ((in >> (4 * p)) & 1u) __builtin_memcpy(out + 2 * p, &two, 2);
+                }
+            }
+        } else {
+            __builtin_memcpy(out, &w, 16);
+        }
     }
     if (tally_wanted(a.tally)) {
         long long v = 2ll * (long long)t.cnt - (long long)t.nsum;
@@ -280,32 +361,128 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
     }
 }
 
+// Fills the rest of a shape from (rows, sweeps per launch, whole) and
+// estimates its time per sweep; false if it does not fit.
+bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even) {
+    const bool rag = L % 16 != 0, cut = !rag && sh.words < L / 16;  // cut: halo pieces beside the tile
+    const int halo = sh.rows >= L ? 0 : 2 * sh.sweeps, R = sh.rows + 2 * halo;
+    const int K = rag ? bands2d_pieces(L) : sh.words + (cut ? 2 : 0);
+    if ((int64_t)R * K > (int64_t)kMaxLdsBytes) return false;
+    const size_t lds = bands2d_lds(R * K);
+    if (lds > kMaxLdsBytes - 1024 || halo > L || (cut && sh.sweeps > 8)) return false;
+    const int launches = bands2d_launches(sh, n_sweeps, even);
+    if (launches > n_sweeps) return false;
+    const int64_t pieces = (int64_t)R * K;
+    const int rounds = (int)((pieces + kMaxThreads - 1) / kMaxThreads);
+    sh.threads = (int)std::max<int64_t>(64, ((pieces + rounds - 1) / rounds + 63) / 64 * 64);
+    // whole rows of threads with 1, 2 or 4 words each, where they suffice (4 of rows that
+    // share pieces do not fit in the registers)
+    const int most = rag ? 2 : 4;
+    for (int n = most; n > 0; n /= 2) {
+        const int lanes = (R + n - 1) / n * K;
+        if (lanes <= kMaxThreads) sh.threads = (lanes + 63) / 64 * 64;
+    }
+    if (sh.threads > kMaxThreads) sh.threads = kMaxThreads;
+    if (sh.whole)
+        if (const int tuned = small2d_threads(L, ea)) sh.threads = tuned;
+    // Workgroups per compute unit, and how many run there at once.
+    const int64_t groups = (int64_t)n_rep * bands2d_groups(L, sh);
+    const double per_cu = (double)((groups + 255) / 256);
+    const double at_once = std::max(1.0, std::min({per_cu, (double)(kMaxLdsBytes / lds), 2048.0 / sh.threads}));
+    // A half-sweep of one round takes about `latency` ns from barrier to barrier,
+    // a busy compute unit updates a piece in about `piece` ns, a launch costs
+    // about 3 us and its first loads and last stores 2 us more.  The shapes this
+    // picks are within 7 % of the best measured over bands of 2 .. 128 rows and
+    // 1 .. 8 sweeps (edges 130 .. 3000, 1 .. 64 replicas) and tiles of 2 .. 256 rows and
+    // 1 .. 256 words (edges 64 .. 4096).
+    const double latency = (sh.threads >= pieces ? 340.0 : 410.0) * (rag ? 1.2 : 1.0) * rounds;
+    // (a tile's words in registers, at most four per thread, or all of them in LDS)
+    const bool kept = (R + most - 1) / most * K <= sh.threads;
+    const double piece = (kept ? (ea ? 0.75 : 0.68) : ea ? 1.2 : 1.1) * (rag ? 1.2 : 1.0);
+    const double half = std::max(latency * per_cu / at_once, per_cu * (sh.rows + halo) * K * piece);
+    const double memory = per_cu * R * 16.0 * K * (ea ? 4.0 : 2.0) / 20.0;
+    sh.ns_per_sweep = (5000.0 + memory) * launches / n_sweeps + 2.0 * half;
+    return true;
+}
+
 }  // namespace
 
-hipError_t launch_tiles2d(const Bands2dArgs &b, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s) {
+// Pieces of 16 sites that a staged row has: where 16 does not divide the edge a row may
+// share its first and its last one with others.
+int bands2d_pieces(int L) { return L % 16 == 0 ? L / 16 : (L + 14 + 15) / 16; }
+size_t bands2d_lds(int cells) { return 8 * (size_t)cells + 8 * kPad; }
+
+bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out) {
+    BandShape best;
+    const int all = L % 16 == 0 ? L / 16 : 0;  // pieces per row, where tiles are cut along rows
+    auto offer = [&](int rows, int words, int sweeps) {
+        BandShape sh;
+        sh.rows = std::min(rows, L);
+        sh.words = words;
+        sh.sweeps = sweeps;
+        sh.whole = rows >= L && words >= all;
+        if (complete(sh, L, n_rep, ea, n_sweeps, even) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
+    };
+    offer(L, all, std::min(n_sweeps, 256));
+    for (int sweeps : {1, 2, 3, 4, 5, 6, 8}) {
+        if (sweeps > (even ? (n_sweeps + 1) / 2 : n_sweeps)) continue;
+        // rows that give each compute unit 1, 2, 4 or 8 tiles, and a few sizes
+        for (int parts = 1; parts <= std::max(all, 1); ++parts) {
+            if (all && all % parts) continue;
+            const int words = all / parts;
+            for (int per_cu : {1, 2, 4, 8}) {
+                const int strips = 256 * per_cu / std::min(256 * 8, n_rep * parts);
+                if (strips > 0) offer(std::max(2, (L + strips - 1) / strips), words, sweeps);
+            }
+            for (int rows : {8, 16, 32, 64, 128})
+                if (rows < L && (!all || rows == 32 || rows == 128)) offer(rows, words, sweeps);
+        }
+    }
+    const char *er = getenv("SPINMC_BANDS2D_ROWS"), *es = getenv("SPINMC_BANDS2D_SWEEPS");
+    const char *ew = getenv("SPINMC_BANDS2D_WORDS");
+    if (er && es && atoi(er) > 0 && atoi(es) > 0) {
+        best = BandShape{};
+        offer(std::min(atoi(er), L), ew && atoi(ew) > 0 ? std::min(atoi(ew), all) : all,
+              std::min(atoi(es), std::max(1, n_sweeps)));
+    }
+    *out = best;
+    return best.rows > 0;
+}
+
+int bands2d_launches(const BandShape &sh, int n_sweeps, bool even) {
+    const int n = (n_sweeps + sh.sweeps - 1) / sh.sweeps;
+    return sh.whole || !even ? n : n + (n & 1);
+}
+
+int bands2d_groups(int L, const BandShape &sh) {
+    return ((L + sh.rows - 1) / sh.rows) * (L % 16 == 0 ? (L / 16 + sh.words - 1) / sh.words : 1);
+}
+
+hipError_t launch_bands2d(const Bands2dArgs &b, const BandShape &sh, int sweeps, const Tally &tally, hipStream_t s) {
+    const bool rag = b.L % 16 != 0, ea = b.coup != nullptr;
     KArgs a;
     a.b = b;
     a.tally = tally;
-    a.K = b.L / 16;
-    a.words = sh.words;
-    a.side = sh.words < a.K ? 1 : 0;
-    a.W = sh.words + 2 * a.side;
+    a.K = bands2d_pieces(b.L);
+    a.words = rag ? a.K : sh.words;
+    a.side = a.words < a.K ? 1 : 0;
+    a.W = a.words + 2 * a.side;
     a.rows = sh.rows;
     a.halo = sh.rows < b.L ? 2 * sweeps : 0;
-    a.xtiles = (a.K + sh.words - 1) / sh.words;
+    if (sweeps < 1 || sh.rows < 1 || sh.rows > b.L || (!sh.whole && (sweeps > sh.sweeps || b.src == b.dst)) || b.L < 4 ||
+        b.L % 2 || b.rep_per_sample < 1 || a.words < 1 || a.words > a.K || a.halo > b.L || (a.side && sweeps > 8))
+        return hipErrorInvalidValue;
+    a.xtiles = (a.K + a.words - 1) / a.words;
     a.tiles = bands2d_groups(b.L, sh);
     a.sweeps = sweeps;
     a.one2 = 0x00010001u;
-    if (b.L % 16 || sh.words < 1 || sh.words > a.K || sh.rows > b.L || a.halo > b.L || (a.side && sweeps > 8))
-        return hipErrorInvalidValue;
-    const int cells = (sh.rows + 2 * a.halo) * a.W;
-    const size_t lds = 8 * (size_t)cells;
-    const bool ea = b.coup != nullptr;
+    const int R = sh.rows + 2 * a.halo;
+    const size_t lds = bands2d_lds(R * a.W);
     // as few words per thread as the threads allow, in whole rows
     int per = 0;
     a.lanes = sh.threads;
-    for (const int n : {4, 2, 1}) {
-        const int lanes = (sh.rows + 2 * a.halo + n - 1) / n * a.W;
+    for (int n = rag ? 2 : 4; n > 0; n /= 2) {
+        const int lanes = (R + n - 1) / n * a.W;
         if (lanes > sh.threads) break;
         per = n;
         a.lanes = lanes;
@@ -313,17 +490,26 @@ hipError_t launch_tiles2d(const Bands2dArgs &b, const BandShape &sh, int sweeps,
     const int64_t blocks = (int64_t)b.n_rep * a.tiles;
     if (const char *why = launch_config_error((uint64_t)blocks, (uint64_t)sh.threads, lds))
         return reject_launch("k_tiles2d", (uint64_t)blocks, (uint64_t)sh.threads, lds, why);
-    using Kernel = void (*)(KArgs);
-    const Kernel kernel = per == 1   ? (ea ? k_tiles2d<true, 1> : k_tiles2d<false, 1>)
-                          : per == 2 ? (ea ? k_tiles2d<true, 2> : k_tiles2d<false, 2>)
-                          : per == 4 ? (ea ? k_tiles2d<true, 4> : k_tiles2d<false, 4>)
-                                     : (ea ? k_tiles2d<true, 0> : k_tiles2d<false, 0>);
-    if (lds > 65536)
-        if (hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)kMaxLdsBytes - 1024))
-            return e;
-    SMC_LAUNCH(kernel, dim3((unsigned)blocks), dim3(sh.threads), lds, s, a);
-    return hipGetLastError();
+#define SMC_TILES(EE, RR, NN)                                                                     \
+    if (ea == EE && rag == RR && per == NN) {                                                     \
+        if (lds > 65536)                                                                          \
+            if (hipError_t e = hipFuncSetAttribute((const void *)k_tiles2d<EE, RR, NN>,           \
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize,    \
+                                                   (int)kMaxLdsBytes - 1024))                     \
+                return e;                                                                         \
+        SMC_LAUNCH((k_tiles2d<EE, RR, NN>), dim3((unsigned)blocks), dim3(sh.threads), lds, s, a); \
+        return hipGetLastError();                                                                 \
+    }
+#define SMC_TILES_NI(EE, RR) SMC_TILES(EE, RR, 0) SMC_TILES(EE, RR, 1) SMC_TILES(EE, RR, 2)
+    SMC_TILES_NI(false, false)
+    SMC_TILES_NI(false, true)
+    SMC_TILES_NI(true, false)
+    SMC_TILES_NI(true, true)
+    SMC_TILES(false, false, 4)
+    SMC_TILES(true, false, 4)
+#undef SMC_TILES_NI
+#undef SMC_TILES
+    return hipErrorInvalidValue;
 }
 
 }  // namespace smc
