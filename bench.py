@@ -42,6 +42,10 @@ KERNEL_SOURCES = {
 }
 
 
+# names of the path kernels in traces and counters, where they differ from the plans' names
+TRACE_NAMES = {"k_pt3d_chain": "k_small3d", "k_uneven2d_sweep": "k_bins2d"}
+
+
 def kernel_source_hash(kernel: str = "k_ising2d_split") -> str:
     """sha256 over the sources a sweep kernel is compiled from."""
     import hashlib
@@ -102,6 +106,7 @@ def kt_summary(db: str, log: str, kernel: str, L: int, command: str):
     bench line the same run printed; written next to the traffic summary."""
     import sqlite3
 
+    plan_name = kernel
     con = sqlite3.connect(db)
     rows = con.execute("select name, total_calls, total_duration, average, percentage from top_kernels").fetchall()
     bench_line = ""
@@ -116,6 +121,7 @@ def kt_summary(db: str, log: str, kernel: str, L: int, command: str):
              f"{'kernel':40s} {'calls':>7s} {'total_us':>12s} {'avg_us':>10s} {'pct':>7s}"]
     for name, calls, total, avg, pct in rows:
         lines.append(f"{short_name(name):40s} {calls:7d} {total:12.1f} {avg:10.3f} {pct:7.2f}")
+    kernel = TRACE_NAMES.get(kernel, kernel)
     # the same run times the batched launch and then single-lattice launches:
     # the kernel's dispatches per grid size, from the kernels view
     lines.append(f"# {kernel} per grid size (work-items): dispatches, mean duration in microseconds")
@@ -135,8 +141,8 @@ def kt_summary(db: str, log: str, kernel: str, L: int, command: str):
         import json
 
         d = json.loads(bench_line)
-        if kernel in ("k_pt3d_chain", "k_uneven2d_sweep"):
-            t = d.get("tempering", {}).get("ea3d_L16" if kernel == "k_pt3d_chain" else "ea2d_uneven", {})
+        if kernel in TRACE_NAMES.values():
+            t = d.get("tempering", {}).get("ea3d_L16" if kernel == "k_small3d" else "ea2d_uneven", {})
             for key in ("steps", "ms", "replica_sweeps_per_s", "speedup_vs_per_instance"):
                 if key in t:
                     lines.append(f"bench_line_{key}: {t[key]}")
@@ -146,7 +152,7 @@ def kt_summary(db: str, log: str, kernel: str, L: int, command: str):
             lines.append(f"bench_line_roofline_frac: {r['frac']}")
             lines.append(f"bench_line_ns_per_flip: {d['value']}")
     os.makedirs(PROFILES, exist_ok=True)
-    path = os.path.join(PROFILES, f"{kernel}_L{L}_kernel_trace.txt")
+    path = os.path.join(PROFILES, f"{plan_name}_L{L}_kernel_trace.txt")
     with open(path, "w") as fh:
         fh.write("\n".join(lines) + "\n")
     print("\n".join(lines))
@@ -200,9 +206,9 @@ def valu_summary(db: str, command: str):
              "# cu    = SQ_BUSY_CU_CYCLES / C",
              f"{'kernel':24s} {'disp':>5s} {'VALU_insts':>11s} {'gui_cycles':>11s} {'issue':>6s} {'dual':>6s} "
              f"{'busy':>6s} {'cu':>6s}"]
-    names = ("k_ising2d_split", "k_pt3d_chain", "k_uneven2d_sweep", "k_heis3d_tiled", "k_heis3d_half",
-             "k_ising3d_half", "k_ising3d_pass", "k_half_sweep_generic", "k_msc2d", "k_dcb2d_packed", "k_dcb2d",
-             "k_dcb3d", "k_heis_dcb2d", "k_philox_bench", "k_dcb_rng")
+    names = ("k_ising2d_split", "k_tiles2d", "k_small3d", "k_bins2d", "k_heis3d_tiled", "k_heis3d_half",
+             "k_pairs3d_half", "k_ising3d_half", "k_ising3d_pass", "k_pieces", "k_half_sweep_generic", "k_msc2d",
+             "k_dcb2d_packed", "k_dcb2d", "k_dcb3d", "k_heis_dcb2d", "k_philox_bench", "k_dcb_rng")
     for k in names:
         a = acc.get(k, {})
         if "SQ_INSTS_VALU" not in a or "GRBM_GUI_ACTIVE" not in a:

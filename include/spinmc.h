@@ -62,7 +62,7 @@
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place, or, for
- *   calls of three and more sweeps (Ising with L >= 512: six) and L >= 48, on
+ *   calls of three and more sweeps (Ising with L >= 512: six, and L < 1024) and L >= 48, on
  *   a library-held packed copy of half a byte per site (two launches per sweep),
  *   and with L = 16 or 32 on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
