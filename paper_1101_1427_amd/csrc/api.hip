@@ -85,19 +85,50 @@ int run_uneven2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, void *spins,
     a.inst = (const smc_inst *)ip;
     a.bins = (const Bin2d *)bp;
     a.work = (const int32_t *)wp;
-    a.row_of_rep = sw.row_of_rep;
     a.thr = thr;
-    a.E = sw.E;
+    a.n_temps = sw.n_temps;
+    a.beta_per_chain = sw.beta_per_chain;
+    a.beta = sw.beta;
+    a.acc = sw.acc;
     a.key = make_key(desc->seed);
     a.sweeps = m;
+    // the chains' state twice: a launch reads one and writes the other
+    const size_t n_rep = (size_t)desc->n_rep;
+    void *ep = nullptr, *rp = nullptr;
+    if ((rc = ensure(c, kEnergy64, 2 * sizeof(int64_t) * n_rep, &ep))) return rc;
+    if ((rc = ensure(c, kRows, 3 * sizeof(int32_t) * n_rep, &rp))) return rc;
+    int32_t *const caller = sw.slot_of_temp;
+    int64_t *E[2] = {(int64_t *)ep, (int64_t *)ep + n_rep};
+    int32_t *row[2] = {(int32_t *)rp, (int32_t *)rp + n_rep}, *slot[2] = {caller, (int32_t *)rp + 2 * n_rep};
+    int e = 0, p = 0;  // the current ones
+    const bool fused = bins.size() <= kBinsAtOnce;  // exchange rounds at the start of the next step's launch
+    auto round = [&](uint32_t t) {
+        sw.E = E[e];
+        sw.row_of_rep = row[p];
+        sw.slot_of_temp = slot[p];
+        sw.t = t;
+        return launch_pt_swap(sw, s);
+    };
+    sw.E = E[0];
+    sw.row_of_rep = row[0];
     SMC_HIP(launch_pt_prepare(sw, energy, s));
     for (int32_t k = 0; k < n_steps; ++k) {
-        sw.t = (uint32_t)(step0 + (uint64_t)k);
-        a.t = sw.t * (uint32_t)m;
+        const uint32_t t = (uint32_t)(step0 + (uint64_t)k);
+        a.t = t * (uint32_t)m;
+        a.swap = fused && k > 0 ? 1 : 0;
+        a.swap_t = t - 1u;
+        a.row_in = row[p];
+        a.slot_in = slot[p];
+        a.row_out = row[1 - p];
+        a.slot_out = slot[1 - p];
+        a.E_in = E[e];
+        a.E_out = E[1 - e];
         SMC_HIP(launch_bins2d(a, (int)bins.size(), lds, !pp || k == 0, !pp || k == n_steps - 1, s));
-        SMC_HIP(launch_pt_swap(sw, s));
+        e = 1 - e;
+        if (a.swap) p = 1 - p;
+        if (!fused || k == n_steps - 1) SMC_HIP(round(t));
     }
-    SMC_HIP(launch_pt_finish(sw, energy, s));
+    SMC_HIP(launch_pt_finish(sw, energy, s, p ? caller : nullptr));
     return SMC_OK;
 }
 

@@ -21,10 +21,16 @@
 //
 // Bound: VALU (about 0.45 ps per update at full issue), then the HBM traffic
 // of 1 B per site and step.
-// 256 chains of 16 temperatures, edges 32 .. 256 (77.6e6 sites): 61 us per step
-// (0.78 ps per update) and 5 us for the exchange round; a launch per edge in a
-// graph with couplings read from global memory took about 85 us, and 2 ms per
-// call to build the graph for arrays it had not met.
+// 256 chains of 16 temperatures, edges 32 .. 256 (77.6e6 sites): 53 us per step
+// (0.68 ps per update) and 4 us for the exchange round (a byte per two sites: 61);
+// a launch per edge in a graph with couplings read from global memory took about 85 us,
+// and 2 ms per call to build the graph for arrays it had not met.
+//
+// Batches of up to kBinsAtOnce bins, all resident at once, make the exchange round of a step at
+// the start of the next launch (SWAP), each replica for its own pair, instead of in a
+// launch of its own: 16 temperatures of one 64^2 chain 8.3 -> 7.0 us per step, of 64 chains
+// of 128^2 21.2 -> 19.5. In larger batches the round's four dependent loads stand before
+// the sweeps of every workgroup that follows: 57 -> 58 us in the batch above.
 #include "bins2d.hpp"
 
 #include <algorithm>
@@ -126,7 +132,36 @@ struct Walk {
     }
 };
 
-template <bool EA>
+// The threshold row of replica r after the exchange round: its pair's decision, which
+// both replicas of the pair make alike from the state before it, and its entries of the
+// state after it.
+__device__ __forceinline__ int exchanged_row(const Bins2dArgs &a, int r, int row) {
+#pragma clang fp contract(off)
+    const int n = a.n_temps, q = r / n, s = r - q * n, base = a.beta_per_chain ? q * n : 0;
+    const int32_t *slot = a.slot_in + (int64_t)q * n;
+    if (row < 0) {
+        a.slot_out[r] = slot[s];
+    } else {
+        const int k = row - base, other = ((uint32_t)k ^ a.swap_t) & 1u ? k - 1 : k + 1;
+        int now = k;
+        if (other >= 0 && other < n) {
+            const int lo = min(k, other), t = slot[other], A = lo == k ? s : t, B = lo == k ? t : s;
+            const uint4 w = philox4x32_10(make_uint4((uint32_t)lo, a.swap_t, (uint32_t)q, 2 * kTagSwap), a.key);
+            const double x = (a.beta[base + lo + 1] - a.beta[base + lo]) *
+                             (double)(a.E_in[(int64_t)q * n + B] - a.E_in[(int64_t)q * n + A]);
+            if (x >= 0.0 || below_exp(unit53(w.x, w.y), x)) {
+                now = other;
+                if (lo == k && a.acc) a.acc[(int64_t)q * (n - 1) + k] += 1ull;
+            }
+        }
+        a.slot_out[(int64_t)q * n + now] = s;
+        row = base + now;
+    }
+    a.row_out[r] = row;
+    return row;
+}
+
+template <bool EA, bool SWAP>
 __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in, int raw_out, uint32_t one2) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ RepRow tab[kBinReps];
@@ -139,7 +174,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
     if (tid < reps) {
         RepRow t;
         t.r = a.work[bin.first + tid];
-        t.row = a.row_of_rep[t.r];
+        t.row = a.row_in[t.r];
+        if constexpr (SWAP) t.row = exchanged_row(a, t.r, t.row);
         const ThrRow th = table2d(a.thr[t.row < 0 ? 0 : t.row]);
         const Lut3 K = lut_of(th);
         t.lut = make_uint2(K.lo, K.hi);
@@ -248,7 +284,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
         for (int i = tid; i < n; i += kThreads) dst[i] = src[i];
     }
     __syncthreads();
-    if (tid < reps && dE[tid] != 0) a.E[tab[tid].r] += 4ll * dE[tid];
+    if (tid < reps) a.E_out[tab[tid].r] = a.E_in[tab[tid].r] + 4ll * dE[tid];
 }
 
 }  // namespace
@@ -296,19 +332,12 @@ double bins2d_ns(int L, int n_rep) {
 hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_in, bool raw_out, hipStream_t s) {
     if (a.sweeps < 1 || ((!raw_in || !raw_out) && !a.packed)) return hipErrorInvalidValue;
     const uint32_t one2 = 0x00010001u;
-    if (a.coup) {
-        if (lds > 60000)
-            (void)hipFuncSetAttribute((const void *)k_bins2d<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)kBinBytes);
-        SMC_LAUNCH(k_bins2d<true>, dim3((unsigned)n_bins), dim3(kThreads), lds, s, a, raw_in ? 1 : 0, raw_out ? 1 : 0,
-                   one2);
-    } else {
-        if (lds > 60000)
-            (void)hipFuncSetAttribute((const void *)k_bins2d<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)kBinBytes);
-        SMC_LAUNCH(k_bins2d<false>, dim3((unsigned)n_bins), dim3(kThreads), lds, s, a, raw_in ? 1 : 0, raw_out ? 1 : 0,
-                   one2);
-    }
+    using Kernel = void (*)(Bins2dArgs, int, int, uint32_t);
+    const Kernel kernel = a.coup ? (a.swap ? k_bins2d<true, true> : k_bins2d<true, false>)
+                                 : (a.swap ? k_bins2d<false, true> : k_bins2d<false, false>);
+    if (lds > 60000)
+        (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinBytes);
+    SMC_LAUNCH(kernel, dim3((unsigned)n_bins), dim3(kThreads), lds, s, a, raw_in ? 1 : 0, raw_out ? 1 : 0, one2);
     return hipGetLastError();
 }
 

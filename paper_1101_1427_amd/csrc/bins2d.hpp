@@ -10,6 +10,9 @@ namespace smc {
 // Edges that the bins serve.
 inline bool uneven2d_edge_supported(int L) { return L >= 16 && L <= 256 && L % 16 == 0; }
 
+// Bins that are resident at once (four workgroups per compute unit).
+constexpr int kBinsAtOnce = 1024;
+
 // Up to kBinReps replicas of one edge that a workgroup sweeps together.
 constexpr int kBinReps = 64;
 struct Bin2d {
@@ -27,9 +30,20 @@ struct Bins2dArgs {
     const smc_inst *inst;      // device [n_rep]
     const Bin2d *bins;
     const int32_t *work;
-    const int32_t *row_of_rep; // threshold row per replica; -1 leaves the replica unchanged
     const ThrRow *thr;
-    int64_t *E;                // tracked energy per replica
+    // The state of the chains before the launch and after it: threshold row per replica (-1
+    // leaves the chain unchanged), slot per temperature, tracked energy per replica.  The
+    // workgroups read the one and write the other.
+    const int32_t *row_in, *slot_in;
+    int32_t *row_out, *slot_out;  // with `swap` only
+    const int64_t *E_in;
+    int64_t *E_out;
+    // With `swap` the exchange round of step swap_t comes before the sweeps.
+    int swap;
+    uint32_t swap_t;
+    int n_temps, beta_per_chain;
+    const double *beta;
+    unsigned long long *acc;      // [n_chains][n_temps - 1] or nullptr
     Key key;
     uint32_t t;                // first sweep
     int sweeps;

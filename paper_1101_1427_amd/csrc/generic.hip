@@ -275,10 +275,11 @@ __global__ void k_pt_swap(SwapArgs a) {
     }
 }
 
-__global__ void k_pt_finish(SwapArgs a, double *energy_out) {
+__global__ void k_pt_finish(SwapArgs a, double *energy_out, int32_t *slots_out) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= a.n_chains * a.n_temps) return;
     energy_out[r] = (double)a.E[r];
+    if (slots_out) slots_out[r] = a.slot_of_temp[r];
 }
 
 int64_t sites_of(int dim, int L) { return dim == 3 ? (int64_t)L * L * L : (int64_t)L * L; }
@@ -353,9 +354,9 @@ hipError_t launch_pt_swap(const SwapArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s) {
+hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s, int32_t *slots_out) {
     const int n = a.n_chains * a.n_temps;
-    SMC_LAUNCH(k_pt_finish, dim3((n + 255) / 256), dim3(256), 0, s, a, energy_out);
+    SMC_LAUNCH(k_pt_finish, dim3((n + 255) / 256), dim3(256), 0, s, a, energy_out, slots_out);
     return hipGetLastError();
 }
 

@@ -196,7 +196,8 @@ size_t measure_scratch_bytes(const Batch &b, int max_L);
 // Parallel tempering helpers.
 hipError_t launch_pt_prepare(const SwapArgs &a, const double *energy_in, hipStream_t s);
 hipError_t launch_pt_swap(const SwapArgs &a, hipStream_t s);
-hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s);
+// Energies out; slots_out: where the slots are wanted, if not in a.slot_of_temp.
+hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s, int32_t *slots_out = nullptr);
 
 // ---- tuned launch shapes (tune.hip) ----
 // Launch shapes measured by smc_autotune, per device (the current one),
