@@ -138,9 +138,10 @@ __global__ __launch_bounds__(kThreads) void k_heis3d_half(Heis3dArgs a, int c) {
 // Bound: at 256^3 the HBM traffic (95 us per sweep, 5.3 TB/s with the halos);
 // below, the latency of a plane step (1.5 us alone on a compute unit, the wait
 // for the plane that it requests), so short segments fill the chip first.
-// Per sweep: one 64^3 lattice 10 us (58 with segments of 32 planes), 128^3 20
+// Per sweep: one 64^3 lattice 9.1 us (58 with segments of 32 planes), 128^3 19.6
 // (58); on edges that took the half-sweep kernel 96^3 16 us (31), 160^3 36 (88),
-// 200^3 74 (163).
+// 200^3 74 (163).  Drawing for both half-steps at the start of a step was 0.5 % slower
+// at 256^3 and 3 % at 64^3.
 constexpr int kTile = 32;
 constexpr int kMaxSeg = 32;
 constexpr int kW = kTile + 4;       // staged width with the halo
@@ -344,19 +345,22 @@ __global__ __launch_bounds__(kTiledThreads) void k_heis3d_tiled(TiledArgs a) {
     for (int z = z0 - 1; z <= z1; ++z) {
         const bool fetch = z + 2 <= z1 + 1;
         if (fetch) load_plane<POW2>(src, a, x0, y0, z + 2, pr);
-        // the draws of both half-steps depend on the sites alone: made together,
-        // two chains in flight, and before the first wait
-        const Cell c0 = cell0<POW2>(x0, y0, z, a), c1 = cell1<POW2>(x0, y0, z - 1, a);
-        uint4 w[2] = {make_uint4(c0.h, a.t, (uint32_t)r, 2 * kTagHeis),
-                      make_uint4(c1.h, a.t, (uint32_t)r, 2 * kTagHeis + 1u)};
-        philox4x32_10_multi<2>(w, a.key);
         // colour 0 of plane z on the tile and a one-site ring (planes z-1 .. z+1)
-        if (c0.on && update_cell(ring, slot_of(z - 1), slot_of(z), slot_of(z + 1), c0, w[0], beta))
-            n_acc += c0.own && z >= z0 && z < z1 ? 1 : 0;
+        const Cell c0 = cell0<POW2>(x0, y0, z, a);
+        if (c0.on) {
+            const uint4 w = philox4x32_10_wide(make_uint4(c0.h, a.t, (uint32_t)r, 2 * kTagHeis), a.key);
+            if (update_cell(ring, slot_of(z - 1), slot_of(z), slot_of(z + 1), c0, w, beta))
+                n_acc += c0.own && z >= z0 && z < z1 ? 1 : 0;
+        }
         __syncthreads();
         // colour 1 of plane z-1 on the tile (planes z-2 .. z)
-        if (z >= z0 + 1 && c1.on)
-            n_acc += update_cell(ring, slot_of(z - 2), slot_of(z - 1), slot_of(z), c1, w[1], beta) ? 1 : 0;
+        if (z >= z0 + 1) {
+            const Cell c1 = cell1<POW2>(x0, y0, z - 1, a);
+            if (c1.on) {
+                const uint4 w = philox4x32_10_wide(make_uint4(c1.h, a.t, (uint32_t)r, 2 * kTagHeis + 1u), a.key);
+                n_acc += update_cell(ring, slot_of(z - 2), slot_of(z - 1), slot_of(z), c1, w, beta) ? 1 : 0;
+            }
+        }
         // plane z+2 into the slot of plane z-3.  The wait is explicit and on
         // every path, so that no load is left pending across the loop (the
         // next step's request would otherwise wait behind this step's stores).
