@@ -424,8 +424,11 @@ bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape
         if (complete(sh, L, n_rep, ea, n_sweeps, even) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
     };
     offer(L, all, std::min(n_sweeps, 256));
+    // no tile takes less than its launches (8 sweeps each at most) and the shortest half-sweeps
+    const int fewest = std::max((n_sweeps + 7) / 8, even ? 2 : 1);
+    const bool search = best.rows == 0 || best.ns_per_sweep > 5000.0 * fewest / n_sweeps + 2.0 * 340.0;
     for (int sweeps : {1, 2, 3, 4, 5, 6, 8}) {
-        if (sweeps > (even ? (n_sweeps + 1) / 2 : n_sweeps)) continue;
+        if (!search || sweeps > (even ? (n_sweeps + 1) / 2 : n_sweeps)) continue;
         // rows that give each compute unit 1, 2, 4 or 8 tiles, and a few sizes
         for (int parts = 1; parts <= std::max(all, 1); ++parts) {
             if (all && all % parts) continue;
