@@ -21,8 +21,9 @@
 //
 // Bound: VALU (about 0.45 ps per update at full issue), then the HBM traffic
 // of 1 B per site and step.
-// 256 chains of 16 temperatures, edges 32 .. 256 (77.6e6 sites): 53 us per step
-// (0.68 ps per update) and 4 us for the exchange round (a byte per two sites: 61);
+// 256 chains of 16 temperatures, edges 32 .. 256 (77.6e6 sites): 48 us per step
+// (0.62 ps per update) and 4 us for the exchange round (a byte per two sites: 61; lanes
+// that walk over columns and rows of both parities: 53);
 // a launch per edge in a graph with couplings read from global memory took about 85 us,
 // and 2 ms per call to build the graph for arrays it had not met.
 //
@@ -30,7 +31,8 @@
 // the start of the next launch (SWAP), each replica for its own pair, instead of in a
 // launch of its own: 16 temperatures of one 64^2 chain 8.3 -> 7.0 us per step, of 64 chains
 // of 128^2 21.2 -> 19.5. In larger batches the round's four dependent loads stand before
-// the sweeps of every workgroup that follows: 57 -> 58 us in the batch above.
+// the sweeps of every workgroup that follows: 57 -> 58 us in the batch above (before
+// the lanes kept their columns).
 #include "bins2d.hpp"
 
 #include <algorithm>
@@ -63,19 +65,17 @@ __device__ __forceinline__ ThrRow table2d(const ThrRow &th) {
     return t;
 }
 
-// Colour-c sites of word k of row y (yG = y L/16) of the replica at S; adds the
-// flips and the unsatisfied bonds of the flipped sites.
+// Colour-c sites of word k of the row whose first word is yG: mine and row point to word
+// k of row 0 of the own array and of the other, to_beside is the distance of the word after (odd:
+// the own sites are the odd ones) or before it, periodic in the row; adds the flips and the
+// unsatisfied bonds of the flipped sites.
 template <bool EA>
-__device__ __forceinline__ void update(uint32_t *S, int G, int words, int y, int yG, int k, uint32_t c, uint32_t t,
-                                       uint32_t r, Key key, const Lut3 &K, const ThrRow *thr, uint32_t one2,
-                                       uint32_t &cnt, uint32_t &nsum) {
-    const bool odd = ((uint32_t)y & 1u) != c;  // own sites are the odd ones
-    uint32_t *const mine = S + (c ? words : 0) + yG + k;
-    const uint32_t *const row = S + (c ? 0 : words) + k;
-    const uint32_t own = *mine, par = row[yG];
+__device__ __forceinline__ void update(uint32_t *mine, const uint32_t *row, int G, int words, int yG, int k, bool odd,
+                                       int to_beside, uint32_t c, uint32_t t, uint32_t r, Key key, const Lut3 &K,
+                                       const ThrRow *thr, uint32_t one2, uint32_t &cnt, uint32_t &nsum) {
+    const uint32_t own = mine[yG], par = row[yG];
     const uint32_t up = row[yG == words - G ? 0 : yG + G], dn = row[yG == 0 ? words - G : yG - G];
-    // the word after (odd own sites) or before it, periodic in the row
-    const uint32_t beside = row[yG + (odd ? (k == G - 1 ? 1 - G : 1) : (k == 0 ? G - 1 : -1))];
+    const uint32_t beside = row[yG + to_beside];
     const uint32_t g = (uint32_t)(yG + k);
     const uint4 w = philox4x32_10(make_uint4(g, t, r, 2 * kTagHead + c), key);
     const uint32_t side = __builtin_amdgcn_alignbit(odd ? beside : par, odd ? par : beside, odd ? 4u : 28u);
@@ -97,7 +97,7 @@ __device__ __forceinline__ void update(uint32_t *S, int G, int words, int y, int
     if (__builtin_expect(__any(has_tie(eq)), 0))
         exact_decisions(o, w, table2d(*thr), K, 8u * g, c, t, r, key, has_tie(eq));
     const uint32_t f = flags_of(o.F0, o.F1);
-    *mine = own ^ f;
+    mine[yG] = own ^ f;
     // Delta E of a flip with n unsatisfied bonds is 4 (2 - n)
     cnt += (uint32_t)__builtin_popcount(f);
     nsum = __builtin_amdgcn_udot8(n, f, nsum, false);
@@ -228,8 +228,11 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
     // ---- the sweeps: a wave (or several) per replica
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int share = reps >= kWaves ? 1 : kWaves / reps;  // waves per replica
-    const int step = 64 * share, i0 = 64 * (wave % share) + lane;
-    const int y0 = i0 / G, k0 = i0 - y0 * G, dy = step / G, dk = step - dy * G;
+    // (an even number of rows at a time: a lane stays in its column and on rows of one
+    // parity, so that where its neighbours lie does not change from word to word)
+    const int dy = (64 * share / G) & ~1, i0 = 64 * (wave % share) + lane;
+    const int y0 = i0 / G, k0 = i0 - y0 * G, first = y0 < dy ? y0 * G : words;
+    const int to_next = k0 == G - 1 ? 1 - G : 1, to_prev = k0 == 0 ? G - 1 : -1;
     const int rep0 = wave / share, reps_step = share > 1 ? kBinReps : kWaves;
     uint32_t cnt = 0, nsum = 0;
     auto flush = [&](int rep) {
@@ -243,6 +246,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
         const uint32_t t = a.t + (uint32_t)sw;
 #pragma unroll 1
         for (uint32_t c = 0; c < 2; ++c) {
+            const bool odd = ((uint32_t)y0 & 1u) != c;  // own sites are the odd ones
+            const int to_beside = odd ? to_next : to_prev;
             for (int rep = rep0; rep < reps; rep += reps_step) {
                 const int row = __builtin_amdgcn_readfirstlane(tab[rep].row);
                 if (row < 0) continue;  // a chain without a valid permutation: unchanged
@@ -250,16 +255,11 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
                 Lut3 K;
                 K.lo = __builtin_amdgcn_readfirstlane(tab[rep].lut.x);
                 K.hi = __builtin_amdgcn_readfirstlane(tab[rep].lut.y);
-                uint32_t *S = smem + 2 * rep * words;
-                for (int y = y0, k = k0; y < L;) {
-                    update<EA>(S, G, words, y, y * G, k, c, t, r, a.key, K, a.thr + row, one2, cnt, nsum);
-                    y += dy;
-                    k += dk;
-                    if (k >= G) {
-                        k -= G;
-                        ++y;
-                    }
-                }
+                uint32_t *mine = smem + (2 * rep + (int)c) * words + k0;
+                const uint32_t *other = smem + (2 * rep + 1 - (int)c) * words + k0;
+                for (int yG = first; yG < words; yG += dy * G)
+                    update<EA>(mine, other, G, words, yG, k0, odd, to_beside, c, t, r, a.key, K, a.thr + row, one2, cnt,
+                               nsum);
                 if (reps > kWaves) flush(rep);
             }
             __syncthreads();
@@ -292,8 +292,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_bins2d(Bins2dArgs a, int raw_in
 // Share of the lanes that have a piece in the rounds of a half-sweep, with
 // per replicas in a bin.
 static double lanes_used(int L, int per) {
-    const int pieces = L * L / 16, lanes = 64 * (per >= kWaves ? 1 : kWaves / per);
-    return (double)pieces / ((pieces + lanes - 1) / lanes * lanes);
+    const int G = L / 16, pieces = L * G, lanes = 64 * (per >= kWaves ? 1 : kWaves / per), used = (lanes / G & ~1) * G;
+    return (double)pieces / ((pieces + used - 1) / used * lanes);
 }
 
 size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, std::vector<int32_t> *work) {
