@@ -100,8 +100,11 @@
  *   SPINMC_L2D_H2 (heights of the bands of the first and second half of
  *   the grid) and SPINMC_L2D_PAD (row padding in bytes) set the launch
  *   shape of the one-pass 2D Ising sweep (and keep the edges it serves on
- *   it).  SPINMC_HEIS3D=0 sends uniform 3D
- *   Heisenberg batches to the generic kernel.
+ *   it).  Small uniform Heisenberg batches (3D L up to 22, 2D L up to 114) run
+ *   whole replicas on chip for the call where an estimate says that it is
+ *   faster; SPINMC_HEIS_SMALL=0 keeps them on the half-sweeps, =1 takes it
+ *   wherever it fits.  SPINMC_HEIS3D=0 sends uniform Heisenberg batches to the
+ *   generic kernel.
  */
 #ifndef SPINMC_H
 #define SPINMC_H

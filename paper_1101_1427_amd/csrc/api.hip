@@ -710,6 +710,17 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         for (int r = 0; r < desc->n_rep; ++r) bf[r] = (float)beta[r];
         if ((rc = upload(c, s, kTables, bf.data(), sizeof(float) * bf.size(), &p))) return rc;
         a.beta_f = (const float *)p;
+        if (use_heis_small(desc, n_sweeps)) {
+            constexpr int32_t kPerLaunch = 1024;  // sweeps, so that one launch stays short
+            SweepTimer timer(s, (n_sweeps + kPerLaunch - 1) / kPerLaunch);
+            for (int32_t done = 0; done < n_sweeps; done += kPerLaunch)
+                SMC_HIP(launch_heis_small((float *)spins, a.beta_f, dE_accum, desc->n_rep, desc->dim, desc->L, a.key,
+                                          (uint32_t)(sweep0 + (uint64_t)done),
+                                          n_sweeps - done < kPerLaunch ? n_sweeps - done : kPerLaunch,
+                                          desc->renorm_every, s));
+            timer.finish();
+            return SMC_OK;
+        }
         void *pp = nullptr;
         const size_t bytes = (size_t)desc->n_rep * 3 * sizeof(float) * (size_t)plan.b.N;
         bool tiled = use_heis3d_tiled(desc);

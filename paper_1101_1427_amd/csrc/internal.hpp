@@ -106,6 +106,10 @@ bool heis3d_supported(int dim, int L);
 int heis3d_half_groups(int L);  // workgroups per replica
 hipError_t launch_heis3d_half(float *spins, const float *beta, const Tally &acc, int n_rep, int L, Key key, uint32_t t,
                               int c, hipStream_t s);
+// Small 2D and 3D lattices on chip for several sweeps, in place.
+bool heis_small_supported(int dim, int L);
+hipError_t launch_heis_small(float *spins, const float *beta, int64_t *acc, int n_rep, int dim, int L, Key key,
+                             uint32_t t, int sweeps, int renorm_every, hipStream_t s);
 // One-pass (tiled, colour 0 then colour 1 in one launch) sweep from src to dst, even L >= 32;
 // with renorm the spins written to dst are renormalised.
 bool heis3d_tiled_supported(int dim, int L);

@@ -174,6 +174,25 @@ bool use_heis3d(const smc_desc *d) {
     return d->model == SMC_HEISENBERG && d->L > 0 && heis3d_supported(d->dim, d->L);
 }
 
+// Small uniform Heisenberg lattices keep whole replicas in LDS for a call where an estimate
+// says that it is faster: a sweep takes a compute unit 1 us and 0.95 ns per site of its
+// replica (half as much again once for loads and stores), the half-sweep launches 8.5 us
+// and 15 ps per site of the batch (one 22^3 lattice 11.1 against 9.2 us, 50 of them 11.3
+// against 17.9).  SPINMC_HEIS_SMALL=0 and SPINMC_HEIS3D=0 keep the half-sweeps, =1 takes this
+// kernel wherever it fits (same results).
+bool use_heis_small(const smc_desc *d, int64_t n_sweeps) {
+    for (const char *name : {"SPINMC_HEIS_SMALL", "SPINMC_HEIS3D"}) {
+        const char *env = getenv(name);
+        if (env && env[0] == '0') return false;
+    }
+    if (d->model != SMC_HEISENBERG || d->L <= 0 || !heis_small_supported(d->dim, d->L)) return false;
+    const char *env = getenv("SPINMC_HEIS_SMALL");
+    if (env && env[0] == '1') return true;
+    const double N = d->dim == 3 ? (double)d->L * d->L * d->L : (double)d->L * d->L;
+    const double small = (1.0 + 0.95e-3 * N + 0.5e-3 * N / (double)n_sweeps) * ((d->n_rep + 255) / 256);
+    return small < 8.5 + 15e-6 * N * d->n_rep;
+}
+
 // ... and those with any even edge of at least 32 the one-pass tiled kernel
 // (SPINMC_HEIS_TILED=0 keeps the two half-sweep launches).
 bool use_heis3d_tiled(const smc_desc *d) {
