@@ -10,9 +10,15 @@ namespace {
 __global__ __launch_bounds__(1024) void k_collect(const int64_t *slots, int64_t *dE, int per_rep, int assign) {
     __shared__ long long red[16];
     const int64_t *p = slots + (int64_t)blockIdx.x * per_rep;
+    // (the total before, read along with the slots)
+    const int64_t before = threadIdx.x == 0 && !assign ? dE[blockIdx.x] : 0;
     long long v = 0;
+    if (per_rep <= (int)blockDim.x) {
+        if ((int)threadIdx.x < per_rep) v = p[threadIdx.x];
+    } else {
 #pragma unroll 8
-    for (int i = (int)threadIdx.x; i < per_rep; i += (int)blockDim.x) v += p[i];
+        for (int i = (int)threadIdx.x; i < per_rep; i += (int)blockDim.x) v += p[i];
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -20,7 +26,7 @@ __global__ __launch_bounds__(1024) void k_collect(const int64_t *slots, int64_t 
     if (threadIdx.x == 0) {
         long long sum = 0;
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) sum += red[w];
-        dE[blockIdx.x] = assign ? sum : dE[blockIdx.x] + sum;
+        dE[blockIdx.x] = before + sum;
     }
 }
 
