@@ -48,20 +48,6 @@ __device__ __forceinline__ void into_place(uint4 &v, I i, I N) {
     if (i > N - 16) v = bytes_down(v, (uint32_t)min(i - (N - 16), (I)16));
 }
 
-// Eight bytes of LDS at p (8-byte aligned), four at p (4-byte aligned), and
-// the eight at p + d for any d: an unaligned LDS read is served about one lane
-// per clock (90 clocks per wavefront measured), three aligned words and two
-// byte alignments in a fraction of that.
-__device__ __forceinline__ uint2 lds8(const uint8_t *p) { return *(const uint2 *)__builtin_assume_aligned(p, 8); }
-__device__ __forceinline__ uint32_t lds4(const uint8_t *p) {
-    return *(const uint32_t *)__builtin_assume_aligned(p, 4);
-}
-__device__ __forceinline__ uint2 lds8_at(const uint8_t *p, int d) {
-    const uint8_t *q = p + (d & ~3);
-    const uint32_t a = lds4(q), b = lds4(q + 4), c = lds4(q + 8), s = (uint32_t)d & 3u;
-    return make_uint2(alignbyte(b, a, s), alignbyte(c, b, s));
-}
-
 // The end of a row in a piece of which `left` sites (even, > 0) remain in
 // the row; left >= 16: a whole piece.
 struct RowEnd {
