@@ -169,14 +169,28 @@ class Batch:
             return n_samples * self.dim * self.sites()
         return max(int(r[3]) + self.dim * self.sites(int(r[0])) for r in self.inst)
 
+    def _instances(self):
+        """The instance table as int64 [n_rep][4 or more]; ValueError unless it has a row per replica
+        (a shorter one would otherwise be spread over the replicas, a longer one cut)."""
+        if self.inst is None:
+            raise TypeError("an uneven batch (L == 0) needs inst")
+        try:
+            inst = np.asarray(self.inst, np.int64)
+        except (TypeError, ValueError):  # rows of other forms, entry by entry
+            inst = np.array([[int(r[k]) for k in range(4)] for r in self.inst], np.int64)
+        if inst.ndim != 2 or inst.shape[0] != self.n_rep or inst.shape[1] < 4:
+            raise ValueError(f"inst has shape {inst.shape}: need a row (L, sample, spin_off, coup_off) for each of "
+                             f"{self.n_rep} replicas")
+        return inst
+
     def desc(self, spins_len: int, coup_len: int) -> Desc:
         d = Desc(self.model, self.dim, self.L, self.n_rep, self.rep_per_sample, self.renorm_every,
                  self.seed & 0xFFFFFFFFFFFFFFFF, None, spins_len, coup_len)
         if self.L == 0:
-            inst = np.asarray(self.inst, np.int64)
+            inst = self._instances()
             rows = np.empty(self.n_rep, INST_DTYPE)
             for k, name in enumerate(INST_DTYPE.names):
-                rows[name] = inst[:self.n_rep, k]
+                rows[name] = inst[:, k]
             d._inst_keep = rows  # keep alive for the call
             d.inst = rows.ctypes.data_as(C.POINTER(Inst))
         return d
