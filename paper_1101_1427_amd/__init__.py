@@ -57,7 +57,7 @@ def lib():
         L = C.CDLL(LIB_PATH)
         vp, P = C.c_void_p, C.POINTER
         L.smc_spin_init.argtypes = [P(Desc), vp, vp, vp]
-        L.smc_metropolis_sweep.argtypes = [P(Desc), vp, vp, vp, C.c_uint64, C.c_int32, vp, vp]
+        L.smc_metropolis_sweep.argtypes = [P(Desc), vp, vp, P(C.c_double), C.c_uint64, C.c_int32, vp, vp]
         L.smc_pt_sweep_swap.argtypes = [P(Desc), P(PTDesc), vp, vp, vp, vp, C.c_uint64, C.c_int32, vp, vp]
         L.smc_measure_energy_magnetisation.argtypes = [P(Desc), vp, vp, vp, vp, vp]
         L.smc_measure_energy_magnetisation_noalloc.argtypes = [P(Desc), vp, vp, vp, vp, vp]
@@ -72,26 +72,26 @@ def lib():
         L.smc_kernel_timing_enable.restype = C.c_int
         L.smc_kernel_timing_read.argtypes = [P(C.c_double), P(C.c_int64)]
         L.smc_kernel_timing_read.restype = C.c_int
-        L.smc_msc_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_uint64, C.c_int32,
+        L.smc_msc_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32,
                                     C.c_int32, C.c_void_p, C.c_void_p]
         L.smc_msc_sweep.restype = C.c_int
         L.smc_msc_plan.argtypes = [P(Desc), C.c_int32, C.c_int32, P(C.c_int32), P(C.c_char_p)]
         L.smc_msc_plan.restype = C.c_int
-        L.smc_dcb_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_uint64, C.c_int32,
+        L.smc_dcb_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32,
                                     C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
         L.smc_dcb_sweep.restype = C.c_int
-        L.smc_heis_dcb_sweep.argtypes = [P(Desc), C.c_void_p, vp, C.c_uint64, C.c_int32, C.c_int32,
+        L.smc_heis_dcb_sweep.argtypes = [P(Desc), C.c_void_p, P(C.c_double), C.c_uint64, C.c_int32, C.c_int32,
                                          C.c_int32, C.c_int32, C.c_int32, C.c_double, C.c_void_p, C.c_void_p]
         L.smc_heis_dcb_sweep.restype = C.c_int
         L.smc_autotune.argtypes = [P(Desc), C.c_char_p, C.c_void_p]
         L.smc_autotune.restype = C.c_int
-        L.smc_dcb_plan.argtypes = [P(Desc), vp, C.c_int32, P(C.c_char_p)]
+        L.smc_dcb_plan.argtypes = [P(Desc), P(C.c_double), C.c_int32, P(C.c_char_p)]
         L.smc_dcb_plan.restype = C.c_int
         L.smc_rng_study_state_bytes.argtypes = [P(Desc), C.c_int32, C.c_int32, P(C.c_int64)]
         L.smc_rng_study_state_bytes.restype = C.c_int
         L.smc_rng_study_init.argtypes = [P(Desc), C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
         L.smc_rng_study_init.restype = C.c_int
-        L.smc_rng_study_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, vp, C.c_int32, C.c_int32,
+        L.smc_rng_study_sweep.argtypes = [P(Desc), C.c_void_p, C.c_void_p, P(C.c_double), C.c_int32, C.c_int32,
                                           C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
         L.smc_rng_study_sweep.restype = C.c_int
         L.smc_philox_bench.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32, C.c_int32, C.c_int32,
@@ -132,9 +132,9 @@ def _betas(beta, n: int):
     return b if b.shape == (n,) and b.flags.c_contiguous else np.ascontiguousarray(np.broadcast_to(b, (n,)))
 
 
-def _address(a):
-    """Address of a host array's first element (the array has to outlive the call)."""
-    return a.__array_interface__["data"][0]
+def _doubles(a):
+    """A float64 array as a `const double *` argument (the array has to outlive the call)."""
+    return C.byref(C.c_double.from_address(a.__array_interface__["data"][0]))
 
 
 @dataclass
@@ -212,7 +212,7 @@ def metropolis_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, coup
     d = _desc(batch, spins, couplings)
     b = _betas(beta, batch.n_rep)
     _check(lib().smc_metropolis_sweep(C.byref(d), _ptr(spins), _ptr(couplings),
-                                      _address(b), sweep0, n_sweeps,
+                                      _doubles(b), sweep0, n_sweeps,
                                       _ptr(dE_accum), _stream(stream)), "smc_metropolis_sweep")
 
 
@@ -223,7 +223,7 @@ def msc_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, couplings=N
     a host sequence [n_rep], equal within each group."""
     d = _desc(batch, spins, couplings)
     b = _betas(beta, batch.n_rep)
-    _check(lib().smc_msc_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
+    _check(lib().smc_msc_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _doubles(b),
                                sweep0, n_sweeps, word_bits, _ptr(dE_accum), _stream(stream)), "smc_msc_sweep")
 
 
@@ -242,7 +242,7 @@ def dcb_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, tile: int, 
         if dE_trace.numel() < n_sweeps * batch.n_rep:
             raise ValueError(f"dE_trace holds {dE_trace.numel()} entries, needs n_sweeps * n_rep = "
                              f"{n_sweeps * batch.n_rep}")
-    _check(lib().smc_dcb_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
+    _check(lib().smc_dcb_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _doubles(b),
                                sweep0, n_sweeps, tile, hits, 1 if palindromic else 0, _ptr(dE_accum),
                                _ptr(dE_trace), _stream(stream)), "smc_dcb_sweep")
 
@@ -262,7 +262,7 @@ def heis_dcb_sweep(batch: Batch, spins, beta, sweep0: int, n_sweeps: int, tile: 
         raise TypeError(f"spins must be a contiguous {want} device tensor for precision {precision}")
     d = _desc(batch, spins, None)
     b = _betas(beta, batch.n_rep)
-    _check(lib().smc_heis_dcb_sweep(C.byref(d), _ptr(spins), _address(b), sweep0,
+    _check(lib().smc_heis_dcb_sweep(C.byref(d), _ptr(spins), _doubles(b), sweep0,
                                     n_sweeps, tile, hits, precision, 1 if palindromic else 0, float(cap),
                                     _ptr(accepts), _stream(stream)), "smc_heis_dcb_sweep")
 
@@ -280,7 +280,7 @@ def dcb_plan(batch: Batch, beta, tile: int) -> str:
     d = batch.desc(batch.spins_shape()[0], batch.coup_len())
     b = _betas(beta, batch.n_rep)
     name = C.c_char_p()
-    _check(lib().smc_dcb_plan(C.byref(d), _address(b), tile, C.byref(name)),
+    _check(lib().smc_dcb_plan(C.byref(d), _doubles(b), tile, C.byref(name)),
            "smc_dcb_plan")
     return name.value.decode()
 
@@ -350,7 +350,7 @@ def rng_study_sweep(batch: Batch, spins, beta, n_sweeps: int, tile: int, hits: i
     """n_sweeps double-checkerboard sweeps drawing from a study generator (smc_rng_study_sweep)."""
     d = _desc(batch, spins, couplings)
     b = _betas(beta, batch.n_rep)
-    _check(lib().smc_rng_study_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _address(b),
+    _check(lib().smc_rng_study_sweep(C.byref(d), _ptr(spins), _ptr(couplings), _doubles(b),
                                      n_sweeps, tile, hits, generator, _ptr(state),
                                      state.numel() * state.element_size(), _ptr(dE_accum), _stream(stream)),
            "smc_rng_study_sweep")
