@@ -383,7 +383,7 @@ bool sweep3d_asked_for() {
 bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
     const char *env = getenv("SPINMC_PAIRS3D");
     if ((env && env[0] == '0') || d->L <= 0 || (d->model != SMC_ISING && d->model != SMC_EA) ||
-        !pairs3d_supported(d->dim, d->L))
+        !pairs3d_supported(d->dim, d->L) || !pairs3d_launchable(d->L, d->n_rep))
         return false;
     if (env && env[0] == '1') return true;
     if (d->L % 16) return n_sweeps >= 2;

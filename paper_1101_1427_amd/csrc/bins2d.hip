@@ -337,8 +337,16 @@ hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_i
                                  : (a.swap ? k_bins2d<false, true> : k_bins2d<false, false>);
     if (lds > 60000)
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinBytes);
-    SMC_LAUNCH(kernel, dim3((unsigned)n_bins), dim3(kThreads), lds, s, a, raw_in ? 1 : 0, raw_out ? 1 : 0, one2);
-    return hipGetLastError();
+    // (a launch has fewer than 2^32 work-items)
+    constexpr int kMost = (1 << 23) - 1;
+    for (int first = 0; first < n_bins; first += kMost) {
+        Bins2dArgs part = a;
+        part.bins += first;
+        SMC_LAUNCH(kernel, dim3((unsigned)std::min(kMost, n_bins - first)), dim3(kThreads), lds, s, part, raw_in ? 1 : 0,
+                   raw_out ? 1 : 0, one2);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace smc

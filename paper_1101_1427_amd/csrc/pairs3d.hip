@@ -296,6 +296,10 @@ int word_groups(int L) { return (words_in(L) + kThreads - 1) / kThreads; }
 
 bool pairs3d_supported(int dim, int L) { return dim == 3 && L >= 16 && L <= 1024 && L % 2 == 0; }
 
+bool pairs3d_launchable(int L, int n_rep) {
+    return launch_config_error((uint64_t)word_groups(L) * (uint64_t)n_rep, kThreads, 0) == nullptr;
+}
+
 size_t pairs3d_bytes(int L, int n_rep) { return (size_t)n_rep * 8 * (size_t)span_of(L); }
 
 // Planes of a thread: more of them read the planes beside less often and start with more

@@ -17,6 +17,9 @@ struct Pairs3dArgs {
 };
 
 bool pairs3d_supported(int dim, int L);
+// Whether the launches for a batch stay below 2^32 work-items (a thread per 16 sites;
+// the kernels on the caller's bytes have up to 16 times fewer threads).
+bool pairs3d_launchable(int L, int n_rep);
 // Bytes of the packed copy.
 size_t pairs3d_bytes(int L, int n_rep);
 hipError_t launch_pairs3d_pack(const int8_t *spins, const int8_t *coup, const Pairs3dArgs &a, hipStream_t s);

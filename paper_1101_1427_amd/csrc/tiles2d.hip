@@ -385,8 +385,11 @@ bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even)
     if (sh.threads > kMaxThreads) sh.threads = kMaxThreads;
     if (sh.whole)
         if (const int tuned = small2d_threads(L, ea)) sh.threads = tuned;
+    // A launch has fewer than 2^32 work-items: of a great many lattices each gets fewer threads.
+    const int64_t groups = (int64_t)n_rep * bands2d_groups(L, sh), room = 0xFFFFFFFFll / groups / 64 * 64;
+    if (room < 64) return false;
+    sh.threads = (int)std::min<int64_t>(sh.threads, room);
     // Workgroups per compute unit, and how many run there at once.
-    const int64_t groups = (int64_t)n_rep * bands2d_groups(L, sh);
     const double per_cu = (double)((groups + 255) / 256);
     const double at_once = std::max(1.0, std::min({per_cu, (double)(kMaxLdsBytes / lds), 2048.0 / sh.threads}));
     // A half-sweep of one round takes about `latency` ns from barrier to barrier,
