@@ -283,9 +283,9 @@ int smc_measure_energy_magnetisation_noalloc(const smc_desc *desc, const void *s
  * Autotuning of launch shapes; it never changes results.  It measures, on
  * scratch lattices of the batch's shape with random spins, and keeps for
  * later calls in the process on this device:
- *  - 2D Ising / EA with an edge in {16, 32, ..., 256}: the workgroup size of
- *    sweeps that hold a whole lattice on chip (calls choose it by a rule
- *    unless it was measured);
+ *  - uniform 2D Ising / EA with an edge in {16, 32, ..., 256}: the workgroup
+ *    size of sweeps that hold a whole lattice on chip, per edge, model and
+ *    replica count;
  *  - uniform 2D Ising with L a power of two in [1024, 16384]: the band
  *    height of the one-pass sweep (rows per workgroup, 4 .. 128), per edge
  *    and replica count;

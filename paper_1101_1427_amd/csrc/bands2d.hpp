@@ -17,6 +17,8 @@ struct BandShape {
 // The shape for a batch of n_rep lattices and n_sweeps sweeps; false if none
 // fits in LDS.  even: see bands2d_launches.
 bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out);
+// The shape that holds whole lattices, of workgroups of at most most_threads.
+bool bands2d_whole(int L, int n_rep, bool ea, int n_sweeps, int most_threads, BandShape *out);
 int bands2d_groups(int L, const BandShape &sh);  // workgroups per replica
 int bands2d_pieces(int L);                       // pieces per staged row
 size_t bands2d_lds(int cells);                   // bytes for so many staged pieces

@@ -208,14 +208,11 @@ hipError_t launch_pt_finish(const SwapArgs &a, double *energy_out, hipStream_t s
 // kind, edge, model (0 Ising, 1 EA) and replica count.  The launchers take
 // an environment override first, then a tuned shape, then their default;
 // no shape changes results.
-enum ShapeKind { kShapeBand2d = 0, kShapePass3d = 1, kShapeHalf3d = 2 };
+enum ShapeKind { kShapeBand2d = 0, kShapePass3d = 1, kShapeHalf3d = 2, kShapeWhole2d = 3, kShapeKinds = 4 };
 struct Shape {
-    int v[3];  // band2d: rows per band; pass3d: rows per strip, segments per thread, planes per z segment; half3d: rows per thread
+    int v[3];  // band2d: rows per band; pass3d: rows per strip, segments per thread, planes per z segment; half3d: rows per
+               // thread; whole2d: most threads of a workgroup that holds a whole 2D lattice
 };
-// Workgroup size of the whole-lattice shape of the 2D bands for an edge (a
-// multiple of 16 up to 256): SPINMC_U2D_THREADS, else what smc_autotune
-// measured, else 0 (the shape's own).
-int small2d_threads(int L, bool ea);
 bool tuned_shape(int kind, int L, int model, int n_rep, Shape *out);
 void set_tuned_shape(int kind, int L, int model, int n_rep, const Shape &s);
 

@@ -34,6 +34,7 @@
 #include <algorithm>
 
 #include "bands2d.hpp"
+#include "bins2d.hpp"
 #include "halves.hpp"
 #include "rows.hpp"
 
@@ -361,6 +362,25 @@ __global__ __launch_bounds__(kMaxThreads) void k_tiles2d(KArgs a) {
     }
 }
 
+// Threads of a workgroup, at most `limit` of them (a multiple of 64), for R rows of K words:
+// whole rows of threads with 1, 2 or `most` = 4 words each (2: rows that share pieces, of
+// which 4 do not fit in the registers), as few words as the limit allows; else any number.
+int threads_for(int R, int K, int most, int limit) {
+    for (int n = 1; n <= most; n *= 2) {
+        const int lanes = (R + n - 1) / n * K;
+        if (lanes <= limit) return (lanes + 63) / 64 * 64;
+    }
+    const int64_t words = (int64_t)R * K, rounds = (words + limit - 1) / limit;
+    return (int)std::max<int64_t>(64, ((words + rounds - 1) / rounds + 63) / 64 * 64);
+}
+
+// SPINMC_U2D_THREADS, for an edge that is a multiple of 16 up to 256; else 0.
+int whole_threads_asked_for(int L) {
+    const char *f = getenv("SPINMC_U2D_THREADS");
+    const int v = f && uneven2d_edge_supported(L) ? atoi(f) : 0;
+    return v == 64 || v == 128 || v == 256 || v == 512 ? v : 0;
+}
+
 // Fills the rest of a shape from (rows, sweeps per launch, whole) and
 // estimates its time per sweep; false if it does not fit.
 bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even) {
@@ -374,17 +394,10 @@ bool complete(BandShape &sh, int L, int n_rep, bool ea, int n_sweeps, bool even)
     if (launches > n_sweeps) return false;
     const int64_t pieces = (int64_t)R * K;
     const int rounds = (int)((pieces + kMaxThreads - 1) / kMaxThreads);
-    sh.threads = (int)std::max<int64_t>(64, ((pieces + rounds - 1) / rounds + 63) / 64 * 64);
-    // whole rows of threads with 1, 2 or 4 words each, where they suffice (4 of rows that
-    // share pieces do not fit in the registers)
     const int most = rag ? 2 : 4;
-    for (int n = most; n > 0; n /= 2) {
-        const int lanes = (R + n - 1) / n * K;
-        if (lanes <= kMaxThreads) sh.threads = (lanes + 63) / 64 * 64;
-    }
-    if (sh.threads > kMaxThreads) sh.threads = kMaxThreads;
+    sh.threads = threads_for(R, K, most, kMaxThreads);
     if (sh.whole)
-        if (const int tuned = small2d_threads(L, ea)) sh.threads = tuned;
+        if (const int asked = whole_threads_asked_for(L)) sh.threads = asked;
     // A launch has fewer than 2^32 work-items: of a great many lattices each gets fewer threads.
     const int64_t groups = (int64_t)n_rep * bands2d_groups(L, sh), room = 0xFFFFFFFFll / groups / 64 * 64;
     if (room < 64) return false;
@@ -451,8 +464,24 @@ bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape
         offer(std::min(atoi(er), L), ew && atoi(ew) > 0 ? std::min(atoi(ew), all) : all,
               std::min(atoi(es), std::max(1, n_sweeps)));
     }
+    // (a measured limit of the workgroup holds for the shape, not for the choice of it)
+    Shape tuned;
+    if (best.whole && all && !whole_threads_asked_for(L) && tuned_shape(kShapeWhole2d, L, ea ? 1 : 0, n_rep, &tuned))
+        best.threads = std::min(best.threads, threads_for(L, all, 4, tuned.v[0]));
     *out = best;
     return best.rows > 0;
+}
+
+bool bands2d_whole(int L, int n_rep, bool ea, int n_sweeps, int most_threads, BandShape *out) {
+    BandShape sh;
+    sh.rows = L;
+    sh.words = L % 16 == 0 ? L / 16 : 0;
+    sh.sweeps = std::min(n_sweeps, 256);
+    sh.whole = true;
+    if (!complete(sh, L, n_rep, ea, n_sweeps, true)) return false;
+    sh.threads = std::min(sh.threads, threads_for(L, bands2d_pieces(L), L % 16 ? 2 : 4, most_threads));
+    *out = sh;
+    return true;
 }
 
 int bands2d_launches(const BandShape &sh, int n_sweeps, bool even) {

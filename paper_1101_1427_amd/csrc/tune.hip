@@ -26,10 +26,9 @@ namespace smc {
 namespace {
 
 std::mutex g_tune_mutex;
-std::map<std::tuple<int, int, int>, int> g_tuned;  // (device, edge, EA) -> workgroup size of the whole-lattice 2D sweep
 std::map<std::tuple<int, int, int, int, int>, Shape> g_shapes;  // (device, kind, edge, model, replicas) -> shape
 
-const char *const kKindName[] = {"band2d", "pass3d", "half3d"};
+const char *const kKindName[kShapeKinds] = {"band2d", "pass3d", "half3d", "u2d"};
 
 int current_device() {
     int dev = 0;
@@ -211,30 +210,22 @@ void set_tuned_shape(int kind, int L, int model, int n_rep, const Shape &sh) {
     g_shapes[std::make_tuple(current_device(), kind, L, model, n_rep)] = sh;
 }
 
-int small2d_threads(int L, bool ea) {
-    if (!uneven2d_edge_supported(L)) return 0;
-    if (const char *f = getenv("SPINMC_U2D_THREADS")) {
-        const int v = atoi(f);
-        if (v == 64 || v == 128 || v == 256 || v == 512) return v;
-    }
-    std::lock_guard<std::mutex> lk(g_tune_mutex);
-    auto it = g_tuned.find(std::make_tuple(current_device(), L, ea ? 1 : 0));
-    return it == g_tuned.end() ? 0 : it->second;
-}
-
 namespace {
 
-// Workgroup size of the whole-lattice shape for (device, edge, model): the
-// sweep kernel runs 16 sweeps of up to 4096 scratch replicas with every
-// candidate size and the fastest is kept.  The choice changes the schedule
-// only, never the results.
-int tune_small2d(StreamCtx &c, hipStream_t s, int L, bool ea, int n_rep, Key key) {
+// Workgroup size of 2D sweeps that hold a whole lattice: limits of 64 .. 1024
+// threads, of those that give the same workgroup the smallest, timed on 16
+// sweeps of up to 4096 scratch replicas.  The largest limit's is the default.
+int tune_whole2d(StreamCtx &c, hipStream_t s, int L, bool ea, int n_rep, Key key) {
     const char *env = getenv("SPINMC_AUTOTUNE");
     if (getenv("SPINMC_U2D_THREADS") || (env && env[0] == '0')) return SMC_OK;
-    const auto id = std::make_tuple(current_device(), L, ea ? 1 : 0);
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mutex);
-        if (g_tuned.count(id)) return SMC_OK;
+    constexpr int kSweeps = 16;
+    BandShape sh;
+    std::vector<Shape> cands;
+    int threads = 0;
+    for (int limit = 64; limit <= 1024; limit *= 2) {
+        if (!bands2d_whole(L, n_rep, ea, kSweeps, limit, &sh)) return SMC_OK;
+        if (sh.threads != threads) cands.push_back(Shape{{limit, 0, 0}});
+        threads = sh.threads;
     }
     const int64_t N = (int64_t)L * L;
     Batch b{};
@@ -263,28 +254,14 @@ int tune_small2d(StreamCtx &c, hipStream_t s, int L, bool ea, int n_rep, Key key
     a.key = key;
     a.n_rep = b.n_rep;
     a.L = L;
-    BandShape sh;
-    sh.rows = L;
-    sh.words = L / 16;
-    sh.sweeps = 16;
-    sh.whole = true;
-    int best = 0;
-    float best_ms = 1e30f;
-    for (sh.threads = 64; sh.threads <= 512; sh.threads <<= 1) {
-        float ms = 0.0f;
-        rc = time_calls(s, 3, [&](int k) {
-            a.t = 16u * (uint32_t)k;
-            return launch_bands2d(a, sh, 16, Tally{}, s);
-        }, &ms);
-        if (rc) return rc;
-        if (ms < best_ms) {
-            best_ms = ms;
-            best = sh.threads;
-        }
-    }
-    std::lock_guard<std::mutex> lk(g_tune_mutex);
-    g_tuned[id] = best;
-    return SMC_OK;
+    return pick_shape(kShapeWhole2d, L, ea ? 1 : 0, n_rep, cands, cands.back(), s, [&](int k) {
+        Shape now;
+        if (!tuned_shape(kShapeWhole2d, L, ea ? 1 : 0, n_rep, &now) ||
+            !bands2d_whole(L, n_rep, ea, kSweeps, now.v[0], &sh))
+            return hipErrorInvalidValue;
+        a.t = kSweeps * (uint32_t)k;
+        return launch_bands2d(a, sh, kSweeps, Tally{}, s);
+    });
 }
 
 }  // namespace
@@ -303,16 +280,11 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
     const int model = ea ? 1 : 0;
     const bool spin_model = desc->model == SMC_ISING || ea;
     // what this batch has to tune
-    std::map<int, int> count;  // 2D edges of the whole-lattice bands -> replicas
-    if (desc->dim == 2 && spin_model)
-        for (int r = 0; r < desc->n_rep; ++r) {
-            const int L = desc->L > 0 ? desc->L : desc->inst[r].L;
-            if (uneven2d_edge_supported(L)) ++count[L];
-        }
+    const bool whole2d = desc->dim == 2 && spin_model && desc->L > 0 && uneven2d_edge_supported(desc->L);
     const bool band2d = desc->dim == 2 && desc->model == SMC_ISING && desc->L > 0 && lattice2d_supported(desc->L);
     const bool seg3d = desc->dim == 3 && spin_model && desc->L > 0 && sweep3d_shape(desc);
     const bool pass3d = seg3d && pass3d_enabled(desc);
-    if (count.empty() && !band2d && !seg3d) return SMC_OK;
+    if (!whole2d && !band2d && !seg3d) return SMC_OK;
     const int dev = current_device();
     const std::string tag = device_tag(dev);
     std::vector<std::string> keep;  // lines of other devices
@@ -330,18 +302,14 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
                     keep.emplace_back(line);
                     continue;
                 }
-                if (!strcmp(kind, "u2d")) {
-                    if (uneven2d_edge_supported(L) && (m == 0 || m == 1) &&
-                        (v0 == 64 || v0 == 128 || v0 == 256 || v0 == 512)) {
-                        std::lock_guard<std::mutex> lk(g_tune_mutex);
-                        g_tuned[std::make_tuple(dev, L, m)] = v0;
-                    }
-                    continue;
-                }
-                for (int k = 0; k < 3; ++k) {
+                for (int k = 0; k < kShapeKinds; ++k) {
+                    // (u2d lines of replicas 0 hold sizes that were not compared with the default: not taken)
                     if (strcmp(kind, kKindName[k]) || n < 1 || (m != 0 && m != 1)) continue;
                     const bool ok = k == kShapeBand2d   ? (lattice2d_supported(L) && v0 >= 4 && v0 % 4 == 0 && L % v0 == 0)
                                     : k == kShapePass3d ? pass3d_shape_valid(L, m == 1, v0, v1, v2)
+                                    : k == kShapeWhole2d
+                                        ? (uneven2d_edge_supported(L) &&
+                                           (v0 == 64 || v0 == 128 || v0 == 256 || v0 == 512 || v0 == 1024))
                                                         : (sweep3d_supported(L) && (v0 == 1 || v0 == 2 || v0 == 4 ||
                                                                                     v0 == 8 || v0 == 16));
                     if (ok) set_tuned_shape(k, L, m, n, Shape{{v0, v1, v2}});
@@ -358,8 +326,8 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
     StreamCtx &c = ctx_for(s);
     const Key key = make_key(desc->seed);
     Shape known;
-    for (auto &kv : count)
-        if ((rc = tune_small2d(c, s, kv.first, ea, kv.second, key))) return rc;
+    if (whole2d && !tuned_shape(kShapeWhole2d, desc->L, model, desc->n_rep, &known))
+        if ((rc = tune_whole2d(c, s, desc->L, ea, desc->n_rep, key))) return rc;
     if (band2d && !tuned_shape(kShapeBand2d, desc->L, 0, desc->n_rep, &known))
         if ((rc = tune_band2d(c, s, plan.b, key))) return rc;
     if (pass3d && !tuned_shape(kShapePass3d, desc->L, model, desc->n_rep, &known))
@@ -373,15 +341,11 @@ int smc_autotune(const smc_desc *desc, const char *cache_path, void *stream) {
         FILE *f = fopen(cache_path, "w");
         if (!f) return fail(SMC_EINVAL, "cannot write the autotune cache %s", cache_path);
         fprintf(f, "# spinmc autotune cache: device kind edge model(0 Ising, 1 EA) replicas v0 v1 v2\n"
-                   "# u2d: workgroup size of the whole-lattice 2D sweep (replicas 0: any); band2d: rows per band of\n"
+                   "# u2d: most threads of a workgroup that holds a whole 2D lattice; band2d: rows per band of\n"
                    "# the one-pass 2D sweep; pass3d: rows per strip, segments per thread, planes per z segment of\n"
                    "# the one-pass 3D sweep; half3d: rows per thread of the 3D half-sweeps\n");
         for (const std::string &l : keep) fputs(l.c_str(), f);
         std::lock_guard<std::mutex> lk(g_tune_mutex);
-        for (const auto &kv : g_tuned)
-            if (std::get<0>(kv.first) == dev)
-                fprintf(f, "%s u2d %d %d 0 %d 0 0\n", tag.c_str(), std::get<1>(kv.first), std::get<2>(kv.first),
-                        kv.second);
         for (const auto &kv : g_shapes)
             if (std::get<0>(kv.first) == dev)
                 fprintf(f, "%s %s %d %d %d %d %d %d\n", tag.c_str(), kKindName[std::get<1>(kv.first)],
