@@ -331,12 +331,16 @@ int smc_kernel_timing_enable(int enable);
 int smc_kernel_timing_read(double *elapsed_ms, int64_t *launches);
 
 /*
- * How smc_pt_sweep_swap will execute: the number of kernel launches (at most)
- * for a call of n_steps steps and the name of the sweep kernel (a static string).
- * 3D lattices of edge 16 with n_temps <= 32 (EA: rep_per_sample a multiple
- * of n_temps) run all steps of a call in one launch, one workgroup per chain
- * with the chain resident in LDS; other shapes take three launches per step
- * (two half-sweeps and the exchange round) plus two.  No device work.
+ * How smc_pt_sweep_swap will execute, for 16-byte aligned spins and
+ * couplings: the number of kernel launches (at most) for a call of n_steps
+ * steps and the name of the sweep kernel (a static string; as in
+ * smc_sweep_plan). 3D lattices of edge 16 with n_temps <= 32 (EA:
+ * rep_per_sample a multiple of n_temps), and of the other small edges where
+ * an estimate says so, run all steps of a call in one launch, one workgroup
+ * per chain with the chain resident in LDS; the general path takes 2 m
+ * launches per step, one for its energy sums where a replica has 16 and more
+ * workgroups and one for the exchange round, plus two, and two more around a
+ * packed copy.  No device work.
  */
 int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, int32_t *launches,
                 const char **kernel_name);
@@ -370,8 +374,8 @@ int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
                   int32_t n_sweeps, int32_t word_bits, int64_t *dE_accum, void *stream);
 
 /*
- * How smc_msc_sweep will execute: the number of sweep-kernel launches for a
- * call of n_sweeps sweeps and the sweep kernel's name (a static string),
+ * How smc_msc_sweep will execute: the number of sweep-kernel launches (at most)
+ * for a call of n_sweeps sweeps and the sweep kernel's name (a static string),
  * for aligned buffers.  The same argument checks as smc_msc_sweep on desc
  * and word_bits; no device work.
  */

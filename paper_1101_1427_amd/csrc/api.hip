@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <functional>
 #include <map>
 #include <mutex>
@@ -201,6 +202,8 @@ bool small2d_enabled() {
 // replica and launch they add to the caller's total directly (16 additions
 // to one address take about a microsecond, the collecting launch takes
 // more); otherwise each keeps a slot, collected once by finish().
+constexpr int kFewGroups = 16;
+
 struct CallTally {
     Tally t{nullptr, nullptr, 0};
     int n_rep = 0, groups = 0;
@@ -210,7 +213,7 @@ struct CallTally {
         groups = groups_per_rep;
         t.total = total;
         t.first = 1;
-        if (!total || groups < 16) return SMC_OK;
+        if (!total || groups < kFewGroups) return SMC_OK;
         void *p = nullptr;
         if (int rc = ensure(c, kTallySlots, sizeof(int64_t) * (size_t)n_rep * (size_t)groups, &p)) return rc;
         t.slots = (int64_t *)p;
@@ -236,15 +239,15 @@ struct CallTally {
 // half-sweeps.  So does a call of one sweep unless the lattice fits in LDS as a whole.
 // SPINMC_BANDS2D=0 keeps the half-sweeps (same results), and so does
 // SPINMC_PT_SPLIT2D=0 in tempering (even is false there).
-bool use_bands2d(const smc_desc *d, const SweepArgs &a, int32_t n_sweeps, bool even, BandShape *sh) {
+bool use_bands2d(const smc_desc *d, int32_t n_sweeps, bool even, BandShape *sh) {
     const char *env = getenv("SPINMC_BANDS2D");
-    if ((env && env[0] == '0') || a.b.dim != 2 || a.b.L <= 0) return false;
+    if ((env && env[0] == '0') || d->dim != 2 || d->L <= 0 || d->model == SMC_HEISENBERG) return false;
     const bool forced = env && env[0] == '1';
     if (!forced && small2d_shape(d) && !small2d_enabled()) return false;
     const char *split = getenv("SPINMC_PT_SPLIT2D");
     if (!forced && !even && split && split[0] == '0') return false;
-    if (!bands2d_shape(a.b.L, a.b.n_rep, a.coup != nullptr, n_sweeps, even, sh)) return false;
-    return forced || sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)a.b.n_rep * (double)a.b.N);
+    if (!bands2d_shape(d->L, d->n_rep, d->model == SMC_EA, n_sweeps, even, sh)) return false;
+    return forced || sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)d->n_rep * (double)sites(2, d->L));
 }
 
 // Edges that the one-pass kernel (lattice2d.hip) serves: up to 2^25 sites and edge
@@ -451,6 +454,44 @@ int run_pt_pairs3d(StreamCtx &c, hipStream_t s, const SweepArgs &a, Pairs3dArgs 
     return SMC_OK;
 }
 
+// Where the steps of a tempering call run.  The packed copy and the bands give way to the
+// half-sweeps where there is no room for their scratch.
+enum PtRoute { kPtSmall3d, kPtSplit2d, kPtBins2d, kPtPairs3d, kPtBands2d, kPtHalves };
+
+PtRoute pt_route(const smc_desc *d, const void *spins, const int8_t *coup, const std::vector<ThrRow> &rows, int n_temps,
+                 int n_chains, int32_t n_steps, int m, BandShape *sh) {
+    if (use_small3d_pt(d, n_temps, n_chains)) return kPtSmall3d;
+    const bool bands = use_bands2d(d, m, false, sh);
+    if (use_pt_split2d(d, spins, rows) && !(bands && bands_before_lattice2d(d, m))) return kPtSplit2d;
+    // (few replicas: bands of their rows give more workgroups than a bin each)
+    if (use_uneven2d(d, spins, coup, rows) &&
+        !(bands && sh->ns_per_sweep * m < bins2d_ns(d->L, d->n_rep) * m + 3500.0))
+        return kPtBins2d;
+    if (use_pairs3d(d, (int64_t)n_steps * m)) return kPtPairs3d;
+    return bands ? kPtBands2d : kPtHalves;
+}
+
+// The most launches of a tempering call of n_steps steps of m sweeps on a route.
+int64_t pt_launches(PtRoute route, const Batch &b, const SweepArgs &a, const BandShape &sh, int64_t n_steps, int64_t m) {
+    // per step: the sweeps, the sums of 16 and more workgroups collected, the exchange round
+    auto steps = [&](int64_t sweeps, int groups) { return n_steps * (sweeps + (groups >= kFewGroups ? 1 : 0) + 1); };
+    const int64_t halves = 2 + steps(2 * m, half_sweep_groups(a));  // prepare, finish
+    switch (route) {
+        case kPtSmall3d: return 1;
+        // prepare, zero, to split; per step: thresholds, m sweeps, collect, add, exchange; from split, copy, finish
+        case kPtSplit2d: return 6 + n_steps * (m + 4);
+        // prepare, finish; per step the launches of every edge's bins and, of many bins, the exchange round
+        case kPtBins2d: return 2 + n_steps * (bins2d_launches(b.n_rep) + 1);
+        // prepare, pack, unpack, finish
+        case kPtPairs3d:
+            return std::max(halves, 4 + steps(2 * m, pairs3d_groups(b.L, pairs3d_planes(b.L, b.n_rep))));
+        // prepare, a copy back, finish
+        case kPtBands2d:
+            return std::max(halves, 3 + steps(bands2d_launches(sh, (int)m, false), bands2d_groups(b.L, sh)));
+        default: return halves;
+    }
+}
+
 // The sweeps of a call on the general path.
 int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps,
                 int64_t *dE) {
@@ -462,7 +503,7 @@ int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a,
         last_error().clear();
     }
     BandShape sh;
-    if (use_bands2d(desc, a, n_sweeps, true, &sh)) {
+    if (use_bands2d(desc, n_sweeps, true, &sh)) {
         void *other = nullptr;
         if (sh.whole || ensure(c, kBands2d, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
             return run_bands2d(c, s, a, sh, other, sweep0, n_sweeps, dE);
@@ -592,6 +633,16 @@ int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, in
     const int rows_n = pt->beta_per_chain ? pt->n_chains : 1;
     std::vector<ThrRow> all_rows((size_t)rows_n * pt->n_temps);
     for (size_t k = 0; k < all_rows.size(); ++k) all_rows[k] = threshold_row(pt->beta[k], desc->dim);
+    SweepArgs a;
+    memset(&a, 0, sizeof a);
+    a.b = plan.b;
+    a.min_L = plan.min_L;
+    a.max_L = plan.max_L;
+    BandShape sh;
+    const PtRoute route = pt_route(desc, nullptr, nullptr, all_rows, pt->n_temps,
+                                   std::max(1, desc->n_rep / pt->n_temps), n_steps, m, &sh);
+    const int64_t most = n_steps > 0 ? pt_launches(route, plan.b, a, sh, n_steps, m) : 0;
+    *launches = (int32_t)std::min<int64_t>(most, INT32_MAX);
     const bool fits = use_pt3d(desc, pt->n_temps);
     bool fits2d = !fits && desc->dim == 2 && (desc->model == SMC_ISING || desc->model == SMC_EA);
     if (fits2d) {
@@ -606,21 +657,10 @@ int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, in
             fits2d = r.m[1].x <= 0xFFFFu && r.m[2].x <= 0xFFFFu;
         }
     }
-    if (fits) {
-        *launches = n_steps > 0 ? 1 : 0;
-        *kernel_name = "k_pt3d_chain";
-    } else if (use_pt_split2d(desc, (const void *)nullptr, all_rows)) {
-        // prepare, zero, to split; per step: thresholds, m sweeps, collect, add, exchange; from split, copy, finish
-        *launches = n_steps > 0 ? 6 + n_steps * (m + 4) : 0;
-        *kernel_name = "k_ising2d_split";
-    } else if (fits2d) {
-        // prepare; per step the sweeps of every edge and the exchange round; finish
-        *launches = n_steps > 0 ? 2 + 2 * n_steps : 0;
-        *kernel_name = "k_uneven2d_sweep";
-    } else {
-        *launches = n_steps > 0 ? (2 * m + 1) * n_steps + 2 : 0;
-        *kernel_name = "k_half_sweep_generic";
-    }
+    *kernel_name = fits ? "k_pt3d_chain"
+                   : use_pt_split2d(desc, (const void *)nullptr, all_rows) ? "k_ising2d_split"
+                   : fits2d ? "k_uneven2d_sweep"
+                            : "k_half_sweep_generic";
     return SMC_OK;
 }
 
@@ -776,7 +816,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.thr = (const ThrRow *)p;
     BandShape sh;
     if (use_lattice2d(desc, spins, rows) &&
-        !(bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, a, n_sweeps, true, &sh))) {
+        !(bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, n_sweeps, true, &sh))) {
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);
         void *pp = nullptr;
@@ -1322,7 +1362,9 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     void *thr = nullptr, *bdev = nullptr, *E64 = nullptr, *rowrep = nullptr;
     if ((rc = upload(c, s, kTables, rows.data(), sizeof(ThrRow) * rows.size(), &thr))) return rc;
     if ((rc = upload(c, s, kBeta, pt->beta, sizeof(double) * rows.size(), &bdev))) return rc;
-    if (use_small3d_pt(desc, n, pt->n_chains)) {
+    BandShape sh;
+    const PtRoute route = pt_route(desc, spins, couplings, rows, n, pt->n_chains, n_steps, m, &sh);
+    if (route == kPtSmall3d) {
         // every step of the call in one launch, a workgroup per chain
         Small3dArgs sa;
         memset(&sa, 0, sizeof sa);
@@ -1371,21 +1413,17 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     a.thr = (const ThrRow *)thr;
     a.row_of_rep = (const int32_t *)rowrep;
 
-    BandShape sh;
-    const bool bands = use_bands2d(desc, a, m, false, &sh);
-    if (use_pt_split2d(desc, spins, rows) && !(bands && bands_before_lattice2d(desc, m)))
+    if (route == kPtSplit2d)
         return run_pt_split2d(c, s, desc, spins, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
-    // (few replicas: bands of their rows give more workgroups than a bin each)
-    if (use_uneven2d(desc, spins, couplings, rows) &&
-        !(bands && sh.ns_per_sweep * m < bins2d_ns(desc->L, desc->n_rep) * m + 3500.0))
+    if (route == kPtBins2d)
         return run_uneven2d(c, s, desc, spins, couplings, sw, (const ThrRow *)thr, energy, step0, n_steps, m);
-    if (use_pairs3d(desc, (int64_t)n_steps * m)) {
+    if (route == kPtPairs3d) {
         Pairs3dArgs pa;
         if (pairs3d_args(c, a, &pa) == SMC_OK)
             return run_pt_pairs3d(c, s, a, pa, sw, energy, step0, n_steps, m);
         last_error().clear();
     }
-    if (bands) {
+    if (route == kPtBands2d) {
         void *other = nullptr;
         if (sh.whole || ensure(c, kBands2d, (size_t)desc->n_rep * (size_t)plan.b.N, &other) == SMC_OK)
             return run_pt_bands2d(c, s, a, sh, other, sw, energy, step0, n_steps, m);

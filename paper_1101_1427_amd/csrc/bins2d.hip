@@ -47,6 +47,7 @@ using namespace halves;
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
+constexpr int kMost = (1 << 23) - 1;     // bins of a launch: fewer than 2^32 work-items
 constexpr size_t kBinBytes = 36 * 1024;  // four workgroups and their tables in 160 KB
 constexpr size_t kSmallBin = 10 * 1024;  // most bytes of a bin of several replicas
 
@@ -329,6 +330,8 @@ double bins2d_ns(int L, int n_rep) {
     return 2.0 * std::max(700.0 * rounds * ((n_rep + 1023) / 1024), 1.3 * per_cu);
 }
 
+int bins2d_launches(int n_bins) { return (n_bins + kMost - 1) / kMost; }
+
 hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_in, bool raw_out, hipStream_t s) {
     if (a.sweeps < 1 || ((!raw_in || !raw_out) && !a.packed)) return hipErrorInvalidValue;
     const uint32_t one2 = 0x00010001u;
@@ -337,8 +340,6 @@ hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_i
                                  : (a.swap ? k_bins2d<false, true> : k_bins2d<false, false>);
     if (lds > 60000)
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBinBytes);
-    // (a launch has fewer than 2^32 work-items)
-    constexpr int kMost = (1 << 23) - 1;
     for (int first = 0; first < n_bins; first += kMost) {
         Bins2dArgs part = a;
         part.bins += first;

@@ -54,6 +54,8 @@ struct Bins2dArgs {
 size_t make_bins2d(const std::vector<smc_inst> &rows, std::vector<Bin2d> *bins, std::vector<int32_t> *work);
 // Estimate of a sweep's time (ns) for a uniform batch.
 double bins2d_ns(int L, int n_rep);
+// Launches for so many bins (of fewer than 2^32 work-items each).
+int bins2d_launches(int n_bins);
 // raw_in: from the caller's spins and couplings (else from the packed copy);
 // raw_out: to the caller's spins.
 hipError_t launch_bins2d(const Bins2dArgs &a, int n_bins, size_t lds, bool raw_in, bool raw_out, hipStream_t s);
