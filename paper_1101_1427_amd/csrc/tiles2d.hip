@@ -450,7 +450,7 @@ bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape
             if (all && all % parts) continue;
             const int words = all / parts;
             for (int per_cu : {1, 2, 4, 8}) {
-                const int strips = 256 * per_cu / std::min(256 * 8, n_rep * parts);
+                const int strips = 256 * per_cu / (int)std::min<int64_t>(256 * 8, (int64_t)n_rep * parts);
                 if (strips > 0) offer(std::max(2, (L + strips - 1) / strips), words, sweeps);
             }
             for (int rows : {8, 16, 32, 64, 128})

@@ -38,6 +38,12 @@ def test_tiles_of_many_lattices(L, n_sweeps):
         assert sh.threads >= 64 and sh.threads % 64 == 0 and n_rep * tiles * sh.threads < 1 << 32, (L, n_rep, sh.threads)
 
 
+def test_many_lattices_do_not_divide_by_zero():
+    """The parts of all rows, 16 of each of 2^28 lattices, are a multiple of 2^32; no shape serves the call
+    (64 threads of each lattice are more than a launch has)."""
+    assert _shape(256, 1 << 28, False, 10) is None
+
+
 @pytest.mark.gpu
 def test_sweep_of_2_22_lattices():
     """2^22 Ising lattices of 128^2 (69 GB), a thread per word of each: as many work-items as no launch has."""
