@@ -493,8 +493,9 @@ int64_t pt_launches(PtRoute route, const Batch &b, const SweepArgs &a, const Ban
 }
 
 // The sweeps of a call on the general path.
+// bands: the shape of the bands, where the caller has asked for it.
 int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a, uint64_t sweep0, int32_t n_sweeps,
-                int64_t *dE) {
+                int64_t *dE, const BandShape *bands = nullptr) {
     if (use_small3d(desc) && !(desc->L % 16 == 0 && sweep3d_asked_for()))
         return run_small3d(s, a, sweep0, n_sweeps, dE);
     if (use_pairs3d(desc, n_sweeps)) {
@@ -503,7 +504,8 @@ int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a,
         last_error().clear();
     }
     BandShape sh;
-    if (use_bands2d(desc, n_sweeps, true, &sh)) {
+    if (bands) sh = *bands;
+    if (bands || use_bands2d(desc, n_sweeps, true, &sh)) {
         void *other = nullptr;
         if (sh.whole || ensure(c, kBands2d, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
             return run_bands2d(c, s, a, sh, other, sweep0, n_sweeps, dE);
@@ -815,8 +817,9 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     if ((rc = upload(c, s, kTables, rows.data(), sizeof(ThrRow) * rows.size(), &p))) return rc;
     a.thr = (const ThrRow *)p;
     BandShape sh;
-    if (use_lattice2d(desc, spins, rows) &&
-        !(bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, n_sweeps, true, &sh))) {
+    const bool lattice2d = use_lattice2d(desc, spins, rows);
+    const bool bands = lattice2d && bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, n_sweeps, true, &sh);
+    if (lattice2d && !bands) {
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);
         void *pp = nullptr;
@@ -923,7 +926,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         timer.finish();
         return tally.finish(s);
     }
-    return run_generic(c, s, desc, a, sweep0, n_sweeps, dE_accum);
+    return run_generic(c, s, desc, a, sweep0, n_sweeps, dE_accum, bands ? &sh : nullptr);
 }
 
 int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, const double *beta, uint64_t sweep0,

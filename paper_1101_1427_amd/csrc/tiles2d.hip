@@ -431,30 +431,66 @@ size_t bands2d_lds(int cells) { return 8 * (size_t)cells + 8 * kPad; }
 bool bands2d_shape(int L, int n_rep, bool ea, int n_sweeps, bool even, BandShape *out) {
     BandShape best;
     const int all = L % 16 == 0 ? L / 16 : 0;  // pieces per row, where tiles are cut along rows
+    // (of shapes with the same estimate the one with fewer sweeps per launch; the whole lattice before all)
+    bool whole_first = false;
     auto offer = [&](int rows, int words, int sweeps) {
         BandShape sh;
         sh.rows = std::min(rows, L);
         sh.words = words;
         sh.sweeps = sweeps;
         sh.whole = rows >= L && words >= all;
-        if (complete(sh, L, n_rep, ea, n_sweeps, even) && (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep)) best = sh;
+        if (complete(sh, L, n_rep, ea, n_sweeps, even) &&
+            (best.rows == 0 || sh.ns_per_sweep < best.ns_per_sweep ||
+             (sh.ns_per_sweep == best.ns_per_sweep && !whole_first && sweeps < best.sweeps))) {
+            best = sh;
+            whole_first = false;
+        }
     };
     offer(L, all, std::min(n_sweeps, 256));
-    // no tile takes less than its launches (8 sweeps each at most) and the shortest half-sweeps
-    const int fewest = std::max((n_sweeps + 7) / 8, even ? 2 : 1);
-    const bool search = best.rows == 0 || best.ns_per_sweep > 5000.0 * fewest / n_sweeps + 2.0 * 340.0;
-    for (int sweeps : {1, 2, 3, 4, 5, 6, 8}) {
-        if (!search || sweeps > (even ? (n_sweeps + 1) / 2 : n_sweeps)) continue;
-        // rows that give each compute unit 1, 2, 4 or 8 tiles, and a few sizes
+    whole_first = best.rows > 0;
+    // The search would take as long on the host as a short call on the chip, so what cannot win
+    // is left out before its estimate is made: nothing takes less than its launches, its traffic and the
+    // shortest half-sweeps or its updates (the figures are those of the estimate).
+    const double slower = all ? 1.0 : 1.2, shortest = 340.0 * slower;
+    const double kept = (ea ? 0.75 : 0.68) * slower, in_lds = (ea ? 1.2 : 1.1) * slower;
+    const double traffic = 16.0 * (ea ? 4.0 : 2.0) / 20.0;
+    const int most = all ? 4 : 2;
+    const auto beaten = [&](double least) { return best.rows > 0 && least * (1.0 - 1e-9) > best.ns_per_sweep; };
+    for (int sweeps : {8, 6, 5, 4, 3, 2, 1}) {
+        if (sweeps > (even ? (n_sweeps + 1) / 2 : n_sweeps)) continue;
+        BandShape any;
+        any.sweeps = sweeps;
+        const int launches = bands2d_launches(any, n_sweeps, even);
+        const double per_sweep = (double)launches / n_sweeps;
+        if (launches > n_sweeps || beaten(5000.0 * per_sweep + 2.0 * shortest)) continue;
         for (int parts = 1; parts <= std::max(all, 1); ++parts) {
             if (all && all % parts) continue;
-            const int words = all / parts;
+            const int words = all / parts, K = all ? words + (parts > 1 ? 2 : 0) : bands2d_pieces(L);
+            const int room = (int)((kMaxLdsBytes - 1024) / (8 * (size_t)K));  // rows in LDS
+            // (of all heights: the sites once, with the halos of the tallest tiles)
+            const double each = n_rep / 256.0 * parts * K * (1.0 + (room < L ? 2.0 * sweeps / room : 0.0)) * L;
+            if (beaten((5000.0 + each * traffic) * per_sweep + 2.0 * each * kept)) continue;
+            int last = 0;
+            auto consider = [&](int rows) {
+                rows = std::min(rows, L);
+                const int halo = rows < L ? 2 * sweeps : 0, R = rows + 2 * halo;
+                if (rows == last || R > room) return;
+                last = rows;
+                const int64_t per_cu = ((int64_t)n_rep * parts * ((L + rows - 1) / rows) + 255) / 256;
+                const double memory = per_cu * R * K * traffic;
+                const double at_once = std::min<int64_t>(per_cu, kMaxLdsBytes / bands2d_lds(R * K));
+                const double piece = (R + most - 1) / most * K <= kMaxThreads ? kept : in_lds;
+                const double half = std::max(shortest * per_cu / at_once, per_cu * (rows + halo) * K * piece);
+                if (!beaten((5000.0 + memory) * per_sweep + 2.0 * half)) offer(rows, words, sweeps);
+            };
+            // rows that give each compute unit 1, 2, 4 or 8 tiles, and a few sizes
+            const int strips_of = (int)std::min<int64_t>(256 * 8, (int64_t)n_rep * parts);
             for (int per_cu : {1, 2, 4, 8}) {
-                const int strips = 256 * per_cu / (int)std::min<int64_t>(256 * 8, (int64_t)n_rep * parts);
-                if (strips > 0) offer(std::max(2, (L + strips - 1) / strips), words, sweeps);
+                const int strips = 256 * per_cu / strips_of;
+                if (strips > 0) consider(std::max(2, (L + strips - 1) / strips));
             }
             for (int rows : {8, 16, 32, 64, 128})
-                if (rows < L && (!all || rows == 32 || rows == 128)) offer(rows, words, sweeps);
+                if (rows < L && (!all || rows == 32 || rows == 128)) consider(rows);
         }
     }
     const char *er = getenv("SPINMC_BANDS2D_ROWS"), *es = getenv("SPINMC_BANDS2D_SWEEPS");

@@ -17,11 +17,11 @@ class BandShape(C.Structure):
                 ("ns_per_sweep", C.c_double)]
 
 
-def _shape(L, n_rep, ea, n_sweeps):
+def _shape(L, n_rep, ea, n_sweeps, even=True):
     f = S.lib()["_ZN3smc13bands2d_shapeEiibibPNS_9BandShapeE"]
     f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_int, C.c_bool, C.c_int, C.c_bool, C.c_void_p]
     sh = BandShape()
-    return sh if f(L, n_rep, ea, n_sweeps, True, C.byref(sh)) else None
+    return sh if f(L, n_rep, ea, n_sweeps, even, C.byref(sh)) else None
 
 
 @pytest.mark.parametrize("L", [16, 48, 96, 112, 128, 192, 256, 100, 514])
