@@ -16,8 +16,11 @@
  * - Array arguments marked DEVICE are device pointers owned by the caller
  *   (e.g. torch tensors on the current HIP device); arrays marked HOST are
  *   read during the call only.  The library never frees caller memory.  It
- *   keeps internal device scratch (threshold tables, ping-pong buffers),
+ *   keeps internal device scratch per stream (threshold tables, and one
+ *   buffer for the second lattice or packed copy of the call that needs most),
  *   allocated on first use and grown as needed; SMC_ENOMEM if that fails.
+ *   Where sweeps can do without such a copy, in place, they do when it would
+ *   take more than half of the memory that is free.
  * - `stream` is a hipStream_t (NULL = the default stream).  Every call is
  *   asynchronous with respect to the host on that stream; its results are
  *   valid once the stream has reached the call.

@@ -75,7 +75,7 @@ int run_uneven2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, void *spins,
     // Between the steps of a call the replicas stay in a packed copy; without
     // room for it every step reads and writes the caller's arrays.
     const Bin2d &end = bins.back();
-    if (n_steps > 1 && ensure(c, kBinsPacked, (size_t)(end.packed + (int64_t)end.count * end.L * end.L / 2), &pp)) {
+    if (n_steps > 1 && ensure_spare(c, (size_t)(end.packed + (int64_t)end.count * end.L * end.L / 2), &pp)) {
         last_error().clear();
         pp = nullptr;
     }
@@ -400,7 +400,7 @@ bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
 int pairs3d_args(StreamCtx &c, const SweepArgs &a, Pairs3dArgs *p) {
     void *q = nullptr;
     const size_t bytes = pairs3d_bytes(a.b.L, a.b.n_rep);
-    if (int rc = ensure(c, kPairs3d, bytes, &q)) return rc;
+    if (int rc = ensure_spare(c, bytes, &q)) return rc;
     p->packed = (uint32_t *)q;
     p->rep_per_sample = a.b.rep_per_sample;
     p->thr = a.thr;
@@ -507,7 +507,7 @@ int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a,
     if (bands) sh = *bands;
     if (bands || use_bands2d(desc, n_sweeps, true, &sh)) {
         void *other = nullptr;
-        if (sh.whole || ensure(c, kBands2d, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
+        if (sh.whole || ensure_spare(c, (size_t)a.b.n_rep * (size_t)a.b.N, &other) == SMC_OK)
             return run_bands2d(c, s, a, sh, other, sweep0, n_sweeps, dE);
         last_error().clear();  // no room for a second lattice: the half-sweeps need none
     }
@@ -766,7 +766,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         void *pp = nullptr;
         const size_t bytes = (size_t)desc->n_rep * 3 * sizeof(float) * (size_t)plan.b.N;
         bool tiled = use_heis3d_tiled(desc);
-        if (tiled && ensure(c, kHeisPing, bytes, &pp)) {
+        if (tiled && ensure_spare(c, bytes, &pp)) {
             last_error().clear();  // no room for a second lattice: the half-sweeps need none
             tiled = false;
         }
@@ -823,7 +823,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);
         void *pp = nullptr;
-        if ((rc = ensure(c, kPingPong, 2 * bytes, &pp))) return rc;
+        if ((rc = ensure(c, kLattices, 2 * bytes, &pp))) return rc;
         uint8_t *A = (uint8_t *)pp, *B = A + bytes;
         // energy changes: per-wave partial sums over the call, collected once at the end
         int64_t *part = nullptr;
@@ -895,7 +895,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             // a second buffer; an odd count ends with one copy back
             const size_t bytes = (size_t)desc->n_rep * (size_t)plan.b.N;
             void *q = nullptr;
-            if ((rc = ensure(c, kPass3d, bytes, &q))) return rc;
+            if ((rc = ensure(c, kLattices, bytes, &q))) return rc;
             int8_t *A = (int8_t *)spins, *B = (int8_t *)q;
             Shape shape{{0, 0, 0}};
             if (!pass3d_launch_shape(desc->L, packed != nullptr, desc->n_rep, &shape))
@@ -1278,7 +1278,7 @@ int run_pt_split2d(StreamCtx &c, hipStream_t s, const smc_desc *desc, void *spin
     const size_t slots = lattice2d_de_slots(L, n_rep);
     if (slots == 0) return fail(SMC_EINVAL, "no band shape for L=%d", L);
     void *pp = nullptr, *q = nullptr, *tr = nullptr, *dd = nullptr, *op = nullptr;
-    if ((rc = ensure(c, kPingPong, 2 * bytes, &pp))) return rc;
+    if ((rc = ensure(c, kLattices, 2 * bytes, &pp))) return rc;
     if ((rc = ensure(c, kL2dPart, slots * sizeof(int64_t), &q))) return rc;
     if ((rc = ensure(c, kPtThr, sizeof(ThrRow) * (size_t)n_rep, &tr))) return rc;
     if ((rc = ensure(c, kPtDelta, sizeof(int64_t) * (size_t)n_rep, &dd))) return rc;
@@ -1428,7 +1428,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     }
     if (route == kPtBands2d) {
         void *other = nullptr;
-        if (sh.whole || ensure(c, kBands2d, (size_t)desc->n_rep * (size_t)plan.b.N, &other) == SMC_OK)
+        if (sh.whole || ensure_spare(c, (size_t)desc->n_rep * (size_t)plan.b.N, &other) == SMC_OK)
             return run_pt_bands2d(c, s, a, sh, other, sw, energy, step0, n_steps, m);
         last_error().clear();  // no room for a second lattice: the half-sweeps need none
     }

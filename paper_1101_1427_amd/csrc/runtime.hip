@@ -89,6 +89,21 @@ int ensure(StreamCtx &c, Slot slot, size_t bytes, void **out) {
     return SMC_OK;
 }
 
+bool spare_fits(size_t bytes, size_t held, size_t free_bytes) {
+    return bytes <= held || bytes <= (free_bytes + held) / 2;
+}
+
+int ensure_spare(StreamCtx &c, size_t bytes, void **out) {
+    const size_t held = c.dev[kLattices].bytes;
+    if (bytes > held) {
+        size_t free_bytes = 0, total = 0;
+        SMC_HIP(hipMemGetInfo(&free_bytes, &total));
+        if (!spare_fits(bytes, held, free_bytes))
+            return fail(SMC_ENOMEM, "a copy of %zu bytes would take more than half of the free memory", bytes);
+    }
+    return ensure(c, kLattices, bytes, out);
+}
+
 int release(StreamCtx &c, Slot slot) {
     Buffer &b = c.dev[slot];
     if (b.p) {

@@ -53,26 +53,21 @@ enum Slot {
     kEnergy64,
     kRows,
     kBeta,
-    kPingPong,
     kWork,
     kTuneSpins,
-    kHeisPing,
     kL2dPart,
     kMscSpins,
     kMscCoup,
     kMscEnergy,
     kMscGauge,
     kDcbSlots,
-    kBins2d,     // bins of the 2D tempering batches and their packed copy
-    kBinsPacked,
-    kBands2d,    // second lattice of the 2D bands
-    kPairs3d,    // packed copy of the 3D half-sweeps
+    kLattices,   // second lattices or packed copies: a call has one kind of them at most
+    kBins2d,     // bins of the 2D tempering batches
     kTallySlots, // per-workgroup sums of a sweep call
     kPtThr,
     kPtDelta,
     kPtOut,
     kBonds3d,    // bit-packed 3D EA bonds of the segment sweep
-    kPass3d,     // second lattice buffer of the one-pass 3D sweep
     kTuneA,      // scratch lattices of the launch-shape tuner
     kTuneB,
     kNumSlots
@@ -86,6 +81,11 @@ struct StreamCtx {
 StreamCtx &ctx_for(hipStream_t s);
 // Device buffer of at least `bytes` in a slot of the set.
 int ensure(StreamCtx &c, Slot slot, size_t bytes, void **out);
+// kLattices for a path that another stands in for where there is no room (SMC_ENOMEM): it is
+// not grown to more than half of the memory that is free, so that a caller who fills
+// the card with lattices keeps the rest.
+int ensure_spare(StreamCtx &c, size_t bytes, void **out);
+bool spare_fits(size_t bytes, size_t held, size_t free_bytes);
 // Frees a slot's device buffer once the set's stream has finished with it.
 int release(StreamCtx &c, Slot slot);
 // Host bytes into a slot through its pinned staging area.
