@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kMaxThreads) void k_heis_small(KArgs a) {
         if (tid == 0) {
             long long tot = 0;
             for (int w = 0; w < nt >> 6; ++w) tot += red[w];
-            a.acc[r] += tot;
+            atomicAdd((unsigned long long *)&a.acc[r], (unsigned long long)tot);
         }
     }
 }

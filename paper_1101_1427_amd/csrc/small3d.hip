@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kMaxThreads, LOG ? 8 : 4) void k_small3d(KArgs a) {
             a.b.energy[i] = (double)energy_of(st, tid);
             if (a.b.acc && tid < n - 1) a.b.acc[(int64_t)q * (n - 1) + tid] += (unsigned long long)st.acc[tid];
         } else if (a.b.dE) {
-            a.b.dE[i] += energy_of(st, tid);
+            atomicAdd((unsigned long long *)&a.b.dE[i], (unsigned long long)energy_of(st, tid));
         }
     }
 }

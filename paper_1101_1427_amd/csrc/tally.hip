@@ -10,8 +10,6 @@ namespace {
 __global__ __launch_bounds__(1024) void k_collect(const int64_t *slots, int64_t *dE, int per_rep, int assign) {
     __shared__ long long red[16];
     const int64_t *p = slots + (int64_t)blockIdx.x * per_rep;
-    // (the total before, read along with the slots)
-    const int64_t before = threadIdx.x == 0 && !assign ? dE[blockIdx.x] : 0;
     long long v = 0;
     if (per_rep <= (int)blockDim.x) {
         if ((int)threadIdx.x < per_rep) v = p[threadIdx.x];
@@ -26,7 +24,11 @@ __global__ __launch_bounds__(1024) void k_collect(const int64_t *slots, int64_t 
     if (threadIdx.x == 0) {
         long long sum = 0;
         for (int w = 0; w < (int)(blockDim.x >> 6); ++w) sum += red[w];
-        dE[blockIdx.x] = before + sum;
+        // (calls on other streams may add to the same total)
+        if (assign)
+            dE[blockIdx.x] = sum;
+        else
+            atomicAdd((unsigned long long *)&dE[blockIdx.x], (unsigned long long)sum);
     }
 }
 
