@@ -207,7 +207,7 @@ def valu_summary(db: str, command: str):
              f"{'kernel':24s} {'disp':>5s} {'VALU_insts':>11s} {'gui_cycles':>11s} {'issue':>6s} {'dual':>6s} "
              f"{'busy':>6s} {'cu':>6s}"]
     names = ("k_ising2d_split", "k_tiles2d", "k_small3d", "k_bins2d", "k_heis3d_tiled", "k_heis3d_half",
-             "k_pairs3d_half", "k_ising3d_half", "k_ising3d_pass", "k_pieces", "k_half_sweep_generic", "k_msc2d",
+             "k_pairs3d_half", "k_ising3d_half", "k_ising3d_pass", "k_half_sweep_pieces", "k_half_sweep_generic", "k_msc2d",
              "k_dcb2d_packed", "k_dcb2d", "k_dcb3d", "k_heis_dcb2d", "k_philox_bench", "k_dcb_rng")
     for k in names:
         a = acc.get(k, {})
@@ -785,6 +785,18 @@ def dcb3d(S, W, L=256, hits=(1, 10, 100), beta=0.22, flips=4e9):
     return {"workload": f"3D Ising {L}^3, beta = {beta}, one lattice, 16^3 tiles", "rows": rows}
 
 
+def sweep3d_kernel(S, b, n_sweeps: int, env) -> str:
+    """The kernel that runs a call of n_sweeps sweeps of one L^3 lattice (L a multiple of 16 from 48 on) under the
+    given environment.  smc_sweep_plan names the kernel of a call of one sweep: without a path asked for, longer
+    calls run on a packed copy (Ising from L = 512: six sweeps and more, and not L = 1024), and
+    the general path is named as a whole."""
+    if "SPINMC_SWEEP3D" in env:
+        return "k_half_sweep_pieces"
+    if env or n_sweeps < 3 or (b.model == S.ISING and b.L >= 512 and (n_sweeps < 6 or b.L >= 1024)):
+        return S.sweep_plan(b)[1]
+    return "k_pairs3d_half"
+
+
 def sweep3d(S, W, sizes=(256, 512, 1024), beta=0.2216, flips=8e9, models=("ising", "ea"), tune=True):
     """Plain 3D checkerboard sweeps (Ising, and EA with one coupling sample)
     on one L^3 lattice: ps per attempted flip for a call as it comes (the packed
@@ -828,7 +840,7 @@ def sweep3d(S, W, sizes=(256, 512, 1024), beta=0.2216, flips=8e9, models=("ising
                 ms = _timed(lambda: S.metropolis_sweep(b, spins, [beta], 2, n, couplings=coup))
                 kernel_ms, launches = S.kernel_timing_read()
                 S.kernel_timing_enable(False)
-                kernel = S.sweep_plan(b)[1]  # the path taken under this row's environment
+                kernel = sweep3d_kernel(S, b, n, env)
                 for k in env:
                     os.environ.pop(k, None)
                 ps = ms * 1e9 / (n * L ** 3)
