@@ -134,6 +134,8 @@ def _betas(beta, n: int):
 
 def _doubles(a):
     """A float64 array as a `const double *` argument (the array has to outlive the call)."""
+    if a.size and a.flags.writeable:
+        return C.c_double.from_buffer(a)  # (passed by reference; a third of the time of the address below)
     return C.byref(C.c_double.from_address(a.__array_interface__["data"][0]))
 
 

@@ -33,3 +33,18 @@ def test_only_doubles(call):
     for other in ((C.c_float * 32)(*([0.5] * 32)), C.byref(C.c_float(0.5)), 4096, C.c_void_p(4096), b"0.5"):
         with pytest.raises(C.ArgumentError):
             run(other)
+
+
+def test_forms_of_beta():
+    """A number, a list, and arrays of any kind reach the library as the same doubles."""
+    import numpy as np
+
+    b = S.Batch(S.ISING, 2, 128, 3, 1)
+    fixed = np.array([0.4, 0.5, 0.0])
+    fixed.setflags(write=False)
+    for beta in ([0.4, 0.5, 0.0], (0.4, 0.5, 0.0), fixed, np.array([0.4, 0.5, 0.0]), np.array([[0.4, 9], [0.5, 9], [0, 9]])[:, 0]):
+        assert S.dcb_plan(b, beta, 64) == "k_dcb2d"  # (a replica at beta = 0)
+        assert S.dcb_plan(b, np.asarray(beta) + 0.1, 64) == "k_dcb2d_packed"
+    assert S.dcb_plan(b, 0.4, 64) == S.dcb_plan(S.Batch(S.ISING, 2, 128, 1, 1), [0.4], 64) == "k_dcb2d_packed"
+    with pytest.raises(S.SpinMCError):
+        S.dcb_plan(S.Batch(S.ISING, 2, 128, 0, 1), [], 64)
