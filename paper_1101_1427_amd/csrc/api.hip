@@ -199,10 +199,12 @@ bool small2d_enabled() {
 }
 
 // The per-replica sums of one sweep call.  With fewer than 16 workgroups per
-// replica and launch they add to the caller's total directly (16 additions
-// to one address take about a microsecond, the collecting launch takes
-// more); otherwise each keeps a slot, collected once by finish().
-constexpr int kFewGroups = 16;
+// replica and launch, or at most 32 in all, they add to the caller's total directly
+// (the collecting launch takes 2 to 4 us: one 48^3 Ising lattice, 27 workgroups, one sweep
+// 12.1 -> 8.3 us, ten 76.9 -> 74.9); otherwise each keeps a slot, collected once by
+// finish() (four lattices of 64 workgroups each, ten sweeps: 142 us without slots, 104 with
+// them, 64 of 32 each 257 and 161).
+bool few_groups(int groups, int n_rep) { return groups < 16 || (int64_t)groups * n_rep <= 32; }
 
 struct CallTally {
     Tally t{nullptr, nullptr, 0};
@@ -213,7 +215,7 @@ struct CallTally {
         groups = groups_per_rep;
         t.total = total;
         t.first = 1;
-        if (!total || groups < kFewGroups) return SMC_OK;
+        if (!total || few_groups(groups, reps)) return SMC_OK;
         void *p = nullptr;
         if (int rc = ensure(c, kTallySlots, sizeof(int64_t) * (size_t)n_rep * (size_t)groups, &p)) return rc;
         t.slots = (int64_t *)p;
@@ -474,7 +476,7 @@ PtRoute pt_route(const smc_desc *d, const void *spins, const int8_t *coup, const
 // The most launches of a tempering call of n_steps steps of m sweeps on a route.
 int64_t pt_launches(PtRoute route, const Batch &b, const SweepArgs &a, const BandShape &sh, int64_t n_steps, int64_t m) {
     // per step: the sweeps, the sums of 16 and more workgroups collected, the exchange round
-    auto steps = [&](int64_t sweeps, int groups) { return n_steps * (sweeps + (groups >= kFewGroups ? 1 : 0) + 1); };
+    auto steps = [&](int64_t sweeps, int groups) { return n_steps * (sweeps + (few_groups(groups, b.n_rep) ? 0 : 1) + 1); };
     const int64_t halves = 2 + steps(2 * m, half_sweep_groups(a));  // prepare, finish
     switch (route) {
         case kPtSmall3d: return 1;
