@@ -70,7 +70,8 @@
  *   and with L = 16 or 32 on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
  *   in-place half-sweeps per sweep, 16 sites per thread (a pair of sites per
- *   thread where an edge is below 16), or, for uniform 3D batches of edge 4
+ *   thread where an edge is below 16, and in small batches where one is no
+ *   multiple of 16), or, for uniform 3D batches of edge 4
  *   .. 24, whole replicas held on chip for the call (tempering too, with up
  *   to 64 temperatures that fit and enough chains), or of larger edges the
  *   packed copy (calls of two and more sweeps), or, for uniform 2D batches where an
@@ -91,7 +92,7 @@
  *   SPINMC_SMALL3D=0 keeps the small 3D edges on the half-sweeps,
  *   SPINMC_PAIRS3D=0 the 3D half-sweeps on the caller's bytes (=1 takes the
  *   packed copy wherever it fits) and SPINMC_PIECES=0 a pair of sites per
- *   thread; the launch shapes of the 3D kernels asked for below keep their
+ *   thread (=1: 16 sites wherever no edge is below 16); the launch shapes of the 3D kernels asked for below keep their
  *   edges on those; SPINMC_SWEEP3D_PASS=0 keeps
  *   the two launches per sweep for
  *   every edge, =1 takes the one launch from edge 32 (SPINMC_PASS3D_TY,

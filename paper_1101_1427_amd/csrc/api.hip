@@ -640,7 +640,7 @@ int smc_pt_plan(const smc_desc *desc, const smc_pt_desc *pt, int32_t n_steps, in
     SweepArgs a;
     memset(&a, 0, sizeof a);
     a.b = plan.b;
-    a.min_L = plan.min_L;
+    a.pieces = plan.pieces;
     a.max_L = plan.max_L;
     BandShape sh;
     const PtRoute route = pt_route(desc, nullptr, nullptr, all_rows, pt->n_temps,
@@ -745,7 +745,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.spins = spins;
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
-    a.min_L = plan.min_L;
+    a.pieces = plan.pieces;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     void *p = nullptr;
@@ -1000,7 +1000,7 @@ int smc_msc_sweep(const smc_desc *desc, void *spins, const int8_t *couplings, co
     a.coup = ea ? couplings : nullptr;
     a.thr = (const ThrRow *)p;
     a.key = make_key(desc->seed);
-    a.min_L = plan.min_L;
+    a.pieces = plan.pieces;
     a.max_L = plan.max_L;
     a.row_of_rep = nullptr;
     a.rng_shift = word_bits == 64 ? 6 : 5;  // the draw group r / word_bits
@@ -1413,7 +1413,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
     a.spins = spins;
     a.coup = desc->model == SMC_EA ? couplings : nullptr;
     a.key = make_key(desc->seed);
-    a.min_L = plan.min_L;
+    a.pieces = plan.pieces;
     a.max_L = plan.max_L;
     a.thr = (const ThrRow *)thr;
     a.row_of_rep = (const int32_t *)rowrep;

@@ -310,12 +310,11 @@ hipError_t launch_init_couplings(int dim, int n_samples, const smc_inst *samples
     return hipGetLastError();
 }
 
-// A piece of 16 sites spans at most two rows when every edge is at least 16;
-// smaller edges keep a thread per pair of sites, and so does
-// SPINMC_PIECES=0 (same results).
+// SPINMC_PIECES=0: never a thread per 16 sites, =1: wherever it can (same results).
 static bool use_pieces(const SweepArgs &a) {
     const char *env = getenv("SPINMC_PIECES");
-    return a.min_L >= 16 && !(env && env[0] == '0');
+    if (env && (env[0] == '0' || env[0] == '1')) return env[0] == '1' && a.pieces != kNoPieces;
+    return a.pieces == kPieces;
 }
 
 int half_sweep_groups(const SweepArgs &a) {

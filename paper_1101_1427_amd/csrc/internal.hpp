@@ -58,6 +58,11 @@ __device__ __forceinline__ smc_inst replica_geom(const Batch &b, int r) {
     return b.inst[r];
 }
 
+// Whether the general half-sweeps of a batch take a thread per 16 sites: they cannot where
+// an edge is below 16 (kNoPieces), and a thread per pair of sites is faster where rows end
+// inside pieces and the batch is small (kFewPieces).
+enum PieceUse { kNoPieces = 0, kFewPieces = 1, kPieces = 2 };
+
 struct SweepArgs {
     Batch b;
     void *spins;
@@ -68,7 +73,8 @@ struct SweepArgs {
     Key key;
     uint32_t t;                // sweep index
     Tally tally;               // energy changes (accepted moves: Heisenberg)
-    int min_L, max_L;          // smallest and largest edge in the batch
+    int max_L;                 // largest edge in the batch
+    int pieces;                // half-sweeps by pieces of 16 sites (PieceUse)
     int rng_shift;             // the Metropolis draws of replica r use index r >> rng_shift
 };
 

@@ -312,6 +312,17 @@ void fill_uniform_samples(const smc_desc *d, Plan &plan) {
     }
 }
 
+// A piece of 16 sites spans at most two rows when every edge is at least 16.  Where rows end inside
+// pieces a thread takes half as long again as where they do not, which counts once the
+// chip is full: below 2^18 (2D) or 2^19 (3D) sites in the batch a thread per pair of sites is
+// faster (per half-sweep with one and with the other, 2D EA: one 50^2 lattice 4.4 and 3.9 us, 16
+// of 100^2 5.2 and 4.6, 64 of 100^2 5.6 and 6.0; 3D EA: one 18^3 6.2 and 4.3, one 50^3 6.2
+// and 4.7, four 6.5 and 6.1, eight 6.8 and 8.2; Ising 26^3 5.3 and 4.9, 64 of them 6.1 and 8.3).
+PieceUse piece_use(int dim, int min_L, bool ragged, int64_t all_sites) {
+    if (min_L < 16) return kNoPieces;
+    return !ragged || all_sites >= (int64_t)1 << (dim == 3 ? 19 : 18) ? kPieces : kFewPieces;
+}
+
 int validate(const smc_desc *d, bool need_coup, Plan &plan) {
     if (!d) return fail(SMC_EINVAL, "desc is NULL");
     if (d->model < SMC_ISING || d->model > SMC_HEISENBERG) return fail(SMC_EINVAL, "unknown model %d", d->model);
@@ -336,7 +347,8 @@ int validate(const smc_desc *d, bool need_coup, Plan &plan) {
         if (d->L > (d->dim == 3 ? 1024 : 65536)) return fail(SMC_EINVAL, "L too large (got %d)", d->L);
         b.N = sites(d->dim, d->L);
         if (b.N / 2 > 0xFFFFFFFFll) return fail(SMC_EINVAL, "lattice too large for 32-bit site counters");
-        plan.min_L = plan.max_L = d->L;
+        plan.max_L = d->L;
+        plan.pieces = piece_use(d->dim, d->L, d->L % 16 != 0, (int64_t)d->n_rep * b.N);
         if ((int64_t)d->n_rep * b.N * per_site > d->spins_len)
             return fail(SMC_EINVAL, "spin buffer too small: need %lld elements, have %lld",
                         (long long)((int64_t)d->n_rep * b.N * per_site), (long long)d->spins_len);
@@ -355,6 +367,9 @@ int validate(const smc_desc *d, bool need_coup, Plan &plan) {
     } else {
         if (!d->inst) return fail(SMC_EINVAL, "inst is required when L == 0");
         std::map<int32_t, smc_inst> seen;
+        int min_L = 0;
+        bool ragged = false;
+        int64_t all = 0;
         for (int r = 0; r < d->n_rep; ++r) {
             const smc_inst &g = d->inst[r];
             if (g.L % 2 || g.L < 4 || g.L > (d->dim == 3 ? 1024 : 65536))
@@ -372,8 +387,11 @@ int validate(const smc_desc *d, bool need_coup, Plan &plan) {
                 }
             }
             if (g.L > plan.max_L) plan.max_L = g.L;
-            if (r == 0 || g.L < plan.min_L) plan.min_L = g.L;
+            if (r == 0 || g.L < min_L) min_L = g.L;
+            ragged |= g.L % 16 != 0;
+            all += N;
         }
+        plan.pieces = piece_use(d->dim, min_L, ragged, all);
         for (auto &kv : seen) plan.samples.push_back(kv.second);
         plan.n_samples = (int64_t)plan.samples.size();
     }

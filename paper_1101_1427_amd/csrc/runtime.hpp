@@ -115,7 +115,8 @@ bool use_pt_split2d(const smc_desc *d, const void *spins, const std::vector<ThrR
 // --------------------------------------------------------------- validation --
 struct Plan {
     Batch b;
-    int min_L = 0, max_L = 0;
+    int max_L = 0;
+    PieceUse pieces = kNoPieces;
     int64_t n_samples = 0;
     std::vector<smc_inst> samples;  // distinct samples (EA): L, sample, -, coup_off
 };

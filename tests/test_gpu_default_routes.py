@@ -72,4 +72,5 @@ def test_tempering_on_packed_lattices(monkeypatch, L, n_temps, m):
 def test_pieces_of_3d_rows(monkeypatch, model, L):
     for name in ("SPINMC_SMALL3D", "SPINMC_PAIRS3D"):
         monkeypatch.setenv(name, "0")
+    monkeypatch.setenv("SPINMC_PIECES", "1")
     test_gpu_pieces.test_pieces_against_oracle(monkeypatch, model, 3, L, "0")
