@@ -65,7 +65,8 @@
  *   sweep that alternates between the caller's lattice and a library-held
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place, or, for
- *   calls of three and more sweeps (Ising with L >= 512: six, and L < 1024) and L >= 48, on
+ *   calls of three and more sweeps (Ising with L >= 512: six, and L < 1024) and L >= 48
+ *   that update 2^22 and more sites or make eight and more sweeps, on
  *   a library-held packed copy of half a byte per site (two launches per sweep),
  *   and with L = 16 or 32 on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two
@@ -74,7 +75,7 @@
  *   multiple of 16), or, for uniform 3D batches of edge 4
  *   .. 24, whole replicas held on chip for the call (tempering too, with up
  *   to 64 temperatures that fit and enough chains), or of larger edges the
- *   packed copy (calls of two and more sweeps), or, for uniform 2D batches where an
+ *   packed copy (calls of two and more sweeps, as above), or, for uniform 2D batches where an
  *   estimate says that it is faster, bands of rows, tiles (or a whole lattice)
  *   held on chip for several sweeps per launch, alternating with a library-held
  *   second lattice.  Small 2D batches (L a multiple of 16 up to 128, or 256

@@ -369,34 +369,6 @@ int run_small3d(hipStream_t s, const SweepArgs &a, uint64_t sweep0, int32_t n_sw
     return SMC_OK;
 }
 
-// 3D batches of edge 16 and more run calls of several sweeps on a packed copy
-// of their lattices (packing and unpacking take about as long as one
-// sweep saves two or three times over; against the one-pass kernel of Ising edges from
-// 512, five times).  Per sweep, packing included, against the kernels on the caller's
-// bytes: EA 256^3 24.0 -> 15.3 us (20 sweeps), 512^3 143 -> 82 (10), 1024^3 1000 -> 702 (6),
-// Ising 512^3 92 -> 68 (10), 768^3 290 -> 226 (6); Ising 1024^3 stays (565 and, with tuned
-// strips, 545 against 544 and more).
-// SPINMC_PAIRS3D=0 keeps the kernels on the caller's bytes (same results), and
-// so does a launch shape of those asked for in the environment.
-bool sweep3d_asked_for() {
-    for (const char *name : {"SPINMC_SWEEP3D", "SPINMC_SWEEP3D_Z", "SPINMC_SWEEP3D_PASS", "SPINMC_SWEEP3D_NT",
-                             "SPINMC_SWEEP3D_PACK"})
-        if (getenv(name)) return true;
-    return false;
-}
-
-bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
-    const char *env = getenv("SPINMC_PAIRS3D");
-    if ((env && env[0] == '0') || d->L <= 0 || (d->model != SMC_ISING && d->model != SMC_EA) ||
-        !pairs3d_supported(d->dim, d->L) || !pairs3d_launchable(d->L, d->n_rep))
-        return false;
-    if (env && env[0] == '1') return true;
-    if (d->L % 16) return n_sweeps >= 2;
-    if (sweep3d_asked_for()) return false;
-    if (d->model == SMC_ISING && pass3d_enabled(d)) return n_sweeps >= 6 && d->L < 1024;
-    return n_sweeps >= 3 && d->L >= 32;
-}
-
 // The packed copy of a call; SMC_ENOMEM (the caller's bytes serve then) if
 // there is no room for it.
 int pairs3d_args(StreamCtx &c, const SweepArgs &a, Pairs3dArgs *p) {

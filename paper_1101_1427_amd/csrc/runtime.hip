@@ -11,6 +11,7 @@
 #include <utility>
 #include <vector>
 
+#include "pairs3d.hpp"
 #include "runtime.hpp"
 #include "small3d.hpp"
 
@@ -283,6 +284,39 @@ bool use_sweep3d(const smc_desc *d, const void *spins, const int8_t *coup, const
     for (const ThrRow &r : rows)
         if (r.m[1].x > 0xFFFFu || r.m[2].x > 0xFFFFu || r.m[3].x > 0xFFFFu) return false;
     return true;
+}
+
+// 3D batches of edge 16 and more run calls of several sweeps on a packed copy
+// of their lattices (packing and unpacking take about as long as one
+// sweep saves two or three times over; against the one-pass kernel of Ising edges from
+// 512, five times).  Per sweep, packing included, against the kernels on the caller's
+// bytes: EA 256^3 24.0 -> 15.3 us (20 sweeps), 512^3 143 -> 82 (10), 1024^3 1000 -> 702 (6),
+// Ising 512^3 92 -> 68 (10), 768^3 290 -> 226 (6); Ising 1024^3 stays (565 and, with tuned
+// strips, 545 against 544 and more).
+// Short calls on small lattices are bound by their launches, of which packing and unpacking
+// are two: up to seven sweeps of fewer than 2^22 sites in all stay on the caller's bytes (three
+// of one 48^3 Ising lattice, call and wait: 60 us with the copy, 39 without; five of one 96^3
+// 90 and 66, throughput 43 and 47; eight of one 64^3 110 and 82, throughput 60 and 65).
+// SPINMC_PAIRS3D=0 keeps the kernels on the caller's bytes (same results), and
+// so does a launch shape of those asked for in the environment.
+bool sweep3d_asked_for() {
+    for (const char *name : {"SPINMC_SWEEP3D", "SPINMC_SWEEP3D_Z", "SPINMC_SWEEP3D_PASS", "SPINMC_SWEEP3D_NT",
+                             "SPINMC_SWEEP3D_PACK"})
+        if (getenv(name)) return true;
+    return false;
+}
+
+bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
+    const char *env = getenv("SPINMC_PAIRS3D");
+    if ((env && env[0] == '0') || d->L <= 0 || (d->model != SMC_ISING && d->model != SMC_EA) ||
+        !pairs3d_supported(d->dim, d->L) || !pairs3d_launchable(d->L, d->n_rep))
+        return false;
+    if (env && env[0] == '1') return true;
+    if (n_sweeps < 8 && n_sweeps * d->n_rep * sites(3, d->L) < (int64_t)1 << 22) return false;
+    if (d->L % 16) return n_sweeps >= 2;
+    if (sweep3d_asked_for()) return false;
+    if (d->model == SMC_ISING && pass3d_enabled(d)) return n_sweeps >= 6 && d->L < 1024;
+    return n_sweeps >= 3 && d->L >= 32;
 }
 
 // Tempering of a uniform 2D Ising batch on the one-pass colour-split sweep:

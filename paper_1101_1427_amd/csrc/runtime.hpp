@@ -110,6 +110,10 @@ bool use_lattice2d(const smc_desc *d, const void *spins, const std::vector<ThrRo
 bool sweep3d_shape(const smc_desc *d);
 bool pass3d_enabled(const smc_desc *d);
 bool use_sweep3d(const smc_desc *d, const void *spins, const int8_t *coup, const std::vector<ThrRow> &rows);
+// The packed copy of 3D lattices for a call of n_sweeps sweeps; a launch shape of the 3D
+// kernels on the caller's bytes asked for in the environment.
+bool use_pairs3d(const smc_desc *d, int64_t n_sweeps);
+bool sweep3d_asked_for();
 bool use_pt_split2d(const smc_desc *d, const void *spins, const std::vector<ThrRow> &rows);
 
 // --------------------------------------------------------------- validation --

@@ -59,9 +59,10 @@ def test_small_workgroups_of_whole_lattices(monkeypatch, L, threads):
 
 # edges just above and between multiples of 16; from 42 on a replica has 16 and more workgroups, whose energy
 # changes go through slots
-@pytest.mark.parametrize("L,n_temps,m", [(18, 5, 1), (20, 3, 2), (26, 3, 1), (34, 4, 2), (42, 2, 3), (50, 3, 1), (48, 3, 2)])
+@pytest.mark.parametrize("L,n_temps,m", [(18, 5, 1), (20, 3, 2), (26, 3, 1), (32, 4, 1), (34, 4, 2), (42, 2, 3), (50, 3, 1), (48, 3, 2)])
 def test_tempering_on_packed_lattices(monkeypatch, L, n_temps, m):
     monkeypatch.setenv("SPINMC_SMALL3D", "0")
+    monkeypatch.setenv("SPINMC_PAIRS3D", "1")  # (so few updates in all stay on the caller's bytes)
     b = S.Batch(S.EA, 3, L, 3 * n_temps, 1, rep_per_sample=n_temps)
     assert S.pt_plan(b, 3, n_temps, W.geometric_ladder(0.8, 2.0, n_temps), 4, sweeps_per_step=m)[0] > 4 * (2 * m + 1)
     test_gpu_pairs3d.test_pairs_tempering_against_oracle(L, n_temps, m)
@@ -74,3 +75,4 @@ def test_pieces_of_3d_rows(monkeypatch, model, L):
         monkeypatch.setenv(name, "0")
     monkeypatch.setenv("SPINMC_PIECES", "1")
     test_gpu_pieces.test_pieces_against_oracle(monkeypatch, model, 3, L, "0")
+
