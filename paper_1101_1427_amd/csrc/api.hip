@@ -571,7 +571,7 @@ int smc_sweep_plan(const smc_desc *desc, int32_t *launches_per_sweep, const char
     if (!launches_per_sweep || !kernel_name) return fail(SMC_EINVAL, "output pointers are required");
     if (desc->model == SMC_HEISENBERG) {
         *launches_per_sweep = 2;
-        if (use_heis3d_tiled(desc)) {
+        if (use_heis3d_tiled(desc, 2)) {
             *launches_per_sweep = 1;
             *kernel_name = "k_heis3d_tiled";
         } else {
@@ -739,7 +739,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         }
         void *pp = nullptr;
         const size_t bytes = (size_t)desc->n_rep * 3 * sizeof(float) * (size_t)plan.b.N;
-        bool tiled = use_heis3d_tiled(desc);
+        bool tiled = use_heis3d_tiled(desc, n_sweeps);
         if (tiled && ensure_spare(c, bytes, &pp)) {
             last_error().clear();  // no room for a second lattice: the half-sweeps need none
             tiled = false;

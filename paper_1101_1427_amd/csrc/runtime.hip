@@ -211,7 +211,7 @@ bool use_heis_small(const smc_desc *d, int64_t n_sweeps) {
 
 // ... and those with any even edge of at least 32 the one-pass tiled kernel
 // (SPINMC_HEIS_TILED=0 keeps the two half-sweep launches).
-bool use_heis3d_tiled(const smc_desc *d) {
+bool use_heis3d_tiled(const smc_desc *d, int64_t n_sweeps) {
     const char *env = getenv("SPINMC_HEIS_TILED");
     if (env && env[0] == '0') return false;
     const char *all = getenv("SPINMC_HEIS3D");
@@ -219,7 +219,12 @@ bool use_heis3d_tiled(const smc_desc *d) {
     if (d->model != SMC_HEISENBERG || d->L <= 0 || !heis3d_tiled_supported(d->dim, d->L)) return false;
     // few sites: two small half-sweep launches are as fast as the tiles' plane
     // steps (46^3: 9.7 against 11.3 us per sweep; 64^3 level, 96^3 31 against 16)
-    return heis3d_supported(d->dim, d->L) || (int64_t)d->n_rep * d->L * d->L * d->L >= (int64_t)1 << 18;
+    if (heis3d_supported(d->dim, d->L)) return true;
+    // a call of one sweep ends with a copy back, which edges that fill less than half of their
+    // tiles cannot make up for (64 of 34^3: 85 against 75 us; 64 of 40^3: 88 against 109)
+    const int64_t tiled = (d->L + 31) / 32 * 32;
+    if (n_sweeps == 1 && tiled * tiled * 10 > (int64_t)d->L * d->L * 28) return false;
+    return (int64_t)d->n_rep * d->L * d->L * d->L >= (int64_t)1 << 18;
 }
 
 // Uniform 3D Ising / EA batches with an edge of 4 .. 24 or 32 keep whole replicas

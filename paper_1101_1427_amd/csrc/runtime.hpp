@@ -98,7 +98,7 @@ ThrRow threshold_row(double beta, int dim);
 
 // ------------------------------------------------------------------ paths ----
 bool use_heis3d(const smc_desc *d);
-bool use_heis3d_tiled(const smc_desc *d);
+bool use_heis3d_tiled(const smc_desc *d, int64_t n_sweeps);
 bool use_heis_small(const smc_desc *d, int64_t n_sweeps);
 // Small 3D edges with whole replicas on chip (SPINMC_SMALL3D=0: never).
 bool use_small3d(const smc_desc *d);
