@@ -80,8 +80,9 @@
  *   held on chip for several sweeps per launch, alternating with a library-held
  *   second lattice.  Small 2D batches (L a multiple of 16 up to 128, or 256
  *   with at least 2^19 sites in the batch: "k_uneven2d_sweep") run on these
- *   bands as well, and so do calls of two and more sweeps on power-of-two
- *   edges up to 2048 (eight and more: 4096) with at most 2^25 sites in the batch.  All paths give
+ *   bands as well, and so do calls of enough sweeps (two to six, of edge
+ *   4096 eight to twelve, the more the larger the batch) on
+ *   power-of-two edges up to 4096 with at most 2^25 sites in the batch.  All paths give
  *   identical results.  Environment variables for comparisons and tuning
  *   (read at each call): SPINMC_PT3D=0, SPINMC_UNEVEN2D=0 and
  *   SPINMC_PT_SPLIT2D=0 send tempering to the general path,

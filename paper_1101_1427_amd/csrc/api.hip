@@ -252,22 +252,6 @@ bool use_bands2d(const smc_desc *d, int32_t n_sweeps, bool even, BandShape *sh) 
     return forced || sh->ns_per_sweep < 2.0 * (3500.0 + 1.2e-3 * (double)d->n_rep * (double)sites(2, d->L));
 }
 
-// Edges that the one-pass kernel (lattice2d.hip) serves: up to 2^25 sites and edge
-// 4096 the tiles are faster, because they move the lattice once per several
-// sweeps and need one launch for them (1024^2: 1.7 against 6.4 us per sweep,
-// eight of 2048^2: 20 against 33, 4096^2: 10.4 against 13.2, in calls of fewer than 8
-// sweeps 18 against 14.5); above, the one-pass kernel's fewer instructions per
-// site win (16 of 2048^2: 36.3 against 39.2, 8192^2: 34 against 40).  A launch shape
-// asked for in the environment is the one-pass kernel's.
-bool bands_before_lattice2d(const smc_desc *d, int32_t n_sweeps) {
-    for (const char *name : {"SPINMC_L2D_CHUNKS", "SPINMC_L2D_H", "SPINMC_L2D_H1", "SPINMC_L2D_H2", "SPINMC_L2D_PAD",
-                             "SPINMC_L2D_FUSE"})
-        if (getenv(name)) return false;
-    const char *env = getenv("SPINMC_BANDS2D");
-    if (env && env[0] == '1') return true;
-    return d->L <= (n_sweeps >= 8 ? 4096 : 2048) && (int64_t)d->n_rep * d->L * d->L <= (int64_t)1 << 25;
-}
-
 // Sweeps on bands, from a.spins to `other` and back, launch by launch.
 struct BandRun {
     Bands2dArgs ba;
@@ -436,7 +420,7 @@ PtRoute pt_route(const smc_desc *d, const void *spins, const int8_t *coup, const
                  int n_chains, int32_t n_steps, int m, BandShape *sh) {
     if (use_small3d_pt(d, n_temps, n_chains)) return kPtSmall3d;
     const bool bands = use_bands2d(d, m, false, sh);
-    if (use_pt_split2d(d, spins, rows) && !(bands && bands_before_lattice2d(d, m))) return kPtSplit2d;
+    if (use_pt_split2d(d, spins, rows) && !(bands && bands_before_lattice2d(d, m, true))) return kPtSplit2d;
     // (few replicas: bands of their rows give more workgroups than a bin each)
     if (use_uneven2d(d, spins, coup, rows) &&
         !(bands && sh->ns_per_sweep * m < bins2d_ns(d->L, d->n_rep) * m + 3500.0))
@@ -792,7 +776,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
     a.thr = (const ThrRow *)p;
     BandShape sh;
     const bool lattice2d = use_lattice2d(desc, spins, rows);
-    const bool bands = lattice2d && bands_before_lattice2d(desc, n_sweeps) && use_bands2d(desc, n_sweeps, true, &sh);
+    const bool bands = lattice2d && bands_before_lattice2d(desc, n_sweeps, false) && use_bands2d(desc, n_sweeps, true, &sh);
     if (lattice2d && !bands) {
         // one-pass sweeps on the colour-split layout, ping-pong between two buffers
         const size_t bytes = (size_t)desc->n_rep * lattice2d_split_bytes(desc->L);

@@ -262,6 +262,32 @@ bool use_lattice2d(const smc_desc *d, const void *spins, const std::vector<ThrRo
     return true;
 }
 
+// Edges that the one-pass kernel (lattice2d.hip) serves: up to 2^25 sites and edge
+// 4096 the tiles are faster, because they move the lattice once per several
+// sweeps and need one launch for them (1024^2: 1.7 against 6.4 us per sweep,
+// eight of 2048^2: 18.8 against 32.6, 4096^2: 9.8 against 13.3); above, the one-pass kernel's
+// fewer instructions per site win (16 of 2048^2: 36.3 against 39.2, 8192^2: 34 against 40).
+// A call needs sweeps enough for the tiles' even number of launches, the more the fuller they
+// are.  2048^2 from 2^23 sites on 3 (2 sweeps of 4 lattices 46 against 41 us, 3 of them 55 and
+// 60) and from 2^24 on 4 (3 of 6 lattices 70 and 61, 4 of 8 115 and 134); 1024^2, where the one-pass
+// kernel is a quarter faster per site, 2, 3 and from 24 2^20 on 6 (2 of 24 lattices 58 and 52, 3
+// of them 67 and 76; 5 of 32 130 and 126, 6 of them 146 and 151); 4096^2 8 and from 2^24 on 12 (two
+// lattices: 10 sweeps 212 and 208, 12 of them 242 and 249).  Tempering, where the one-pass kernel
+// needs four more launches per step, takes tiles from one sweep per step on (4096^2: 8).
+// A launch shape asked for in the environment is the one-pass kernel's.
+bool bands_before_lattice2d(const smc_desc *d, int32_t n_sweeps, bool tempering) {
+    for (const char *name : {"SPINMC_L2D_CHUNKS", "SPINMC_L2D_H", "SPINMC_L2D_H1", "SPINMC_L2D_H2", "SPINMC_L2D_PAD",
+                             "SPINMC_L2D_FUSE"})
+        if (getenv(name)) return false;
+    const char *env = getenv("SPINMC_BANDS2D");
+    if (env && env[0] == '1') return true;
+    const int64_t sites = (int64_t)d->n_rep * d->L * d->L, M = 1 << 20;
+    if (d->L > 4096 || sites > 32 * M) return false;
+    if (d->L > 2048) return n_sweeps >= (tempering || sites <= 16 * M ? 8 : 12);
+    if (tempering || sites <= 8 * M) return true;
+    return n_sweeps >= (d->L > 1024 ? (sites <= 16 * M ? 3 : 4) : (sites <= 16 * M ? 2 : sites <= 24 * M ? 3 : 6));
+}
+
 // Uniform 3D Ising / EA batches with an edge that is a multiple of 16 take
 // the segment-per-thread half-sweeps when spins (and couplings) are 16-byte
 // aligned and every threshold has a 16-bit high half; SPINMC_SWEEP3D=0 keeps

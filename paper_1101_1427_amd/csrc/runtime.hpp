@@ -107,6 +107,8 @@ bool use_small3d(const smc_desc *d);
 bool use_pt3d(const smc_desc *d, int n_temps);
 bool use_small3d_pt(const smc_desc *d, int n_temps, int n_chains);
 bool use_lattice2d(const smc_desc *d, const void *spins, const std::vector<ThrRow> &rows);
+// Whether 2D tiles come before the one-pass kernel on an edge that both serve.
+bool bands_before_lattice2d(const smc_desc *d, int32_t n_sweeps, bool tempering);
 bool sweep3d_shape(const smc_desc *d);
 bool pass3d_enabled(const smc_desc *d);
 bool use_sweep3d(const smc_desc *d, const void *spins, const int8_t *coup, const std::vector<ThrRow> &rows);
