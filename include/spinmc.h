@@ -66,7 +66,8 @@
  *   second lattice of the same size (an odd sweep count ends with one
  *   device copy back), below in two launches per sweep, in place, or, for
  *   calls of three and more sweeps (Ising with L >= 512: six, and L < 1024) and L >= 48
- *   that update 2^22 and more sites or make eight and more sweeps, on
+ *   that update 2^22 and more sites (below, edges that are no multiple of 16:
+ *   2^20) or make eight and more sweeps, on
  *   a library-held packed copy of half a byte per site (two launches per sweep),
  *   and with L = 16 or 32 on chip for the call;
  *   everything else takes the general path ("k_half_sweep_generic"): two

@@ -325,9 +325,10 @@ bool use_sweep3d(const smc_desc *d, const void *spins, const int8_t *coup, const
 // Ising 512^3 92 -> 68 (10), 768^3 290 -> 226 (6); Ising 1024^3 stays (565 and, with tuned
 // strips, 545 against 544 and more).
 // Short calls on small lattices are bound by their launches, of which packing and unpacking
-// are two: up to seven sweeps of fewer than 2^22 sites in all stay on the caller's bytes (three
-// of one 48^3 Ising lattice, call and wait: 60 us with the copy, 39 without; five of one 96^3
-// 90 and 66, throughput 43 and 47; eight of one 64^3 110 and 82, throughput 60 and 65).
+// are two: up to seven sweeps of fewer than 2^22 sites in all, of ragged rows 2^20, stay on the
+// caller's bytes (three of one 48^3 Ising lattice, call and wait: 60 us with the copy, 39
+// without; five of one 96^3 90 and 66, throughput 43 and 47; eight of one 64^3 110 and 82,
+// throughput 60 and 65; three of 32 of 26^3 EA 61 and 53, throughput 31 and 40).
 // SPINMC_PAIRS3D=0 keeps the kernels on the caller's bytes (same results), and
 // so does a launch shape of those asked for in the environment.
 bool sweep3d_asked_for() {
@@ -343,7 +344,7 @@ bool use_pairs3d(const smc_desc *d, int64_t n_sweeps) {
         !pairs3d_supported(d->dim, d->L) || !pairs3d_launchable(d->L, d->n_rep))
         return false;
     if (env && env[0] == '1') return true;
-    if (n_sweeps < 8 && n_sweeps * d->n_rep * sites(3, d->L) < (int64_t)1 << 22) return false;
+    if (n_sweeps < 8 && n_sweeps * d->n_rep * sites(3, d->L) < (int64_t)1 << (d->L % 16 ? 20 : 22)) return false;
     if (d->L % 16) return n_sweeps >= 2;
     if (sweep3d_asked_for()) return false;
     if (d->model == SMC_ISING && pass3d_enabled(d)) return n_sweeps >= 6 && d->L < 1024;

@@ -18,7 +18,7 @@ def _packed(model, L, n_rep, n):
 @pytest.mark.parametrize("model,L,n_rep,n,packed", [
     (S.ISING, 48, 1, 3, False), (S.ISING, 48, 1, 7, False), (S.ISING, 48, 1, 8, True),
     (S.EA, 64, 5, 3, False), (S.EA, 64, 6, 3, True),   # 3.9e6 and 4.7e6 updates
-    (S.EA, 50, 16, 2, False), (S.EA, 50, 17, 2, True), (S.EA, 64, 64, 2, False),
+    (S.EA, 50, 4, 2, False), (S.EA, 50, 5, 2, True), (S.EA, 64, 64, 2, False),
     (S.EA, 256, 1, 3, True), (S.ISING, 512, 1, 5, False), (S.ISING, 512, 1, 6, True), (S.ISING, 1024, 1, 100, False),
     (S.EA, 1024, 1, 3, True), (S.ISING, 14, 1000, 100, False)])
 def test_which_calls(monkeypatch, model, L, n_rep, n, packed):
