@@ -199,23 +199,27 @@ bool small2d_enabled() {
 }
 
 // The per-replica sums of one sweep call.  With fewer than 16 workgroups per
-// replica and launch, or at most 32 in all, they add to the caller's total directly
-// (the collecting launch takes 2 to 4 us: one 48^3 Ising lattice, 27 workgroups, one sweep
-// 12.1 -> 8.3 us, ten 76.9 -> 74.9); otherwise each keeps a slot, collected once by
-// finish() (four lattices of 64 workgroups each, ten sweeps: 142 us without slots, 104 with
-// them, 64 of 32 each 257 and 161).
-bool few_groups(int groups, int n_rep) { return groups < 16 || (int64_t)groups * n_rep <= 32; }
+// replica and launch, or at most 32 in all, or 256 over the launches, they add to the
+// caller's total directly (the collecting launch takes 2 to 4 us: one 48^3 Ising lattice, 27
+// workgroups, one sweep 12.1 -> 8.3 us, ten 76.9 -> 74.9; one sweep of two lattices of 64 workgroups
+// 12.7 -> 10.4, of four of 35 11.8 and 11.5, three of them 28.7 and 32.3); otherwise each keeps
+// a slot, collected once by finish() (four lattices of 64 workgroups each, ten sweeps: 142 us
+// without slots, 104 with them, 64 of 32 each 257 and 161).
+bool few_groups(int groups, int n_rep, int64_t launches) {
+    const int64_t all = (int64_t)groups * n_rep;
+    return groups < 16 || all <= 32 || all * launches <= 256;
+}
 
 struct CallTally {
     Tally t{nullptr, nullptr, 0};
     int n_rep = 0, groups = 0;
 
-    int begin(StreamCtx &c, int reps, int groups_per_rep, int64_t *total) {
+    int begin(StreamCtx &c, int reps, int groups_per_rep, int64_t launches, int64_t *total) {
         n_rep = reps;
         groups = groups_per_rep;
         t.total = total;
         t.first = 1;
-        if (!total || few_groups(groups, reps)) return SMC_OK;
+        if (!total || few_groups(groups, reps, launches)) return SMC_OK;
         void *p = nullptr;
         if (int rc = ensure(c, kTallySlots, sizeof(int64_t) * (size_t)n_rep * (size_t)groups, &p)) return rc;
         t.slots = (int64_t *)p;
@@ -289,10 +293,10 @@ struct BandRun {
 int run_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandShape &sh, void *other, uint64_t sweep0,
                 int32_t n_sweeps, int64_t *dE) {
     CallTally tally;
-    int rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), dE);
+    const int launches = bands2d_launches(sh, n_sweeps, true);
+    int rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), launches, dE);
     if (rc) return rc;
     BandRun run(a, sh, other);
-    const int launches = bands2d_launches(sh, n_sweeps, true);
     SweepTimer timer(s, launches);
     if ((rc = run.sweeps(s, sweep0, n_sweeps, launches, tally))) return rc;
     timer.finish();
@@ -309,7 +313,7 @@ int run_pt_bands2d(StreamCtx &c, hipStream_t s, const SweepArgs &a, const BandSh
     for (int32_t k = 0; k < n_steps; ++k) {
         sw.t = (uint32_t)(step0 + (uint64_t)k);
         CallTally tally;
-        if ((rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), sw.E))) return rc;
+        if ((rc = tally.begin(c, a.b.n_rep, bands2d_groups(a.b.L, sh), launches, sw.E))) return rc;
         if ((rc = run.sweeps(s, (uint64_t)sw.t * (uint64_t)m, m, launches, tally))) return rc;
         if ((rc = tally.finish(s))) return rc;
         SMC_HIP(launch_pt_swap(sw, s));
@@ -375,7 +379,7 @@ int run_pairs3d(StreamCtx &c, hipStream_t s, const SweepArgs &a, Pairs3dArgs &p,
                 int64_t *dE) {
     const int planes = pairs3d_planes(p.L, p.n_rep);
     CallTally tally;
-    int rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), dE);
+    int rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), 2 * (int64_t)n_sweeps, dE);
     if (rc) return rc;
     SMC_HIP(launch_pairs3d_pack((const int8_t *)a.spins, a.coup, p, s));
     SweepTimer timer(s, 2 * (int64_t)n_sweeps);
@@ -398,7 +402,7 @@ int run_pt_pairs3d(StreamCtx &c, hipStream_t s, const SweepArgs &a, Pairs3dArgs 
     for (int32_t k = 0; k < n_steps; ++k) {
         sw.t = (uint32_t)(step0 + (uint64_t)k);
         CallTally tally;
-        if ((rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), sw.E))) return rc;
+        if ((rc = tally.begin(c, p.n_rep, pairs3d_groups(p.L, planes), 2 * (int64_t)m, sw.E))) return rc;
         for (int j = 0; j < m; ++j) {
             p.t = sw.t * (uint32_t)m + (uint32_t)j;
             for (int col = 0; col < 2; ++col)
@@ -432,7 +436,9 @@ PtRoute pt_route(const smc_desc *d, const void *spins, const int8_t *coup, const
 // The most launches of a tempering call of n_steps steps of m sweeps on a route.
 int64_t pt_launches(PtRoute route, const Batch &b, const SweepArgs &a, const BandShape &sh, int64_t n_steps, int64_t m) {
     // per step: the sweeps, the sums of 16 and more workgroups collected, the exchange round
-    auto steps = [&](int64_t sweeps, int groups) { return n_steps * (sweeps + (few_groups(groups, b.n_rep) ? 0 : 1) + 1); };
+    auto steps = [&](int64_t sweeps, int groups) {
+        return n_steps * (sweeps + (few_groups(groups, b.n_rep, sweeps) ? 0 : 1) + 1);
+    };
     const int64_t halves = 2 + steps(2 * m, half_sweep_groups(a));  // prepare, finish
     switch (route) {
         case kPtSmall3d: return 1;
@@ -470,7 +476,7 @@ int run_generic(StreamCtx &c, hipStream_t s, const smc_desc *desc, SweepArgs &a,
         last_error().clear();  // no room for a second lattice: the half-sweeps need none
     }
     CallTally tally;
-    int rc = tally.begin(c, a.b.n_rep, half_sweep_groups(a), dE);
+    int rc = tally.begin(c, a.b.n_rep, half_sweep_groups(a), 2 * (int64_t)n_sweeps, dE);
     if (rc) return rc;
     SweepTimer timer(s, 2 * (int64_t)n_sweeps);
     for (int32_t k = 0; k < n_sweeps; ++k) {
@@ -733,7 +739,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             float *A = (float *)spins, *B = (float *)pp;
             const int planes = heis3d_tiled_planes(desc->L, desc->n_rep);
             CallTally tally;
-            if ((rc = tally.begin(c, desc->n_rep, heis3d_tiled_groups(desc->L, planes), dE_accum))) return rc;
+            if ((rc = tally.begin(c, desc->n_rep, heis3d_tiled_groups(desc->L, planes), n_sweeps, dE_accum))) return rc;
             SweepTimer timer(s, n_sweeps);
             for (int32_t k = 0; k < n_sweeps; ++k) {
                 a.t = (uint32_t)(sweep0 + (uint64_t)k);
@@ -751,7 +757,8 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         }
         const bool fast = use_heis3d(desc);
         CallTally tally;
-        if ((rc = tally.begin(c, desc->n_rep, fast ? heis3d_half_groups(desc->L) : heis_half_sweep_groups(a), dE_accum)))
+        if ((rc = tally.begin(c, desc->n_rep, fast ? heis3d_half_groups(desc->L) : heis_half_sweep_groups(a),
+                              2 * (int64_t)n_sweeps, dE_accum)))
             return rc;
         SweepTimer timer(s, 2 * (int64_t)n_sweeps);  // the renormalisations run inside the same pair
         for (int32_t k = 0; k < n_sweeps; ++k) {
@@ -859,7 +866,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
             if (!pass3d_launch_shape(desc->L, packed != nullptr, desc->n_rep, &shape))
                 return fail(SMC_EINVAL, "no strip shape for L=%d", desc->L);
             CallTally tally;
-            if ((rc = tally.begin(c, desc->n_rep, pass3d_groups(desc->L, shape), dE_accum))) return rc;
+            if ((rc = tally.begin(c, desc->n_rep, pass3d_groups(desc->L, shape), n_sweeps, dE_accum))) return rc;
             SweepTimer timer(s, n_sweeps);
             for (int32_t k = 0; k < n_sweeps; ++k) {
                 const uint32_t t = (uint32_t)(sweep0 + (uint64_t)k);
@@ -873,7 +880,7 @@ int smc_metropolis_sweep(const smc_desc *desc, void *spins, const int8_t *coupli
         }
         const int Z = sweep3d_rows(desc->L, desc->model == SMC_EA, desc->n_rep);
         CallTally tally;
-        if ((rc = tally.begin(c, desc->n_rep, sweep3d_groups(desc->L, Z), dE_accum))) return rc;
+        if ((rc = tally.begin(c, desc->n_rep, sweep3d_groups(desc->L, Z), 2 * (int64_t)n_sweeps, dE_accum))) return rc;
         SweepTimer timer(s, 2 * (int64_t)n_sweeps);
         for (int32_t k = 0; k < n_sweeps; ++k) {
             const uint32_t t = (uint32_t)(sweep0 + (uint64_t)k);
@@ -1395,7 +1402,7 @@ int smc_pt_sweep_swap(const smc_desc *desc, const smc_pt_desc *pt, void *spins, 
         const uint32_t t = (uint32_t)(step0 + (uint64_t)k);
         sw.t = t;
         CallTally tally;
-        if ((rc = tally.begin(c, desc->n_rep, half_sweep_groups(a), sw.E))) return rc;
+        if ((rc = tally.begin(c, desc->n_rep, half_sweep_groups(a), 2 * (int64_t)m, sw.E))) return rc;
         for (int j = 0; j < m; ++j) {
             a.t = t * (uint32_t)m + (uint32_t)j;
             for (int col = 0; col < 2; ++col) {

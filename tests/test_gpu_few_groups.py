@@ -1,5 +1,5 @@
 """Energy changes at the line between adding to the caller's totals directly (fewer than
-16 workgroups per replica, or at most 32 in all) and slots: equal to the measured energies."""
+16 workgroups per replica, or at most 32 in all, or 256 over the launches) and slots: equal to the measured energies."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("model,dim,L,n_rep", [
     (S.EA, 3, 40, 2), (S.EA, 3, 40, 3),        # 16 workgroups per replica: 32 and 48 in all
     (S.ISING, 3, 48, 1), (S.ISING, 3, 48, 2),  # 27: 27 and 54
-    (S.ISING, 3, 64, 1),                       # 64
+    (S.ISING, 3, 64, 1), (S.ISING, 3, 64, 2),   # 64 and, over the two launches of a sweep, 256
     (S.EA, 2, 512, 1), (S.EA, 2, 1000, 1)])
 @pytest.mark.parametrize("n", [1, 4])
 def test_sums_equal_measured_energies(monkeypatch, model, dim, L, n_rep, n):
