@@ -220,11 +220,15 @@ bool use_heis3d_tiled(const smc_desc *d, int64_t n_sweeps) {
     // few sites: two small half-sweep launches are as fast as the tiles' plane
     // steps (46^3: 9.7 against 11.3 us per sweep; 64^3 level, 96^3 31 against 16)
     if (heis3d_supported(d->dim, d->L)) return true;
-    // a call of one sweep ends with a copy back, which edges that fill less than half of their
-    // tiles cannot make up for (64 of 34^3: 85 against 75 us; 64 of 40^3: 88 against 109)
-    const int64_t tiled = (d->L + 31) / 32 * 32;
-    if (n_sweeps == 1 && tiled * tiled * 10 > (int64_t)d->L * d->L * 28) return false;
-    return (int64_t)d->n_rep * d->L * d->L * d->L >= (int64_t)1 << 18;
+    // an odd number of sweeps ends with a copy back, which edges that waste most of their tiles
+    // do not make up for in one sweep, nor, where the batch fills the chip, in three (64 of 34^3
+    // 85 against 75 and 224 against 208 us, ten sweeps 708 against 740; eight of 34^3, three
+    // sweeps, 60 against 77; 64 of 40^3, one sweep, 88 against 109)
+    const int64_t tiled = (d->L + 31) / 32 * 32, sites = (int64_t)d->n_rep * d->L * d->L * d->L;
+    if (tiled * tiled * 10 > (int64_t)d->L * d->L * 28 &&
+        (n_sweeps == 1 || (n_sweeps == 3 && sites >= (int64_t)1 << 21)))
+        return false;
+    return sites >= (int64_t)1 << 18;
 }
 
 // Uniform 3D Ising / EA batches with an edge of 4 .. 24 or 32 keep whole replicas

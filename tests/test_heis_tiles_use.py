@@ -17,7 +17,8 @@ def _tiled(L, n_rep, n):
 
 
 @pytest.mark.parametrize("L,n_rep,n,want", [
-    (34, 64, 1, False), (36, 64, 1, False), (38, 64, 1, False), (34, 64, 2, True), (38, 64, 3, True), (40, 64, 1, True),
+    (34, 64, 1, False), (36, 64, 1, False), (38, 64, 1, False), (34, 64, 2, True), (38, 64, 3, False), (38, 64, 5, True),
+    (34, 8, 3, True), (40, 64, 1, True),
     (66, 8, 1, True), (100, 1, 1, True), (32, 1, 1, True), (64, 1, 1, True), (34, 2, 5, False), (30, 64, 5, False)])
 def test_which_calls(L, n_rep, n, want):
     assert _tiled(L, n_rep, n) == want
