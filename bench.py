@@ -39,6 +39,8 @@ KERNEL_SOURCES = {
     "k_pt3d_chain": ("small3d.hip", "small3d.hpp", "halves.hpp", "rows.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp",
                      "tables.hpp"),
     "k_uneven2d_sweep": ("bins2d.hip", "halves.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp", "tables.hpp"),
+    "k_pairs3d_half": ("pairs3d.hip", "pairs3d.hpp", "halves.hpp", "rows.hpp", "segment3d.hpp", "intrin.hpp", "philox.hpp",
+                       "tables.hpp"),
 }
 
 
@@ -98,6 +100,7 @@ KT_WORKLOADS = {
     "k_ising3d_half": "3D Ising and EA (one +-J sample), one L^3 lattice per model, L up to {L}",
     "k_pt3d_chain": "3D +-J tempering, L = {L}: 512 samples x 2 replicas x 32 temperatures, chain-resident",
     "k_uneven2d_sweep": "uneven 2D +-J tempering batch: 4096 instances x 16 temperatures, edges 32 .. {L}",
+    "k_pairs3d_half": "3D EA (one +-J sample), one L^3 lattice, L = {L}",
 }
 
 
@@ -158,7 +161,7 @@ def kt_summary(db: str, log: str, kernel: str, L: int, command: str):
     print("\n".join(lines))
 
 
-def valu_summary(db: str, command: str):
+def valu_summary(dbs: list[str], commands: list[str]):
     """VALU use of the hot kernels from a rocprofv3 --pmc run with
     SQ_INSTS_VALU, SQ_ACTIVE_INST_VALU, SQ_ACTIVE_INST_VALU2,
     SQ_BUSY_CU_CYCLES and GRBM_GUI_ACTIVE, per dispatch of each kernel's
@@ -175,12 +178,15 @@ def valu_summary(db: str, command: str):
               (SQ_ACTIVE_INST_VALU counts one quad-cycle per instruction, so
               dual-issued quad-cycles are counted twice; the profiler's
               VALUBusy is SQ_ACTIVE_INST_VALU / C);
-      cu    = SQ_BUSY_CU_CYCLES / C: the share of CU-cycles with work."""
+      cu    = SQ_BUSY_CU_CYCLES / C: the share of CU-cycles with work.
+    Several databases (of one run each): a kernel's largest grid of all."""
     import sqlite3
 
     cu_num = 256
-    con = sqlite3.connect(db)
-    rows = con.execute("select kernel_name, counter_name, value, grid_size from counters_collection").fetchall()
+    rows = []
+    for db in dbs:
+        con = sqlite3.connect(db)
+        rows += con.execute("select kernel_name, counter_name, value, grid_size from counters_collection").fetchall()
     # per kernel: its largest grid, and of that grid the instantiation with
     # the most dispatches (the 2D sweep: the split-to-split launches)
     count = {}
@@ -197,7 +203,7 @@ def valu_summary(db: str, command: str):
         if k in pick and (grid, name) == (pick[k][0], pick[k][2]):
             acc.setdefault(k, {}).setdefault(cname, []).append(val)
     lines = ["# VALU use per dispatch of each kernel's largest grid, most frequent instantiation (rocprofv3 --pmc)",
-             f"# command: {command}",
+             *[f"# command: {c}" for c in commands],
              "# C = CU_NUM (256) x GRBM_GUI_ACTIVE (8-XCD sum / 8): CU-cycles of the dispatch",
              "# issue = SQ_INSTS_VALU / C: wave64 VALU instructions per CU per cycle (1.0 = one per SIMD per",
              "#         quad-cycle; gfx950 dual-issues, so up to 2)",
@@ -207,7 +213,7 @@ def valu_summary(db: str, command: str):
              f"{'kernel':24s} {'disp':>5s} {'VALU_insts':>11s} {'gui_cycles':>11s} {'issue':>6s} {'dual':>6s} "
              f"{'busy':>6s} {'cu':>6s}"]
     names = ("k_ising2d_split", "k_tiles2d", "k_small3d", "k_bins2d", "k_heis3d_tiled", "k_heis3d_half",
-             "k_pairs3d_half", "k_ising3d_half", "k_ising3d_pass", "k_half_sweep_pieces", "k_half_sweep_generic", "k_msc2d",
+             "k_pairs3d_half", "k_pairs3d_half_ragged", "k_heis_small", "k_ising3d_half", "k_ising3d_pass", "k_half_sweep_pieces", "k_half_sweep_generic", "k_msc2d",
              "k_dcb2d_packed", "k_dcb2d", "k_dcb3d", "k_heis_dcb2d", "k_philox_bench", "k_dcb_rng")
     for k in names:
         a = acc.get(k, {})
@@ -272,11 +278,15 @@ def pmc_summary(fetch_db: str, write_db: str, cfetch_db: str, cwrite_db: str, ke
         # the split-to-split launches, not the first and last sweeps of a call
         # (which read and write the caller's rows)
         name = max((n for n in acc if key in n), key=lambda n: (len(acc[n]), sum(acc[n]) / len(acc[n])))
+        # (a call's first and last step read and write the caller's arrays in launches of the same instantiation)
+        if key == "k_bins2d":
+            return name, sorted(acc[name])[len(acc[name]) // 2]
         return name, sum(acc[name]) / len(acc[name])
 
-    kf, kfv = mean_of(per_kernel(fetch_db, "FETCH_SIZE", True), kernel)
+    traced = TRACE_NAMES.get(kernel, kernel)
+    kf, kfv = mean_of(per_kernel(fetch_db, "FETCH_SIZE", True), traced)
     fetch_grid = per_kernel.grids[kf]
-    kw, kwv = mean_of(per_kernel(write_db, "WRITE_SIZE", True), kernel)
+    kw, kwv = mean_of(per_kernel(write_db, "WRITE_SIZE", True), traced)
     write_grid = per_kernel.grids[kw]
     # the copy kernel: the one that fetched the most; its sums over the run
     # divided by the number of 1 GiB copies
@@ -299,11 +309,22 @@ def pmc_summary(fetch_db: str, write_db: str, cfetch_db: str, cwrite_db: str, ke
         algorithmic = 1.0 * L ** 3
         what = (f"one launch = one half-sweep of a 3D Ising {L}^3 lattice; algorithmic bytes = half of the "
                 f"sweep's one read and one write of every spin (1 B per site per launch)")
+    elif kernel == "k_pairs3d_half":
+        algorithmic = 0.75 * L ** 3
+        what = (f"one launch = one half-sweep of a 3D EA {L}^3 lattice on the packed copy; algorithmic bytes = one read of "
+                f"either colour's half bytes and one write of the updated one's (0.75 B per site)")
+    elif kernel == "k_uneven2d_sweep":
+        import workloads as W
+
+        cfg = W.ea2d_uneven()
+        algorithmic = 1.0 * cfg.n_temps * sum(int(e) ** 2 for e in cfg.sizes)
+        what = (f"one launch (k_bins2d) = one step of the uneven tempering batch, {algorithmic:.0f} sites, between a call's "
+                f"first and last; algorithmic bytes = half a byte per site read and written")
     else:
         algorithmic = BYTES_PER_FLIP * L * L * 3
         what = f"one launch = one sweep of a batch of three 2D Ising {L}x{L} lattices"
     lines = [f"# rocprofv3 --pmc summary: {kernel}, {what}",
-             "# figures are means per dispatch of the counter over the dispatches of the kernel's instantiation and "
+             f"# figures are {'medians' if traced == 'k_bins2d' else 'means'} per dispatch of the counter over the dispatches of the kernel's instantiation and "
              + ("grid with the most dispatches in the run (the timed batch)" if grid_rule == "most" else
                 "largest grid in the run (the largest lattice)")]
     lines += [f"# command: {c}" for c in commands]
@@ -480,9 +501,8 @@ def under_profiler() -> bool:
 
 # Profiled runs (rocprofv3 with hardware counters) have stopped with a
 # malformed-packet queue error while thousands of small kernels were queued
-# back to back without a host synchronisation (the autotuner's replica copies;
-# dcb_scan's double-checkerboard launches at L = 64 with a budget of 2e8
-# flips).  Under a profiler the sections that queue many small launches are
+# back to back without a host synchronisation (dcb_scan's double-checkerboard
+# launches at L = 64 with a budget of 2e8 flips).  Under a profiler the sections that queue many small launches are
 # held to the sizes with which profiled runs have completed.
 PROFILED_LIMITS = {
     "dcb_scan": ("flips", 2e6),
@@ -854,6 +874,44 @@ def sweep3d(S, W, sizes=(256, 512, 1024), beta=0.2216, flips=8e9, models=("ising
             "rows": rows}
 
 
+def call_kernels(S, W):
+    """ps per attempted flip of one call each on the kernels that hold lattices on chip or copy them: 2D tiles
+    (4096^2 Ising, and 1024 EA lattices of 200^2), whole small 3D lattices (tempering of edge 16), bins of
+    the uneven tempering batch, the packed 3D copy (EA 512^3, and 64 Ising lattices of 100^3) and
+    small Heisenberg lattices (256 of 22^3).  Few launches, for a profiler."""
+    import numpy as np
+    import torch
+
+    rows = []
+
+    def add(kernel, workload, flips, fn):
+        fn()
+        rows.append({"kernel": kernel, "workload": workload, "ps_per_flip": round(_timed(fn) * 1e9 / flips, 4)})
+
+    for kernel, model, dim, L, n_rep, n in (
+            ("k_tiles2d", S.ISING, 2, 4096, 1, 16), ("k_tiles2d", S.EA, 2, 200, 1024, 16),
+            ("k_pairs3d_half", S.EA, 3, 512, 1, 6), ("k_pairs3d_half_ragged", S.ISING, 3, 100, 64, 6),
+            ("k_heis_small", S.HEISENBERG, 3, 22, 256, 16)):
+        b = S.Batch(model, dim, L, n_rep, W.seed_for(107))
+        spins = torch.empty(b.spins_shape()[0], dtype=torch.float32 if model == S.HEISENBERG else torch.int8, device="cuda")
+        coup = torch.empty(b.coup_len(), dtype=torch.int8, device="cuda") if model == S.EA else None
+        S.spin_init(b, spins, coup)
+        add(kernel, f"{n_rep} x {L}^{dim}, {n} sweeps", n * n_rep * L ** dim,
+            lambda: S.metropolis_sweep(b, spins, np.full(n_rep, 0.4), 0, n, couplings=coup))
+        del spins, coup
+    cfg = W.ea3d_tempering()
+    b, spins, coup, E, sot = _pt_batch(S, S.EA, 3, cfg.L, cfg.n_chains, cfg.n_temps, cfg.seed, rps=2 * cfg.n_temps)
+    add("k_small3d", f"{cfg.n_chains} chains of {cfg.n_temps} at edge {cfg.L}, 20 steps", 20 * b.n_rep * cfg.L ** 3,
+        lambda: S.pt_sweep_swap(b, cfg.n_chains, cfg.n_temps, cfg.betas, spins, sot, E, 0, 20, couplings=coup))
+    cfg = W.ea2d_uneven()
+    inst = W.uneven_table(2, cfg.sizes, cfg.n_temps, S.EA)
+    b, spins, coup, E, sot = _pt_batch(S, S.EA, 2, 0, cfg.n_chains, cfg.n_temps, cfg.seed, inst=inst)
+    sites = sum(int(r[0]) ** 2 for r in inst)
+    add("k_bins2d", f"{cfg.n_chains} uneven chains of {cfg.n_temps}, 10 steps", 10 * sites,
+        lambda: S.pt_sweep_swap(b, cfg.n_chains, cfg.n_temps, cfg.betas, spins, sot, E, 0, 10, couplings=coup))
+    return rows
+
+
 def heis_dcb2d(S, W, sweeps=4, L=4096, hits=100, tiles=(32, 64)):
     """The paper's Heisenberg benchmark (Sec. 4): 2D, L = 4096, double
     checkerboard with k = 100 hits, in the three arithmetic modes (float32
@@ -1103,23 +1161,19 @@ def tau_dcb(S, W, L=128, tile=16, hits=(1, 2, 5, 10, 20, 50, 100), n_rep=256, up
 
 def tempering_ea2d_uneven(S, W, steps, per_inst_chains=64, per_inst_steps=3):
     """Uneven 2D EA batch, 4096 instances x 16 temperatures, edges from
-    {32, ..., 256}: the batch in one call (a graph of steps), against one call
+    {32, ..., 256}: the batch in one call (a launch per step and one for the exchange round), against one call
     per instance on a sample of instances (weighted to the batch's edge mix)."""
     import numpy as np
     import torch
 
     cfg = W.ea2d_uneven(steps=steps)
     nc, nt = cfg.n_chains, cfg.n_temps
-    if under_profiler() and os.environ.get("SPINMC_AUTOTUNE", "") != "0":
-        raise RuntimeError("tempering.ea2d_uneven: the workgroup-size autotuner queues thousands of small copies; "
-                           "set SPINMC_AUTOTUNE=0 for profiled runs")
     profiler_guard("tempering.ea2d_uneven", cfg.steps)
     inst = W.uneven_table(2, cfg.sizes, nt, S.EA)
     b, spins, coup, E, sot = _pt_batch(S, S.EA, 2, 0, nc, nt, cfg.seed, inst=inst)
     sites = int(sum(int(r[0]) ** 2 for r in inst))
     _, kernel = S.pt_plan(b, nc, nt, cfg.betas, cfg.steps)
-    # warm-up with the same step graphs as the timed call (32-step graph and the remainder)
-    warm = 32 + cfg.steps % 32 if cfg.steps >= 32 else cfg.steps
+    warm = min(32, cfg.steps)
     S.pt_sweep_swap(b, nc, nt, cfg.betas, spins, sot, E, 0, warm, couplings=coup)
     ms = _timed(lambda: S.pt_sweep_swap(b, nc, nt, cfg.betas, spins, sot, E, warm, cfg.steps, couplings=coup))
     rate = cfg.steps * nc * nt / (ms * 1e-3)
@@ -1359,7 +1413,10 @@ def main():
     ap.add_argument("--kt-summary", nargs=2, metavar=("KT_DB", "KT_LOG"),
                     help="write the kernel-trace summary from a rocprofv3 database and the run's output")
     ap.add_argument("--kt-command", default="", help="command line recorded in the kernel-trace summary")
-    ap.add_argument("--valu-summary", metavar="DB", help="write the VALU utilisation summary from a --pmc database")
+    ap.add_argument("--call-kernels-only", action="store_true",
+                    help="only a few calls on the kernels that hold or copy lattices (for profiling)")
+    ap.add_argument("--valu-summary", nargs="+", metavar="DB",
+                    help="write the VALU utilisation summary from --pmc databases")
     ap.add_argument("--no-autotune", action="store_true",
                     help="keep the default launch shapes (no smc_autotune before the measurements)")
     ap.add_argument("--preheat-s", type=float, default=1.0,
@@ -1371,10 +1428,10 @@ def main():
         print(json.dumps(oracle_job(kind, float(sec), int(idx))))
         return
     if args.valu_summary:
-        valu_summary(args.valu_summary, args.pmc_command[0] if args.pmc_command else "")
+        valu_summary(args.valu_summary, args.pmc_command)
         return
     kernel_L = {"k_heis3d_tiled": 256, "k_ising3d_half": max(args.sweep3d_sizes),
-                "k_ising3d_pass": max(args.sweep3d_sizes), "k_pt3d_chain": 16,
+                "k_ising3d_pass": max(args.sweep3d_sizes), "k_pt3d_chain": 16, "k_pairs3d_half": 512,
                 "k_uneven2d_sweep": 256}.get(args.pmc_kernel, args.L)
     if args.kt_summary:
         kt_summary(*args.kt_summary, kernel=args.pmc_kernel, L=kernel_L, command=args.kt_command)
@@ -1411,6 +1468,9 @@ def main():
     if args.sweep3d_only:
         print(json.dumps({"sweep3d": sweep3d(S, W, sizes=tuple(args.sweep3d_sizes), models=tuple(args.sweep3d_models),
                                              tune=not args.no_autotune)}))
+        return
+    if args.call_kernels_only:
+        print(json.dumps({"call_kernels": call_kernels(S, W)}))
         return
     if args.heis_dcb_only:
         print(json.dumps({"heis_dcb2d": heis_dcb2d(S, W, sweeps=args.heis_dcb_sweeps)}))
