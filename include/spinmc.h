@@ -32,9 +32,8 @@
  *   these limits is not issued and the call returns SMC_EHIP with the
  *   kernel and the broken limit in smc_last_error().
  * - Calls on a stream that is capturing a graph return SMC_EINVAL and issue
- *   nothing: they stage host tables through pinned buffers, may grow their
- *   scratch and build graphs of their own, none of which can be recorded into
- *   a caller's capture.
+ *   nothing: they stage host tables through pinned buffers and may grow their
+ *   scratch, neither of which can be recorded into a caller's capture.
  * - Inverse temperatures and uneven-batch tables are HOST arrays: the
  *   acceptance thresholds floor(2^32 exp(-beta Delta E)) are computed from
  *   them on the host in float64 with the C library's exp, so that every

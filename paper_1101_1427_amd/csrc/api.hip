@@ -239,7 +239,7 @@ struct CallTally {
 
 // Uniform 2D batches run several sweeps per launch on bands of rows in LDS
 // where the estimate says that it is faster than two half-sweep launches per
-// sweep (measured: about 3.5 us and 1.2 fs per site each).  Edges that are
+// sweep (measured: about 3.5 us and 1.2 ps per site each).  Edges that are
 // multiples of 16 are cut along their rows too; others in bands of whole rows of half
 // a byte per site, of which large edges have too few in LDS, so they keep the
 // half-sweeps.  So does a call of one sweep unless the lattice fits in LDS as a whole.

@@ -1,6 +1,6 @@
 // Generic kernels: initial state, per-site half-sweeps for any edge L and
-// dimension, Heisenberg renormalisation and the parallel-tempering exchange.  The optimised kernels (lattice2d.hip,
-// small3d.hip) produce the same results; these serve every shape.
+// dimension, Heisenberg renormalisation and the parallel-tempering exchange.
+// The optimised kernels produce the same results; these serve every shape.
 #include <stdlib.h>
 #include <string.h>
 

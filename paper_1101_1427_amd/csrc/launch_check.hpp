@@ -1,7 +1,6 @@
 // Host-side validation of a kernel launch configuration on gfx950, applied to
-// every launch and graph kernel node the library issues, before it reaches
-// the runtime.  Plain C++ (no HIP types) so that the check itself can be
-// compiled and unit-tested on a machine without a GPU.
+// every launch the library issues, before it reaches the runtime.  Plain C++
+// (no HIP types) so that the check itself can be compiled and unit-tested on a machine without a GPU.
 #pragma once
 #include <stdint.h>
 

@@ -151,10 +151,10 @@ int upload(StreamCtx &c, hipStream_t s, Slot slot, const void *src, size_t bytes
     return SMC_OK;
 }
 
-// Calls stage host data (tables, instance lists) through pinned buffers,
-// grow their scratch on demand and build graphs of their own; none of that
-// can be recorded into a caller's stream capture, so a call on a capturing
-// stream is refused before anything is issued.
+// Calls stage host data (tables, instance lists) through pinned buffers and
+// grow their scratch on demand; neither can be recorded into a caller's
+// stream capture, so a call on a capturing stream is refused before anything
+// is issued.
 int refuse_capture(hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     SMC_HIP(hipStreamIsCapturing(s, &cap));
@@ -180,8 +180,6 @@ ThrRow threshold_row(double beta, int dim) {
     return row;
 }
 
-// The chain-resident tempering kernel serves 3D edge-16 batches of at most
-// 32 temperatures with 16-byte aligned spins and thresholds below 2^32.
 // Uniform 3D Heisenberg batches with a power-of-two edge take the indexed
 // kernel (SPINMC_HEIS3D=0 sends them to the generic one).
 bool use_heis3d(const smc_desc *d) {
